@@ -12,14 +12,14 @@ SRC = PKG / "csrc" / "lookupffn.hip"
 LIB = PKG / "liblookupffn.so"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-N_PARTS = 17         # csrc/lookupffn.hip compiles as parts 0 .. 16 (-DLFFN_PART=i), linked together
-SLOW_FIRST = [10, 11, 8, 9, 6, 5]   # the wide BH kernels take the longest: start them first
+N_PARTS = 12         # csrc/lookupffn.hip compiles as parts 0 .. 11 (-DLFFN_PART=i), linked together
+SLOW_FIRST = [6, 5, 4, 3]   # the BH kernels take the longest: start them first
 OBJ_DIR = PKG / "_build"
-# Per-part compiler settings.  Part 16 is the staged gather's plain 13-slot, 128-byte-slice kernel: with the
+# Per-part compiler settings.  Part 11 is the staged gather's plain 13-slot, 128-byte-slice kernel: with the
 # instruction scheduler set to favour instruction-level parallelism it measured 4 % faster (93.5 against 97.4 us
 # for 16384 tokens x 96 tables, alternating runs on one machine); the 64-byte-slice kernels measured 4 % slower
 # with it, so they stay with the default.
-PART_FLAGS = {16: ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+PART_FLAGS = {11: ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

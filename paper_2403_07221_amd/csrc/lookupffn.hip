@@ -23,7 +23,7 @@
 
 // Build parts.  This file compiles whole (LFFN_PART undefined) or as parts that are linked together, so
 // that the kernel families compile side by side: part 0 holds the C ABI, the host logic and the hash and
-// re-pack kernels; parts 1 .. 16 hold one family of kernel launchers each (declared just below).  No
+// re-pack kernels; parts 1 .. 11 hold one family of kernel launchers each (declared just below).  No
 // kernel is instantiated in two parts.
 #ifdef LFFN_PART
 #define LFFN_HAS(p) (LFFN_PART == (p))
@@ -47,30 +47,24 @@ int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3
 int gather_direct_load();  // makes the runtime load part 1's code object now (lookupffn_init)
 // parts 2, 3: the LDS-staged gather kernel (plain sum; weighted and multi-probe)
 int gather_lds_plain_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
-int gather_lds_plain13_part(const GatherLdsArgs &a, int fr, dim3 grid, size_t lds, hipStream_t s);  // part 16
+int gather_lds_plain13_part(const GatherLdsArgs &a, int fr, dim3 grid, size_t lds, hipStream_t s);  // part 11
 int gather_lds_weighted_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
 int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
-// part 12: the lagged, bank-interleaved staged gather (prepared tables, tau <= 8)
+// part 7: the lagged, bank-interleaved staged gather (prepared tables, tau <= 8)
 int gather_ring_part(int threads, int tok, const GatherRingArgs &a, dim3 grid, hipStream_t s);
-// part 13: hash and gather of a few tokens, one or several chained layers, in one launch
+// part 8: hash and gather of a few tokens, one or several chained layers, in one launch
 int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
 int forward_stack_load();
-// parts 14, 15: the hash with a token per row of lanes, d_pad = 1024 (four tokens per wavefront) and 512 (eight)
+// parts 9, 10: the hash with a token per row of lanes, d_pad = 1024 (four tokens per wavefront) and 512 (eight)
 int hash_row16_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s);
 int hash_row8_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s);
 int hash_row16_load();
 int hash_row8_load();
-// parts 4 .. 11: the BH hash kernel.  Plain: d_pad = 64 .. 256, 512, 1024; weighted: d_pad = 64 .. 256, then
-// 512 and 1024 each split by the way the rows are read (four coordinates at a time or one by one): the
-// wide weighted kernels are the slowest to compile by far
-int bh_plain_lo_part(int L, const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
-int bh_plain_512_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
-int bh_plain_1024_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
-int bh_weighted_lo_part(int L, const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
-int bh_weighted_512_vec4_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
-int bh_weighted_512_scalar_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
-int bh_weighted_1024_vec4_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
-int bh_weighted_1024_scalar_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s);
+// parts 4 .. 6: the BH hash kernel, d_pad = 64 .. 256, 512 and 1024.  wmode: 0 codes only, 1 weights of tau 4, 8, 16, 2 weights
+// of any other tau
+int bh_lo_part(int L, int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s);
+int bh_512_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s);
+int bh_1024_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s);
 }  // namespace lffn_host
 
 namespace {
@@ -133,7 +127,7 @@ int launch_gather_lds_fr(const GatherLdsArgs &a, dim3 grid, size_t lds, hipStrea
 }
 
 // fr = 16 KB copy rounds per table slice, sw = lanes per token (both fixed by the plan)
-// SW8: this part also holds the 128-byte-slice form of TOK (part 16 holds the plain one with 13 slots)
+// SW8: this part also holds the 128-byte-slice form of TOK (part 11 holds the plain one with 13 slots)
 template <int TOK, bool WEIGHTED = false, bool SW8 = true>
 int launch_gather_lds_t(const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
@@ -167,32 +161,38 @@ int launch_gather_lds_probes(const GatherLdsArgs &a, int fr, int sw, dim3 grid, 
     return LFFN_E_UNSUPPORTED;
 }
 
-template <int L, int TB, bool VEC4, bool WEIGHTED>
-int launch_bh_k(const BhArgs &a, dim3 grid, size_t lds, hipStream_t s)
+template <int L, int TB, int WMODE>
+int launch_bh_k(const BhArgs &a, dim3 grid, hipStream_t s)
 {
-    auto kern = bh_hash_kernel<L, TB, VEC4, WEIGHTED>;
+    auto kern = bh_hash_kernel<L, TB, WMODE>;
+    const bool query = lffn_host::attr_only();
+    const size_t lds = query ? 160 * 1024 : BhLds<L, WMODE == 2>::bytes(a.P);
     int rc = allow_lds(reinterpret_cast<const void *>(kern), lds);
-    if (rc != LFFN_OK || lffn_host::attr_only()) return rc;
+    if (rc != LFFN_OK || query) return rc;
     hipLaunchKernelGGL(kern, grid, dim3(kBhThreads), lds, s, a);
     return LFFN_OK;
 }
 
-template <int L, bool VEC4, bool WEIGHTED>
-int launch_bh_v(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
+template <int L, int WMODE>
+int launch_bh_b(const BhArgs &a, int block, dim3 grid, hipStream_t s)
 {
     switch (block) {
-        case 16: return launch_bh_k<L, 1, VEC4, WEIGHTED>(a, grid, lds, s);
-        case 32: return launch_bh_k<L, 2, VEC4, WEIGHTED>(a, grid, lds, s);
-        case 64: return launch_bh_k<L, 4, VEC4, WEIGHTED>(a, grid, lds, s);
+        case 16: return launch_bh_k<L, 1, WMODE>(a, grid, s);
+        case 32: return launch_bh_k<L, 2, WMODE>(a, grid, s);
+        case 64: return launch_bh_k<L, 4, WMODE>(a, grid, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
 
-template <int L, bool WEIGHTED>
-int launch_bh_w(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
+template <int L>
+int launch_bh(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s)
 {
-    return a.x_vec4 ? launch_bh_v<L, true, WEIGHTED>(a, block, grid, lds, s)
-                    : launch_bh_v<L, false, WEIGHTED>(a, block, grid, lds, s);
+    switch (wmode) {
+        case 0: return launch_bh_b<L, 0>(a, block, grid, s);
+        case 1: return launch_bh_b<L, 1>(a, block, grid, s);
+        case 2: return launch_bh_b<L, 2>(a, block, grid, s);
+    }
+    return LFFN_E_UNSUPPORTED;
 }
 
 }  // namespace
@@ -232,7 +232,7 @@ int gather_lds_plain_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 
 }
 #endif
 
-#if LFFN_HAS(16)
+#if LFFN_HAS(11)
 // The plain sum with 13 token slots and 128-byte slices -- the kernel of the 16384-token benchmark layer -- is
 // compiled on its own so that it can take the scheduler setting that suits it (see build.py).
 int gather_lds_plain13_part(const GatherLdsArgs &a, int fr, dim3 grid, size_t lds, hipStream_t s)
@@ -264,7 +264,7 @@ int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3
 }
 #endif
 
-#if LFFN_HAS(12)
+#if LFFN_HAS(7)
 template <int THREADS, int TOK>
 int launch_gather_ring_t(const GatherRingArgs &a, dim3 grid, hipStream_t s)
 {
@@ -299,7 +299,7 @@ int gather_ring_part(int threads, int tok, const GatherRingArgs &a, dim3 grid, h
 }
 #endif
 
-#if LFFN_HAS(13)
+#if LFFN_HAS(8)
 template <int R>
 int launch_forward_stack_r(int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s)
 {
@@ -332,7 +332,7 @@ int forward_stack_load()
 }
 #endif
 
-#if LFFN_HAS(14) || LFFN_HAS(15)
+#if LFFN_HAS(9) || LFFN_HAS(10)
 // WMODE of the lane-row kernel: 0 codes only, 1 weights reduced in registers (tau divides the lanes of a token),
 // 2 weights of any tau through the z window
 inline int row_wmode(const HashArgs &a, int lpt) { return !(a.weights || a.wpk) ? 0 : lpt % a.tau == 0 ? 1 : 2; }
@@ -367,7 +367,7 @@ int launch_hash_row_m(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hi
 }
 #endif
 
-#if LFFN_HAS(14)
+#if LFFN_HAS(9)
 int hash_row16_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
     // built for the row lengths of the paper's models (d = 768 and 1024, three rounds); any other multiple of
@@ -385,7 +385,7 @@ int hash_row16_load()
 }
 #endif
 
-#if LFFN_HAS(15)
+#if LFFN_HAS(10)
 int hash_row8_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
     if (n_rounds == 3 && a.d == 512) return launch_hash_row_m<64, 8>(3, a, grid, lds, s);  // the paper's small models
@@ -401,69 +401,23 @@ int hash_row8_load()
 #endif
 
 #if LFFN_HAS(4)
-int bh_plain_lo_part(int L, const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
+int bh_lo_part(int L, int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s)
 {
     switch (L) {
-        case 6: return launch_bh_w<6, false>(a, block, grid, lds, s);
-        case 7: return launch_bh_w<7, false>(a, block, grid, lds, s);
-        case 8: return launch_bh_w<8, false>(a, block, grid, lds, s);
+        case 6: return launch_bh<6>(wmode, a, block, grid, s);
+        case 7: return launch_bh<7>(wmode, a, block, grid, s);
+        case 8: return launch_bh<8>(wmode, a, block, grid, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
 #endif
 
 #if LFFN_HAS(5)
-int bh_plain_512_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
-{
-    return launch_bh_w<9, false>(a, block, grid, lds, s);
-}
+int bh_512_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s) { return launch_bh<9>(wmode, a, block, grid, s); }
 #endif
 
 #if LFFN_HAS(6)
-int bh_plain_1024_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
-{
-    return launch_bh_w<10, false>(a, block, grid, lds, s);
-}
-#endif
-
-#if LFFN_HAS(7)
-int bh_weighted_lo_part(int L, const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
-{
-    switch (L) {
-        case 6: return launch_bh_w<6, true>(a, block, grid, lds, s);
-        case 7: return launch_bh_w<7, true>(a, block, grid, lds, s);
-        case 8: return launch_bh_w<8, true>(a, block, grid, lds, s);
-    }
-    return LFFN_E_UNSUPPORTED;
-}
-#endif
-
-#if LFFN_HAS(8)
-int bh_weighted_512_vec4_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
-{
-    return launch_bh_v<9, true, true>(a, block, grid, lds, s);
-}
-#endif
-
-#if LFFN_HAS(9)
-int bh_weighted_512_scalar_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
-{
-    return launch_bh_v<9, false, true>(a, block, grid, lds, s);
-}
-#endif
-
-#if LFFN_HAS(10)
-int bh_weighted_1024_vec4_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
-{
-    return launch_bh_v<10, true, true>(a, block, grid, lds, s);
-}
-#endif
-
-#if LFFN_HAS(11)
-int bh_weighted_1024_scalar_part(const BhArgs &a, int block, dim3 grid, size_t lds, hipStream_t s)
-{
-    return launch_bh_v<10, false, true>(a, block, grid, lds, s);
-}
+int bh_1024_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s) { return launch_bh<10>(wmode, a, block, grid, s); }
 #endif
 
 #if LFFN_HAS(0)
@@ -1306,6 +1260,18 @@ int gather_from_abi(Mode mode, const uint16_t *codes, const float *weights, cons
 }
 
 // ---- BH{m} hash --------------------------------------------------------------------------------
+// The BH kernel reduces a table's weight inside one 16-coordinate tile of z (tau = 4, 8, 16); for any other tau it
+// forms the weights from z through a window in LDS.
+bool bh_weights_in_registers(int tau) { return tau == 4 || tau == 8 || tau == 16; }
+
+// The range of P and tau the BH entry points accept: the bit strings (and the z window) of 64 tokens beside 64 KB.
+// The kernel needs less for every shape in it (at most 124 KB).
+bool bh_shape_fits(int P, int N, bool window)
+{
+    const size_t bytes = 64 * 1024 + 256 * (size_t)hash_bit_words(P, N) + (window ? 256 * (size_t)((N < 128 ? N : 128) + 17) : 0);
+    return P <= 64 && bytes <= 150 * 1024;
+}
+
 int check_bh(const void *x, const float *bmats, int64_t n, int d, int k, int tau, int block, int n_factors,
              int x_dtype, bool weighted = false)
 {
@@ -1322,14 +1288,10 @@ int check_bh(const void *x, const float *bmats, int64_t n, int d, int k, int tau
     if (b != 16 && b != 32 && b != 64) return LFFN_E_UNSUPPORTED;
     if (b > N) return LFFN_E_SIZE;
     const int64_t P = ((int64_t)k * tau + N - 1) / N;
-    if (P > 64 || bh_lds_bytes((int)P, N, weighted && !(tau == 4 || tau == 8 || tau == 16)) > 150 * 1024) return LFFN_E_UNSUPPORTED;
+    if (P > 64 || !bh_shape_fits((int)P, N, weighted && !bh_weights_in_registers(tau))) return LFFN_E_UNSUPPORTED;
     if (!aligned(x, x_dtype == LFFN_F32 ? 4 : 2) || !aligned(bmats, (block & LFFN_PREPARED) ? 256 : 4)) return LFFN_E_ALIGN;
     return LFFN_OK;
 }
-
-// The BH kernel reduces a table's weight inside one 16-coordinate tile of z (tau = 4, 8, 16: the weighted
-// instantiations).  For any other tau the plain instantiation forms the weights from z through a window in LDS.
-bool bh_weights_in_kernel(int tau) { return tau == 4 || tau == 8 || tau == 16; }
 
 int64_t bh_pack_bytes(int d, int k, int tau, int block, int n_factors)
 {
@@ -1377,30 +1339,21 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     a.x_vec4 = d % 4 == 0 && aligned(x, a.x_kind ? 8 : 16);
     a.scale = (float)(1.0 / std::sqrt((double)N));
     if (!a.apack || (!a.codes && !a.packed) || out.probes) return LFFN_E_NULL;
-    a.window = out.weights && !bh_weights_in_kernel(tau);  // weights through the z window of the plain kernels
     TimedLaunch tl(0, s);
     if (pack_from) {
         int rc = launch_bh_pack(pack_from, apack_scratch, d, k, tau, block, n_factors, s);
         if (rc != LFFN_OK) return rc;
     }
-    int64_t blocks = ((n + kBhTok - 1) / kBhTok + kBhWaves - 1) / kBhWaves;
-    if (blocks > 4096) blocks = 4096;
+    const int wmode = !out.weights ? 0 : bh_weights_in_registers(tau) ? 1 : 2;
+    const int wpg = L == 10 ? 4 : L == 9 ? 2 : 1;  // waves that share a token group
+    const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
+    const int64_t blocks = (n + per_block - 1) / per_block;
+    if (blocks > 0x7FFFFFFFLL) return LFFN_E_SIZE;
     const dim3 grid((unsigned)blocks);
-    const size_t lds = bh_lds_bytes(a.P, N, a.window != 0);
-    const bool weighted = (a.weights || a.wpk) && !a.window;  // the instantiations that reduce weights in registers
     int rc;
-    if (L <= 8)
-        rc = weighted ? lffn_host::bh_weighted_lo_part(L, a, block, grid, lds, s)
-                      : lffn_host::bh_plain_lo_part(L, a, block, grid, lds, s);
-    else if (!weighted)
-        rc = L == 9 ? lffn_host::bh_plain_512_part(a, block, grid, lds, s)
-                    : lffn_host::bh_plain_1024_part(a, block, grid, lds, s);
-    else if (L == 9)
-        rc = a.x_vec4 ? lffn_host::bh_weighted_512_vec4_part(a, block, grid, lds, s)
-                      : lffn_host::bh_weighted_512_scalar_part(a, block, grid, lds, s);
-    else
-        rc = a.x_vec4 ? lffn_host::bh_weighted_1024_vec4_part(a, block, grid, lds, s)
-                      : lffn_host::bh_weighted_1024_scalar_part(a, block, grid, lds, s);
+    if (L <= 8) rc = lffn_host::bh_lo_part(L, wmode, a, block, grid, s);
+    else if (L == 9) rc = lffn_host::bh_512_part(wmode, a, block, grid, s);
+    else rc = lffn_host::bh_1024_part(wmode, a, block, grid, s);
     if (rc != LFFN_OK) return rc;
     LFFN_HIP(hipGetLastError());
     tl.done();
@@ -1694,25 +1647,17 @@ int lookupffn_init(void)
                 if (rc != LFFN_OK && rc != LFFN_E_UNSUPPORTED) return rc;
             }
     }
-    for (int L = 6; L <= 10; ++L)
-        for (int block : {16, 32, 64})
-            for (int vec4 = 0; vec4 < 2; ++vec4)
-                for (int weighted = 0; weighted < 2; ++weighted) {
-                    ba.x_vec4 = vec4;
-                    if (L <= 8)
-                        rc = weighted ? lffn_host::bh_weighted_lo_part(L, ba, block, dim3(1), lds, nullptr)
-                                      : lffn_host::bh_plain_lo_part(L, ba, block, dim3(1), lds, nullptr);
-                    else if (!weighted)
-                        rc = L == 9 ? lffn_host::bh_plain_512_part(ba, block, dim3(1), lds, nullptr)
-                                    : lffn_host::bh_plain_1024_part(ba, block, dim3(1), lds, nullptr);
-                    else if (L == 9)
-                        rc = vec4 ? lffn_host::bh_weighted_512_vec4_part(ba, block, dim3(1), lds, nullptr)
-                                  : lffn_host::bh_weighted_512_scalar_part(ba, block, dim3(1), lds, nullptr);
-                    else
-                        rc = vec4 ? lffn_host::bh_weighted_1024_vec4_part(ba, block, dim3(1), lds, nullptr)
-                                  : lffn_host::bh_weighted_1024_scalar_part(ba, block, dim3(1), lds, nullptr);
-                    if (rc != LFFN_OK && rc != LFFN_E_UNSUPPORTED) return rc;
-                }
+    for (int block : {16, 32, 64})
+        for (int wmode = 0; wmode < 3; ++wmode) {
+            for (int L = 6; L <= 8; ++L) {
+                rc = lffn_host::bh_lo_part(L, wmode, ba, block, dim3(1), nullptr);
+                if (rc != LFFN_OK) return rc;
+            }
+            for (auto part : {lffn_host::bh_512_part, lffn_host::bh_1024_part}) {
+                rc = part(wmode, ba, block, dim3(1), nullptr);
+                if (rc != LFFN_OK) return rc;
+            }
+        }
     return LFFN_OK;
 }
 
