@@ -18,6 +18,13 @@
 // runs on XCD b % 8) each sweep all their tokens for one slice before moving
 // to the next one, so after first touch the row fetches are L2 hits instead of
 // trips to the Infinity Cache / HBM.
+//
+// What bounds it: with few tokens the wait for codes and rows, with many the L2.  Codes and weights are read eight at
+// a time whatever k is (one by one they cost a wait per table: 1001 tokens, 97 half tables, weighted 60 -> 20 us), and
+// a launch of fewer than two full workgroups per compute unit goes out as one-wave workgroups.  The multi-probe form
+// keeps eight to sixteen rows in flight across table boundaries (64 tokens, 96 tables, tau = 8: pass 143 -> 82 us;
+// 4096 tokens, tau = 11: 1560 -> 1270 us); the other two measured slower with a second set of rows in flight (2000
+// tokens weighted 48 -> 55 us: the registers cost half the waves).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -27,7 +34,7 @@
 namespace lffn {
 
 constexpr int kGatherThreads = 256;
-constexpr int kGatherWaves = kGatherThreads / 64;
+constexpr int kGatherWaves = kGatherThreads / 64;  // of a full workgroup; few tokens are launched in one-wave workgroups
 constexpr int kXcds = 8;
 
 struct GatherArgs {
@@ -42,9 +49,8 @@ struct GatherArgs {
     int n_slices;      // ceil(nvec / LPT)
     int n_units;       // n_slices * token_splits; a unit = (slice, contiguous range of token blocks)
     int tb_per_unit;   // token blocks in one unit
-    int ntb;           // token blocks in total; a token block = kGatherWaves * (64/LPT) tokens
+    int ntb;           // token blocks in total; a token block = (waves of a workgroup) * (64/LPT) tokens
     int xcd_mode;      // 1: block order is XCD-sliced (see above); 0: plain
-    int codes_vec8;    // 1: k % 8 == 0 and codes (and weights) 16-byte aligned -> read 8 at a time
     int code_stride;   // codes (and weights, and groups of 1 + tau shares) per token in the arrays; k unless
                        // the launch covers only some of the tables
     int accumulate;    // 1: the sums start from what y holds (fp32 y, fp32 rows) instead of zero
@@ -113,10 +119,32 @@ struct Acc {
     }
 };
 
-__device__ __forceinline__ uint32_t code_of(const uint4 &c, int u)
+// Eight consecutive codes of a token.  A token's codes start at any 2-byte boundary (k may be odd), so the 16 bytes
+// are one load of that alignment, which the hardware takes; fewer than eight are read one by one.
+struct CodeChunk {
+    uint32_t c[4];
+    __device__ __forceinline__ void load(const uint16_t *codes) { __builtin_memcpy(c, codes, 16); }
+    // m < 8 codes; the places past them repeat the last one
+    __device__ __forceinline__ void load_part(const uint16_t *codes, int m)
+    {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            c[u] = codes[2 * u < m ? 2 * u : m - 1] | ((uint32_t)codes[2 * u + 1 < m ? 2 * u + 1 : m - 1] << 16);
+    }
+    __device__ __forceinline__ uint32_t code(int u) const { return (u & 1) ? (c[u >> 1] >> 16) : (c[u >> 1] & 0xFFFFu); }
+    // the same for an index that is not a constant (the same in every lane)
+    __device__ __forceinline__ uint32_t code_at(int u) const
+    {
+        const uint32_t w = u < 4 ? (u < 2 ? c[0] : c[1]) : (u < 6 ? c[2] : c[3]);
+        return (u & 1) ? (w >> 16) : (w & 0xFFFFu);
+    }
+};
+
+// eight consecutive values from any 4-byte boundary
+__device__ __forceinline__ void load_floats8(const float *p, float (&f)[8])
 {
-    const uint32_t w = u < 2 ? c.x : u < 4 ? c.y : u < 6 ? c.z : c.w;
-    return (u & 1) ? (w >> 16) : (w & 0xFFFFu);
+    __builtin_memcpy(&f[0], p, 16);
+    __builtin_memcpy(&f[4], p + 4, 16);
 }
 
 // WMODE: 0 = plain sum, 1 = weighted form, 2 = multi-probe form
@@ -143,7 +171,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
     const int tb = (unit / a.n_slices) * a.tb_per_unit + tbl;
     if (tb >= a.ntb) return;
 
-    const long long t = ((long long)tb * kGatherWaves + wave) * TPW + lane / LPT;
+    const long long t = ((long long)tb * (blockDim.x >> 6) + wave) * TPW + lane / LPT;
     const int vec = slice * LPT + (int)(lane % LPT);
     if (t >= a.n || vec >= a.nvec) return;  // no barrier below: early exit is safe
 
@@ -169,98 +197,140 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
         }
     }
 
-    int j0 = 0;
+    // Chunks of eight codes; the k % 8 tables left over are fetched together too (the places past them fetch the last
+    // table again and are not added).
+    const int nch = k >> 3, rest = k & 7;
     if constexpr (WMODE == 2) {
+        // The probes of all tables as one sequence, eight rows at a time, the next eight in flight while these are
+        // added: entry q is probe q % (tau + 1) of table q / (tau + 1) and its share is wp[q]; table and probe of an
+        // entry are the same in every lane.
         const float *wp = a.weights + t * a.code_stride * (tau + 1);
-        const int np = tau + 1;
-        for (int j = 0; j < k; ++j, wp += np) {
-            const uint32_t g = crow[j] & rmask;
-            int pr = 0;
-            for (; pr + 3 <= np; pr += 3) {  // three probes at a time: rows and shares first, then the adds
-                uint4 r[3];
-                float w[3];
-#pragma unroll
-                for (int u = 0; u < 3; ++u) {
-                    const int q = pr + u;
-                    r[u] = row(j, q == 0 ? g : g ^ (1u << (q - 1)));
-                    w[u] = wp[q];
+        const int np = tau + 1, total = k * np;
+        CodeChunk cur, nxt;
+        auto fetch_codes = [&](CodeChunk &c, int j) {
+            if (j + 8 <= k)
+                c.load(crow + j);
+            else if (j < k)
+                c.load_part(crow + j, k - j);
+        };
+        fetch_codes(cur, 0);
+        fetch_codes(nxt, 8);
+        int j = 0, pr = 0;  // next entry to fetch
+        uint32_t g = cur.code(0) & rmask;
+        auto next_row = [&]() -> uint4 {
+            const uint4 r = row(j, pr == 0 ? g : g ^ (1u << (pr - 1)));
+            if (++pr == np) {
+                pr = 0;
+                ++j;
+                if ((j & 7) == 0) {
+                    cur = nxt;
+                    fetch_codes(nxt, j + 8);
                 }
-#pragma unroll
-                for (int u = 0; u < 3; ++u) acc.fma(r[u], w[u]);
+                g = cur.code_at(j & 7) & rmask;
             }
-            for (; pr < np; ++pr) acc.fma(row(j, pr == 0 ? g : g ^ (1u << (pr - 1))), wp[pr]);
+            return r;
+        };
+        uint4 r[2][8];
+        float w[2][8];
+        auto issue = [&](int q, int b) {
+            load_floats8(wp + q, w[b]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r[b][u] = next_row();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto add = [&](int b) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc.fma(r[b][u], w[b][u]);
+        };
+        const int full = total & ~7;
+        if (full) issue(0, 0);
+        for (int q = 0; q < full; q += 16) {
+            if (q + 8 < full) issue(q + 8, 1);
+            add(0);
+            if (q + 8 >= full) break;
+            if (q + 16 < full) issue(q + 16, 0);
+            add(1);
         }
-        j0 = k;
+        for (int q = full; q < total; ++q) {
+            const float wq = wp[q];
+            acc.fma(next_row(), wq);
+        }
     } else if constexpr (WMODE == 1) {
         const float *wrow = a.weights + t * a.code_stride;
-        if (a.codes_vec8) {
-            const uint4 *c8 = reinterpret_cast<const uint4 *>(crow);
-            const float4 *w4 = reinterpret_cast<const float4 *>(wrow);
-            const int nch = k >> 3;
-            uint4 cn = c8[0];
-            float4 wan = w4[0], wbn = w4[1];
+        if (nch) {
+            CodeChunk cn;
+            float wn[8];
+            cn.load(crow);
+            load_floats8(wrow, wn);
             for (int ch = 0; ch < nch; ++ch) {
-                const uint4 c = cn;
-                const float4 wa = wan, wb = wbn;
+                const CodeChunk c = cn;
+                float w[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) w[u] = wn[u];
                 const int nx = ch + 1 < nch ? ch + 1 : ch;  // next chunk's codes and weights go out first
-                cn = c8[nx];
-                wan = w4[2 * nx];
-                wbn = w4[2 * nx + 1];
+                cn.load(crow + nx * 8);
+                load_floats8(wrow + nx * 8, wn);
                 uint4 r[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, code_of(c, u));
-                acc.fma(r[0], wa.x);
-                acc.fma(r[1], wa.y);
-                acc.fma(r[2], wa.z);
-                acc.fma(r[3], wa.w);
-                acc.fma(r[4], wb.x);
-                acc.fma(r[5], wb.y);
-                acc.fma(r[6], wb.z);
-                acc.fma(r[7], wb.w);
+                for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, c.code(u));
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc.fma(r[u], w[u]);
             }
-            j0 = nch * 8;
         }
-        for (; j0 < k; ++j0) acc.fma(row(j0, crow[j0]), wrow[j0]);
-    } else if (a.codes_vec8) {
-        const uint4 *c8 = reinterpret_cast<const uint4 *>(crow);
-        const int nch = k >> 3;  // chunks of 8 codes
+        if (rest) {
+            CodeChunk c;
+            float w[7];
+            c.load_part(crow + nch * 8, rest);
+#pragma unroll
+            for (int u = 0; u < 7; ++u) w[u] = wrow[nch * 8 + (u < rest ? u : rest - 1)];
+            uint4 r[7];
+#pragma unroll
+            for (int u = 0; u < 7; ++u) r[u] = row(nch * 8 + (u < rest ? u : rest - 1), c.code(u));
+#pragma unroll
+            for (int u = 0; u < 7; ++u)
+                if (u < rest) acc.fma(r[u], w[u]);
+        }
+    } else {
         int ch = 0;
         if (nch >= 2) {
-            uint4 c0 = c8[0], c1 = c8[1];
+            CodeChunk c0, c1;
+            c0.load(crow);
+            c1.load(crow + 8);
             for (; ch + 2 <= nch; ch += 2) {
-                const uint4 u0 = c0, u1 = c1;
+                const CodeChunk u0 = c0, u1 = c1;
                 // fetch the next two code chunks before the row loads of this pair go out
                 const int nx = ch + 2 <= nch - 2 ? ch + 2 : nch - 2;
-                c0 = c8[nx];
-                c1 = c8[nx + 1];
+                c0.load(crow + nx * 8);
+                c1.load(crow + nx * 8 + 8);
                 uint4 r[16];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, code_of(u0, u));
+                for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, u0.code(u));
 #pragma unroll
-                for (int u = 0; u < 8; ++u) r[8 + u] = row(ch * 8 + 8 + u, code_of(u1, u));
+                for (int u = 0; u < 8; ++u) r[8 + u] = row(ch * 8 + 8 + u, u1.code(u));
 #pragma unroll
                 for (int u = 0; u < 16; ++u) acc.add(r[u]);
             }
         }
         if (ch < nch) {
-            const uint4 u0 = c8[ch];
+            CodeChunk u0;
+            u0.load(crow + ch * 8);
             uint4 r[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, code_of(u0, u));
+            for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, u0.code(u));
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc.add(r[u]);
-            ++ch;
         }
-        j0 = nch * 8;
-    }
-    for (; j0 + 4 <= k; j0 += 4) {
-        uint4 r[4];
+        if (rest) {
+            CodeChunk c;
+            c.load_part(crow + nch * 8, rest);
+            uint4 r[7];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] = row(j0 + u, crow[j0 + u]);
+            for (int u = 0; u < 7; ++u) r[u] = row(nch * 8 + (u < rest ? u : rest - 1), c.code(u));
 #pragma unroll
-        for (int u = 0; u < 4; ++u) acc.add(r[u]);
+            for (int u = 0; u < 7; ++u)
+                if (u < rest) acc.add(r[u]);
+        }
     }
-    for (; j0 < k; ++j0) acc.add(row(j0, crow[j0]));
 
     // ---- a6: store, streaming (y is written once and not read again here) -------------
     const size_t e = (size_t)t * a.d_out + (size_t)vec * Acc<KIND>::W;

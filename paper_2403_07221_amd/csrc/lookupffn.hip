@@ -43,7 +43,7 @@ struct AttrOnly {
     ~AttrOnly();
 };
 // part 1: the direct gather kernel
-int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3 grid, hipStream_t s);
+int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s);
 int gather_direct_load();  // makes the runtime load part 1's code object now (lookupffn_init)
 // parts 2, 3: the LDS-staged gather kernel (plain sum; weighted and multi-probe)
 int gather_lds_plain_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
@@ -90,27 +90,27 @@ thread_local int t_attr_only = 0;
 
 // ---------------------------------------------------------------- kernel launchers (templates: every part may use them)
 template <int KIND, int LPT>
-void launch_gather_t(const GatherArgs &a, bool probes, dim3 grid, hipStream_t s)
+void launch_gather_t(const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s)
 {
     if (probes)
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 2>), grid, dim3(kGatherThreads), 0, s, a);
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 2>), grid, dim3(threads), 0, s, a);
     else if (a.weights)
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1>), grid, dim3(kGatherThreads), 0, s, a);
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1>), grid, dim3(threads), 0, s, a);
     else
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0>), grid, dim3(kGatherThreads), 0, s, a);
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0>), grid, dim3(threads), 0, s, a);
 }
 
 template <int KIND>
-int launch_gather_lpt(int lpt, const GatherArgs &a, bool probes, dim3 grid, hipStream_t s)
+int launch_gather_lpt(int lpt, const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s)
 {
     switch (lpt) {
-        case 1: launch_gather_t<KIND, 1>(a, probes, grid, s); break;
-        case 2: launch_gather_t<KIND, 2>(a, probes, grid, s); break;
-        case 4: launch_gather_t<KIND, 4>(a, probes, grid, s); break;
-        case 8: launch_gather_t<KIND, 8>(a, probes, grid, s); break;
-        case 16: launch_gather_t<KIND, 16>(a, probes, grid, s); break;
-        case 32: launch_gather_t<KIND, 32>(a, probes, grid, s); break;
-        case 64: launch_gather_t<KIND, 64>(a, probes, grid, s); break;
+        case 1: launch_gather_t<KIND, 1>(a, probes, grid, threads, s); break;
+        case 2: launch_gather_t<KIND, 2>(a, probes, grid, threads, s); break;
+        case 4: launch_gather_t<KIND, 4>(a, probes, grid, threads, s); break;
+        case 8: launch_gather_t<KIND, 8>(a, probes, grid, threads, s); break;
+        case 16: launch_gather_t<KIND, 16>(a, probes, grid, threads, s); break;
+        case 32: launch_gather_t<KIND, 32>(a, probes, grid, threads, s); break;
+        case 64: launch_gather_t<KIND, 64>(a, probes, grid, threads, s); break;
         default: return LFFN_E_UNSUPPORTED;
     }
     return LFFN_OK;
@@ -201,12 +201,12 @@ int launch_bh(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s)
 namespace lffn_host {
 
 #if LFFN_HAS(1)
-int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3 grid, hipStream_t s)
+int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s)
 {
     switch (kind) {
-        case kElemF32: return launch_gather_lpt<kElemF32>(lpt, a, probes, grid, s);
-        case kElemBF16: return launch_gather_lpt<kElemBF16>(lpt, a, probes, grid, s);
-        case kElemF16: return launch_gather_lpt<kElemF16>(lpt, a, probes, grid, s);
+        case kElemF32: return launch_gather_lpt<kElemF32>(lpt, a, probes, grid, threads, s);
+        case kElemBF16: return launch_gather_lpt<kElemBF16>(lpt, a, probes, grid, threads, s);
+        case kElemF16: return launch_gather_lpt<kElemF16>(lpt, a, probes, grid, threads, s);
     }
     return LFFN_E_DTYPE;
 }
@@ -1052,11 +1052,14 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
     a.d_out = d_out;
     const uint32_t row_bytes = (uint32_t)d_out * esz;
     a.nvec = (int)(row_bytes / 16);
-    a.codes_vec8 = j_first == 0 && (k % 8 == 0) && aligned(codes, 16) && (!weights || aligned(weights, 16));
 
     int lpt = opt.lanes_per_token;
     if (lpt == 0) {
         lpt = 8;  // 128-byte slices: one L2 line per (token, table)
+        // rows that are no whole number of lines: every piece crosses into a second line, so twice the width halves
+        // those, while the slice of all tables still fits an XCD's L2 (1001 tokens, 97 half tables of 128 rows of
+        // 1296 bytes: pass 29.7 -> 26.0 us; where the slice does not fit, 96 x 256 rows of 1536 bytes, 139 -> 164 us)
+        if (!T.prepared && row_bytes % 128 != 0 && ((int64_t)k << tau) * 256 <= (int64_t)4 << 20) lpt = 16;
         while (lpt > 1 && lpt / 2 >= a.nvec) lpt /= 2;
     }
     if (T.prepared && lpt * 16 > T.pw) lpt = T.pw / 16;  // a token's piece lies inside one prepared piece
@@ -1072,12 +1075,20 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
         a.slice_stride = (unsigned long long)lpt * 16;
     }
     a.tables = T.p + ((size_t)j_first << tau) * a.row_stride;  // row (j << tau) + code of either layout
-    const int64_t ntb = (n + (int64_t)kGatherWaves * tpw - 1) / ((int64_t)kGatherWaves * tpw);
+    int cus = 0;
+    int rc = device_cus(&cus);
+    if (rc != LFFN_OK) return rc;
+    // too few full workgroups to give every compute unit two: one wave a workgroup spreads the same waves wider
+    const int64_t full = (n + (int64_t)kGatherWaves * tpw - 1) / ((int64_t)kGatherWaves * tpw);
+    const int waves = full * a.n_slices < 2 * (int64_t)cus ? 1 : kGatherWaves;
+    const int64_t ntb = (n + (int64_t)waves * tpw - 1) / ((int64_t)waves * tpw);
     if (ntb > (int64_t(1) << 30)) return LFFN_E_SIZE;
     a.ntb = (int)ntb;
 
     const double table_bytes = (double)k * (double)(1u << tau) * row_bytes;
-    bool xcd = table_bytes > 4.0 * 1024 * 1024 && ntb >= 64;
+    // below about 1000 tokens the order makes no difference; 2000 tokens, weighted pass of 96 tables 48 -> 44 us, tau = 11
+    // 153 -> 121 us
+    bool xcd = table_bytes > 4.0 * 1024 * 1024 && full >= 32;
     if (opt.xcd_order == 1) xcd = true;
     if (opt.xcd_order == -1) xcd = false;
     a.xcd_mode = xcd;
@@ -1096,7 +1107,7 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
     if (blocks > 0x7FFFFFFFLL) return LFFN_E_SIZE;
     const dim3 grid((unsigned)blocks);
     TimedLaunch tl(1, s);
-    int rc = lffn_host::gather_direct_part(T.kind, lpt, a, mode == kProbes, grid, s);
+    rc = lffn_host::gather_direct_part(T.kind, lpt, a, mode == kProbes, grid, 64 * waves, s);
     if (rc != LFFN_OK) return rc;
     LFFN_HIP(hipGetLastError());
     tl.done();
