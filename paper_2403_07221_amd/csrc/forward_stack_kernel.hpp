@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gather_lds_kernel.hpp"
 #include "hash_kernel.hpp"
 
 namespace lffn {
@@ -88,11 +89,24 @@ __global__ __launch_bounds__(1024) void forward_stack_kernel(StackArgs a)
     H1024Lane L;
     h1024_lane_setup((uint32_t)(uintptr_t)tp, lane, L);
     const bool vec_ok = (a.d % 4) == 0;
+    // The signs of a layer's first projection are copied to LDS while the layer before gathers its rows: they are
+    // read once per launch, so every read misses the L2, and requested where they are used that trip is in the chain
+    // of the layers.  They lie in wave 0's transpose area, which is idle between two hashes (held in registers
+    // through the gather they make the fp32 form spill); wave 0 requests, waits for and reads them itself.
+    // 8 tokens through 12 layers of 768 (k = 96): 94.0 -> 90.2 us a pass.
+    static_assert(R * N <= kH1024TransposeWords * 4, "a projection's signs fit the transpose area");
+    auto request_signs = [&](const int8_t *sg) {
+#pragma unroll
+        for (int rd = 0; rd < R; ++rd)
+            lds_dma16(reinterpret_cast<const char *>(sg) + rd * N, lane * 16u, (uint32_t)(uintptr_t)tp + rd * N);
+    };
+    const bool hasher = __builtin_amdgcn_readfirstlane((int)wave) == 0;
+    if (hasher) request_signs(a.signs[0]);
     __syncthreads();
 
     for (int l = 0; l < a.n_layers; ++l) {
         float *cur = rowbuf + (l & 1) * N, *nxt = rowbuf + ((l + 1) & 1) * N;
-        if (wave == 0) {
+        if (hasher) {
             // ---- a1: the row in layout A (lane = i[9:4], register = i[3:0]) -------------------------
             float xv[NREG];
             if (l == 0) {
@@ -108,16 +122,20 @@ __global__ __launch_bounds__(1024) void forward_stack_kernel(StackArgs a)
                 }
             }
             const int8_t *sg = a.signs[l];
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the signs' copy has landed
             for (int p = 0; p < P; ++p) {
                 uint32_t sw[R][4];
 #pragma unroll
                 for (int rd = 0; rd < R; ++rd) {
-                    const uint4 w = *reinterpret_cast<const uint4 *>(sg + ((size_t)p * R + rd) * N + lane * 16);
+                    const uint4 w = p == 0
+                        ? *reinterpret_cast<const uint4 *>(tp + (rd * N + lane * 16) / 4)
+                        : *reinterpret_cast<const uint4 *>(sg + ((size_t)p * R + rd) * N + lane * 16);
                     sw[rd][0] = w.x;
                     sw[rd][1] = w.y;
                     sw[rd][2] = w.z;
                     sw[rd][3] = w.w;
                 }
+                wave_lds_fence();  // the rounds write the transpose area
                 float v[NREG];
 #pragma unroll
                 for (int e = 0; e < NREG; ++e) v[e] = xv[e];
@@ -134,6 +152,7 @@ __global__ __launch_bounds__(1024) void forward_stack_kernel(StackArgs a)
             // ---- a4: code j -> byte offset of row (j << tau) + code ---------------------------------
             for (int j = (int)lane; j < a.k; j += 64)
                 rowoff[j] = (((uint32_t)j << a.tau) + hash_code_at(bitw, (unsigned)j, a.tau)) * a.row_stride;
+            if (l + 1 < a.n_layers) request_signs(a.signs[l + 1]);
         }
         __syncthreads();
 
