@@ -119,7 +119,9 @@ int64_t lookupffn_workspace_bytes_gather(int64_t n_tokens, int k);
  * Whole forward pass: Hash then Gather on the same stream (Sec. 3.1, eq. "lookup").
  * Scratch: lookupffn_workspace_bytes(n_tokens, k) bytes (0 if n_tokens == 0).
  * Batches of up to 512 tokens ("small_tokens" below) whose shape lookupffn_forward_stack takes run as that
- * call's single launch with n_layers = 1 (no scratch touched); y has the same bits either way.
+ * call's single launch with n_layers = 1 (no scratch touched); so do, for widths d of 33 .. 512, those whose
+ * selected rows one launch finishes sooner (while no step is being timed: lookupffn_timing_enable).  y has the same
+ * bits either way.
  */
 int lookupffn_forward(const void *x, const int8_t *signs, const void *tables, void *y,
                       int64_t n_tokens, int d, int k, int tau, int d_out,
@@ -297,7 +299,8 @@ int lookupffn_timing_read_each(int which, double *ms_out, int64_t capacity, int6
  *                                     default: 128 bytes up to tau = 8, 64 bytes from tau = 9 on
  *   "small_tokens"     -1 / 1..2^20   lookupffn_forward: batches up to this many tokens take the single-launch
  *                                     kernel of lookupffn_forward_stack when the shape is that kernel's and no
- *                                     hash or gather path is forced (default 512; -1: never)
+ *                                     hash or gather path is forced (default 512; -1: never); widths of 33 .. 512
+ *                                     have a single-launch kernel of their own under the same option
  *   "token_slots"      1 .. 32        staged kernels: at most this many tokens per lane group and chunk
  *   "hash_path"        1 / 2 / 3      1: always the generic hash kernel; 2: never the token-per-lane-row kernel
  *                                     (four tokens per wavefront at d_pad = 1024, eight at 512); 3: that kernel

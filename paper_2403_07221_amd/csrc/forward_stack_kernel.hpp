@@ -45,6 +45,7 @@ struct StackArgs {
     const char *tables[kStackMaxLayers];   // per layer, all in the same layout
     long long n;
     int d, d_out, k, tau, P, n_layers;
+    int n_rounds;  // read by forward_small_kernel; forward_stack_kernel has its own as a template parameter
     int x_kind;  // element type of x: 0 fp32, 1 bf16, 2 IEEE half
     float scale;
     uint32_t row_dwords;  // dwords of one table row
@@ -65,12 +66,81 @@ __host__ __device__ inline size_t stack_lds_bytes(int P, int k)
     return ((size_t)kH1024TransposeWords + stack_bit_words(P) + stack_code_words(k) + 2 * 1024) * 4;
 }
 
+// a5: every lane sums its dword of the k selected rows, in table order, and hands the one or two columns to `store`.
+template <int KIND, class Store>
+__device__ __forceinline__ void stack_gather(const StackArgs &a, const char *tables, const uint32_t *rowoff, int n_off,
+                                             unsigned tid, Store store)
+{
+    constexpr bool HALF16 = KIND != 0;  // two 16-bit columns per dword
+    constexpr int CH = HALF16 ? kStackChunk / 2 : kStackChunk;  // two accumulators and the unpacking need registers too
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(tables), 0, (int)a.table_bytes, 0x00020000);
+    for (uint32_t q = tid; q < a.row_dwords; q += blockDim.x) {
+        const uint32_t b = q * 4u;
+        const uint32_t voff = (b >> a.piece_shift) * a.slice_stride + (b & ((1u << a.piece_shift) - 1u));
+        float acc0 = 0.0f, acc1 = 0.0f;
+        uint32_t ra[CH], rb[CH];
+        auto issue = [&](uint32_t (&r)[CH], int j0) {
+#pragma unroll
+            for (int u = 0; u < CH; u += 4) {
+                const uint4 o = *reinterpret_cast<const uint4 *>(rowoff + j0 + u);  // same for all lanes
+                r[u] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.x), 0);
+                r[u + 1] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.y), 0);
+                r[u + 2] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.z), 0);
+                r[u + 3] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.w), 0);
+            }
+        };
+        // tables past k in the last chunk were fetched from offset 0 (a valid row) and are not added
+        auto add_n = [&](const uint32_t (&r)[CH], int n_add) {
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                if (u < n_add) {
+                    if constexpr (HALF16) {
+                        const float2 e = widen16x2<KIND == 0 ? 1 : KIND>(r[u]);
+                        acc0 += e.x;
+                        acc1 += e.y;
+                    } else {
+                        acc0 += __uint_as_float(r[u]);
+                    }
+                }
+            }
+        };
+        auto add = [&](const uint32_t (&r)[CH], int j0) {
+            if (j0 + CH <= a.k)
+                add_n(r, CH);
+            else
+                add_n(r, a.k - j0);
+        };
+        const int n_ch = n_off / CH;
+        issue(ra, 0);
+        for (int c = 0; c < n_ch; c += 2) {
+            if (c + 1 < n_ch) issue(rb, (c + 1) * CH);
+            add(ra, c * CH);
+            if (c + 2 < n_ch) issue(ra, (c + 2) * CH);
+            if (c + 1 < n_ch) add(rb, (c + 1) * CH);
+        }
+        store(q * (HALF16 ? 2 : 1), acc0, acc1);
+    }
+}
+
+// column `col` of token t's output (and the next one, for 16-bit rows)
+template <int KIND>
+__device__ __forceinline__ void stack_store_y(const StackArgs &a, long long t, uint32_t col, float acc0, float acc1)
+{
+    const size_t e = (size_t)t * a.d_out + col;
+    if (a.y_kind == kElemF32) {
+        static_cast<float *>(a.y)[e] = acc0;
+        if constexpr (KIND != 0) static_cast<float *>(a.y)[e + 1] = acc1;
+    } else {
+        static_cast<uint16_t *>(a.y)[e] = (uint16_t)narrow16(acc0, a.y_kind);
+        if constexpr (KIND != 0) static_cast<uint16_t *>(a.y)[e + 1] = (uint16_t)narrow16(acc1, a.y_kind);
+    }
+}
+
 template <int R, int KIND>
 __global__ __launch_bounds__(1024) void forward_stack_kernel(StackArgs a)
 {
     constexpr int N = 1024, NREG = 16;
-    constexpr bool HALF16 = KIND != 0;  // two 16-bit columns per dword
-    constexpr int CH = HALF16 ? kStackChunk / 2 : kStackChunk;  // two accumulators and the unpacking need registers too
     extern __shared__ uint32_t lds[];
     const unsigned tid = threadIdx.x;
     const unsigned lane = tid & 63u;
@@ -156,69 +226,16 @@ __global__ __launch_bounds__(1024) void forward_stack_kernel(StackArgs a)
         }
         __syncthreads();
 
-        // ---- a5: every lane sums its dword of the k selected rows, in table order -----------------------
-        const __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(a.tables[l]), 0, (int)a.table_bytes, 0x00020000);
+        // ---- a5 ------------------------------------------------------------------------------------
         const bool last = l + 1 == a.n_layers;
-        for (uint32_t q = tid; q < a.row_dwords; q += blockDim.x) {
-            const uint32_t b = q * 4u;
-            const uint32_t voff = (b >> a.piece_shift) * a.slice_stride + (b & ((1u << a.piece_shift) - 1u));
-            float acc0 = 0.0f, acc1 = 0.0f;
-            uint32_t ra[CH], rb[CH];
-            auto issue = [&](uint32_t (&r)[CH], int j0) {
-#pragma unroll
-                for (int u = 0; u < CH; u += 4) {
-                    const uint4 o = *reinterpret_cast<const uint4 *>(rowoff + j0 + u);  // same for all lanes
-                    r[u] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.x), 0);
-                    r[u + 1] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.y), 0);
-                    r[u + 2] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.z), 0);
-                    r[u + 3] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, __builtin_amdgcn_readfirstlane(o.w), 0);
-                }
-            };
-            // tables past k in the last chunk were fetched from offset 0 (a valid row) and are not added
-            auto add_n = [&](const uint32_t (&r)[CH], int n_add) {
-#pragma unroll
-                for (int u = 0; u < CH; ++u) {
-                    if (u < n_add) {
-                        if constexpr (HALF16) {
-                            const float2 e = widen16x2<KIND == 0 ? 1 : KIND>(r[u]);
-                            acc0 += e.x;
-                            acc1 += e.y;
-                        } else {
-                            acc0 += __uint_as_float(r[u]);
-                        }
-                    }
-                }
-            };
-            auto add = [&](const uint32_t (&r)[CH], int j0) {
-                if (j0 + CH <= a.k)
-                    add_n(r, CH);
-                else
-                    add_n(r, a.k - j0);
-            };
-            const int n_ch = n_off / CH;
-            issue(ra, 0);
-            for (int c = 0; c < n_ch; c += 2) {
-                if (c + 1 < n_ch) issue(rb, (c + 1) * CH);
-                add(ra, c * CH);
-                if (c + 2 < n_ch) issue(ra, (c + 2) * CH);
-                if (c + 1 < n_ch) add(rb, (c + 1) * CH);
-            }
-            const uint32_t col = q * (HALF16 ? 2 : 1);
-            if (!last) {
-                nxt[col] = acc0;
-                if constexpr (HALF16) nxt[col + 1] = acc1;
+        stack_gather<KIND>(a, a.tables[l], rowoff, n_off, tid, [&](uint32_t col, float acc0, float acc1) {
+            if (last) {
+                stack_store_y<KIND>(a, t, col, acc0, acc1);
             } else {
-                const size_t e = (size_t)t * a.d_out + col;
-                if (a.y_kind == kElemF32) {
-                    static_cast<float *>(a.y)[e] = acc0;
-                    if constexpr (HALF16) static_cast<float *>(a.y)[e + 1] = acc1;
-                } else {
-                    static_cast<uint16_t *>(a.y)[e] = (uint16_t)narrow16(acc0, a.y_kind);
-                    if constexpr (HALF16) static_cast<uint16_t *>(a.y)[e + 1] = (uint16_t)narrow16(acc1, a.y_kind);
-                }
+                nxt[col] = acc0;
+                if constexpr (KIND != 0) nxt[col + 1] = acc1;
             }
-        }
+        });
         __syncthreads();
     }
 }

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "bh_hash_kernel.hpp"
+#include "forward_small_kernel.hpp"
 #include "forward_stack_kernel.hpp"
 #include "gather_kernel.hpp"
 #include "gather_lds_kernel.hpp"
@@ -54,6 +55,7 @@ int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3
 int gather_ring_part(int threads, int tok, const GatherRingArgs &a, dim3 grid, hipStream_t s);
 // part 8: hash and gather of a few tokens, one or several chained layers, in one launch
 int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
+int forward_small_part(int L, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
 int forward_stack_load();
 // parts 9, 10: the hash with a token per row of lanes, d_pad = 1024 (four tokens per wavefront) and 512 (eight)
 int hash_row16_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s);
@@ -320,6 +322,30 @@ int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, in
         case 2: return launch_forward_stack_r<2>(kind, a, grid, threads, lds, s);
         case 3: return launch_forward_stack_r<3>(kind, a, grid, threads, lds, s);
         case 4: return launch_forward_stack_r<4>(kind, a, grid, threads, lds, s);
+    }
+    return LFFN_E_UNSUPPORTED;
+}
+
+template <int L>
+int launch_forward_small_l(int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s)
+{
+    switch (kind) {
+        case kElemF32: hipLaunchKernelGGL((forward_small_kernel<L, kElemF32>), grid, dim3(threads), lds, s, a); break;
+        case kElemBF16: hipLaunchKernelGGL((forward_small_kernel<L, kElemBF16>), grid, dim3(threads), lds, s, a); break;
+        case kElemF16: hipLaunchKernelGGL((forward_small_kernel<L, kElemF16>), grid, dim3(threads), lds, s, a); break;
+        default: return LFFN_E_DTYPE;
+    }
+    return LFFN_OK;
+}
+
+int forward_small_part(int L, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s)
+{
+    if (threads < 64 || threads > 1024 || threads % 64) return LFFN_E_UNSUPPORTED;
+    switch (L) {
+        case 6: return launch_forward_small_l<6>(kind, a, grid, threads, lds, s);
+        case 7: return launch_forward_small_l<7>(kind, a, grid, threads, lds, s);
+        case 8: return launch_forward_small_l<8>(kind, a, grid, threads, lds, s);
+        case 9: return launch_forward_small_l<9>(kind, a, grid, threads, lds, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
@@ -1373,6 +1399,11 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
 
 // ---------------------------------------------------------------- the forward pass, all variants
 // ---------------------------------------------------------------- the one-launch path for a few tokens
+int64_t stack_table_bytes(const TableRef &T, int k, int tau, int d_out)
+{
+    return T.prepared ? prepared_tables_bytes(k, tau, d_out) : ((int64_t)k << tau) * d_out * (T.kind ? 2 : 4);
+}
+
 // Whether forward_stack_kernel takes this shape (checked without a HIP call).
 bool stack_shape_ok(const void *x, const int8_t *const *signs, const void *const *tables, int n_layers, int64_t n,
                     int d, int k, int tau, int d_out, int n_rounds, int x_dtype, int table_dtype)
@@ -1387,13 +1418,37 @@ bool stack_shape_ok(const void *x, const int8_t *const *signs, const void *const
         if (!aligned(signs[l], 16)) return false;
     const int P = (int)(((int64_t)k * tau + 1023) / 1024);
     if (stack_lds_bytes(P, k) > 64 * 1024) return false;
-    const TableRef T = table_ref(tables[0], table_dtype, tau);
-    const int64_t bytes = T.prepared ? prepared_tables_bytes(k, tau, d_out)
-                                     : ((int64_t)k << tau) * d_out * (T.kind ? 2 : 4);
-    return bytes < (int64_t(1) << 31);
+    return stack_table_bytes(table_ref(tables[0], table_dtype, tau), k, tau, d_out) < (int64_t(1) << 31);
 }
 
-// Call only with stack_shape_ok(...) true and every argument validated.
+// Whether forward_small_kernel takes this single layer: d_pad 64 .. 512 (any number of rounds, any alignment the
+// entry points accept: rows and signs are read element by element) and a table set below 2 GiB.  `by_rate`: leave out
+// the batches that the two kernels finish sooner.  A token's rows come in through one compute unit, so with one token
+// each (256) the launch saved always counts, beyond that while the rows are few.  One launch against two, us a pass
+// (fp32, tau = 8 where not said):
+//   256 tokens: k = 96, 768 wide 14.9 / 18.7; k = 256, 512 wide 22.5 / 30.9; k = 256, 1024 wide 38.2 / 49.6
+//   512 tokens: k = 64, 256 wide (32 MiB of rows) 10.0 / 12.9; tau = 7, k = 97, 512 wide (97 MiB) 17.5 / 14.3; k = 96,
+//   768 wide (144 MiB) 26.6 / 21.3; k = 8, 64 wide 10.3 / 12.7
+// Tables that do not stay in the 256 MiB memory-side cache gain nothing (tau = 10, k = 128, 1024 wide: 1 token 15.2 /
+// 14.5, 16 tokens 16.4 / 18.3, 64 tokens 26.9 / 24.8).
+// The counters of lookupffn_timing_* time hash and gather apart: while they are on the two kernels run.
+constexpr int64_t kSmallOneEach = 256, kSmallRowBytes = 40 << 20, kSmallTableBytes = 256 << 20;
+bool small_shape_ok(int64_t n, int d, int k, int tau, int d_out, int table_dtype, const void *tables, bool by_rate)
+{
+    const int L = log2_pad(d);
+    if (L < 6 || L > 9 || n > 0x7FFFFFFF || g_tm.on.load()) return false;
+    const int N = 1 << L;
+    const int P = (int)(((int64_t)k * tau + N - 1) / N);
+    if (small_lds_bytes(P, N, k) > 64 * 1024) return false;
+    const TableRef T = table_ref(tables, table_dtype, tau);
+    const int64_t bytes = stack_table_bytes(T, k, tau, d_out);
+    if (bytes >= (int64_t(1) << 31)) return false;
+    if (!by_rate) return true;
+    const int64_t row = (int64_t)d_out * (T.prepared || !T.kind ? 4 : 2);
+    return bytes <= kSmallTableBytes && (n <= kSmallOneEach || n * k * row <= kSmallRowBytes);
+}
+
+// Call only with stack_shape_ok(...) (d_pad = 1024) or small_shape_ok(...) true and every argument validated.
 int launch_forward_stack(const void *x, const int8_t *const *signs, const void *const *tables, void *y, int64_t n,
                          int d, int k, int tau, int d_out, int n_rounds, int n_layers, int x_dtype, int table_dtype,
                          hipStream_t s)
@@ -1412,10 +1467,12 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
     a.d_out = d_out;
     a.k = k;
     a.tau = tau;
-    a.P = (int)(((int64_t)k * tau + 1023) / 1024);
+    const int L = log2_pad(d), N = 1 << L;
+    a.P = (int)(((int64_t)k * tau + N - 1) / N);
     a.n_layers = n_layers;
+    a.n_rounds = n_rounds;
     a.x_kind = x_dtype;  // LFFN_F32 / BF16 / F16 are the kernels' kinds 0 / 1 / 2
-    a.scale = (float)(1.0 / std::sqrt(1024.0));
+    a.scale = (float)(1.0 / std::sqrt((double)N));
     const int64_t rows = int64_t(1) << tau;
     if (T.prepared) {
         a.row_dwords = (uint32_t)d_out;
@@ -1433,13 +1490,15 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
     }
     int threads = (int)((a.row_dwords + 63) / 64 * 64);
     if (threads > 1024) threads = 1024;
+    if (L != 10) threads = std::max(threads, 64 * std::min(a.P, 16));  // a wave per projection
     TimedLaunch tl(1, s);
-    int rc = lffn_host::forward_stack_part(n_rounds, T.kind, a, dim3((unsigned)n), threads, stack_lds_bytes(a.P, k), s);
+    int rc = L == 10
+        ? lffn_host::forward_stack_part(n_rounds, T.kind, a, dim3((unsigned)n), threads, stack_lds_bytes(a.P, k), s)
+        : lffn_host::forward_small_part(L, T.kind, a, dim3((unsigned)n), threads, small_lds_bytes(a.P, N, k), s);
     if (rc != LFFN_OK) return rc;
     LFFN_HIP(hipGetLastError());
     tl.done();
-    t_last_gather = "forward_stack_kernel";
-    t_last_hash = "forward_stack_kernel";
+    t_last_gather = t_last_hash = L == 10 ? "forward_stack_kernel" : "forward_small_kernel";
     return LFFN_OK;
 }
 
@@ -1482,7 +1541,8 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
     const Options opt = options_snapshot();
     if (!h.bh() && mode == kPlain && opt.gather_path == 0 && opt.hash_path == 0 && opt.small_tokens >= 0 &&
         n <= (opt.small_tokens ? opt.small_tokens : kSmallTokensDefault) &&
-        stack_shape_ok(x, &h.signs, &tables, 1, n, d, k, tau, d_out, h.n_rounds, x_dtype, table_dtype))
+        (stack_shape_ok(x, &h.signs, &tables, 1, n, d, k, tau, d_out, h.n_rounds, x_dtype, table_dtype) ||
+         small_shape_ok(n, d, k, tau, d_out, table_dtype, tables, opt.small_tokens == 0)))
         return launch_forward_stack(x, &h.signs, &tables, y, n, d, k, tau, d_out, h.n_rounds, 1, x_dtype, table_dtype, s);
     rc = get_scratch(workspace, workspace_bytes, need, &sc);
     if (rc != LFFN_OK) return rc;
