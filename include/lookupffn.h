@@ -121,7 +121,7 @@ int64_t lookupffn_workspace_bytes_gather(int64_t n_tokens, int k);
  * Batches of up to 512 tokens ("small_tokens" below) whose shape lookupffn_forward_stack takes run as that
  * call's single launch with n_layers = 1 (no scratch touched); so do, for widths d of 33 .. 512, those whose
  * selected rows one launch finishes sooner (while no step is being timed: lookupffn_timing_enable).  y has the same
- * bits either way.
+ * bits either way.  y may overlap x: such a call is two launches unless y is x with rows of the same length in bytes.
  */
 int lookupffn_forward(const void *x, const int8_t *signs, const void *tables, void *y,
                       int64_t n_tokens, int d, int k, int tau, int d_out,
@@ -139,7 +139,8 @@ int64_t lookupffn_workspace_bytes(int64_t n_tokens, int k);
  * and layout (LFFN_PREPARED in table_dtype: every tables[l] is a prepared copy).  One workgroup per token;
  * the per-element sums are the same sequential fp32 sums as lookupffn_forward makes, so the result equals
  * a loop of n_layers lookupffn_forward calls bit for bit.  No scratch memory, no allocation, no
- * synchronisation: the call can be captured in a HIP graph.
+ * synchronisation: the call can be captured in a HIP graph.  y must not overlap x unless it is x with rows of the
+ * same length in bytes.
  * Shapes: 512 < d <= 1024, n_rounds <= 4, n_layers <= 32, one layer's tables below 2 GiB, signs 16-byte
  * aligned, x rows 16-byte aligned when d % 4 == 0; anything else returns LFFN_E_UNSUPPORTED and the caller
  * loops over lookupffn_forward instead.  n_layers > 1 with d_out != d returns LFFN_E_SIZE.

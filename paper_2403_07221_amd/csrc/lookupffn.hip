@@ -1448,6 +1448,22 @@ bool small_shape_ok(int64_t n, int d, int k, int tau, int d_out, int table_dtype
     return bytes <= kSmallTableBytes && (n <= kSmallOneEach || n * k * row <= kSmallRowBytes);
 }
 
+// One launch that reads x and signs and writes y: workgroups run in any order, so y must not lie where another token is
+// still to be read from.  In place with rows of one length is fine: a workgroup reads its own row before it writes it.
+bool one_launch_overlap_ok(const void *x, const int8_t *signs, const void *y, int64_t n, int d, int k, int tau,
+                           int d_out, int n_rounds, int x_dtype, int table_dtype)
+{
+    const int N = 1 << log2_pad(d);
+    const int64_t P = ((int64_t)k * tau + N - 1) / N;
+    const int64_t x_row = (int64_t)d * (x_dtype == LFFN_F32 ? 4 : 2);
+    const int64_t y_row = (int64_t)d_out * ((table_dtype & (LFFN_Y_BF16 | LFFN_Y_F16)) ? 2 : 4);
+    auto apart = [&](const void *p, int64_t bytes) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(y);
+        return a + (uintptr_t)bytes <= b || b + (uintptr_t)(n * y_row) <= a;
+    };
+    return apart(signs, P * n_rounds * N) && (apart(x, n * x_row) || (x == y && x_row == y_row));
+}
+
 // Call only with stack_shape_ok(...) (d_pad = 1024) or small_shape_ok(...) true and every argument validated.
 int launch_forward_stack(const void *x, const int8_t *const *signs, const void *const *tables, void *y, int64_t n,
                          int d, int k, int tau, int d_out, int n_rounds, int n_layers, int x_dtype, int table_dtype,
@@ -1542,7 +1558,8 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
     if (!h.bh() && mode == kPlain && opt.gather_path == 0 && opt.hash_path == 0 && opt.small_tokens >= 0 &&
         n <= (opt.small_tokens ? opt.small_tokens : kSmallTokensDefault) &&
         (stack_shape_ok(x, &h.signs, &tables, 1, n, d, k, tau, d_out, h.n_rounds, x_dtype, table_dtype) ||
-         small_shape_ok(n, d, k, tau, d_out, table_dtype, tables, opt.small_tokens == 0)))
+         small_shape_ok(n, d, k, tau, d_out, table_dtype, tables, opt.small_tokens == 0)) &&
+        one_launch_overlap_ok(x, h.signs, y, n, d, k, tau, d_out, h.n_rounds, x_dtype, table_dtype))
         return launch_forward_stack(x, &h.signs, &tables, y, n, d, k, tau, d_out, h.n_rounds, 1, x_dtype, table_dtype, s);
     rc = get_scratch(workspace, workspace_bytes, need, &sc);
     if (rc != LFFN_OK) return rc;
