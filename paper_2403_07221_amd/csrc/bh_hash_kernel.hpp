@@ -351,49 +351,47 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
             const unsigned pf = (unsigned)(p * a.n_factors + f);
             const unsigned pf_next = pf + 1 < n_pf ? pf + 1 : pf;  // after the last factor: harmless re-reads
             const bool next_B = WPG > 1 && f + 1 < a.n_factors;
-            if (WPG > 1 && f == 0 && w * 256u >= (unsigned)a.d) {
-                // all of this wave's coordinates are padding: zeros stay zeros up to the exchange
+            // ---- block-diagonal factor on the matrix cores ---------------------------------
+            // A wave whose coordinates are all padding (d_pad = 1024, d <= 768) multiplies its zeros like the others: an
+            // infinite or NaN entry makes NaN of them.  Passing over its first factor would save little and cost the
+            // codes-only and register-weight forms registers they spill (d = 768, 16384 tokens: block 16 50.7 against 48.8 us, block 64
+            // weighted 99.3 against 96.7; two projections of tau = 9, block 64, 32768 tokens 363 against 366).
 #pragma unroll
-                for (int i = 0; i < D; ++i) ring[i] = load_quad(pf_next, next_B, i);
-            } else {
-                // ---- block-diagonal factor on the matrix cores ---------------------------------
+            for (int blk = 0; blk < LT / TB; ++blk) {
+                mfma_f4 acc[TB];
 #pragma unroll
-                for (int blk = 0; blk < LT / TB; ++blk) {
-                    mfma_f4 acc[TB];
+                for (int o = 0; o < TB; ++o) {
+                    acc[o] = mfma_f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                    for (int o = 0; o < TB; ++o) {
-                        acc[o] = mfma_f4{0.0f, 0.0f, 0.0f, 0.0f};
+                    for (int ii = 0; ii < TB; ++ii) {
+                        const int qi = (blk * TB + o) * TB + ii;
+                        const u32x4 cur = ring[qi % D];
 #pragma unroll
-                        for (int ii = 0; ii < TB; ++ii) {
-                            const int qi = (blk * TB + o) * TB + ii;
-                            const u32x4 cur = ring[qi % D];
-#pragma unroll
-                            for (int kk = 0; kk < 4; ++kk)
-                                acc[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                    __uint_as_float(cur[kk]), v[blk * TB + ii][kk], acc[o], 0, 0, 0);
-                            ring[qi % D] = qi + D < LQ ? load_quad(pf, layB, qi + D) : load_quad(pf_next, next_B, qi + D - LQ);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
+                        for (int kk = 0; kk < 4; ++kk)
+                            acc[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                __uint_as_float(cur[kk]), v[blk * TB + ii][kk], acc[o], 0, 0, 0);
+                        ring[qi % D] = qi + D < LQ ? load_quad(pf, layB, qi + D) : load_quad(pf_next, next_B, qi + D - LQ);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-#pragma unroll
-                    for (int o = 0; o < TB; ++o)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[blk * TB + o][r] = acc[o][r];
                 }
-
-                // ---- Walsh-Hadamard transform, ascending stride, then the scale -----------------
 #pragma unroll
-                for (int i = 0; i < LT; ++i) tile_stages(v[i]);
+                for (int o = 0; o < TB; ++o)
 #pragma unroll
-                for (int h = 1; h < 4; h <<= 1)  // strides 16, 32: tiles of a unit
-#pragma unroll
-                    for (int i = 0; i < LT; ++i)
-                        if ((i & h) == 0) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) reg_butterfly(v[i][r], v[i + h][r]);
-                        }
-                if constexpr (WPG == 2) unit_stage(v, 1);  // stride 64 is inside a wave in both layouts
+                    for (int r = 0; r < 4; ++r) v[blk * TB + o][r] = acc[o][r];
             }
+
+            // ---- Walsh-Hadamard transform, ascending stride, then the scale -----------------
+#pragma unroll
+            for (int i = 0; i < LT; ++i) tile_stages(v[i]);
+#pragma unroll
+            for (int h = 1; h < 4; h <<= 1)  // strides 16, 32: tiles of a unit
+#pragma unroll
+                for (int i = 0; i < LT; ++i)
+                    if ((i & h) == 0) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) reg_butterfly(v[i][r], v[i + h][r]);
+                    }
+            if constexpr (WPG == 2) unit_stage(v, 1);  // stride 64 is inside a wave in both layouts
             if (layB) exchange(v);
             if constexpr (WPG != 2) unit_stage(v, 1);
             unit_stage(v, 2);
