@@ -346,8 +346,10 @@ def main():
     B.lookupffn_timing_enable(0)
     B.lookupffn_timing_reset()
     kernel = B.lookupffn_last_gather_kernel()
-    fused = kernel == "forward_stack_kernel"          # hash and gather in one kernel: no hash launch of its own
-    assert gather_n == args.steps * launches_per_step and hash_n == (0 if fused else args.warmup * launches_per_step)
+    # hash and gather in one kernel: no hash launch of its own (forward_small_kernel counts as both steps)
+    fused = kernel in ("forward_stack_kernel", "forward_small_kernel")
+    assert gather_n == args.steps * launches_per_step
+    assert hash_n == (0 if kernel == "forward_stack_kernel" else args.warmup * launches_per_step)
 
     ms_per_step = (t1 - t0) * 1e3 / args.steps
     tokens_per_s = w.n_tokens / (ms_per_step * 1e-3)

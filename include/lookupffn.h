@@ -120,8 +120,7 @@ int64_t lookupffn_workspace_bytes_gather(int64_t n_tokens, int k);
  * Scratch: lookupffn_workspace_bytes(n_tokens, k) bytes (0 if n_tokens == 0).
  * Batches of up to 512 tokens ("small_tokens" below) whose shape lookupffn_forward_stack takes run as that
  * call's single launch with n_layers = 1 (no scratch touched); so do, for widths d of 33 .. 512, those whose
- * selected rows one launch finishes sooner (while no step is being timed: lookupffn_timing_enable).  y has the same
- * bits either way.  y may overlap x: such a call is two launches unless y is x with rows of the same length in bytes.
+ * selected rows one launch finishes sooner.  y has the same bits either way.  y may overlap x: such a call is two launches unless y is x with rows of the same length in bytes.
  */
 int lookupffn_forward(const void *x, const int8_t *signs, const void *tables, void *y,
                       int64_t n_tokens, int d, int k, int tau, int d_out,
@@ -275,7 +274,9 @@ int lookupffn_release_workspace(void);
 /*
  * Kernel timing for benchmarks.  `mask` selects which launches are bracketed by a pair of
  * HIP events recorded on the launch stream: bit 0 = hash kernel, bit 1 = gather kernel
- * (0 = off, 3 = both; each bracketed launch costs a few microseconds of queue time).
+ * (0 = off, 3 = both; each bracketed launch costs a few microseconds of queue time).  The mask does not
+ * change which kernels run.  A launch that is hash and gather in one counts with its whole duration: the one
+ * for widths up to 512 under each of the two, the one of lookupffn_forward_stack as gather only.
  * lookupffn_timing_read synchronises on the recorded events and returns, for
  * `which` (0 = hash kernel, 1 = gather kernel), the summed elapsed milliseconds and the
  * number of launches since the last reset; lookupffn_timing_read_each copies the first `capacity`

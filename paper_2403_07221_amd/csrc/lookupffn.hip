@@ -530,7 +530,7 @@ struct TimedLaunch {
     hipStream_t s;
     hipEvent_t a = nullptr, b = nullptr;
     bool on;
-    TimedLaunch(int which_, hipStream_t s_) : which(which_), s(s_), on((g_tm.on.load() >> which_) & 1)
+    TimedLaunch(int which_, hipStream_t s_, bool counted = true) : which(which_), s(s_), on(counted && ((g_tm.on.load() >> which_) & 1))
     {
         if (!on) return;
         {
@@ -1431,12 +1431,11 @@ bool stack_shape_ok(const void *x, const int8_t *const *signs, const void *const
 //   768 wide (144 MiB) 26.6 / 21.3; k = 8, 64 wide 10.3 / 12.7
 // Tables that do not stay in the 256 MiB memory-side cache gain nothing (tau = 10, k = 128, 1024 wide: 1 token 15.2 /
 // 14.5, 16 tokens 16.4 / 18.3, 64 tokens 26.9 / 24.8).
-// The counters of lookupffn_timing_* time hash and gather apart: while they are on the two kernels run.
 constexpr int64_t kSmallOneEach = 256, kSmallRowBytes = 40 << 20, kSmallTableBytes = 256 << 20;
 bool small_shape_ok(int64_t n, int d, int k, int tau, int d_out, int table_dtype, const void *tables, bool by_rate)
 {
     const int L = log2_pad(d);
-    if (L < 6 || L > 9 || n > 0x7FFFFFFF || g_tm.on.load()) return false;
+    if (L < 6 || L > 9 || n > 0x7FFFFFFF) return false;
     const int N = 1 << L;
     const int P = (int)(((int64_t)k * tau + N - 1) / N);
     if (small_lds_bytes(P, N, k) > 64 * 1024) return false;
@@ -1507,13 +1506,15 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
     int threads = (int)((a.row_dwords + 63) / 64 * 64);
     if (threads > 1024) threads = 1024;
     if (L != 10) threads = std::max(threads, 64 * std::min(a.P, 16));  // a wave per projection
-    TimedLaunch tl(1, s);
+    // forward_small_kernel is the call's hash and its gather, and counts as each with its whole duration
+    TimedLaunch th(0, s, L != 10), tl(1, s);
     int rc = L == 10
         ? lffn_host::forward_stack_part(n_rounds, T.kind, a, dim3((unsigned)n), threads, stack_lds_bytes(a.P, k), s)
         : lffn_host::forward_small_part(L, T.kind, a, dim3((unsigned)n), threads, small_lds_bytes(a.P, N, k), s);
     if (rc != LFFN_OK) return rc;
     LFFN_HIP(hipGetLastError());
     tl.done();
+    th.done();
     t_last_gather = t_last_hash = L == 10 ? "forward_stack_kernel" : "forward_small_kernel";
     return LFFN_OK;
 }
