@@ -209,7 +209,8 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
     float *ztail = reinterpret_cast<float *>(area + L::AREA);   // [16 tokens][16]
     uint32_t *bits = area + L::AREA + L::TAIL;                  // [16 tokens][n_bitw]
     const float scale = a.scale;
-    const long long t0 = ((long long)blockIdx.x * S::SETS + set) * kBhTok;  // first token of the set
+    // first token of the set; blocks past one grid row's limit of work-items continue in the next row
+    const long long t0 = (((long long)blockIdx.y * gridDim.x + blockIdx.x) * S::SETS + set) * kBhTok;
 
     // unit u of this wave in layout A (B = false) or B: index of its 64 coordinates
     auto unit_index = [&](bool B, int u) -> unsigned {

@@ -1384,9 +1384,11 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     const int wmode = !out.weights ? 0 : bh_weights_in_registers(tau) ? 1 : 2;
     const int wpg = L == 10 ? 4 : L == 9 ? 2 : 1;  // waves that share a token group
     const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
+    // A launch holds fewer than 2^32 work-items along x: rows of up to 2^22 workgroups, of equal length (a workgroup past
+    // the batch does a full hash of no token).  2^40 tokens, the most the entry points take, are at most 2^14 rows.
     const int64_t blocks = (n + per_block - 1) / per_block;
-    if (blocks > 0x7FFFFFFFLL) return LFFN_E_SIZE;
-    const dim3 grid((unsigned)blocks);
+    const int64_t grid_rows = (blocks + (int64_t(1) << 22) - 1) >> 22;
+    const dim3 grid((unsigned)((blocks + grid_rows - 1) / grid_rows), (unsigned)grid_rows);
     int rc;
     if (L <= 8) rc = lffn_host::bh_lo_part(L, wmode, a, block, grid, s);
     else if (L == 9) rc = lffn_host::bh_512_part(wmode, a, block, grid, s);
