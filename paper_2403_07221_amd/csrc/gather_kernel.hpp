@@ -29,6 +29,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "elem16.hpp"
 
 namespace lffn {
@@ -120,10 +122,17 @@ struct Acc {
 };
 
 // Eight consecutive codes of a token.  A token's codes start at any 2-byte boundary (k may be odd), so the 16 bytes
-// are one load of that alignment, which the hardware takes; fewer than eight are read one by one.
+// are one load of that alignment, which the hardware takes.
 struct CodeChunk {
     uint32_t c[4];
     __device__ __forceinline__ void load(const uint16_t *codes) { __builtin_memcpy(c, codes, 16); }
+    // the first M codes only
+    template <int M>
+    __device__ __forceinline__ void load_first(const uint16_t *codes)
+    {
+        c[0] = c[1] = c[2] = c[3] = 0;
+        __builtin_memcpy(c, codes, 2 * M);
+    }
     // m < 8 codes; the places past them repeat the last one
     __device__ __forceinline__ void load_part(const uint16_t *codes, int m)
     {
@@ -145,6 +154,21 @@ __device__ __forceinline__ void load_floats8(const float *p, float (&f)[8])
 {
     __builtin_memcpy(&f[0], p, 16);
     __builtin_memcpy(&f[4], p + 4, 16);
+}
+
+// f(the number `rest`, 1 .. 7, as a constant); nothing for 0
+template <class F>
+__device__ __forceinline__ void left_over(int rest, F f)
+{
+    switch (rest) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 5: f(std::integral_constant<int, 5>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 7: f(std::integral_constant<int, 7>{}); break;
+    }
 }
 
 // WMODE: 0 = plain sum, 1 = weighted form, 2 = multi-probe form
@@ -197,8 +221,12 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
         }
     }
 
-    // Chunks of eight codes; the k % 8 tables left over are fetched together too (the places past them fetch the last
-    // table again and are not added).
+    // Chunks of eight codes; the k % 8 tables left over are fetched together too, by code for their very number.  One
+    // form for any number, which fetched seven rows and added `rest` of them, cost up to 40 % of a pass over few tables:
+    // 16384 tokens, 768 wide, tau = 6, that form against this one, us: k = 1 15.1 / 11.1, k = 9 27.8 / 20.5, k = 12
+    // 28.1 / 23.3; seven left over gain nothing (k = 15 30.0 / 30.2, weighted 34.5 / 35.6).  Requesting the left-over
+    // codes with the last whole chunk instead held them through the loop (72 -> 76, 93 -> 102 registers): k = 100
+    // weighted 261 -> 286.
     const int nch = k >> 3, rest = k & 7;
     if constexpr (WMODE == 2) {
         // The probes of all tables as one sequence, eight rows at a time, the next eight in flight while these are
@@ -277,19 +305,18 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
                 for (int u = 0; u < 8; ++u) acc.fma(r[u], w[u]);
             }
         }
-        if (rest) {
+        left_over(rest, [&](auto m) {
+            constexpr int M = decltype(m)::value;
             CodeChunk c;
-            float w[7];
-            c.load_part(crow + nch * 8, rest);
+            float w[M];
+            c.template load_first<M>(crow + nch * 8);
+            __builtin_memcpy(w, wrow + nch * 8, 4 * M);
+            uint4 r[M];
 #pragma unroll
-            for (int u = 0; u < 7; ++u) w[u] = wrow[nch * 8 + (u < rest ? u : rest - 1)];
-            uint4 r[7];
+            for (int u = 0; u < M; ++u) r[u] = row(nch * 8 + u, c.code(u));
 #pragma unroll
-            for (int u = 0; u < 7; ++u) r[u] = row(nch * 8 + (u < rest ? u : rest - 1), c.code(u));
-#pragma unroll
-            for (int u = 0; u < 7; ++u)
-                if (u < rest) acc.fma(r[u], w[u]);
-        }
+            for (int u = 0; u < M; ++u) acc.fma(r[u], w[u]);
+        });
     } else {
         int ch = 0;
         if (nch >= 2) {
@@ -320,16 +347,16 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc.add(r[u]);
         }
-        if (rest) {
+        left_over(rest, [&](auto m) {
+            constexpr int M = decltype(m)::value;
             CodeChunk c;
-            c.load_part(crow + nch * 8, rest);
-            uint4 r[7];
+            c.template load_first<M>(crow + nch * 8);
+            uint4 r[M];
 #pragma unroll
-            for (int u = 0; u < 7; ++u) r[u] = row(nch * 8 + (u < rest ? u : rest - 1), c.code(u));
+            for (int u = 0; u < M; ++u) r[u] = row(nch * 8 + u, c.code(u));
 #pragma unroll
-            for (int u = 0; u < 7; ++u)
-                if (u < rest) acc.add(r[u]);
-        }
+            for (int u = 0; u < M; ++u) acc.add(r[u]);
+        });
     }
 
     // ---- a6: store, streaming (y is written once and not read again here) -------------
