@@ -1425,15 +1425,22 @@ bool stack_shape_ok(const void *x, const int8_t *const *signs, const void *const
 
 // Whether forward_small_kernel takes this single layer: d_pad 64 .. 512 (any number of rounds, any alignment the
 // entry points accept: rows and signs are read element by element) and a table set below 2 GiB.  `by_rate`: leave out
-// the batches that the two kernels finish sooner.  A token's rows come in through one compute unit, so with one token
-// each (256) the launch saved always counts, beyond that while the rows are few.  One launch against two, us a pass
-// (fp32, tau = 8 where not said):
+// the batches that the two kernels finish sooner.  A token's rows come in through one compute unit, a lane to each of up
+// to 1024 dwords.  One launch against two, us a pass (fp32, tau = 8 where not said):
 //   256 tokens: k = 96, 768 wide 14.9 / 18.7; k = 256, 512 wide 22.5 / 30.9; k = 256, 1024 wide 38.2 / 49.6
 //   512 tokens: k = 64, 256 wide (32 MiB of rows) 10.0 / 12.9; tau = 7, k = 97, 512 wide (97 MiB) 17.5 / 14.3; k = 96,
 //   768 wide (144 MiB) 26.6 / 21.3; k = 8, 64 wide 10.3 / 12.7
-// Tables that do not stay in the 256 MiB memory-side cache gain nothing (tau = 10, k = 128, 1024 wide: 1 token 15.2 /
-// 14.5, 16 tokens 16.4 / 18.3, 64 tokens 26.9 / 24.8).
-constexpr int64_t kSmallOneEach = 256, kSmallRowBytes = 40 << 20, kSmallTableBytes = 256 << 20;
+// So with at most a token to each compute unit the launch saved always counts, beyond that while the rows are few.  Wider
+// rows are taken 1024 dwords after another, and every turn of up to 32 rows is a chain of about 2 us of its own, however
+// few the tokens: up to four turns one launch wins (2048 wide, k = 64: 1 token 12.0 / 13.6, 128 tokens 14.3 / 15.9), with
+// more only when the two kernels are long too, for many tables and tokens (k = 8, 6144 wide 15.5 / 13.6; k = 40, 4096
+// wide 18.8 / 13.6; k = 64, 4096 wide: 1 token 18.6 / 13.5, 64 tokens 19.7 / 17.4, 128 tokens 23.0 / 25.6; k = 96, 2048
+// wide: 1 token 14.8 / 12.9, 64 tokens 15.5 / 17.9), and with a second token on a compute unit up to one and a half (300
+// tokens: k = 8, 4096 wide 21.3 / 13.5, 2048 wide 14.7 / 13.6; k = 16, 1280 wide 11.2 / 12.7).
+// Tables that do not stay in the 256 MiB memory-side cache gain at some sizes and lose at others, and keep the two kernels
+// (other tokens in every pass, tau = 10, k = 128, 1024 wide: 1 token 15.2 / 14.5, 16 tokens 16.4 / 18.3, 64 tokens 26.9 /
+// 24.8).
+constexpr int64_t kSmallRowBytes = 40 << 20, kSmallTableBytes = 256 << 20;
 bool small_shape_ok(int64_t n, int d, int k, int tau, int d_out, int table_dtype, const void *tables, bool by_rate)
 {
     const int L = log2_pad(d);
@@ -1445,8 +1452,12 @@ bool small_shape_ok(int64_t n, int d, int k, int tau, int d_out, int table_dtype
     const int64_t bytes = stack_table_bytes(T, k, tau, d_out);
     if (bytes >= (int64_t(1) << 31)) return false;
     if (!by_rate) return true;
+    int cus = 0;
+    if (bytes > kSmallTableBytes || device_cus(&cus) != LFFN_OK) return false;
     const int64_t row = (int64_t)d_out * (T.prepared || !T.kind ? 4 : 2);
-    return bytes <= kSmallTableBytes && (n <= kSmallOneEach || n * k * row <= kSmallRowBytes);
+    const int64_t turns = (row * ((k + kStackChunk - 1) / kStackChunk) + 2048) / 4096;
+    if (row > 4096 && !(n <= cus ? turns <= 4 || (k >= 64 && n >= 10 * turns) : turns <= 1)) return false;
+    return n <= cus || n * k * row <= kSmallRowBytes;
 }
 
 // One launch that reads x and signs and writes y: workgroups run in any order, so y must not lie where another token is
