@@ -36,7 +36,8 @@ __global__ __launch_bounds__(1024) void forward_small_kernel(StackArgs a)
     const int n_bitw = small_bit_words(P, N);
     uint32_t *rowoff = bitw + n_bitw;
     const int n_off = stack_code_words(a.k);
-    const long long t = blockIdx.x;
+    const long long t = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    if (t >= a.n) return;  // the whole workgroup
 
     // a1: the row, coordinate lane + 64 r in register r (as hash_kernel lays it out)
     float xv[NREG];

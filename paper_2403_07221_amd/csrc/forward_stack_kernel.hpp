@@ -152,7 +152,8 @@ __global__ __launch_bounds__(1024) void forward_stack_kernel(StackArgs a)
     uint32_t *rowoff = bitw + n_bitw;
     const int n_off = stack_code_words(a.k);
     float *rowbuf = reinterpret_cast<float *>(rowoff + n_off);  // [2][1024]
-    const long long t = blockIdx.x;
+    const long long t = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    if (t >= a.n) return;  // the whole workgroup
 
     // bit string, row offsets (those past k stay 0, a valid row), row buffers (the padding d .. 1023 stays 0)
     for (unsigned i = tid; i < (unsigned)(n_bitw + n_off) + 2u * N; i += blockDim.x) bitw[i] = 0;

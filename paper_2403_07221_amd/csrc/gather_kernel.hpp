@@ -180,15 +180,16 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
     const unsigned wave = threadIdx.x >> 6;
 
     // ---- block -> (slice, token block) -------------------------------------------------
+    const unsigned block = blockIdx.y * gridDim.x + blockIdx.x;  // rows of the grid are a multiple of the XCD count
     int unit, tbl;
     if (a.xcd_mode) {
-        const int xcd = (int)(blockIdx.x % kXcds);
-        const int q = (int)(blockIdx.x / kXcds);
+        const int xcd = (int)(block % kXcds);
+        const int q = (int)(block / kXcds);
         unit = (q / a.tb_per_unit) * kXcds + xcd;
         tbl = q % a.tb_per_unit;
     } else {
-        unit = (int)(blockIdx.x % (unsigned)a.n_units);
-        tbl = (int)(blockIdx.x / (unsigned)a.n_units);
+        unit = (int)(block % (unsigned)a.n_units);
+        tbl = (int)(block / (unsigned)a.n_units);
     }
     if (unit >= a.n_units) return;
     const int slice = unit % a.n_slices;

@@ -792,6 +792,17 @@ int device_cus(int *cus)
     return LFFN_OK;
 }
 
+// A launch holds fewer than 2^32 work-items along x and wraps beyond, with no error: rows of up to 2^21 workgroups (of up
+// to 1024 work-items), of equal length and a multiple of the XCD count; the kernels pass over the workgroups past `blocks`.
+// The most that the entry points take is 2^36 workgroups (2^40 tokens, 16 to each), 2^15 rows.
+dim3 grid_of(int64_t blocks)
+{
+    const int64_t most = int64_t(1) << 21;
+    if (blocks <= most) return dim3((unsigned)blocks);
+    const int64_t rows = (blocks + most - 1) / most;
+    return dim3((unsigned)(((blocks + rows - 1) / rows + kXcds - 1) / kXcds * kXcds), (unsigned)rows);
+}
+
 int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t n, int d, int k, int tau,
                 int n_rounds, int x_dtype, hipStream_t s, const Options &opt)
 {
@@ -1131,7 +1142,7 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
         blocks = (int64_t)a.n_units * ntb;
     }
     if (blocks > 0x7FFFFFFFLL) return LFFN_E_SIZE;
-    const dim3 grid((unsigned)blocks);
+    const dim3 grid = grid_of(blocks);
     TimedLaunch tl(1, s);
     rc = lffn_host::gather_direct_part(T.kind, lpt, a, mode == kProbes, grid, 64 * waves, s);
     if (rc != LFFN_OK) return rc;
@@ -1384,11 +1395,7 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     const int wmode = !out.weights ? 0 : bh_weights_in_registers(tau) ? 1 : 2;
     const int wpg = L == 10 ? 4 : L == 9 ? 2 : 1;  // waves that share a token group
     const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
-    // A launch holds fewer than 2^32 work-items along x: rows of up to 2^22 workgroups, of equal length (a workgroup past
-    // the batch does a full hash of no token).  2^40 tokens, the most the entry points take, are at most 2^14 rows.
-    const int64_t blocks = (n + per_block - 1) / per_block;
-    const int64_t grid_rows = (blocks + (int64_t(1) << 22) - 1) >> 22;
-    const dim3 grid((unsigned)((blocks + grid_rows - 1) / grid_rows), (unsigned)grid_rows);
+    const dim3 grid = grid_of((n + per_block - 1) / per_block);  // a workgroup past the batch does a full hash of no token
     int rc;
     if (L <= 8) rc = lffn_host::bh_lo_part(L, wmode, a, block, grid, s);
     else if (L == 9) rc = lffn_host::bh_512_part(wmode, a, block, grid, s);
@@ -1522,8 +1529,8 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
     // forward_small_kernel is the call's hash and its gather, and counts as each with its whole duration
     TimedLaunch th(0, s, L != 10), tl(1, s);
     int rc = L == 10
-        ? lffn_host::forward_stack_part(n_rounds, T.kind, a, dim3((unsigned)n), threads, stack_lds_bytes(a.P, k), s)
-        : lffn_host::forward_small_part(L, T.kind, a, dim3((unsigned)n), threads, small_lds_bytes(a.P, N, k), s);
+        ? lffn_host::forward_stack_part(n_rounds, T.kind, a, grid_of(n), threads, stack_lds_bytes(a.P, k), s)
+        : lffn_host::forward_small_part(L, T.kind, a, grid_of(n), threads, small_lds_bytes(a.P, N, k), s);
     if (rc != LFFN_OK) return rc;
     LFFN_HIP(hipGetLastError());
     tl.done();
