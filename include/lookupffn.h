@@ -322,13 +322,14 @@ const char *lookupffn_strerror(int status);
 /* Text of the last HIP error seen by this thread's most recent failing call ("" if none). */
 const char *lookupffn_last_hip_error(void);
 /* Which gather kernel the calling thread's most recent gather launch used: "gather_kernel" (direct, rows
- * fetched through L2), "gather_lds_kernel" (table slices staged in LDS, double-buffered) or
- * "forward_stack_kernel" (hash and gather of a few tokens in one launch), "gather_ring_kernel" (on request: prepared tables of up to 256 rows, plain sum; slices staged in an LDS ring,
+ * fetched through L2), "gather_lds_kernel" (table slices staged in LDS, double-buffered),
+ * "forward_stack_kernel" or "forward_small_kernel" (hash and gather of a few tokens in one launch, d of 513 .. 1024 and of
+ * 33 .. 512), "gather_ring_kernel" (on request: prepared tables of up to 256 rows, plain sum; slices staged in an LDS ring,
  * token groups lagged so that their reads never meet in a bank); "" before the first launch. */
 const char *lookupffn_last_gather_kernel(void);
 /* The same for the sign-diagonal hash: "hash_row_kernel" (d_pad = 1024 or 512, a token per row of 16 or 8
- * lanes), "hash1024_kernel" (d_pad = 1024, one token per wavefront), "hash_kernel" (any width) or
- * "forward_stack_kernel"; "" before the first launch (the BH hash has one kernel and is not reported). */
+ * lanes), "hash1024_kernel" (d_pad = 1024, one token per wavefront), "hash_kernel" (any width),
+ * "forward_stack_kernel" or "forward_small_kernel"; "" before the first launch (the BH hash has one kernel and is not reported). */
 const char *lookupffn_last_hash_kernel(void);
 /* major*10000 + minor*100 + patch */
 int lookupffn_version(void);

@@ -16,10 +16,11 @@
 // 16384 tokens 85 / 99 / 131 -> 56 / 70 / 98 us; 128 tokens 72 / 90 / 122 -> 20 / 23 / 30 us; 32768 tokens with
 // k = 170, tau = 9 (two projections) and weights, block 64: 576 -> 364 us.
 //
-// What bounds it: the vector ALU and the fp32 matrix products, one after the other -- a SIMD does not overlap
-// them (measured: waves that only multiply beside waves that only add take the sum of both times).  Counters at
-// 32768 tokens, two projections, block 64: 524 k clocks of MFMA and 313 k clocks of vector ALU per SIMD, 821 k
-// clocks in all.  Of the vector instructions of a wave and round two thirds are the butterflies themselves.
+// What bounds it: the vector ALU and the fp32 matrix products, whose times add up.  Counters at 32768 tokens, two
+// projections, block 64: 524 k clocks of matrix products and 286 k of other vector instructions a SIMD, in 856 k clocks.
+// Of the vector instructions of a wave and round two thirds are the butterflies themselves.  At d_pad = 1024 three waves a
+// SIMD leave 168 registers: codes only and the window form fit, the weights in registers spill six, outside the factors'
+// loop.
 //
 // Tile layout.  A tile is 16 coordinates x 16 tokens in 4 VGPRs: lane l = (token l % 16, group g = l / 16).
 // The product leaves coordinate 4g + r in register r (the MFMA result rows in their own order): strides 1 and
@@ -218,8 +219,11 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
         else if constexpr (WPG == 4) return B ? w + 4u * (unsigned)u : 4u * w + (unsigned)u;
         else return B ? (unsigned)(u & 1) + 2u * w + 4u * (unsigned)(u >> 1) : 4u * w + (unsigned)u;
     };
-    // Operand stream: quad qi of factor pf, one dwordx4 per lane straight to registers (no other wave of the
-    // workgroup reads it), D quads ahead of its use, across factors and projections.
+    // Operand stream: quad qi of factor pf, one dwordx4 per lane straight to registers, D quads ahead of its use,
+    // across factors and projections.  At d_pad = 1024 no other wave of the workgroup reads it; at 512 two and below four
+    // do, which is no loss against the earlier form of the kernel that shared copies in LDS (65536 tokens, one projection,
+    // tau = 8, blocks 16 / 32 / 64, that form against this: d = 256 60 / 75 / 105 -> 45 / 58 / 86 us, d = 512
+    // 150 / 142 / 201 -> 87 / 116 / 171).
     const unsigned n_pf = (unsigned)(P * a.n_factors);
     constexpr unsigned UB = 4 * TB * 1024;  // operand bytes of a unit
     const __amdgpu_buffer_rsrc_t ops = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.apack), 0, (int)(n_pf * (N / 64) * UB), 0x00020000);
