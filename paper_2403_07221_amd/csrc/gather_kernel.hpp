@@ -22,8 +22,8 @@
 // What bounds it: with few tokens the wait for codes and rows, with many the L2.  Codes and weights are read eight at
 // a time whatever k is (one by one they cost a wait per table: 1001 tokens, 97 half tables, weighted 60 -> 20 us), and
 // a launch of fewer than two full workgroups per compute unit goes out as one-wave workgroups.  The multi-probe form
-// keeps eight to sixteen rows in flight across table boundaries (64 tokens, 96 tables, tau = 8: pass 143 -> 82 us;
-// 4096 tokens, tau = 11: 1560 -> 1270 us); the other two measured slower with a second set of rows in flight (2000
+// keeps eight to sixteen rows in flight across table boundaries (64 tokens, 96 tables, tau = 8: gather 136 -> 57 us
+// against three rows at a time; 4096 tokens, tau = 11: 1372 -> 1258 us); the other two measured slower with a second set of rows in flight (2000
 // tokens weighted 48 -> 55 us: the registers cost half the waves).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -141,11 +141,12 @@ struct CodeChunk {
             c[u] = codes[2 * u < m ? 2 * u : m - 1] | ((uint32_t)codes[2 * u + 1 < m ? 2 * u + 1 : m - 1] << 16);
     }
     __device__ __forceinline__ uint32_t code(int u) const { return (u & 1) ? (c[u >> 1] >> 16) : (c[u >> 1] & 0xFFFFu); }
-    // the same for an index that is not a constant (the same in every lane)
-    __device__ __forceinline__ uint32_t code_at(int u) const
+    // code 1 becomes code 0, and so on
+    __device__ __forceinline__ void next()
     {
-        const uint32_t w = u < 4 ? (u < 2 ? c[0] : c[1]) : (u < 6 ? c[2] : c[3]);
-        return (u & 1) ? (w >> 16) : (w & 0xFFFFu);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) c[u] = __builtin_amdgcn_alignbit(c[u + 1], c[u], 16);
+        c[3] >>= 16;
     }
 };
 
@@ -232,36 +233,53 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
     if constexpr (WMODE == 2) {
         // The probes of all tables as one sequence, eight rows at a time, the next eight in flight while these are
         // added: entry q is probe q % (tau + 1) of table q / (tau + 1) and its share is wp[q]; table and probe of an
-        // entry are the same in every lane.
+        // entry are the same in every lane.  Eight codes are held, shifted on by one at every table; the next eight are
+        // requested ahead of the rows of the group before the one that runs past them, so that the chain of row
+        // addresses holds no wait.
+        // Codes read by a running index went through LDS, and refilled at a table they made every row in flight arrive
+        // first: gather alone, that form against this, us: 51 tokens, 8 tables, tau = 9 22.3 / 8.8; 2000 tokens, 4 tables,
+        // tau = 5 22.3 / 8.7; 64 tokens, 96 tables, tau = 8 74 / 57; 16384 tokens, 17 tables, tau = 6 174 / 169; 1 token, 96
+        // tables 61.5 / 64.  A load of codes with every group cost 7 to 11 % with many tokens, and no more than 128
+        // registers (four waves a SIMD, with spills) 40 %.
         const float *wp = a.weights + t * a.code_stride * (tau + 1);
         const int np = tau + 1, total = k * np;
-        CodeChunk cur, nxt;
-        auto fetch_codes = [&](CodeChunk &c, int j) {
-            if (j + 8 <= k)
-                c.load(crow + j);
-            else if (j < k)
-                c.load_part(crow + j, k - j);
-        };
-        fetch_codes(cur, 0);
-        fetch_codes(nxt, 8);
-        int j = 0, pr = 0;  // next entry to fetch
-        uint32_t g = cur.code(0) & rmask;
+        const uint32_t np_inv = 65536u / (uint32_t)np + 1u;  // x / np = x * np_inv >> 16 for the x <= 24 below
+        auto over_np = [&](int x) -> int { return (int)((uint32_t)x * np_inv >> 16); };
+        const bool whole = k >= 8;
+        CodeChunk c, nx;             // codes from table j on; the next ones if `fresh`
+        bool fresh = false;
+        int j = 0, pr = 0;           // next entry to fetch
+        int held = whole ? 8 : k;    // first table whose code is not in c
+        if (whole) c.load(crow);
+        else c.load_part(crow, k);
+        uint4 r[2][8];
+        float w[2][8];
         auto next_row = [&]() -> uint4 {
-            const uint4 r = row(j, pr == 0 ? g : g ^ (1u << (pr - 1)));
+            const uint32_t g = c.code(0) & rmask;
+            const uint4 x = row(j, pr == 0 ? g : g ^ (1u << (pr - 1)));
             if (++pr == np) {
                 pr = 0;
                 ++j;
-                if ((j & 7) == 0) {
-                    cur = nxt;
-                    fetch_codes(nxt, j + 8);
-                }
-                g = cur.code_at(j & 7) & rmask;
+                c.next();
             }
-            return r;
+            return x;
         };
-        uint4 r[2][8];
-        float w[2][8];
+        auto take_codes = [&] {
+            if (!fresh) return;
+            const int first = j + 8 <= k ? j : k - 8;
+            c = nx;
+            for (int s = j - first; s > 0; --s) c.next();
+            held = first + 8;
+            fresh = false;
+        };
         auto issue = [&](int q, int b) {
+            take_codes();
+            // the group after this one starts at table j2 and ends in table j3
+            const int j2 = j + over_np(pr + 8), j3 = j2 + over_np(pr + 8 - (j2 - j) * np + 7);
+            if (j2 < k && (j3 < k ? j3 : k - 1) >= held) {
+                nx.load(crow + (j2 + 8 <= k ? j2 : k - 8));
+                fresh = true;
+            }
             load_floats8(wp + q, w[b]);
 #pragma unroll
             for (int u = 0; u < 8; ++u) r[b][u] = next_row();
@@ -271,15 +289,24 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc.fma(r[b][u], w[b][u]);
         };
+        // whole groups; inside the loop both requests are unconditional, so that an addition waits for its own rows only
         const int full = total & ~7;
+        int q0 = 0;
         if (full) issue(0, 0);
-        for (int q = 0; q < full; q += 16) {
-            if (q + 8 < full) issue(q + 8, 1);
+        for (; q0 + 24 <= full; q0 += 16) {
+            issue(q0 + 8, 1);
             add(0);
-            if (q + 8 >= full) break;
-            if (q + 16 < full) issue(q + 16, 0);
+            issue(q0 + 16, 0);
             add(1);
         }
+        if (q0 + 16 <= full) {
+            issue(q0 + 8, 1);
+            add(0);
+            add(1);
+        } else if (full) {
+            add(0);
+        }
+        if (full < total) take_codes();
         for (int q = full; q < total; ++q) {
             const float wq = wp[q];
             acc.fma(next_row(), wq);

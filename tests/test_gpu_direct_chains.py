@@ -78,6 +78,15 @@ def test_left_over_tables(k, tdt, d_out):
     check(61, k, 4, d_out, tdt)
 
 
+# the probe sequence: two to seventeen rows a table, one to five tables in eight rows, whole and partial last eights, less
+# than eight codes, codes of the last eight reached at every place
+@pytest.mark.parametrize("tau", [1, 2, 3, 7, 8, 11, 16])
+@pytest.mark.parametrize("k", [1, 7, 8, 9, 12, 15, 16, 17, 23, 41])
+def test_probe_sequences(k, tau):
+    print(f"direct chains, probes k={k} tau={tau}", flush=True)
+    check(21, min(k, 9) if tau == 16 else k, tau, 8, "f32")
+
+
 # By default a token has eight lanes and a full workgroup 32 tokens; fewer than 512 full workgroups go out as one-wave
 # ones, and from 1024 tokens on tables over 4 MiB in the XCD order: one wave, plain and XCD; four waves, plain and XCD
 @pytest.mark.parametrize("n,k,tau,d_out,tdt", [(1030, 5, 4, 256, "f32"), (1100, 9, 9, 256, "f32"), (2817, 3, 5, 768, "f32"),
