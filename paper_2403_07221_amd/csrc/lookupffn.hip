@@ -1124,8 +1124,9 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
 
     const double table_bytes = (double)k * (double)(1u << tau) * row_bytes;
     // below about 1000 tokens the order makes no difference; 2000 tokens, weighted pass of 96 tables 48 -> 44 us, tau = 11
-    // 153 -> 121 us
-    bool xcd = table_bytes > 4.0 * 1024 * 1024 && full >= 32;
+    // 153 -> 121 us.  Tokens decide, not workgroups: with the 64-byte pieces of prepared tables from tau = 9 on a workgroup has
+    // 64 (1664 tokens, k = 170, 512 wide: tau = 10 pass 137 -> 118 us, tau = 9 105 -> 93, weighted 120 -> 109)
+    bool xcd = table_bytes > 4.0 * 1024 * 1024 && (full >= 32 || n >= 1000);
     if (opt.xcd_order == 1) xcd = true;
     if (opt.xcd_order == -1) xcd = false;
     a.xcd_mode = xcd;

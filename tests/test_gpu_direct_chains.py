@@ -47,7 +47,7 @@ def chain(codes, factors, rows32):
     return acc
 
 
-def check(n, k, tau, d_out, tdt):
+def check(n, k, tau, d_out, tdt, prepared=False):
     rng = np.random.default_rng(n + 31 * k)
     tables = synth.make_tables(n + k, k, 1 << tau, d_out, tdt)
     codes = rng.integers(0, 1 << tau, size=(n, k)).astype(np.uint16)
@@ -55,6 +55,8 @@ def check(n, k, tau, d_out, tdt):
     p = rng.uniform(0.0, 1.0, size=(n, k, tau + 1)).astype(np.float32)
     cd, td = torch.from_numpy(codes.view(np.int16)).cuda(), B.to_device(tables)
     wd, pd = torch.from_numpy(w).cuda(), torch.from_numpy(p).cuda()
+    if prepared:
+        td = B.lookupffn_prepare_tables(td)
     B.lookupffn_set_option("gather_path", 1)
     try:
         y = B.lookupffn_gather(cd, td).cpu().numpy()
@@ -94,6 +96,15 @@ def test_probe_sequences(k, tau):
 def test_default_launch_forms(n, k, tau, d_out, tdt):
     print(f"direct chains n={n} k={k} tau={tau} d_out={d_out} {tdt}", flush=True)
     check(n, k, tau, d_out, tdt)
+
+
+# prepared tables of 512 and 1024 rows are read in pieces of four lanes (a full workgroup has 64 tokens): below and from
+# 1000 tokens on, the plain and the XCD order
+@pytest.mark.parametrize("n", [999, 1000, 1664])
+@pytest.mark.parametrize("k,tau,d_out", [(11, 9, 264), (6, 10, 520)])
+def test_prepared_pieces_in_both_orders(n, k, tau, d_out):
+    print(f"direct chains, prepared n={n} k={k} tau={tau} d_out={d_out}", flush=True)
+    check(n, k, tau, d_out, "f32", prepared=True)
 
 
 # 2817 tokens of 50 pieces of 16 bytes are 575 to 708 full workgroups at every number of lanes: four waves each, the last one's
