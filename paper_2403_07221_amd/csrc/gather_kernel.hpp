@@ -55,6 +55,7 @@ struct GatherArgs {
     int xcd_mode;      // 1: block order is XCD-sliced (see above); 0: plain
     int code_stride;   // codes (and weights, and groups of 1 + tau shares) per token in the arrays; k unless
                        // the launch covers only some of the tables
+    int four_rows;     // plain sum: 1: four rows of a token in flight; 0: sixteen
     int accumulate;    // 1: the sums start from what y holds (fp32 y, fp32 rows) instead of zero
     // The 16-byte piece q of row r = (j << tau) + code in slice s sits at
     //   tables + (s / spp) * slice_stride + (s % spp) * LPT*16 + r * row_stride + q*16
@@ -346,45 +347,52 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
             for (int u = 0; u < M; ++u) acc.fma(r[u], w[u]);
         });
     } else {
-        int ch = 0;
-        if (nch >= 2) {
-            CodeChunk c0, c1;
-            c0.load(crow);
-            c1.load(crow + 8);
-            for (; ch + 2 <= nch; ch += 2) {
-                const CodeChunk u0 = c0, u1 = c1;
-                // fetch the next two code chunks before the row loads of this pair go out
-                const int nx = ch + 2 <= nch - 2 ? ch + 2 : nch - 2;
-                c0.load(crow + nx * 8);
-                c1.load(crow + nx * 8 + 8);
-                uint4 r[16];
+        auto add_rows = [&](auto m, int j0) {  // tables j0 .. j0 + m - 1, all rows in flight
+            constexpr int M = decltype(m)::value;
+            CodeChunk c;
+            c.template load_first<M>(crow + j0);
+            uint4 r[M];
+#pragma unroll
+            for (int u = 0; u < M; ++u) r[u] = row(j0 + u, c.code(u));
+#pragma unroll
+            for (int u = 0; u < M; ++u) acc.add(r[u]);
+        };
+        if (a.four_rows) {
+            int j0 = 0;
+            for (; j0 + 4 <= k; j0 += 4) add_rows(std::integral_constant<int, 4>{}, j0);
+            left_over(k & 3, [&](auto m) { add_rows(m, j0); });
+        } else {
+            int ch = 0;
+            if (nch >= 2) {
+                CodeChunk c0, c1;
+                c0.load(crow);
+                c1.load(crow + 8);
+                for (; ch + 2 <= nch; ch += 2) {
+                    const CodeChunk u0 = c0, u1 = c1;
+                    // fetch the next two code chunks before the row loads of this pair go out
+                    const int nx = ch + 2 <= nch - 2 ? ch + 2 : nch - 2;
+                    c0.load(crow + nx * 8);
+                    c1.load(crow + nx * 8 + 8);
+                    uint4 r[16];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, u0.code(u));
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) r[8 + u] = row(ch * 8 + 8 + u, u1.code(u));
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) acc.add(r[u]);
+                }
+            }
+            if (ch < nch) {
+                CodeChunk u0;
+                u0.load(crow + ch * 8);
+                uint4 r[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, u0.code(u));
 #pragma unroll
-                for (int u = 0; u < 8; ++u) r[8 + u] = row(ch * 8 + 8 + u, u1.code(u));
-#pragma unroll
-                for (int u = 0; u < 16; ++u) acc.add(r[u]);
+                for (int u = 0; u < 8; ++u) acc.add(r[u]);
             }
+            left_over(rest, [&](auto m) { add_rows(m, nch * 8); });
         }
-        if (ch < nch) {
-            CodeChunk u0;
-            u0.load(crow + ch * 8);
-            uint4 r[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) r[u] = row(ch * 8 + u, u0.code(u));
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc.add(r[u]);
-        }
-        left_over(rest, [&](auto m) {
-            constexpr int M = decltype(m)::value;
-            CodeChunk c;
-            c.template load_first<M>(crow + nch * 8);
-            uint4 r[M];
-#pragma unroll
-            for (int u = 0; u < M; ++u) r[u] = row(nch * 8 + u, c.code(u));
-#pragma unroll
-            for (int u = 0; u < M; ++u) acc.add(r[u]);
-        });
     }
 
     // ---- a6: store, streaming (y is written once and not read again here) -------------

@@ -1127,6 +1127,19 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
     // 153 -> 121 us.  Tokens decide, not workgroups: with the 64-byte pieces of prepared tables from tau = 9 on a workgroup has
     // 64 (1664 tokens, k = 170, 512 wide: tau = 10 pass 137 -> 118 us, tau = 9 105 -> 93, weighted 120 -> 109)
     bool xcd = table_bytes > 4.0 * 1024 * 1024 && (full >= 32 || n >= 1000);
+    // Rows of a token in flight in the plain sum, sixteen or four.  Sixteen hide the waits of few wavefronts; with many, and a
+    // slice of all tables beyond an XCD's L2, four keep the wavefronts closer together in the tables, so more rows are still in
+    // the L2.  That pays for rows of 16-bit elements from about nine wavefronts a compute unit on, and for ragged fp32 rows
+    // while there are fewer than thirty; whole fp32 lines and prepared tables gain nothing.  Gather, 16 / 4 rows, us:
+    //   bf16, k = 170, tau = 9: 504 wide 1500 tokens 28 / 39, 3932 96 / 60, 16384 422 / 394, 40000 1088 / 1220; 512 wide 2000
+    //   27 / 36, 8000 118 / 93; k = 128, tau = 10, 1024 wide: 1000 30 / 31, 4000 117 / 87; 97 tables of tau = 8 (3 MiB a
+    //   slice), 768 wide 4000 36 / 48
+    //   fp32, k = 170, tau = 9: 504 wide 1500 70 / 49, 3000 129 / 111, 8000 356 / 419; 512 wide 4000 112 / 102, 16384 456 /
+    //   473; prepared, 768 wide 2500 120 / 141
+    const bool beyond_l2 = ((int64_t)k << tau) * lpt * 16 > (int64_t)4 << 20, ragged = row_bytes % 128 != 0;
+    const int64_t cu_waves = (n + tpw - 1) / tpw * a.n_slices / cus;
+    a.four_rows = mode == kPlain && beyond_l2 && !T.prepared && cu_waves >= 9 &&
+                  (T.kind ? !ragged || cu_waves <= 128 : ragged && cu_waves <= 30);
     if (opt.xcd_order == 1) xcd = true;
     if (opt.xcd_order == -1) xcd = false;
     a.xcd_mode = xcd;

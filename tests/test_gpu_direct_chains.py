@@ -98,6 +98,24 @@ def test_default_launch_forms(n, k, tau, d_out, tdt):
     check(n, k, tau, d_out, tdt)
 
 
+# four rows in flight instead of sixteen: 16-bit rows, and fp32 rows of no whole number of lines, when a slice of all the
+# tables is over 4 MiB and there are nine wavefronts to a compute unit (below and from there on), every number left over
+@pytest.mark.parametrize("tdt,d_out,few,many", [("bf16", 776, 1400, 1500), ("f16", 1024, 1100, 1200), ("f32", 504, 1100, 1300)])
+@pytest.mark.parametrize("k", [17, 18, 19, 20])
+def test_four_rows_in_flight(tdt, d_out, few, many, k):
+    print(f"direct chains, four rows k={k} {tdt} d_out={d_out}", flush=True)
+    tables = synth.make_tables(k, k, 2048, d_out, tdt)
+    codes = np.random.default_rng(k).integers(0, 2048, size=(many, k)).astype(np.uint16)
+    want = oracle.gather(codes, tables, acc64=False)
+    cd, td = torch.from_numpy(codes.view(np.int16)).cuda(), B.to_device(tables)
+    B.lookupffn_set_option("gather_path", 1)
+    try:
+        for n in (few, many):
+            assert np.array_equal(B.lookupffn_gather(cd[:n], td).cpu().numpy(), want[:n])
+    finally:
+        B.lookupffn_set_option("gather_path", 0)
+
+
 # prepared tables of 512 and 1024 rows are read in pieces of four lanes (a full workgroup has 64 tokens): below and from
 # 1000 tokens on, the plain and the XCD order
 @pytest.mark.parametrize("n", [999, 1000, 1664])
