@@ -239,8 +239,8 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
         // addresses holds no wait.
         // Codes read by a running index went through LDS, and refilled at a table they made every row in flight arrive
         // first: gather alone, that form against this, us: 51 tokens, 8 tables, tau = 9 22.3 / 8.8; 2000 tokens, 4 tables,
-        // tau = 5 22.3 / 8.7; 64 tokens, 96 tables, tau = 8 74 / 57; 16384 tokens, 17 tables, tau = 6 174 / 169; 1 token, 96
-        // tables 61.5 / 64.  A load of codes with every group cost 7 to 11 % with many tokens, and no more than 128
+        // tau = 5 22.3 / 8.7; 64 tokens, 96 tables, tau = 8 73 / 53; 16384 tokens, 17 tables, tau = 6 171 / 167; 1 token, 96
+        // tables 59.5 / 60.4, 170 tables 94 / 99.  A load of codes with every group cost 7 to 11 % with many tokens, and no more than 128
         // registers (four waves a SIMD, with spills) 40 %.
         const float *wp = a.weights + t * a.code_stride * (tau + 1);
         const int np = tau + 1, total = k * np;
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
         float w[2][8];
         auto next_row = [&]() -> uint4 {
             const uint32_t g = c.code(0) & rmask;
-            const uint4 x = row(j, pr == 0 ? g : g ^ (1u << (pr - 1)));
+            const uint4 x = row(j, g ^ ((1u << pr) >> 1));  // probe 0: the selected row; p: bit p - 1 flipped
             if (++pr == np) {
                 pr = 0;
                 ++j;
