@@ -12,14 +12,9 @@ SRC = PKG / "csrc" / "lookupffn.hip"
 LIB = PKG / "liblookupffn.so"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-N_PARTS = 12         # csrc/lookupffn.hip compiles as parts 0 .. 11 (-DLFFN_PART=i), linked together
+N_PARTS = 11         # csrc/lookupffn.hip compiles as parts 0 .. 10 (-DLFFN_PART=i), linked together
 SLOW_FIRST = [6, 5, 4, 3]   # the BH kernels take the longest: start them first
 OBJ_DIR = PKG / "_build"
-# Per-part compiler settings.  Part 11 is the staged gather's plain 13-slot, 128-byte-slice kernel: with the
-# instruction scheduler set to favour instruction-level parallelism it measured 4 % faster (93.5 against 97.4 us
-# for 16384 tokens x 96 tables, alternating runs on one machine); the 64-byte-slice kernels measured 4 % slower
-# with it, so they stay with the default.
-PART_FLAGS = {11: ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -47,7 +42,7 @@ def build_library(verbose: bool = False, jobs: int | None = None, only_parts=Non
     keep = only_parts is not None
     tag = "dev" if keep else str(os.getpid())
     objs = [OBJ_DIR / f"lookupffn_part{i}.{tag}.o" for i in range(N_PARTS)]
-    cmds = [[HIPCC, *FLAGS, *PART_FLAGS.get(i, []), f"-DLFFN_PART={i}", "-c", "-o", str(objs[i]), str(SRC)]
+    cmds = [[HIPCC, *FLAGS, f"-DLFFN_PART={i}", "-c", "-o", str(objs[i]), str(SRC)]
             for i in range(N_PARTS)]
     tmp = LIB.with_suffix(f".so.tmp{os.getpid()}")
     try:

@@ -22,11 +22,17 @@
 // quad-shared: each lane keeps only those of the token slots i with i % 4 ==
 // its position in its quad, and a use takes the word through a DPP quad
 // broadcast -- a quarter of the registers and load instructions, one cache
-// line per load.  The vector-memory instructions of a stage (next
-// stage's row copies and codes) are issued a few at a time between the LDS
-// read batches: a wave issues in order, so a burst of them at the top of the
-// stage would hold every wave at the texture-address queue while LDS and the
-// vector ALU sit idle.
+// line per load.
+//
+// What bounds it (16384 tokens, k = 96, tau = 8, 768 wide; pass of hash and gather): the hand-over of the stages -- a stage's
+// copies must land before the barrier, and a build without any row read took as long as the whole (121 us) -- then the
+// bank conflicts of the row reads (no copies: 95 us; neither: 57).  So the next stage's copies are the first thing a stage
+// issues (spread over its reads: 112 -> 109 us), nothing may wait for them in mid-stage (scratch reloads did: weighted 165 ->
+// 141 us, tau = 10 335 -> 291), and a wave's instructions are laid out so that neighbours do not depend on one another (a
+// row's address and weight are formed one slot ahead: 109 -> 105.5 us; multi-probe 1030 -> 729).  With the multi-probe
+// form's lagging groups and shares loaded two sweeps ahead, pass before and after all of it: plain 118 -> 105.6, weighted
+// 165 -> 136, multi-probe 898 -> 682, 65536 bf16 tokens 383 -> 349, tau = 10, k = 128, 1024 wide 335 -> 267, tau = 9, k = 170,
+// 32768 tokens, weighted 876 -> 765 us.
 //
 // Weighted form (Sec. 4: y = sum_j w_j T_j[code_j]): the fp32 weights come table-major and
 // token-contiguous (wpk[j][n_pad]) and are quad-shared like the code words; each row is
@@ -59,15 +65,14 @@ constexpr int kLdsThreads = 1024;
 // column slice of that width and kLdsThreads / SW token groups.
 constexpr int kLdsBufBytes = 64 * 1024;      // one staging buffer (two of them are in use)
 constexpr int kLdsMaxTok = 16;               // token slots per lane the packed padding allows for
-#ifndef LFFN_LDS_RB
-#define LFFN_LDS_RB 3
-#endif
-#ifndef LFFN_LDS_CO
-#define LFFN_LDS_CO 0   // read batch in which the first code load of the next stage is issued
-#endif
-#ifndef LFFN_LDS_WO
-#define LFFN_LDS_WO 4   // same for its first weight load
-#endif
+// f += r, the sums staying in the registers they are in: left to itself the compiler puts a sum where the row was, the
+// accumulators wander through the register file and the 16-slot forms spill
+__device__ __forceinline__ void add_in_place(float (&f)[4], const uint4 &r)
+{
+    asm volatile("v_add_f32 %0, %0, %4\n\tv_add_f32 %1, %1, %5\n\tv_add_f32 %2, %2, %6\n\tv_add_f32 %3, %3, %7"
+                 : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3])
+                 : "v"(r.x), "v"(r.y), "v"(r.z), "v"(r.w));
+}
 
 struct GatherLdsArgs {
     const uint32_t *packed;  // [k/2][n_pad] packed codes (see hash_kernel.hpp)
@@ -96,9 +101,10 @@ struct GatherLdsArgs {
     unsigned long long slice_stride;
 };
 
-// bytes of LDS the kernel needs: two buffers (sw = lanes per token)
-__host__ __device__ inline size_t gather_lds_bytes(int tau, int sw)
+// bytes of LDS the kernel needs: two buffers (sw = lanes per token; alternating rows: and one row piece of zeros)
+__host__ __device__ inline size_t gather_lds_bytes(int tau, int sw, bool alternating)
 {
+    if (alternating) return 2 * (size_t)kLdsBufBytes + 16 * (size_t)sw;
     const size_t tbl = ((size_t)16 * sw) << tau;
     return 2 * (2 * tbl <= (size_t)kLdsBufBytes ? 2 * tbl : tbl);
 }
@@ -108,6 +114,14 @@ __device__ __forceinline__ uint32_t split_at(uint32_t len, uint32_t parts, uint3
 {
     const uint32_t base = len / parts, rem = len - base * parts;
     return base * i + (i < rem ? i : rem);
+}
+
+// a pointer that is the same in every lane, in scalar registers whatever the compiler computed it with
+__device__ __forceinline__ const char *scalar_ptr(const char *p)
+{
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const char *>((uint64_t)hi << 32 | lo);  // (through uint32_t: the builtin's int would be sign-extended)
 }
 
 // One global_load_lds_dwordx4: every active lane copies 16 bytes from gbase + voff to LDS byte
@@ -123,15 +137,51 @@ __device__ __forceinline__ void lds_dma16(const char *gbase, uint32_t voff, uint
 #pragma clang diagnostic ignored "-Winline-asm"
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
-                 : "s"(m), "v"(voff), "s"(gbase)
+                 : "s"(m), "v"(voff), "s"(scalar_ptr(gbase))
                  : "memory", "m0");
 #pragma clang diagnostic pop
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// batch that issues the i-th deferred load of a stage with nbt batches: i itself, wrapped
-__host__ __device__ constexpr int vm_slot(int i, int nbt) { return i % nbt; }
+// The same for the lanes of `lanes` only (every lane is active outside): a lane's 16 bytes go to lds_base + 16 * lane whichever
+// others take part.  The mask is set inside the statement: a branch on the lane would make the compiler treat uniform values
+// that change beside it as divergent.
+__device__ __forceinline__ void lds_dma16_lanes(const char *gbase, uint32_t voff, uint32_t lds_base, uint64_t lanes)
+{
+    const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
+    uint64_t all;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, exec\n\ts_mov_b64 exec, %4\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %2, %3\n\t"
+                 "s_mov_b64 exec, %0"
+                 : "=&s"(all)
+                 : "s"(m), "v"(voff), "s"(scalar_ptr(gbase)), "s"(lanes)
+                 : "memory", "m0");
+#pragma clang diagnostic pop
+}
+
+// word 3 of a raw buffer resource: 32-bit data format, offsets checked against the byte count
+constexpr int kBufferRsrcFlags = 0x00020000;
+
+// Token group g and 16-byte column piece q of thread `tid` (SW lanes per token).  A ds_read_b128 of a wave is served in
+// passes of 16 lanes, and a pass is not 16 consecutive lanes: of the eight quads of 32 lanes it takes 0, 3, 5, 6, then
+// 1, 2, 4, 7 (found by timing reads of chosen bank patterns).  With the eight lanes of a token in consecutive lanes a pass holds
+// halves of four rows and is conflict-free only if two pairs of rows differ in parity; with a token on the quads
+// (0, 3), (5, 6), (1, 2) or (4, 7) a pass holds two whole rows and needs one pair to differ: random 128-byte rows are read at
+// 170 instead of 144 bytes per clock and compute unit (conflict-free 240).  A token of four lanes is one quad either way.
+template <int SW>
+__device__ __forceinline__ void read_role(uint32_t tid, uint32_t &g, uint32_t &q)
+{
+    if constexpr (SW == 8) {
+        const uint32_t b0 = tid >> 2, b1 = tid >> 3, b2 = (tid >> 4) & 1u;  // bits of the quad number (b0, b1: bit 0)
+        g = (tid >> 5) * 4u + ((b0 ^ b1 ^ b2) & 1u) * 2u + b2;
+        q = (b1 & 1u) * 4u + (tid & 3u);
+    } else {
+        g = tid / SW;
+        q = tid % SW;
+    }
+}
 
 // value of `v` in lane Q of the caller's quad (DPP quad_perm [Q,Q,Q,Q])
 template <int Q>
@@ -152,16 +202,15 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t v, int q)
 // Tables per stage TPS: two (FR <= 2: both halves of a code word are consumed in one stage) or one
 // (FR = 4: a 64 KB slice fills a buffer; even stages take the low half of the code word, odd stages
 // the high half).  SW = lanes per token: 8 (128-byte column slices; tau = 7, 8, 9 <-> FR = 1, 2, 4)
-// or 4 (64-byte slices; tau = 8, 9, 10 <-> FR = 1, 2, 4).  The packed codes must be scaled by the
-// row-piece bytes: code << 7 for SW = 8 (what the hash kernels write), code << 6 for SW = 4 (written
-// by the re-pack kernel from ABI codes; 1023 << 7 would not fit the 16-bit half of a code word).
-// PROBES (with WEIGHTED): the multi-probe form (Sec. 3.1, eq. "partial_softmax"): every stage is swept
+// or 4 (64-byte slices; tau = 8, 9, 10 <-> FR = 1, 2, 4).  The packed codes must be scaled by the LDS row
+// stride (gather_lds_shift).
+// MODE: 0 plain sum, 1 weighted, 2 multi-probe (Sec. 3.1, eq. "partial_softmax"): every stage is swept
 // 1 + tau times, sweep p reading the rows code ^ flip(p) with the shares of probe p
 // (wpk[(j * (1 + tau) + p) * n_pad + t]); the staged slice is copied once per stage.
-template <int TOK, int FR, bool WEIGHTED, int SW = 8, bool PROBES = false>
+template <int TOK, int FR, int MODE, int SW = 8>
 __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a)
 {
-    static_assert(!PROBES || WEIGHTED, "the multi-probe form carries weights");
+    constexpr bool WEIGHTED = MODE != 0, PROBES = MODE == 2;
     static_assert(TOK <= kLdsMaxTok, "packed-code padding covers 16 token slots");
     static_assert(FR == 1 || FR == 2 || FR == 4, "table slices of 16, 32 or 64 KB");
     static_assert(SW == 8 || SW == 4, "128- or 64-byte column slices");
@@ -169,13 +218,20 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
     constexpr int G = kLdsThreads / SW;   // token groups per workgroup = rows per copy round
     constexpr uint32_t PIECE = SW * 16u;  // bytes of a row inside the slice
     static_assert(TPS * FR * 16 * 1024 <= kLdsBufBytes, "a stage fits one buffer");
+    // Multi-probe form, tables of up to 32 KB: the rows of two consecutive tables alternate in LDS (four tables in all),
+    // and half of the token groups of a read pass lag one table behind the others, so that a pass reads one table in each
+    // half of the banks (see read_role).  Every group still takes its tables, and their probes, in the same order.
+    constexpr bool LAG = PROBES && FR <= 2;
+    constexpr uint32_t kLdsShift = (SW == 8 ? 7 : 6) + (LAG ? 1 : 0);  // log2 of the LDS row stride: the codes' scale
+    constexpr uint32_t FILLS = LAG ? 2 * FR : TPS * FR;                // copy rounds of a stage
     extern __shared__ uint4 sbuf[];
     const uint32_t tid = threadIdx.x;
-    const uint32_t wave = tid >> 6;
-    const uint32_t g = tid / SW, q = tid % SW;
-    const uint32_t rows = (uint32_t)G * FR;          // == 1 << a.tau (checked by the host)
-    const uint32_t tbl_bytes = rows * PIECE;         // one table slice in LDS
-    const uint32_t buf_bytes = tbl_bytes * TPS;  // one buffer (one stage)
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t g, q;  // read role: token group, column piece
+    read_role<SW>(tid, g, q);
+    constexpr uint32_t rows = (uint32_t)G * FR;      // == 1 << a.tau (checked by the host)
+    constexpr uint32_t tbl_bytes = rows * PIECE;     // one table slice in LDS
+    constexpr uint32_t buf_bytes = tbl_bytes * TPS;  // one buffer (one stage)
     const uint32_t n = (uint32_t)a.n;                // the host uses this kernel only for n < 2^31
     const uint32_t nstages = (uint32_t)a.k / TPS;
     const uint32_t lds0 = (uint32_t)(uintptr_t)sbuf;  // LDS byte address of the staging area
@@ -222,30 +278,36 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
         const uint32_t r0 = s0 + split_at(s1 - s0, parts, part), r1 = s0 + split_at(s1 - s0, parts, part + 1);
         if (r1 <= r0) continue;  // uniform over the workgroup
 
-        const uint32_t vec = slice * (uint32_t)SW + q;
-        const bool vec_ok = vec < (uint32_t)a.nvec;
-
-        // Fill role of this thread: piece (row g, column piece q) of each group of 128 rows.
+        // Fill role of this thread: LDS bytes 16 tid .. 16 tid + 15 of every copy round, i.e. column piece fq of row
+        // tid / SW (of table (tid / SW) % 2 and row tid / (2 SW) where the rows of two tables alternate).
         // Lanes whose piece lies outside the row (ragged last slice) copy piece 0 instead: they
         // never store a result, and this keeps the copy free of divergent control flow.
-        // Offsets inside one table fit 32 bits.
-        const uint32_t foff = g * a.row_stride + (vec_ok ? q : 0u) * 16u;
+        // Offsets inside the tables a round touches fit 32 bits (checked by the host).
         const size_t table_stride = (size_t)a.table_stride;
+        const uint32_t fq = tid % SW;
+        const bool vec_ok = slice * (uint32_t)SW + fq < (uint32_t)a.nvec;
+        const uint32_t foff = (tid / (LAG ? 2u * SW : SW)) * a.row_stride + (vec_ok ? fq : 0u) * 16u;
         const char *slice_base = a.tables + (size_t)(slice / a.spp) * (size_t)a.slice_stride +
                                  (size_t)(slice % a.spp) * PIECE;  // uniform
-        // piece idx = table-in-stage * FR + round, of stage s, into buffer b
-        auto fill_piece = [&](uint32_t s, uint32_t b, int idx) {
-            const uint32_t tb = (uint32_t)idx / FR, f = (uint32_t)idx % FR;
-            const char *tsrc = slice_base + (size_t)(s * TPS + tb) * table_stride +
-                               (size_t)f * G * a.row_stride;  // uniform
-            lds_dma16(tsrc, foff, lds0 + b * buf_bytes + tb * tbl_bytes + (f * kLdsThreads + wave * 64u) * 16u);
+        // copy round idx of stage s into its buffer (idx = table-in-stage * FR + round); with alternating rows a stage is one
+        // table, and the lanes whose 16 bytes belong to the other one take no part
+        auto fill_piece = [&](uint32_t s, uint32_t idx) {
+            if constexpr (LAG) {
+                constexpr uint64_t kEven = SW == 8 ? 0x00FF00FF00FF00FFull : 0x0F0F0F0F0F0F0F0Full;
+                lds_dma16_lanes(slice_base + (size_t)s * table_stride + (size_t)(idx * (G / 2)) * a.row_stride, foff,
+                                lds0 + ((s >> 1) & 1u) * kLdsBufBytes + (idx * kLdsThreads + wave * 64u) * 16u,
+                                s & 1u ? ~kEven : kEven);
+            } else {
+                lds_dma16(slice_base + (size_t)(s * TPS + idx / FR) * table_stride + (size_t)(idx % FR * G) * a.row_stride,
+                          foff, lds0 + (s & 1u) * buf_bytes + (idx * kLdsThreads + wave * 64u) * 16u);
+            }
         };
 
         const uint32_t len = r1 - r0;
         const uint32_t nchunks = (len + G * TOK - 1) / (G * TOK);
         for (uint32_t ch = 0; ch < nchunks; ++ch) {
             const uint32_t c0 = r0 + split_at(len, nchunks, ch), c1 = r0 + split_at(len, nchunks, ch + 1);
-            // Token slots.  The eight lanes of a token group would all hold the same code word and
+            // Token slots.  The lanes of a token group would all hold the same code word and
             // weights, so these are quad-shared: a lane keeps those of the slots 4m + r, r = its
             // position in its quad, in register m, and a use fetches them with a DPP quad broadcast
             // (a quarter of the registers and load instructions).  Slot i of group g is token
@@ -256,292 +318,256 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
             // zero padding (always a valid row), add them, and store nothing.
             constexpr int WQ = (TOK + 3) / 4, FQ = TOK / 4;
             const uint32_t r4 = q & 3u;
-            auto slot_token = [&](int i) -> uint32_t {
-                return i < 4 * FQ ? c0 + (4u * G) * (uint32_t)(i >> 2) + 4u * g + (uint32_t)(i & 3)
-                                  : c0 + (uint32_t)G * (uint32_t)i + g;
+            const uint32_t lq_full = (4u * g + r4) * 4u;  // byte offset of the lane's token in a full quad register
+            const uint32_t lq_tail = (r4 * G + g) * 4u;   // same for the tail register
+            // Register mm's dword of the word row at `row` (uniform: the row's word of token c0), `lane_extra` bytes
+            // further: a buffer load, whose per-lane part is one 32-bit offset for every row.  (With plain pointers the
+            // compiler kept a 64-bit address per row kind and register, 16 of the 128 registers in the 13-slot weighted
+            // form, and spilled in the stage loop, where the reload's wait also waited for the row copies just issued.)
+            auto load_reg = [&](const char *row, int mm, uint32_t lane_extra, uint32_t bytes) -> uint32_t {
+                const __amdgpu_buffer_rsrc_t rs =
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row), 0, (int)bytes, kBufferRsrcFlags);
+                return __builtin_amdgcn_raw_buffer_load_b32(rs, (mm < FQ ? lq_full : lq_tail) + lane_extra, mm * (16 * G), 0);
             };
-            const uint32_t lq_full = (4u * g + r4) * 4u;          // byte offset of the lane's token in a full quad register
-            const uint32_t lq_tail = (r4 * G + g) * 4u;            // same for the tail register
-            auto reg_offset = [&](int m) -> uint32_t {
-                return m < FQ ? (uint32_t)m * (16u * G) + lq_full : (uint32_t)m * (16u * G) + lq_tail;
-            };
-            constexpr int NCR = WQ;  // code registers and code loads per stage
-            auto load_code = [&](uint32_t s, int m, uint32_t(&cr)[NCR]) {
-                const char *base = reinterpret_cast<const char *>(a.packed) + ((size_t)s * a.n_pad + c0) * 4u;  // uniform
-                cr[m] = *reinterpret_cast<const uint32_t *>(base + reg_offset(m));
-            };
-            // LDS row offset of slot i in table u of the stage: the low / high half of its code word.
-            // Both halves are split off the word before the broadcast (once per register and stage),
-            // so a use is one DPP add and the two tables' broadcasts are distinct values.
-            auto row_offset = [&](const uint32_t(&cr)[NCR], int u, int i) -> uint32_t {
-                return u ? quad_bcast(cr[i >> 2] >> 16, i & 3) : quad_bcast(cr[i >> 2] & 0xFFFFu, i & 3);
-            };
-            // weights: table u of stage s, register m
-            constexpr int NWL = TPS * WQ;
-            auto load_weight = [&](uint32_t s, int i, float(&wr)[TPS][WQ]) {
-                const int u = i / WQ, m = i % WQ;
-                const char *base = reinterpret_cast<const char *>(a.wpk) +
-                                   ((size_t)(s * TPS + (uint32_t)u) * a.n_pad + c0) * 4u;  // uniform
-                wr[u][m] = *reinterpret_cast<const float *>(base + reg_offset(m));
+            // code words of word row `wrow` (one word = two tables), register mm
+            auto load_code = [&](uint32_t wrow, int mm) -> uint32_t {
+                return load_reg(reinterpret_cast<const char *>(a.packed) + ((size_t)wrow * a.n_pad + c0) * 4u, mm, 0u, WQ * 16 * G);
             };
 
-            // codes of a stage's two tables per token slot; two sets so that the next stage's codes
-            // load while the current stage is consumed
-            uint32_t crA[NCR], crB[NCR];
-            float wA[TPS][WQ], wB[TPS][WQ];
             Acc<false> acc[TOK];
 #pragma unroll
             for (int i = 0; i < TOK; ++i) acc[i].zero();
 
-            // LDS byte address of this lane's piece of row 0, per (buffer, table-in-stage)
-            const uint32_t qb = lds0 + q * 16u;
+            auto lds_row = [&](uint32_t at) {
+                return *reinterpret_cast<const __attribute__((address_space(3))) u32x4 *>((uintptr_t)at);
+            };
+            // all LDS reads of the stage are done; the copies into the other buffer have landed (vmcnt 0)
+            auto hand_over = [&]() {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            };
 
-            // One stage: consume buffer b with codes `cr`; meanwhile start stage s+1 (rows -> buffer
-            // b^1, codes -> cr_next), its vector-memory instructions spread over the read batches.
-            // `mode_tag`: TPS == 2: ignored.  TPS == 1: 0 = this stage's table is the low half of `cr`,
-            // 1 = the high half, and the next stage needs the next code word (loaded into cr_next).
-            auto run_stage = [&](auto more_tag, auto mode_tag, uint32_t s, uint32_t b, const uint32_t(&cr)[NCR],
-                                 uint32_t(&cr_next)[NCR], const float(&w)[TPS][WQ],
-                                 float(&w_next)[TPS][WQ]) {
-                constexpr bool MORE = decltype(more_tag)::value;
-                constexpr int HALF = decltype(mode_tag)::value;
-                constexpr bool LOADC = TPS == 2 || HALF == 1;  // does the next stage start a new code word?
-                constexpr int RB = LFFN_LDS_RB;              // row reads per batch
-                constexpr int NB = (TOK + RB - 1) / RB;      // batches per table
-                constexpr int NBT = TPS * NB;            // batches per stage
-                uint4 r[2][RB];
-                auto issue = [&](int bi, uint4(&dst)[RB]) {  // bi = u * NB + batch within table u
-                    const int u = bi / NB, b0 = (bi % NB) * RB;
-                    const uint32_t base = qb + b * buf_bytes + (uint32_t)u * tbl_bytes;
+            // stage 0 into buffer 0
 #pragma unroll
-                    for (int i = 0; i < RB; ++i)
-                        if (b0 + i < TOK) {
-                            const uint32_t off = row_offset(cr, TPS == 2 ? u : HALF, b0 + i);
-                            const u32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) u32x4 *>(
-                                (uintptr_t)(base + off));
-                            dst[i] = make_uint4(v.x, v.y, v.z, v.w);
-                        }
+            for (uint32_t idx = 0; idx < FILLS; ++idx) fill_piece(0, idx);
+            uint32_t cr[WQ];
+#pragma unroll
+            for (int mm = 0; mm < WQ; ++mm) cr[mm] = load_code(0, mm);
+
+            if constexpr (!PROBES) {
+                auto load_weight = [&](uint32_t j, int mm) -> float {
+                    return __uint_as_float(load_reg(
+                        reinterpret_cast<const char *>(a.wpk) + ((size_t)j * a.n_pad + c0) * 4u, mm, 0u, WQ * 16 * G));
                 };
-                auto consume = [&](int bi, const uint4(&src)[RB]) {
-                    const int u = bi / NB, b0 = (bi % NB) * RB;
+                uint32_t half[TPS][WQ];  // LDS row offsets, quad-shared, of the stage's tables
+                float w[TPS][WQ];        // their weights
+                auto split_codes = [&](uint32_t s) {
 #pragma unroll
-                    for (int i = 0; i < RB; ++i)
-                        if (b0 + i < TOK) {
-                            if constexpr (WEIGHTED)
-                                acc[b0 + i].fma(src[i], quad_bcast(w[u][(b0 + i) >> 2], (b0 + i) & 3));
-                            else
-                                acc[b0 + i].add(src[i]);
-                            acc[b0 + i].pin();
-                        }
-                };
-                issue(0, r[0]);
-#pragma unroll
-                for (int bi = 0; bi < NBT; ++bi) {
-                    if (bi + 1 < NBT) issue(bi + 1, r[(bi + 1) & 1]);
-                    if constexpr (MORE) {
-                        // vector-memory work of the next stage, a little per batch: row copies first
-                        // (they take longest), then its codes, then its weights
-                        // short stages (up to 8 token slots) of the plain sum with 128-byte slices issue the
-                        // copies together in the first batch (P6, P7: 4 % faster); with 12 or 13 slots, and in
-                        // the weighted form, whose batches also carry weight loads, spreading them measured
-                        // as fast or faster; a 64 KB stage of one 1024-row table (64-byte slices) gains 5 % from the
-                        // early issue (the same form with two 512-row tables per stage loses 6 %)
-                        constexpr bool COPY_FIRST = !WEIGHTED && ((SW == 8 && TOK <= 8) || (SW == 4 && FR == 4));
-#pragma unroll
-                        for (int idx = 0; idx < TPS * FR; ++idx)
-                            if ((COPY_FIRST ? 0 : vm_slot(idx, NBT)) == bi) fill_piece(s + 1, b ^ 1u, idx);
-                        if constexpr (LOADC) {
-#pragma unroll
-                            for (int m = 0; m < NCR; ++m)
-                                if (vm_slot(LFFN_LDS_CO + m, NBT) == bi) load_code((s + 1) * TPS / 2, m, cr_next);
-                        }
-                        if constexpr (WEIGHTED) {
-#pragma unroll
-                            for (int m = 0; m < NWL; ++m)
-                                if (vm_slot(LFFN_LDS_WO + m, NBT) == bi) load_weight(s + 1, m, w_next);
+                    for (int mm = 0; mm < WQ; ++mm) {
+                        if constexpr (TPS == 2) {
+                            half[0][mm] = cr[mm] & 0xFFFFu;
+                            half[1][mm] = cr[mm] >> 16;
+                        } else {
+                            half[0][mm] = (s & 1u) ? cr[mm] >> 16 : cr[mm] & 0xFFFFu;
                         }
                     }
-                    consume(bi, r[bi & 1]);
-                }
-                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): next stage's rows and codes have landed
-                __syncthreads();
-            };
-            // ---- multi-probe form: one sweep of the stage per probe --------------------------------
-            // shares of probe pr for table u of stage s, register m
-            auto load_share = [&](uint32_t s, int i, uint32_t pr, float(&wr)[TPS][WQ]) {
-                const int u = i / WQ, m = i % WQ;
-                const char *base = reinterpret_cast<const char *>(a.wpk) +
-                                   ((size_t)((s * TPS + (uint32_t)u) * ((uint32_t)a.tau + 1u) + pr) * a.n_pad + c0) * 4u;  // uniform
-                wr[u][m] = *reinterpret_cast<const float *>(base + reg_offset(m));
-            };
-            // One sweep: rows code ^ flip with shares `w`; meanwhile the shares of (ns, npr) travel into
-            // w_next and, in a stage's last sweep (FILL), the next stage's row copies and codes.
-            auto sweep = [&](auto fill_tag, auto mode_tag, uint32_t s, uint32_t b, const uint32_t(&cr)[NCR],
-                             uint32_t(&cr_next)[NCR], const float(&w)[TPS][WQ], float(&w_next)[TPS][WQ],
-                             uint32_t flip, bool more_shares, uint32_t ns, uint32_t npr) {
-                constexpr bool FILL = decltype(fill_tag)::value;
-                constexpr int HALF = decltype(mode_tag)::value;
-                constexpr bool LOADC = TPS == 2 || HALF == 1;
-                constexpr int RB = LFFN_LDS_RB;
-                constexpr int NB = (TOK + RB - 1) / RB;
-                constexpr int NBT = TPS * NB;
-                uint4 r[2][RB];
-                auto issue = [&](int bi, uint4(&dst)[RB]) {
-                    const int u = bi / NB, b0 = (bi % NB) * RB;
-                    const uint32_t base = qb + b * buf_bytes + (uint32_t)u * tbl_bytes;
-#pragma unroll
-                    for (int i = 0; i < RB; ++i)
-                        if (b0 + i < TOK) {
-                            const uint32_t off = row_offset(cr, TPS == 2 ? u : HALF, b0 + i) ^ flip;
-                            const u32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) u32x4 *>(
-                                (uintptr_t)(base + off));
-                            dst[i] = make_uint4(v.x, v.y, v.z, v.w);
-                        }
                 };
-                auto consume = [&](int bi, const uint4(&src)[RB]) {
-                    const int u = bi / NB, b0 = (bi % NB) * RB;
-#pragma unroll
-                    for (int i = 0; i < RB; ++i)
-                        if (b0 + i < TOK) {
-                            acc[b0 + i].fma(src[i], quad_bcast(w[u][(b0 + i) >> 2], (b0 + i) & 3));
-                            acc[b0 + i].pin();
-                        }
-                };
-                issue(0, r[0]);
-#pragma unroll
-                for (int bi = 0; bi < NBT; ++bi) {
-                    if (bi + 1 < NBT) issue(bi + 1, r[(bi + 1) & 1]);
-                    // the next sweep's shares first: they are needed soonest
-                    if (more_shares) {
-#pragma unroll
-                        for (int m = 0; m < NWL; ++m)
-                            if (vm_slot(m / 2, NBT) == bi) load_share(ns, m, npr, w_next);  // two per batch, early
-                    }
-                    if constexpr (FILL) {
-#pragma unroll
-                        for (int idx = 0; idx < TPS * FR; ++idx)
-                            if (vm_slot(idx, NBT) == bi) fill_piece(s + 1, b ^ 1u, idx);
-                        if constexpr (LOADC) {
-#pragma unroll
-                            for (int m = 0; m < NCR; ++m)
-                                if (vm_slot(LFFN_LDS_CO + m, NBT) == bi) load_code((s + 1) * TPS / 2, m, cr_next);
-                        }
-                    }
-                    consume(bi, r[bi & 1]);
-                }
-            };
-            // a whole stage: 1 + tau sweeps, then the barrier that publishes the next stage's buffer
-            auto run_stage_probes = [&](auto more_tag, auto mode_tag, uint32_t s, uint32_t b, const uint32_t(&cr)[NCR],
-                                        uint32_t(&cr_next)[NCR], float(&w)[TPS][WQ], float(&w_next)[TPS][WQ]) {
-                constexpr bool MORE = decltype(more_tag)::value;
-                const uint32_t tau = (uint32_t)a.tau;
-                for (uint32_t pr = 0; pr < tau; ++pr) {
-                    sweep(std::integral_constant<bool, false>{}, mode_tag, s, b, cr, cr_next, w, w_next,
-                          pr ? (PIECE << (pr - 1u)) : 0u, true, s, pr + 1u);
+                float wn[TPS][WQ];
+                if constexpr (WEIGHTED) {
 #pragma unroll
                     for (int u = 0; u < TPS; ++u)
 #pragma unroll
-                        for (int m = 0; m < WQ; ++m) w[u][m] = w_next[u][m];
+                        for (int mm = 0; mm < WQ; ++mm) wn[u][mm] = load_weight(u, mm);
                 }
-                sweep(more_tag, mode_tag, s, b, cr, cr_next, w, w_next, PIECE << (tau - 1u), MORE, s + 1u, 0u);
-#pragma unroll
-                for (int u = 0; u < TPS; ++u)
-#pragma unroll
-                    for (int m = 0; m < WQ; ++m) w[u][m] = w_next[u][m];
-                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): next stage's rows, codes and first shares have landed
-                __syncthreads();
-            };
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+                split_codes(0);
+                hand_over();
 
-            using yes = std::integral_constant<bool, true>;
-            using no = std::integral_constant<bool, false>;
-
-            // prologue: stage 0 into buffer 0, its codes
+                for (uint32_t s = 0; s < nstages; ++s) {
+                    const bool more = s + 1 < nstages;
+                    const uint32_t b = s & 1u, sn = more ? s + 1 : s;
+                    const uint32_t qs = lds0 + b * buf_bytes + q * 16u;  // this lane's piece of row 0
+                    if constexpr (WEIGHTED) {
 #pragma unroll
-            for (int idx = 0; idx < TPS * FR; ++idx) fill_piece(0, 0, idx);
+                        for (int u = 0; u < TPS; ++u)
 #pragma unroll
-            for (int i = 0; i < NCR; ++i) load_code(0, i, crA);
-            if constexpr (PROBES) {
+                            for (int mm = 0; mm < WQ; ++mm) w[u][mm] = wn[u][mm];
+                    }
+                    // Slot i of the stage: token slot i % TOK of table i / TOK.  Reads run D rows ahead of the sums; a read's
+                    // address and a row's weight are formed one slot before they are used, so that the instructions of a slot do
+                    // not depend on one another (formed where they are used, every slot waited for them).
+                    constexpr int NS = TPS * TOK, D = TOK > 13 ? 4 : 5;  // (16 slots spill with five rows in flight)
+                    u32x4 rd[D];
+                    auto slot_at = [&](int i) { return quad_bcast(half[i / TOK][(i % TOK) >> 2], (i % TOK) & 3) + qs; };
+                    auto slot_w = [&](int i) { return quad_bcast(w[i / TOK][(i % TOK) >> 2], (i % TOK) & 3); };
 #pragma unroll
-                for (int i = 0; i < NWL; ++i) load_share(0, i, 0u, wA);
-            } else if constexpr (WEIGHTED) {
+                    for (int i = 0; i < D; ++i) rd[i] = lds_row(slot_at(i) + (uint32_t)(i / TOK) * tbl_bytes);
+                    uint32_t at = slot_at(D < NS ? D : 0);
+                    float wb = WEIGHTED ? slot_w(0) : 0.0f;
 #pragma unroll
-                for (int i = 0; i < NWL; ++i) load_weight(0, i, wA);
-            }
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            __syncthreads();
-
-            // all stages but the last start their successor; buffers, code sets and weight sets alternate
-            using t0 = std::integral_constant<int, 0>;
-            using t1 = std::integral_constant<int, 1>;
-            uint32_t s = 0;
-            if constexpr (PROBES) {
-                // the shares of the sweep in progress stay in wA, those in flight in wB
-                if constexpr (TPS == 2) {
-                    for (; s + 2 < nstages; s += 2) {
-                        run_stage_probes(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                        run_stage_probes(yes{}, t0{}, s + 1, 1u, crB, crA, wA, wB);
+                    for (int i = 0; i < NS; ++i) {
+                        // vector-memory work of the next stage: its row copies first (they take longest), then its codes and weights
+                        if (i < 2 && more) {
+#pragma unroll
+                            for (uint32_t idx = 0; idx < TPS * FR; ++idx)
+                                if (idx % 2 == (uint32_t)i) fill_piece(s + 1, idx);
+                        }
+                        if (TPS == 2 || (s & 1u)) {
+#pragma unroll
+                            for (int mm = 0; mm < WQ; ++mm)
+                                if (2 + mm == i) cr[mm] = load_code(sn * TPS / 2, mm);
+                        }
+                        if constexpr (WEIGHTED) {
+#pragma unroll
+                            for (int x = 0; x < TPS * WQ; ++x)
+                                if ((2 + WQ + x) % NS == i) wn[x / WQ][x % WQ] = load_weight(sn * TPS + x / WQ, x % WQ);
+                        }
+                        const u32x4 v = rd[i % D];
+                        const uint4 r = make_uint4(v.x, v.y, v.z, v.w);
+                        const uint32_t ac = at;
+                        const float wc = wb;
+                        if (i + D + 1 < NS) at = slot_at(i + D + 1 < NS ? i + D + 1 : 0);
+                        if (WEIGHTED && i + 1 < NS) wb = slot_w(i + 1 < NS ? i + 1 : 0);
+                        if constexpr (WEIGHTED) {
+                            acc[i % TOK].fma(r, wc);
+                            acc[i % TOK].pin();
+                        } else {
+                            add_in_place(acc[i % TOK].f, r);
+                        }
+                        if (i + D < NS) rd[i % D] = lds_row(ac + (uint32_t)((i + D) / TOK) * tbl_bytes);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-                    if (s + 1 < nstages) {
-                        run_stage_probes(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                        run_stage_probes(no{}, t0{}, s + 1, 1u, crB, crA, wA, wB);
-                    } else {
-                        run_stage_probes(no{}, t0{}, s, 0u, crA, crB, wA, wB);
-                    }
-                } else {
-                    for (; s + 4 < nstages; s += 4) {
-                        run_stage_probes(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                        run_stage_probes(yes{}, t1{}, s + 1, 1u, crA, crB, wA, wB);
-                        run_stage_probes(yes{}, t0{}, s + 2, 0u, crB, crA, wA, wB);
-                        run_stage_probes(yes{}, t1{}, s + 3, 1u, crB, crA, wA, wB);
-                    }
-                    if (s + 2 < nstages) {
-                        run_stage_probes(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                        run_stage_probes(yes{}, t1{}, s + 1, 1u, crA, crB, wA, wB);
-                        run_stage_probes(yes{}, t0{}, s + 2, 0u, crB, crA, wA, wB);
-                        run_stage_probes(no{}, t1{}, s + 3, 1u, crB, crA, wA, wB);
-                    } else {
-                        run_stage_probes(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                        run_stage_probes(no{}, t1{}, s + 1, 1u, crA, crB, wA, wB);
-                    }
-                }
-            } else if constexpr (TPS == 2) {
-                for (; s + 2 < nstages; s += 2) {
-                    run_stage(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                    run_stage(yes{}, t0{}, s + 1, 1u, crB, crA, wB, wA);
-                }
-                if (s + 1 < nstages) {
-                    run_stage(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                    run_stage(no{}, t0{}, s + 1, 1u, crB, crA, wB, wA);
-                } else {
-                    run_stage(no{}, t0{}, s, 0u, crA, crB, wA, wB);
+                    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): next stage's rows, codes and weights have landed
+                    split_codes(sn);
+                    hand_over();
                 }
             } else {
-                // one table per stage, two stages per code word (k is even): word p = s/2 sits in crA for
-                // even p, crB for odd p
-                for (; s + 4 < nstages; s += 4) {
-                    run_stage(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                    run_stage(yes{}, t1{}, s + 1, 1u, crA, crB, wB, wA);
-                    run_stage(yes{}, t0{}, s + 2, 0u, crB, crA, wA, wB);
-                    run_stage(yes{}, t1{}, s + 3, 1u, crB, crA, wB, wA);
-                }
-                if (s + 2 < nstages) {
-                    run_stage(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                    run_stage(yes{}, t1{}, s + 1, 1u, crA, crB, wB, wA);
-                    run_stage(yes{}, t0{}, s + 2, 0u, crB, crA, wA, wB);
-                    run_stage(no{}, t1{}, s + 3, 1u, crB, crA, wB, wA);
-                } else {
-                    run_stage(yes{}, t0{}, s, 0u, crA, crB, wA, wB);
-                    run_stage(no{}, t1{}, s + 1, 1u, crA, crB, wB, wA);
+                // ---- multi-probe form: one table a step, 1 + tau sweeps over it ------------------------------
+                const uint32_t tau = (uint32_t)a.tau, k = (uint32_t)a.k, lag = LAG ? (tid >> 4) & 1u : 0u;
+                const uint32_t nsteps = k + (LAG ? 1u : 0u);
+                const uint32_t crow = (uint32_t)a.n_pad * 4u;  // bytes between word rows (times 1 + tau: 31 bits, host)
+                // code words of the lane's table t - lag (any valid row where it has none)
+                auto load_codes = [&](uint32_t t) {
+                    const uint32_t rb = t ? (t - 1u) >> 1 : 0u, ra = (t < k ? t : k - 1u) >> 1;
+                    const char *row = reinterpret_cast<const char *>(a.packed) + ((size_t)(LAG ? rb : ra) * a.n_pad + c0) * 4u;
+                    const uint32_t extra = LAG && !lag ? (ra - rb) * crow : 0u;
+#pragma unroll
+                    for (int mm = 0; mm < WQ; ++mm) cr[mm] = load_reg(row, mm, extra, (LAG ? crow : 0u) + WQ * 16 * G);
+                };
+                // Shares.  Row (j, probe) of wpk is row j * (1 + tau) + probe, so the rows of successive sweeps follow one
+                // another; `srow_at` is the row of the next sweep to be loaded for the lagging lanes (table 0 in the first step,
+                // where they have none) and the others read `crow * (1 + tau)` bytes further.  A lane without a table reads
+                // past the end of the buffer, which gives zeros.
+                const uint32_t sstep = (tau + 1u) * crow;
+                const char *srow_at = reinterpret_cast<const char *>(a.wpk) + (size_t)c0 * 4u;
+                uint32_t lt = 0, lp = 0;  // step and probe of the sweep that is loaded next
+                uint32_t sx;              // the lane's offset from that row
+                const uint32_t sx_first = LAG && lag ? 1u << 31 : 0u, sx_mid = LAG && !lag ? sstep : 0u,
+                               sx_last = LAG && !lag ? 1u << 31 : 0u;
+                auto share_lane = [&]() {
+                    const uint32_t first = lt == 0 ? ~0u : 0u, last = lt < k ? 0u : ~0u;  // (masks: a choice between the three
+                    sx = (sx_first & first) | (sx_mid & ~(first | last)) | (sx_last & last);  // ends up in scratch memory)
+                };
+                share_lane();
+                auto load_share = [&](int mm) -> float {
+                    return __uint_as_float(load_reg(srow_at, mm, sx, (LAG ? sstep : 0u) + WQ * 16 * G));
+                };
+                auto next_row = [&]() __attribute__((always_inline)) {
+                    if (lp < tau) {
+                        ++lp;
+                        srow_at += crow;
+                    } else if (lt + 1 < nsteps) {  // past the last step: its last row again
+                        srow_at += LAG && lt == 0 ? crow - (long long)sstep : (long long)crow;
+                        lp = 0;
+                        ++lt;
+                        share_lane();
+                    }
+                };
+                float wA[WQ], wB[WQ];  // shares of this sweep and of the next, then of the one after
+#pragma unroll
+                for (int mm = 0; mm < WQ; ++mm) wA[mm] = load_share(mm);
+                next_row();
+#pragma unroll
+                for (int mm = 0; mm < WQ; ++mm) wB[mm] = load_share(mm);
+                next_row();
+                if (LAG && tid < PIECE / 16) sbuf[2 * kLdsBufBytes / 16 + tid] = make_uint4(0u, 0u, 0u, 0u);  // the zero row
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+                hand_over();
+                for (uint32_t t = 0; t < nsteps; ++t) {
+                    const uint32_t j = t - lag, tn = t + 1 < nsteps ? t + 1 : t;
+                    // a group without a table in this step (the first or the last) reads the zero row, whatever the probe
+                    const uint32_t in = !LAG || j < k ? ~0u : 0u;
+                    const uint32_t base = LAG ? ((j & 2u) << 15) + (j & 1u) * PIECE : (j & 1u) * buf_bytes;
+                    const uint32_t lane_base = q * 16u + ((base & in) | (2u * kLdsBufBytes & ~in));
+                    uint32_t off[TOK];
+#pragma unroll
+                    for (int mm = 0; mm < WQ; ++mm) cr[mm] = (cr[mm] >> ((j & 1u) * 16u)) & 0xFFFFu & in;
+#pragma unroll
+                    for (int i = 0; i < TOK; ++i) off[i] = quad_bcast(cr[i >> 2], i & 3) + lane_base;
+                    // Reads run D rows ahead of the sums, into the next sweep; a read's address and a row's share are formed one
+                    // slot before they are used, so that the instructions of a slot do not depend on one another.
+                    constexpr int D = TOK % 2 ? 2 : 4;  // (2 * TOK is a multiple of it)
+                    u32x4 rd[D];
+                    auto flip_of = [&](uint32_t pr) { return (pr ? 1u << (kLdsShift + pr - 1u) : 0u) & in; };
+                    uint32_t flip = 0u;
+                    // PH: the sweep's slot i is in rd[(i + PH) % D]
+                    auto sweep = [&](auto ph_tag, uint32_t pr, float(&w)[WQ]) __attribute__((always_inline)) {
+                        constexpr int PH = decltype(ph_tag)::value;
+                        const uint32_t flip_next = flip_of(pr + 1u);  // after the last sweep: rows that are not added
+                        // address of the row the read of slot i fetches
+                        auto next_at = [&](int i) { return i + D < TOK ? off[i + D < TOK ? i + D : 0] ^ flip : off[i + D < TOK ? 0 : i + D - TOK] ^ flip_next; };
+                        uint32_t at = next_at(0);
+                        float wb = quad_bcast(w[0], 0);
+#pragma unroll
+                        for (int i = 0; i < TOK; ++i) {
+                            const u32x4 v = rd[(i + PH) % D];
+                            const float wc = wb;
+                            if (i + 1 < TOK) wb = quad_bcast(w[(i + 1) >> 2], (i + 1) & 3);
+                            const uint32_t ac = at;
+                            if (i + 1 < TOK) at = next_at(i + 1);
+                            acc[i].fma(make_uint4(v.x, v.y, v.z, v.w), wc);
+                            acc[i].pin();
+                            rd[(i + PH) % D] = lds_row(ac);
+                            if ((i & 3) == 3 || i == TOK - 1) w[i >> 2] = load_share(i >> 2);  // two sweeps ahead
+                            if (i == TOK - 1 && pr >= 1 && pr <= FILLS && t + 1 < k) fill_piece(t + 1, pr - 1);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        next_row();
+                        flip = flip_next;
+                    };
+                    using ph0 = std::integral_constant<int, 0>;
+                    using ph1 = std::integral_constant<int, TOK % D>;
+#pragma unroll
+                    for (int i = 0; i < D; ++i) rd[i] = lds_row(off[i]);
+                    uint32_t pr = 0;
+                    for (; pr < tau; pr += 2) {
+                        sweep(ph0{}, pr, wA);
+                        sweep(ph1{}, pr + 1, wB);
+                    }
+                    if (pr == tau) {  // an odd number of sweeps: the sets change places
+                        sweep(ph0{}, pr, wA);
+#pragma unroll
+                        for (int mm = 0; mm < WQ; ++mm) {
+                            const float x = wA[mm];
+                            wA[mm] = wB[mm];
+                            wB[mm] = x;
+                        }
+                    }
+                    load_codes(tn);
+                    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the next table's rows, codes and first shares have landed
+                    hand_over();
                 }
             }
 
             {
                 // The output addresses are formed here, from a lane index the compiler cannot see through: left
-                // alone it computes all TOK of them before the stage loop and keeps them in registers across it
-                // (the 12-, 13- and 16-slot forms then spill in their hot loop).
+                // alone it computes all TOK of them before the stage loop and keeps them in registers across it.
                 uint32_t lt = tid;
                 asm volatile("" : "+v"(lt));
-                const uint32_t sg = lt / SW, svec = slice * (uint32_t)SW + lt % SW;
+                uint32_t sg, sq;
+                read_role<SW>(lt, sg, sq);
+                const uint32_t svec = slice * (uint32_t)SW + sq;
 #pragma unroll
                 for (int i = 0; i < TOK; ++i) {
                     const uint32_t t = i < 4 * FQ ? c0 + (4u * G) * (uint32_t)(i >> 2) + 4u * sg + (uint32_t)(i & 3)

@@ -2,12 +2,10 @@
 // (tau <= 8), plain sum:
 //   y[t][:] = sum_{j<k} tables[j][code[t][j]][:]        (Sec. 3.1, eq. "lookup")
 // Runs on request only (option gather_path = 4): measured on the RoBERTa-base shape (16384 tokens, k = 96,
-// d_out = 768) it takes 99 us + 11 us for its code re-pack against 90 us for gather_lds_kernel.  Its row reads
+// d_out = 768) it takes 99 us + 11 us for its code re-pack against 77 us for gather_lds_kernel.  Its row reads
 // are conflict-free (measured alone: 135-140 TB/s over the chip against 69-80 TB/s for rows picked at random),
-// but both kernels turn out to be bound by the four vector adds per 16 bytes read (a stand-alone read-and-add
-// loop of this kernel's pattern sits at the vector-ALU issue rate: 0.43 us per table for 12 token slots), and
-// this one pays a barrier, an LDS write and two buffer loads per table on top, and a burst of output stores at
-// the end of its single pass.  Kept because it is the measured answer to "take the bank conflicts out".
+// but it pays a barrier, an LDS write and two buffer loads per table on top, and a burst of output stores at
+// the end of its single pass.  Kept because it is the measured answer to "take the bank conflicts out" of the plain sum.
 //
 // How the reads are made conflict-free:
 //
@@ -79,9 +77,6 @@ struct GatherRingArgs {
     uint32_t table_stride;           // rows * pw
     unsigned long long slice_stride; // k * rows * pw
 };
-
-// word 3 of a raw buffer resource: 32-bit data format, offsets checked against the byte count
-constexpr int kBufferRsrcFlags = 0x00020000;
 
 // THREADS = 1024 (4 waves per SIMD, 128 registers per lane: up to 12 token slots) or 512 (2 waves per SIMD, 256
 // registers: up to 32 slots); a chunk holds THREADS / 4 * TOK tokens either way.

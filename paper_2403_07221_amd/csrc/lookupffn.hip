@@ -48,7 +48,6 @@ int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3
 int gather_direct_load();  // makes the runtime load part 1's code object now (lookupffn_init)
 // parts 2, 3: the LDS-staged gather kernel (plain sum; weighted and multi-probe)
 int gather_lds_plain_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
-int gather_lds_plain13_part(const GatherLdsArgs &a, int fr, dim3 grid, size_t lds, hipStream_t s);  // part 11
 int gather_lds_weighted_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
 int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
 // part 7: the lagged, bank-interleaved staged gather (prepared tables, tau <= 8)
@@ -118,10 +117,10 @@ int launch_gather_lpt(int lpt, const GatherArgs &a, bool probes, dim3 grid, int 
     return LFFN_OK;
 }
 
-template <int TOK, int FR, bool WEIGHTED, int SW, bool PROBES = false>
+template <int TOK, int FR, int MODE, int SW>
 int launch_gather_lds_fr(const GatherLdsArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
-    auto kern = gather_lds_kernel<TOK, FR, WEIGHTED, SW, PROBES>;
+    auto kern = gather_lds_kernel<TOK, FR, MODE, SW>;
     int rc = allow_lds(reinterpret_cast<const void *>(kern), lds);
     if (rc != LFFN_OK || lffn_host::attr_only()) return rc;
     hipLaunchKernelGGL(kern, grid, dim3(kLdsThreads), lds, s, a);
@@ -129,21 +128,20 @@ int launch_gather_lds_fr(const GatherLdsArgs &a, dim3 grid, size_t lds, hipStrea
 }
 
 // fr = 16 KB copy rounds per table slice, sw = lanes per token (both fixed by the plan)
-// SW8: this part also holds the 128-byte-slice form of TOK (part 11 holds the plain one with 13 slots)
-template <int TOK, bool WEIGHTED = false, bool SW8 = true>
+template <int TOK, int MODE = 0>
 int launch_gather_lds_t(const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
-    if constexpr (TOK <= 13 && SW8) {
+    if constexpr (TOK <= 13) {
         if (sw == 8)
-            return fr == 4   ? launch_gather_lds_fr<TOK, 4, WEIGHTED, 8>(a, grid, lds, s)
-                   : fr == 2 ? launch_gather_lds_fr<TOK, 2, WEIGHTED, 8>(a, grid, lds, s)
-                             : launch_gather_lds_fr<TOK, 1, WEIGHTED, 8>(a, grid, lds, s);
+            return fr == 4   ? launch_gather_lds_fr<TOK, 4, MODE, 8>(a, grid, lds, s)
+                   : fr == 2 ? launch_gather_lds_fr<TOK, 2, MODE, 8>(a, grid, lds, s)
+                             : launch_gather_lds_fr<TOK, 1, MODE, 8>(a, grid, lds, s);
     }
     if (sw != 4) return LFFN_E_UNSUPPORTED;
     if constexpr (TOK == 8 || TOK == 13 || TOK == 16) {  // 64-byte slices
-        return fr == 4   ? launch_gather_lds_fr<TOK, 4, WEIGHTED, 4>(a, grid, lds, s)
-               : fr == 2 ? launch_gather_lds_fr<TOK, 2, WEIGHTED, 4>(a, grid, lds, s)
-                         : launch_gather_lds_fr<TOK, 1, WEIGHTED, 4>(a, grid, lds, s);
+        return fr == 4   ? launch_gather_lds_fr<TOK, 4, MODE, 4>(a, grid, lds, s)
+               : fr == 2 ? launch_gather_lds_fr<TOK, 2, MODE, 4>(a, grid, lds, s)
+                         : launch_gather_lds_fr<TOK, 1, MODE, 4>(a, grid, lds, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
@@ -153,12 +151,12 @@ template <int TOK>
 int launch_gather_lds_probes(const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
     if constexpr (TOK <= 13 && TOK != 12) {
-        if (sw == 8 && fr == 2) return launch_gather_lds_fr<TOK, 2, true, 8, true>(a, grid, lds, s);
-        if (sw == 8 && fr == 1) return launch_gather_lds_fr<TOK, 1, true, 8, true>(a, grid, lds, s);
+        if (sw == 8 && fr == 2) return launch_gather_lds_fr<TOK, 2, 2, 8>(a, grid, lds, s);
+        if (sw == 8 && fr == 1) return launch_gather_lds_fr<TOK, 1, 2, 8>(a, grid, lds, s);
     }
     if constexpr (TOK == 8 || TOK == 13 || TOK == 16) {
-        if (sw == 4 && fr == 4) return launch_gather_lds_fr<TOK, 4, true, 4, true>(a, grid, lds, s);
-        if (sw == 4 && fr == 2) return launch_gather_lds_fr<TOK, 2, true, 4, true>(a, grid, lds, s);
+        if (sw == 4 && fr == 4) return launch_gather_lds_fr<TOK, 4, 2, 4>(a, grid, lds, s);
+        if (sw == 4 && fr == 2) return launch_gather_lds_fr<TOK, 2, 2, 4>(a, grid, lds, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
@@ -227,32 +225,20 @@ int gather_lds_plain_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 
     if (tok <= 4) return launch_gather_lds_t<4>(a, fr, sw, grid, lds, s);
     if (tok <= 8) return launch_gather_lds_t<8>(a, fr, sw, grid, lds, s);
     if (tok <= 12) return launch_gather_lds_t<12>(a, fr, sw, grid, lds, s);
-    if (tok <= 13 && sw == 8) return gather_lds_plain13_part(a, fr, grid, lds, s);
-    if (tok <= 13) return launch_gather_lds_t<13, false, false>(a, fr, sw, grid, lds, s);
+    if (tok <= 13) return launch_gather_lds_t<13>(a, fr, sw, grid, lds, s);
     if (tok <= 16 && sw == 4) return launch_gather_lds_t<16>(a, fr, sw, grid, lds, s);
     return LFFN_E_UNSUPPORTED;
-}
-#endif
-
-#if LFFN_HAS(11)
-// The plain sum with 13 token slots and 128-byte slices -- the kernel of the 16384-token benchmark layer -- is
-// compiled on its own so that it can take the scheduler setting that suits it (see build.py).
-int gather_lds_plain13_part(const GatherLdsArgs &a, int fr, dim3 grid, size_t lds, hipStream_t s)
-{
-    return fr == 4   ? launch_gather_lds_fr<13, 4, false, 8>(a, grid, lds, s)
-           : fr == 2 ? launch_gather_lds_fr<13, 2, false, 8>(a, grid, lds, s)
-                     : launch_gather_lds_fr<13, 1, false, 8>(a, grid, lds, s);
 }
 #endif
 
 #if LFFN_HAS(3)
 int gather_lds_weighted_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (tok <= 4) return launch_gather_lds_t<4, true>(a, fr, sw, grid, lds, s);
-    if (tok <= 8) return launch_gather_lds_t<8, true>(a, fr, sw, grid, lds, s);
-    if (tok <= 12) return launch_gather_lds_t<12, true>(a, fr, sw, grid, lds, s);
-    if (tok <= 13) return launch_gather_lds_t<13, true>(a, fr, sw, grid, lds, s);
-    if (tok <= 16 && sw == 4) return launch_gather_lds_t<16, true>(a, fr, sw, grid, lds, s);
+    if (tok <= 4) return launch_gather_lds_t<4, 1>(a, fr, sw, grid, lds, s);
+    if (tok <= 8) return launch_gather_lds_t<8, 1>(a, fr, sw, grid, lds, s);
+    if (tok <= 12) return launch_gather_lds_t<12, 1>(a, fr, sw, grid, lds, s);
+    if (tok <= 13) return launch_gather_lds_t<13, 1>(a, fr, sw, grid, lds, s);
+    if (tok <= 16 && sw == 4) return launch_gather_lds_t<16, 1>(a, fr, sw, grid, lds, s);
     return LFFN_E_UNSUPPORTED;
 }
 
@@ -953,6 +939,10 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     const int groups = kLdsThreads / sw;
     // the kernel indexes tokens and bytes inside one table with 32 bits
     if (n >= (int64_t(1) << 31) - 4096 || (int64_t)rows * d_out * 4 >= (int64_t(1) << 32)) return LFFN_OK;
+    // ... and the multi-probe form the bytes of a stage's two tables, and those between their shares
+    if (mode == kProbes && ((int64_t)rows * d_out * 8 >= (int64_t(1) << 32) ||
+                            (tau + 1) * packed_n_pad(n) * 4 >= (int64_t(1) << 31)))
+        return LFFN_OK;
     int cus = 0;
     int rc = device_cus(&cus);
     if (rc != LFFN_OK) return rc;
@@ -983,9 +973,6 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     }
     const int64_t tpb = lds_tokens_per_block(n, a.n_units, a.token_splits, a.blocks_per_xcd);
     int tok_max = sw == 4 ? 16 : 13;
-    // the multi-probe form holds a share per probe beside the accumulators: 13 slots spill in its
-    // hot loop, 8 measured faster up to tau = 9 (tau = 10 has 16 copy rounds per table to amortise)
-    if (mode == kProbes && tau <= 9) tok_max = 8;
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
@@ -996,8 +983,9 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     if (sw == 4) p->tok = p->tok > 13 ? 16 : p->tok > 8 ? 13 : 8;  // the 64-byte form is built for 8, 13 and 16 token slots
     p->sw = sw;
     p->fr = rows / groups;
-    p->shift = sw == 8 ? 7 : 6;
-    p->lds = gather_lds_bytes(tau, sw);
+    // log2 of the LDS row stride: the multi-probe form alternates the rows of a stage's two tables
+    p->shift = (sw == 8 ? 7 : 6) + (mode == kProbes && p->fr <= 2 ? 1 : 0);
+    p->lds = gather_lds_bytes(tau, sw, mode == kProbes && p->fr <= 2);
     if (p->lds < (size_t)kLdsMinBytes) p->lds = kLdsMinBytes;
     p->grid = (unsigned)cus;
     p->tail = tail;
@@ -1206,8 +1194,7 @@ int plan_gather_ring(int64_t n, int k, int tau, int d_out, const TableRef &T, Mo
 {
     p->use = false;
     // On request only (gather_path 4).  Measured on the RoBERTa-base shape it does not beat the double-buffered
-    // staged kernel: its reads are conflict-free, but both kernels are bound by the four vector adds per 16 bytes
-    // read, and this one pays a barrier and an LDS write per table.
+    // staged kernel: its reads are conflict-free, but it pays a barrier and an LDS write per table.
     if (opt.gather_path != 4 || mode != kPlain || !T.prepared || T.pw < 64) return LFFN_OK;
     if (tau < 7 || tau > 8 || k > 480) return LFFN_OK;   // 256-row slices; the re-pack kernel's 64 x k tile fits LDS
     if (n >= (int64_t(1) << 31) - 4096) return LFFN_OK;
