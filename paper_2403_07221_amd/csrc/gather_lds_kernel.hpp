@@ -101,12 +101,14 @@ struct GatherLdsArgs {
     unsigned long long slice_stride;
 };
 
-// bytes of LDS the kernel needs: two buffers (sw = lanes per token; alternating rows: and one row piece of zeros)
+constexpr int kPrefetchLds = kLdsThreads * 4;  // where the prefetching copies put their bytes
+
+// bytes of LDS the kernel needs: two buffers and that (sw = lanes per token; alternating rows: and one row piece of zeros)
 __host__ __device__ inline size_t gather_lds_bytes(int tau, int sw, bool alternating)
 {
     if (alternating) return 2 * (size_t)kLdsBufBytes + 16 * (size_t)sw;
     const size_t tbl = ((size_t)16 * sw) << tau;
-    return 2 * (2 * tbl <= (size_t)kLdsBufBytes ? 2 * tbl : tbl);
+    return 2 * (2 * tbl <= (size_t)kLdsBufBytes ? 2 * tbl : tbl) + kPrefetchLds;
 }
 
 // balanced split of [0, len) into `parts` pieces: start of piece i (32-bit arithmetic only)
@@ -144,7 +146,21 @@ __device__ __forceinline__ void lds_dma16(const char *gbase, uint32_t voff, uint
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// The same for the lanes of `lanes` only (every lane is active outside): a lane's 16 bytes go to lds_base + 16 * lane whichever
+// Four bytes a lane: brings a cache line per lane into the L2 (the LDS bytes are never read; an LDS copy has no destination
+// register that would have to be waited for).
+__device__ __forceinline__ void lds_dma4(const char *gbase, uint32_t voff, uint32_t lds_base)
+{
+    const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 1\n\tglobal_load_lds_dword %1, %2"
+                 :
+                 : "s"(m), "v"(voff), "s"(scalar_ptr(gbase))
+                 : "memory", "m0");
+#pragma clang diagnostic pop
+}
+
+// The same as lds_dma16 for the lanes of `lanes` only (every lane is active outside): a lane's 16 bytes go to lds_base + 16 * lane whichever
 // others take part.  The mask is set inside the statement: a branch on the lane would make the compiler treat uniform values
 // that change beside it as divergent.
 __device__ __forceinline__ void lds_dma16_lanes(const char *gbase, uint32_t voff, uint32_t lds_base, uint64_t lanes)
@@ -303,6 +319,22 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
             }
         };
 
+        // L2 prefetch role.  The workgroups of a unit stream the same slice in step, so each copy of a stage used to wait for
+        // the memory behind the L2.  They share out the lines of the stage kPrefetch stages ahead: 16384 tokens, k = 96, tau = 8
+        // pass 106 -> 100 us, weighted 136 -> 129, k = 256, 512 wide 386 -> 361, tau = 10 264 -> 243.  (Every workgroup
+        // asking for every line doubles the requests of the copies, which is what they are bound by: slower.)
+        constexpr uint32_t kPrefetch = 3;
+        const uint32_t rows_a_line = a.row_stride < 128u ? 128u / a.row_stride : 1u;
+        const uint32_t tbl_lines = rows / rows_a_line, stage_lines = (uint32_t)TPS * tbl_lines;
+        const bool prefetches = !PROBES && wave * 64u * parts < stage_lines;  // wave-uniform
+        uint32_t line = tid * parts + part;
+        if (line >= stage_lines) line = part % stage_lines;
+        const uint32_t poff = (line / tbl_lines) * (uint32_t)table_stride + (line % tbl_lines) * rows_a_line * a.row_stride;
+        auto prefetch = [&](uint32_t s) {
+            if (prefetches && s < nstages)
+                lds_dma4(slice_base + (size_t)(s * TPS) * table_stride, poff, lds0 + 2u * buf_bytes + wave * 256u);
+        };
+
         const uint32_t len = r1 - r0;
         const uint32_t nchunks = (len + G * TOK - 1) / (G * TOK);
         for (uint32_t ch = 0; ch < nchunks; ++ch) {
@@ -382,6 +414,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                 }
                 __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
                 split_codes(0);
+                for (uint32_t ahead = 1; ahead < kPrefetch; ++ahead) prefetch(ahead);
                 hand_over();
 
                 for (uint32_t s = 0; s < nstages; ++s) {
@@ -440,6 +473,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                     }
                     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): next stage's rows, codes and weights have landed
                     split_codes(sn);
+                    prefetch(s + kPrefetch);
                     hand_over();
                 }
             } else {
