@@ -12,8 +12,8 @@ SRC = PKG / "csrc" / "lookupffn.hip"
 LIB = PKG / "liblookupffn.so"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-N_PARTS = 11         # csrc/lookupffn.hip compiles as parts 0 .. 10 (-DLFFN_PART=i), linked together
-SLOW_FIRST = [6, 5, 4, 3]   # the BH kernels take the longest: start them first
+N_PARTS = 12         # csrc/lookupffn.hip compiles as parts 0 .. 11 (-DLFFN_PART=i), linked together
+SLOW_FIRST = [6, 11, 3, 2, 5, 4]   # the BH and the staged gather's kernels take the longest: start them first
 OBJ_DIR = PKG / "_build"
 
 FLAGS = [

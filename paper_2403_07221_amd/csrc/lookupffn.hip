@@ -46,7 +46,7 @@ struct AttrOnly {
 // part 1: the direct gather kernel
 int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s);
 int gather_direct_load();  // makes the runtime load part 1's code object now (lookupffn_init)
-// parts 2, 3: the LDS-staged gather kernel (plain sum; weighted and multi-probe)
+// parts 2, 3, 11: the LDS-staged gather kernel (plain sum; weighted; multi-probe)
 int gather_lds_plain_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
 int gather_lds_weighted_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
 int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
@@ -89,6 +89,11 @@ thread_local const char *t_last_hash = "";    // the same for the hash kernel
 thread_local int t_attr_only = 0;
 #endif
 
+enum Mode { kPlain = 0, kWeighted = 1, kProbes = 2 };  // what a gather does with a selected row (the staged kernel's MODE)
+
+// token slots the staged gather is built with (64-byte slices: from 8 on)
+constexpr int kLdsSlots[] = {4, 6, 8, 10, 12, 13, 14, 16};
+
 // ---------------------------------------------------------------- kernel launchers (templates: every part may use them)
 template <int KIND, int LPT>
 void launch_gather_t(const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s)
@@ -127,36 +132,41 @@ int launch_gather_lds_fr(const GatherLdsArgs &a, dim3 grid, size_t lds, hipStrea
     return LFFN_OK;
 }
 
-// fr = 16 KB copy rounds per table slice, sw = lanes per token (both fixed by the plan)
-template <int TOK, int MODE = 0>
+// fr = 16 KB copy rounds per table slice, sw = lanes per token (both fixed by the plan).  The multi-probe form takes 128-byte
+// slices for tau 7, 8 and 64-byte slices for tau 9, 10.
+template <int TOK, int MODE>
 int launch_gather_lds_t(const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
-    if constexpr (TOK <= 13) {
-        if (sw == 8)
-            return fr == 4   ? launch_gather_lds_fr<TOK, 4, MODE, 8>(a, grid, lds, s)
-                   : fr == 2 ? launch_gather_lds_fr<TOK, 2, MODE, 8>(a, grid, lds, s)
-                             : launch_gather_lds_fr<TOK, 1, MODE, 8>(a, grid, lds, s);
-    }
-    if (sw != 4) return LFFN_E_UNSUPPORTED;
-    if constexpr (TOK == 8 || TOK == 13 || TOK == 16) {  // 64-byte slices
-        return fr == 4   ? launch_gather_lds_fr<TOK, 4, MODE, 4>(a, grid, lds, s)
-               : fr == 2 ? launch_gather_lds_fr<TOK, 2, MODE, 4>(a, grid, lds, s)
-                         : launch_gather_lds_fr<TOK, 1, MODE, 4>(a, grid, lds, s);
+    if (sw == 8) {
+        if constexpr (MODE != kProbes) {
+            if (fr == 4) return launch_gather_lds_fr<TOK, 4, MODE, 8>(a, grid, lds, s);
+        }
+        if (fr == 2) return launch_gather_lds_fr<TOK, 2, MODE, 8>(a, grid, lds, s);
+        if (fr == 1) return launch_gather_lds_fr<TOK, 1, MODE, 8>(a, grid, lds, s);
+    } else if (sw == 4 && TOK >= 8) {
+        constexpr int T = TOK >= 8 ? TOK : 8;
+        if constexpr (MODE != kProbes) {
+            if (fr == 1) return launch_gather_lds_fr<T, 1, MODE, 4>(a, grid, lds, s);
+        }
+        if (fr == 2) return launch_gather_lds_fr<T, 2, MODE, 4>(a, grid, lds, s);
+        if (fr == 4) return launch_gather_lds_fr<T, 4, MODE, 4>(a, grid, lds, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
 
-// multi-probe form: fp32 tables; 128-byte slices for tau 7, 8, 64-byte slices for tau 9, 10
-template <int TOK>
-int launch_gather_lds_probes(const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
+// tok: token slots, one of kLdsSlots
+template <int MODE>
+int launch_gather_lds_mode(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
-    if constexpr (TOK <= 13 && TOK != 12) {
-        if (sw == 8 && fr == 2) return launch_gather_lds_fr<TOK, 2, 2, 8>(a, grid, lds, s);
-        if (sw == 8 && fr == 1) return launch_gather_lds_fr<TOK, 1, 2, 8>(a, grid, lds, s);
-    }
-    if constexpr (TOK == 8 || TOK == 13 || TOK == 16) {
-        if (sw == 4 && fr == 4) return launch_gather_lds_fr<TOK, 4, 2, 4>(a, grid, lds, s);
-        if (sw == 4 && fr == 2) return launch_gather_lds_fr<TOK, 2, 2, 4>(a, grid, lds, s);
+    switch (tok) {
+        case 4: return launch_gather_lds_t<4, MODE>(a, fr, sw, grid, lds, s);
+        case 6: return launch_gather_lds_t<6, MODE>(a, fr, sw, grid, lds, s);
+        case 8: return launch_gather_lds_t<8, MODE>(a, fr, sw, grid, lds, s);
+        case 10: return launch_gather_lds_t<10, MODE>(a, fr, sw, grid, lds, s);
+        case 12: return launch_gather_lds_t<12, MODE>(a, fr, sw, grid, lds, s);
+        case 13: return launch_gather_lds_t<13, MODE>(a, fr, sw, grid, lds, s);
+        case 14: return launch_gather_lds_t<14, MODE>(a, fr, sw, grid, lds, s);
+        case 16: return launch_gather_lds_t<16, MODE>(a, fr, sw, grid, lds, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
@@ -222,33 +232,21 @@ int gather_direct_load()
 #if LFFN_HAS(2)
 int gather_lds_plain_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (tok <= 4) return launch_gather_lds_t<4>(a, fr, sw, grid, lds, s);
-    if (tok <= 8) return launch_gather_lds_t<8>(a, fr, sw, grid, lds, s);
-    if (tok <= 12) return launch_gather_lds_t<12>(a, fr, sw, grid, lds, s);
-    if (tok <= 13) return launch_gather_lds_t<13>(a, fr, sw, grid, lds, s);
-    if (tok <= 16 && sw == 4) return launch_gather_lds_t<16>(a, fr, sw, grid, lds, s);
-    return LFFN_E_UNSUPPORTED;
+    return launch_gather_lds_mode<kPlain>(tok, a, fr, sw, grid, lds, s);
 }
 #endif
 
 #if LFFN_HAS(3)
 int gather_lds_weighted_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (tok <= 4) return launch_gather_lds_t<4, 1>(a, fr, sw, grid, lds, s);
-    if (tok <= 8) return launch_gather_lds_t<8, 1>(a, fr, sw, grid, lds, s);
-    if (tok <= 12) return launch_gather_lds_t<12, 1>(a, fr, sw, grid, lds, s);
-    if (tok <= 13) return launch_gather_lds_t<13, 1>(a, fr, sw, grid, lds, s);
-    if (tok <= 16 && sw == 4) return launch_gather_lds_t<16, 1>(a, fr, sw, grid, lds, s);
-    return LFFN_E_UNSUPPORTED;
+    return launch_gather_lds_mode<kWeighted>(tok, a, fr, sw, grid, lds, s);
 }
+#endif
 
+#if LFFN_HAS(11)
 int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (tok <= 4) return launch_gather_lds_probes<4>(a, fr, sw, grid, lds, s);
-    if (tok <= 8) return launch_gather_lds_probes<8>(a, fr, sw, grid, lds, s);
-    if (tok <= 13) return launch_gather_lds_probes<13>(a, fr, sw, grid, lds, s);
-    if (tok <= 16) return launch_gather_lds_probes<16>(a, fr, sw, grid, lds, s);
-    return LFFN_E_UNSUPPORTED;
+    return launch_gather_lds_mode<kProbes>(tok, a, fr, sw, grid, lds, s);
 }
 #endif
 
@@ -898,8 +896,6 @@ int64_t lds_tokens_per_block(int64_t n, int n_units, int token_splits, int Bx)
     return (unit_tokens + blocks - 1) / blocks;
 }
 
-enum Mode { kPlain = 0, kWeighted = 1, kProbes = 2 };
-
 // Launch shape of the LDS-staged gather for one problem size (no pointers involved).
 struct LdsPlan {
     bool use = false;
@@ -972,15 +968,19 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
         a.slice_stride = (unsigned long long)sw * 16;
     }
     const int64_t tpb = lds_tokens_per_block(n, a.n_units, a.token_splits, a.blocks_per_xcd);
-    int tok_max = sw == 4 ? 16 : 13;
+    int tok_max = 16;
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
     // Staging pays only when a chunk re-uses each staged row a few times.
     if (opt.gather_path < 2 && chunk < 2 * (int64_t)rows) return LFFN_OK;
     p->tok = (int)((chunk + groups - 1) / groups);
-    if (mode == kProbes && sw == 8 && p->tok > 8) p->tok = 13;  // multi-probe form: 4, 8 or 13 slots
-    if (sw == 4) p->tok = p->tok > 13 ? 16 : p->tok > 8 ? 13 : 8;  // the 64-byte form is built for 8, 13 and 16 token slots
+    // the fewest slots built that hold a chunk: a slot without a token costs what any other does
+    for (int built : kLdsSlots)
+        if (built >= p->tok && (sw == 8 || built >= 8)) {
+            p->tok = built;
+            break;
+        }
     p->sw = sw;
     p->fr = rows / groups;
     // log2 of the LDS row stride: the multi-probe form alternates the rows of a stage's two tables
@@ -1733,7 +1733,7 @@ int lookupffn_init(void)
     const size_t lds = 160 * 1024;
     GatherLdsArgs ga{};
     BhArgs ba{};
-    for (int tok : {4, 8, 12, 13, 16})
+    for (int tok : kLdsSlots)
         for (int fr : {1, 2, 4})
             for (int sw : {4, 8}) {
                 for (int part = 0; part < 3; ++part) {
