@@ -12,7 +12,7 @@ SRC = PKG / "csrc" / "lookupffn.hip"
 LIB = PKG / "liblookupffn.so"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-N_PARTS = 12         # csrc/lookupffn.hip compiles as parts 0 .. 11 (-DLFFN_PART=i), linked together
+N_PARTS = 13         # csrc/lookupffn.hip compiles as parts 0 .. 12 (-DLFFN_PART=i), linked together
 SLOW_FIRST = [6, 11, 3, 2, 5, 4]   # the BH and the staged gather's kernels take the longest: start them first
 OBJ_DIR = PKG / "_build"
 

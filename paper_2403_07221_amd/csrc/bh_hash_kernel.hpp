@@ -60,6 +60,8 @@ struct BhArgs {
     int packed_shift;     // log2 of the row-piece bytes the packed codes are scaled by
     long long n;
     int d, k, tau, n_factors, P;
+    int p_per;            // projections per workgroup: grid z covers P; fewer than P only with `codes`
+    int cross;            // tables run over from one projection into the next
     int x_kind;           // element type of x: 0 fp32, 1 bf16, 2 IEEE half
     int x_vec4;           // rows may be read four coordinates at a time (alignment checked by the host)
     float scale;
@@ -188,14 +190,20 @@ __device__ __forceinline__ void lds_barrier()
 // LOG2N: d_pad = 2^LOG2N (64 .. 1024); TB = block / 16 (1, 2, 4).
 // WMODE: 0 codes only; 1 also the gather weights of the weighted variant (Sec. 4), for tau = 4, 8 or 16 (a
 // table then lies inside one tile); 2 the weights of any other tau, formed from z through a window in LDS.
-template <int LOG2N, int TB, int WMODE>
-__global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
+// FEW: no more workgroups than compute units.  A wave is then alone on its SIMD and each operand quad a trip to the L2 or
+// beyond: it keeps up to sixteen in flight instead of four and may use any number of registers for them (built for
+// d_pad = 1024, block 64).
+//
+// Projections of few tokens go out over workgroups (grid z, p_per each), which ran one after another in one: a table
+// that runs over from the projection before is the business of the workgroup it ends in, which hashes that projection too.
+template <int LOG2N, int TB, int WMODE, bool FEW>
+__global__ __launch_bounds__(kBhThreads, FEW ? 1 : 3) void bh_hash_kernel(BhArgs a)
 {
     using L = BhLds<LOG2N, WMODE == 2>;
     using S = typename L::S;
     constexpr int N = S::N, LT = S::LT, NU = S::NU, WPG = S::WPG, UPS = S::UPS;
     constexpr int LQ = LT * TB;                // operand quads (1 KB: one tile product) per wave and factor
-    constexpr int D = 4;                       // quads in flight (8 cost spills: 1 - 3 us of 20 - 30)
+    constexpr int D = FEW ? (LQ < 16 ? LQ : 16) : 4;  // quads in flight (with three waves a SIMD 8 cost spills: 1 - 3 us of 20 - 30)
     constexpr bool kEndB = WPG > 1;            // the layout a projection ends in
     static_assert(LT >= TB && LT % TB == 0 && LT % 4 == 0 && LQ % D == 0, "units hold whole blocks");
     extern __shared__ uint32_t lds[];
@@ -224,6 +232,8 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
     // do, which is no loss against the earlier form of the kernel that shared copies in LDS (65536 tokens, one projection,
     // tau = 8, blocks 16 / 32 / 64, that form against this: d = 256 60 / 75 / 105 -> 45 / 58 / 86 us, d = 512
     // 150 / 142 / 201 -> 87 / 116 / 171).
+    const int pb = (int)blockIdx.z * a.p_per, pe = P < pb + a.p_per ? P : pb + a.p_per;  // the projections emitted here
+    const int ps = pb > 0 && a.cross ? pb - 1 : pb;                                       // the first one hashed
     const unsigned n_pf = (unsigned)(P * a.n_factors);
     constexpr unsigned UB = 4 * TB * 1024;  // operand bytes of a unit
     const __amdgpu_buffer_rsrc_t ops = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.apack), 0, (int)(n_pf * (N / 64) * UB), 0x00020000);
@@ -235,7 +245,7 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
     };
     u32x4 ring[D];
 #pragma unroll
-    for (int i = 0; i < D; ++i) ring[i] = load_quad(0, false, i);
+    for (int i = 0; i < D; ++i) ring[i] = load_quad((unsigned)(ps * a.n_factors), false, i);
 
     // Transpose of (wave, unit) between layouts A and B
     auto exchange = [&](float (&v)[LT][4]) {
@@ -302,7 +312,7 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
         return hidden(c < (unsigned)a.d ? (tl * (unsigned)a.d + c) * esz : 0x80000000u);
     };
 
-    for (int p = 0; p < P; ++p) {
+    for (int p = ps; p < pe; ++p) {
         // ---- a1: this wave's coordinates of its tokens in layout A, register r of tile i <-> 16*i + g + 4r
         float v[LT][4];
         if (x_vec4 && !a.x_kind) {
@@ -418,7 +428,7 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
         // whole tile.  Four consecutive tables of a unit are reduced together (two pair reductions, one
         // per half of the lane groups) so that lane group g ends with the weight of table g of the four:
         // one store per lane for four tables.  A unit's weights are computed before their stores.
-        if constexpr (WMODE == 1) {
+        if constexpr (WMODE == 1) {  // (no table runs over from one projection into the next: ps == pb)
             auto emit = [&](auto tau_c) {
                 constexpr int TAU = decltype(tau_c)::value;
                 constexpr int TPQ = TAU / 4;    // tiles per group of four tables (1, 2, 4)
@@ -503,14 +513,14 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
 #pragma unroll
                         for (int r = 0; r < 4; ++r) zt[16 * i + 4 * r] = v[4 * u + i][r];
                 }
-                if (p + q > 0)
+                if (p - ps + q > 0)
                     for (unsigned e = st; e < TOK * 16u; e += kSetThreads) zw[(e >> 4) * ZS + (e & 15u)] = ztail[e];
                 lds_barrier();
                 const unsigned lo = (unsigned)(p * N + RUN * q);  // first coordinate of the run in the bit string
                 const int jlo = (int)(lo / (unsigned)tau);
                 int jhi = (int)((lo + RUN) / (unsigned)tau);
                 if (jhi > a.k) jhi = a.k;
-                const int ntab = jhi - jlo;
+                const int ntab = p < pb ? 0 : jhi - jlo;
                 for (int idx = (int)st; idx < TOK * ntab; idx += (int)kSetThreads) {
                     // table-major output: the tokens of a table are neighbours; else a token's tables are
                     const int tt = a.wpk ? (idx & 15) : idx / ntab;
@@ -585,9 +595,12 @@ __global__ __launch_bounds__(kBhThreads, 3) void bh_hash_kernel(BhArgs a)
         for (unsigned s = blockIdx.x; s < (unsigned)(a.k / 2); s += gridDim.x)
             for (long long t = a.n + tid; t < a.n_pad; t += kBhThreads) a.packed[(long long)s * a.n_pad + t] = 0u;
     } else {
+        unsigned jb = 0, je = (unsigned)a.k;
+        if (pb > 0) jb = (unsigned)(pb * N) / (unsigned)a.tau;
+        if (pe < P) je = (unsigned)(pe * N) / (unsigned)a.tau;
         for (unsigned tt = 0; tt < TOK; ++tt) {
             if (t0 + tt >= a.n) break;
-            for (unsigned j = st; j < (unsigned)a.k; j += kSetThreads) a.codes[(t0 + tt) * a.k + j] = (uint16_t)code_at(tt, j);
+            for (unsigned j = jb + st; j < je; j += kSetThreads) a.codes[(t0 + tt) * a.k + j] = (uint16_t)code_at(tt, j);
         }
     }
 }

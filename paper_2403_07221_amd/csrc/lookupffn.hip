@@ -66,6 +66,8 @@ int hash_row8_load();
 int bh_lo_part(int L, int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s);
 int bh_512_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s);
 int bh_1024_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s);
+// part 12: blocks of 64 at d_pad = 1024 for grids of no more workgroups than compute units
+int bh_few_part(int wmode, const BhArgs &a, dim3 grid, hipStream_t s);
 }  // namespace lffn_host
 
 namespace {
@@ -171,10 +173,10 @@ int launch_gather_lds_mode(int tok, const GatherLdsArgs &a, int fr, int sw, dim3
     return LFFN_E_UNSUPPORTED;
 }
 
-template <int L, int TB, int WMODE>
+template <int L, int TB, int WMODE, bool FEW>
 int launch_bh_k(const BhArgs &a, dim3 grid, hipStream_t s)
 {
-    auto kern = bh_hash_kernel<L, TB, WMODE>;
+    auto kern = bh_hash_kernel<L, TB, WMODE, FEW>;
     const bool query = lffn_host::attr_only();
     const size_t lds = query ? 160 * 1024 : BhLds<L, WMODE == 2>::bytes(a.P);
     int rc = allow_lds(reinterpret_cast<const void *>(kern), lds);
@@ -187,9 +189,9 @@ template <int L, int WMODE>
 int launch_bh_b(const BhArgs &a, int block, dim3 grid, hipStream_t s)
 {
     switch (block) {
-        case 16: return launch_bh_k<L, 1, WMODE>(a, grid, s);
-        case 32: return launch_bh_k<L, 2, WMODE>(a, grid, s);
-        case 64: return launch_bh_k<L, 4, WMODE>(a, grid, s);
+        case 16: return launch_bh_k<L, 1, WMODE, false>(a, grid, s);
+        case 32: return launch_bh_k<L, 2, WMODE, false>(a, grid, s);
+        case 64: return launch_bh_k<L, 4, WMODE, false>(a, grid, s);
     }
     return LFFN_E_UNSUPPORTED;
 }
@@ -428,6 +430,18 @@ int bh_512_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s)
 
 #if LFFN_HAS(6)
 int bh_1024_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s) { return launch_bh<10>(wmode, a, block, grid, s); }
+#endif
+
+#if LFFN_HAS(12)
+int bh_few_part(int wmode, const BhArgs &a, dim3 grid, hipStream_t s)
+{
+    switch (wmode) {
+        case 0: return launch_bh_k<10, 4, 0, true>(a, grid, s);
+        case 1: return launch_bh_k<10, 4, 1, true>(a, grid, s);
+        case 2: return launch_bh_k<10, 4, 2, true>(a, grid, s);
+    }
+    return LFFN_E_UNSUPPORTED;
+}
 #endif
 
 #if LFFN_HAS(0)
@@ -1396,9 +1410,26 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     const int wmode = !out.weights ? 0 : bh_weights_in_registers(tau) ? 1 : 2;
     const int wpg = L == 10 ? 4 : L == 9 ? 2 : 1;  // waves that share a token group
     const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
-    const dim3 grid = grid_of((n + per_block - 1) / per_block);  // a workgroup past the batch does a full hash of no token
-    int rc;
-    if (L <= 8) rc = lffn_host::bh_lo_part(L, wmode, a, block, grid, s);
+    const int64_t blocks = (n + per_block - 1) / per_block;
+    dim3 grid = grid_of(blocks);  // a workgroup past the batch does a full hash of no token
+    int cus = 0;
+    int rc = device_cus(&cus);
+    if (rc != LFFN_OK) return rc;
+    // One projection a workgroup while each finds a compute unit to itself (2 tokens: d = 64, block 32, 20 projections pass
+    // 77 -> 16 us, d = 256, 6 projections with tables across them 93 -> 40; codes in the ABI layout only: a word of the
+    // packed layout may hold tables of two projections).  Two projections with tables across them stay together: each
+    // workgroup would hash both.
+    a.p_per = a.P;
+    a.cross = N % tau != 0;
+    if (a.codes && blocks * a.P <= cus && a.P > (a.cross ? 2 : 1)) {
+        a.p_per = 1;
+        grid.z = (unsigned)a.P;
+    }
+    // With a wave alone on its SIMD the form with more operands in flight is faster at d_pad = 1024 with blocks of 64 (128
+    // tokens, d = 768, weighted pass 42.8 -> 41.0 us, 202 tokens 38.5 -> 37.3, 2 tokens 37.3 / 37.5), at other shapes it is
+    // not (block 32: 10 tokens 31.1 / 31.4, block 16: 216 tokens of 256 36.3 / 37.1, block 64: 5 tokens of 512 28.7 / 30.4).
+    if (block == 64 && L == 10 && blocks * grid.z <= cus) rc = lffn_host::bh_few_part(wmode, a, grid, s);
+    else if (L <= 8) rc = lffn_host::bh_lo_part(L, wmode, a, block, grid, s);
     else if (L == 9) rc = lffn_host::bh_512_part(wmode, a, block, grid, s);
     else rc = lffn_host::bh_1024_part(wmode, a, block, grid, s);
     if (rc != LFFN_OK) return rc;
@@ -1756,6 +1787,10 @@ int lookupffn_init(void)
                 rc = lffn_host::gather_ring_part(threads, tok, ra, dim3(1), nullptr);
                 if (rc != LFFN_OK && rc != LFFN_E_UNSUPPORTED) return rc;
             }
+    }
+    for (int wmode = 0; wmode < 3; ++wmode) {
+        rc = lffn_host::bh_few_part(wmode, ba, dim3(1), nullptr);
+        if (rc != LFFN_OK) return rc;
     }
     for (int block : {16, 32, 64})
         for (int wmode = 0; wmode < 3; ++wmode) {
