@@ -45,6 +45,8 @@ struct HashArgs {
     int packed_shift;     // log2 of the row-piece bytes the packed codes are scaled by (7: 128-byte pieces, 6: 64-byte)
     long long n;
     int d, k, tau, n_rounds, P;
+    int p_per;            // projections per workgroup (grid y covers all); fewer than all only with `codes`
+    int cross;            // tables run over from one projection into the next
     int x_kind;           // element type of x: 0 fp32, 1 bf16, 2 IEEE half
     float scale;          // (float)(1 / sqrt(N))
 };
@@ -234,7 +236,15 @@ __device__ __forceinline__ void emit_weights(const HashArgs &a, long long t, int
     }
 }
 
+// The tables that end in the projections [pb, pe), of widths from 64 on: the first, and one past the last
+__device__ __forceinline__ int first_table(const HashArgs &a, int pb, int N) { return pb > 0 ? pb * N / a.tau : 0; }
+__device__ __forceinline__ int end_table(const HashArgs &a, int pe, int N) { return pe < a.P ? pe * N / a.tau : a.k; }
+
 // WMODE: 0 = codes only, 1 = codes and gather weights (Sec. 4), 2 = codes and multi-probe shares
+//
+// Projections of few tokens go out over workgroups (grid y, p_per each; widths from 64 on), which a wave otherwise takes
+// one after another: 7 tokens of 119, k = 170, tau = 8 (11 projections), weighted, hash 21 -> 7 us.  A table that runs over
+// from the projection before is the business of the workgroup it ends in, which hashes that projection too.
 template <int LOG2N, int WMODE>
 __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
 {
@@ -248,12 +258,15 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
     const unsigned lane = tid & 63u;
     const unsigned wave = tid >> 6;
     const int P = a.P, R = a.n_rounds;
+    // the projections emitted here and, where tables cross into the first of them, the one before it
+    const int pb = (int)blockIdx.y * a.p_per, pe = P < pb + a.p_per ? P : pb + a.p_per;
+    const int ps = pb > 0 && a.cross ? pb - 1 : pb;
 
     // ---- block prologue: pack the sign diagonals into per-lane flip words ----------------
     // flip[(p*R + r)*FW + w][lane] bit b  <->  signs[p][r][lane + 64*(32*w + b)] < 0
     uint32_t *flip = lds;
     const int n_flip = P * R * FW * 64;
-    for (int idx = (int)tid; idx < n_flip; idx += kHashThreads) {
+    for (int idx = ps * R * FW * 64 + (int)tid; idx < pe * R * FW * 64; idx += kHashThreads) {
         const int l = idx & 63;
         const int w = (idx >> 6) % FW;
         const int pr = (idx >> 6) / FW;
@@ -297,7 +310,7 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
             for (int i = (int)lane; i < n_bitw; i += 64) bitw[i] = 0;
         }
 
-        for (int p = 0; p < P; ++p) {
+        for (int p = ps; p < pe; ++p) {
             float v[NREG];
 #pragma unroll
             for (int r = 0; r < NREG; ++r) v[r] = xv[r];
@@ -345,8 +358,8 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
                 for (int r = 0; r < NREG; ++r)
                     if ((int)lane + 64 * r < N) zwin[kZTail + (int)lane + 64 * r] = v[r];
                 wave_lds_fence();
-                emit_weights<WMODE>(a, t, p, N, lane, [&](int c) { return zwin[kZTail + c]; });
-                if (p + 1 < P) {
+                if (p >= pb) emit_weights<WMODE>(a, t, p, N, lane, [&](int c) { return zwin[kZTail + c]; });
+                if (p + 1 < pe) {
                     // slide the tail: it becomes the last 16 coordinates up to the end of projection p
                     wave_lds_fence();
                     float keep = 0.0f;
@@ -372,7 +385,7 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
                 a.packed[(long long)s * a.n_pad + t] =
                     (code_at(2u * s) << a.packed_shift) | (code_at(2u * s + 1u) << (16 + a.packed_shift));
         } else {
-            for (int j = (int)lane; j < a.k; j += 64) a.codes[t * a.k + j] = (uint16_t)code_at((unsigned)j);
+            for (int j = first_table(a, pb, N) + (int)lane; j < end_table(a, pe, N); j += 64) a.codes[t * a.k + j] = (uint16_t)code_at((unsigned)j);
         }
         wave_lds_fence();
     }
@@ -559,6 +572,8 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
     const unsigned lane = threadIdx.x & 63u;
     const unsigned wave = threadIdx.x >> 6;
     const int P = a.P;
+    const int pb = (int)blockIdx.y * a.p_per, pe = P < pb + a.p_per ? P : pb + a.p_per;  // as in hash_kernel
+    const int ps = pb > 0 && a.cross ? pb - 1 : pb;
     uint32_t *tp = lds + wave * h1024_wave_words(P, WEIGHTED);  // transpose area, the bit string, the z tail
     uint32_t *bitw = tp + kH1024TransposeWords;
     const int n_bitw = hash_bit_words(P, N);
@@ -587,7 +602,8 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
             sw[rd][3] = w.w;
         }
     };
-    if (P == 1 && gw < a.n) load_masks(0);
+    const bool one = pe - ps == 1;
+    if (one && gw < a.n) load_masks(ps);
 
     float xn[NREG];
     if (gw < a.n) h1024_load_row(a.x, gw, a.d, a.x_kind, vec_ok, lane, xn);
@@ -597,8 +613,8 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
         for (int e = 0; e < NREG; ++e) xv[e] = xn[e];
         if (t + n_waves < a.n) h1024_load_row(a.x, t + n_waves, a.d, a.x_kind, vec_ok, lane, xn);
 
-        for (int p = 0; p < P; ++p) {
-            if (P > 1) load_masks(p);
+        for (int p = ps; p < pe; ++p) {
+            if (!one) load_masks(p);
             float v[NREG];
 #pragma unroll
             for (int e = 0; e < NREG; ++e) v[e] = xv[e];
@@ -622,8 +638,8 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
                     if (c < 0) return ztail[kZTail + c];
                     return __uint_as_float(tp[c ^ ((c >> 4) & 0x3C)]);
                 };
-                emit_weights<WMODE>(a, t, p, N, lane, z_at);
-                if (p + 1 < P) {
+                if (p >= pb) emit_weights<WMODE>(a, t, p, N, lane, z_at);
+                if (p + 1 < pe) {
                     wave_lds_fence();
                     float keep = 0.0f;
                     if (lane < kZTail) keep = z_at(N - kZTail + (int)lane);
@@ -641,7 +657,8 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
                 a.packed[(long long)s * a.n_pad + t] = (hash_code_at(bitw, 2u * s, a.tau) << a.packed_shift) |
                                                        (hash_code_at(bitw, 2u * s + 1u, a.tau) << (16 + a.packed_shift));
         } else {
-            for (int j = (int)lane; j < a.k; j += 64) a.codes[t * a.k + j] = (uint16_t)hash_code_at(bitw, (unsigned)j, a.tau);
+            for (int j = first_table(a, pb, N) + (int)lane; j < end_table(a, pe, N); j += 64)
+                a.codes[t * a.k + j] = (uint16_t)hash_code_at(bitw, (unsigned)j, a.tau);
         }
         wave_lds_fence();
     }

@@ -823,6 +823,8 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
     a.P = (int)(((int64_t)k * tau + N - 1) / N);
     a.x_kind = x_dtype;  // LFFN_F32 / BF16 / F16 are the kernels' kinds 0 / 1 / 2
     a.scale = (float)(1.0 / std::sqrt((double)N));
+    a.p_per = a.P;
+    a.cross = N % tau != 0;
     if (!a.codes && !a.packed) return LFFN_E_NULL;
     if (out.probes && (!a.codes || !a.weights)) return LFFN_E_UNSUPPORTED;  // shares exist in the ABI layout only
     TimedLaunch tl(0, s);
@@ -858,6 +860,19 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
         t_last_hash = "hash_row_kernel";
         return LFFN_OK;
     }
+    // One projection a workgroup while a SIMD gets at most two waves (codes in the ABI layout only: a word of the packed layout
+    // may hold tables of two projections; two projections with tables across them stay together: each workgroup would hash
+    // both).
+    unsigned p_groups = 1;
+    if (a.codes && N >= 64 && a.P > (a.cross ? 2 : 1)) {
+        int cus = 0;
+        int rc = device_cus(&cus);
+        if (rc != LFFN_OK) return rc;
+        if (n * a.P <= 8 * (int64_t)cus) {
+            a.p_per = 1;
+            p_groups = (unsigned)a.P;
+        }
+    }
     // d_pad = 1024 with up to four rounds: the two-layout kernel (needs 16-byte aligned signs, and
     // rows that start on 16-byte boundaries when it loads them as vectors)
     const size_t xrow = (size_t)d * (a.x_kind ? 2 : 4);
@@ -868,7 +883,7 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
         int64_t blocks = (n + kHashWaves - 1) / kHashWaves;
         const int64_t cap = opt.hash_blocks ? opt.hash_blocks : 4096;
         if (blocks > cap) blocks = cap;
-        const dim3 grid((unsigned)blocks);
+        const dim3 grid((unsigned)blocks, p_groups);
         const size_t lds = h1024_lds_bytes(a.P, weighted);
         switch (n_rounds) {
             case 1: launch_hash1024_t<1>(a, out.probes, grid, lds, s); break;
@@ -884,7 +899,7 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
     const size_t lds = hash_lds_bytes(a.P, n_rounds, N, weighted);
     int64_t blocks = (n + kHashWaves - 1) / kHashWaves;
     if (blocks > 2048) blocks = 2048;
-    const dim3 grid((unsigned)blocks);
+    const dim3 grid((unsigned)blocks, p_groups);
     switch (L) {
 #define LFFN_CASE(l) case l: launch_hash_t<l>(a, out.probes, grid, lds, s); break;
         LFFN_CASE(0) LFFN_CASE(1) LFFN_CASE(2) LFFN_CASE(3) LFFN_CASE(4) LFFN_CASE(5) LFFN_CASE(6)
