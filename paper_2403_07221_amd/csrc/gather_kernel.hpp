@@ -23,8 +23,8 @@
 // a time whatever k is (one by one they cost a wait per table: 1001 tokens, 97 half tables, weighted 60 -> 20 us), and
 // a launch of fewer than two full workgroups per compute unit goes out as one-wave workgroups.  The multi-probe form
 // keeps eight to sixteen rows in flight across table boundaries (64 tokens, 96 tables, tau = 8: gather 136 -> 57 us
-// against three rows at a time; 4096 tokens, tau = 11: 1372 -> 1258 us); the other two measured slower with a second set of rows in flight (2000
-// tokens weighted 48 -> 55 us: the registers cost half the waves).
+// against three rows at a time; 4096 tokens, tau = 11: 1372 -> 1258 us); the other two take a second set of rows in flight
+// (DEEP) where there are too few wavefronts for its registers to matter (2000 tokens weighted 48 -> 55 us with it).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -56,6 +56,7 @@ struct GatherArgs {
     int code_stride;   // codes (and weights, and groups of 1 + tau shares) per token in the arrays; k unless
                        // the launch covers only some of the tables
     int four_rows;     // plain sum: 1: four rows of a token in flight; 0: sixteen
+    int deep;          // 1: few wavefronts (DEEP)
     int accumulate;    // 1: the sums start from what y holds (fp32 y, fp32 rows) instead of zero
     // The 16-byte piece q of row r = (j << tau) + code in slice s sits at
     //   tables + (s / spp) * slice_stride + (s % spp) * LPT*16 + r * row_stride + q*16
@@ -174,7 +175,10 @@ __device__ __forceinline__ void left_over(int rest, F f)
 }
 
 // WMODE: 0 = plain sum, 1 = weighted form, 2 = multi-probe form
-template <int KIND, int LPT, int WMODE>
+// DEEP (plain and weighted): for few wavefronts, whose registers nobody else needs: sixteen rows more are requested before
+// sixteen are added, and codes and weights ahead of the rows before them, so that no request waits for an earlier one's data
+// (loads return in order: a code requested behind rows is there only when they are).
+template <int KIND, int LPT, int WMODE, bool DEEP>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
 {
     constexpr int TPW = 64 / LPT;  // tokens per wave
@@ -231,6 +235,62 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
     // codes with the last whole chunk instead held them through the loop (72 -> 76, 93 -> 102 registers): k = 100
     // weighted 261 -> 286.
     const int nch = k >> 3, rest = k & 7;
+    int done = 0;  // tables summed by the deep form: its whole groups of sixteen
+    if constexpr (DEEP) {
+        static_assert(WMODE != 2, "built for the plain and the weighted sum");
+        const float *wrow = WMODE == 1 ? a.weights + t * a.code_stride : nullptr;
+        const int ng = k >> 4;
+        if (ng > 0) {
+            struct Codes {
+                CodeChunk lo, hi;
+            };
+            Codes cc[2];
+            float w[2][16];
+            uint4 r[2][16];
+            auto load_codes = [&](Codes &c, int g) {
+                const int gc = g < ng ? g : ng - 1;
+                c.lo.load(crow + gc * 16);
+                c.hi.load(crow + gc * 16 + 8);
+            };
+            auto load_weights = [&](float(&f)[16], int g) {
+                if constexpr (WMODE == 1) {
+                    const int gc = g < ng ? g : ng - 1;
+                    __builtin_memcpy(&f[0], wrow + gc * 16, 32);
+                    __builtin_memcpy(&f[8], wrow + gc * 16 + 8, 32);
+                }
+            };
+            auto issue = [&](int g, const Codes &c, uint4(&x)[16]) {
+#pragma unroll
+                for (int u = 0; u < 16; ++u) x[u] = row(g * 16 + u, u < 8 ? c.lo.code(u & 7) : c.hi.code(u & 7));
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto add = [&](const uint4(&x)[16], const float(&f)[16]) {
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    if constexpr (WMODE == 1) acc.fma(x[u], f[u]);
+                    else acc.add(x[u]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // group g of the pair (g, g + 1): cur = g & 1; the next group's rows go out before this one is added
+            auto turn = [&](auto cur_tag, int g) {
+                constexpr int C = decltype(cur_tag)::value, X = C ^ 1;
+                load_codes(cc[C], g + 2);
+                load_weights(w[X], g + 1);
+                if (g + 1 < ng) issue(g + 1, cc[X], r[X]);
+                add(r[C], w[C]);
+            };
+            load_codes(cc[0], 0);
+            load_weights(w[0], 0);
+            load_codes(cc[1], 1);
+            issue(0, cc[0], r[0]);
+            for (int g = 0; g < ng; g += 2) {
+                turn(std::integral_constant<int, 0>{}, g);
+                if (g + 1 < ng) turn(std::integral_constant<int, 1>{}, g + 1);
+            }
+        }
+        done = ng << 4;
+    }
     if constexpr (WMODE == 2) {
         // The probes of all tables as one sequence, eight rows at a time, the next eight in flight while these are
         // added: entry q is probe q % (tau + 1) of table q / (tau + 1) and its share is wp[q]; table and probe of an
@@ -314,12 +374,13 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
         }
     } else if constexpr (WMODE == 1) {
         const float *wrow = a.weights + t * a.code_stride;
-        if (nch) {
+        const int ch0 = DEEP ? done >> 3 : 0;
+        if (ch0 < nch) {
             CodeChunk cn;
             float wn[8];
-            cn.load(crow);
-            load_floats8(wrow, wn);
-            for (int ch = 0; ch < nch; ++ch) {
+            cn.load(crow + ch0 * 8);
+            load_floats8(wrow + ch0 * 8, wn);
+            for (int ch = ch0; ch < nch; ++ch) {
                 const CodeChunk c = cn;
                 float w[8];
 #pragma unroll
@@ -357,13 +418,13 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
 #pragma unroll
             for (int u = 0; u < M; ++u) acc.add(r[u]);
         };
-        if (a.four_rows) {
+        if (!DEEP && a.four_rows) {
             int j0 = 0;
             for (; j0 + 4 <= k; j0 += 4) add_rows(std::integral_constant<int, 4>{}, j0);
             left_over(k & 3, [&](auto m) { add_rows(m, j0); });
         } else {
-            int ch = 0;
-            if (nch >= 2) {
+            int ch = DEEP ? done >> 3 : 0;
+            if (!DEEP && nch >= 2) {
                 CodeChunk c0, c1;
                 c0.load(crow);
                 c1.load(crow + 8);

@@ -100,12 +100,23 @@ constexpr int kLdsSlots[] = {4, 6, 8, 10, 12, 13, 14, 16};
 template <int KIND, int LPT>
 void launch_gather_t(const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s)
 {
-    if (probes)
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 2>), grid, dim3(threads), 0, s, a);
-    else if (a.weights)
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1>), grid, dim3(threads), 0, s, a);
+    if (probes) {
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 2, false>), grid, dim3(threads), 0, s, a);
+        return;
+    }
+    if constexpr (LPT == 4 || LPT == 8 || LPT == 16) {  // the host asks for the deep form with these only
+        if (a.deep) {
+            if (a.weights)
+                hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, true>), grid, dim3(threads), 0, s, a);
+            else
+                hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0, true>), grid, dim3(threads), 0, s, a);
+            return;
+        }
+    }
+    if (a.weights)
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, false>), grid, dim3(threads), 0, s, a);
     else
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0>), grid, dim3(threads), 0, s, a);
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0, false>), grid, dim3(threads), 0, s, a);
 }
 
 template <int KIND>
@@ -226,7 +237,7 @@ int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3
 int gather_direct_load()
 {
     hipFuncAttributes attr;
-    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(gather_kernel<kElemF32, 8, 0>));
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(gather_kernel<kElemF32, 8, 0, false>));
     return e == hipSuccess ? LFFN_OK : hip_fail(e, "hipFuncGetAttributes(gather_kernel)");
 }
 #endif
@@ -801,6 +812,17 @@ dim3 grid_of(int64_t blocks)
     return dim3((unsigned)(((blocks + rows - 1) / rows + kXcds - 1) / kXcds * kXcds), (unsigned)rows);
 }
 
+// Projections of few tokens over up to `most` workgroups each: returns the groups and sets the projections of one.  A group
+// but the first also hashes the projection before its own where tables cross into it.  (For codes in the ABI layout only: a
+// word of the packed layout may hold tables of two projections.)
+unsigned split_projections(int P, bool cross, int64_t most, int *p_per)
+{
+    const int64_t groups = most < P ? most : P;
+    const int per = groups < 2 ? P : (int)((P + groups - 1) / groups);
+    *p_per = per + cross < P ? per : P;
+    return (unsigned)((P + *p_per - 1) / *p_per);
+}
+
 int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t n, int d, int k, int tau,
                 int n_rounds, int x_dtype, hipStream_t s, const Options &opt)
 {
@@ -860,18 +882,13 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
         t_last_hash = "hash_row_kernel";
         return LFFN_OK;
     }
-    // One projection a workgroup while a SIMD gets at most two waves (codes in the ABI layout only: a word of the packed layout
-    // may hold tables of two projections; two projections with tables across them stay together: each workgroup would hash
-    // both).
+    // as many workgroups to the projections as leave a SIMD at most two waves
     unsigned p_groups = 1;
-    if (a.codes && N >= 64 && a.P > (a.cross ? 2 : 1)) {
+    if (a.codes && N >= 64) {
         int cus = 0;
         int rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;
-        if (n * a.P <= 8 * (int64_t)cus) {
-            a.p_per = 1;
-            p_groups = (unsigned)a.P;
-        }
+        p_groups = split_projections(a.P, a.cross, 8 * (int64_t)cus / n, &a.p_per);
     }
     // d_pad = 1024 with up to four rounds: the two-layout kernel (needs 16-byte aligned signs, and
     // rows that start on 16-byte boundaries when it loads them as vectors)
@@ -1157,6 +1174,15 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
     const int64_t cu_waves = (n + tpw - 1) / tpw * a.n_slices / cus;
     a.four_rows = mode == kPlain && beyond_l2 && !T.prepared && cu_waves >= 9 &&
                   (T.kind ? !ragged || cu_waves <= 128 : ragged && cu_waves <= 30);
+    // The form with thirty-two rows in flight: up to five wavefronts a compute unit (more lose what their registers cost),
+    // where the walk through the tables is long enough to show.  Gather alone, us, without / with it:
+    //   weighted, fp32, k = 170, tau = 9, 512 wide: 64 tokens 16.5 / 12.0, 256 27.5 / 22.7, 500 39.4 / 36.7; fp16: 128 tokens
+    //   16.0 / 11.2, 500 20.5 / 12.9, 1000 21.8 / 18.8, 2000 (eight wavefronts) 33.7 / 35.4; k = 96, 768 wide 500 tokens
+    //   12.7 / 10.4, 1000 (six) 14.8 / 14.7; k = 64, 64 wide 10.0 / 9.9
+    //   plain: fp32 k = 170 64 tokens 14.3 / 12.0, k = 128, 344 wide 256 tokens 10.8 / 10.0, k = 96 64 tokens 9.2 / 9.3; fp16
+    //   k = 128 9.8 / 10.4
+    a.deep = (lpt == 4 || lpt == 8 || lpt == 16) && cu_waves < 5 &&
+             (mode == kWeighted ? a.k >= 96 : mode == kPlain && !T.kind && a.k >= 128);
     if (opt.xcd_order == 1) xcd = true;
     if (opt.xcd_order == -1) xcd = false;
     a.xcd_mode = xcd;
@@ -1430,16 +1456,11 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     int cus = 0;
     int rc = device_cus(&cus);
     if (rc != LFFN_OK) return rc;
-    // One projection a workgroup while each finds a compute unit to itself (2 tokens: d = 64, block 32, 20 projections pass
-    // 77 -> 16 us, d = 256, 6 projections with tables across them 93 -> 40; codes in the ABI layout only: a word of the
-    // packed layout may hold tables of two projections).  Two projections with tables across them stay together: each
-    // workgroup would hash both.
+    // as many workgroups to the projections as find a compute unit each (2 tokens: d = 64, block 32, 20 projections pass
+    // 77 -> 16 us, d = 256, 6 projections with tables across them 93 -> 40)
     a.p_per = a.P;
     a.cross = N % tau != 0;
-    if (a.codes && blocks * a.P <= cus && a.P > (a.cross ? 2 : 1)) {
-        a.p_per = 1;
-        grid.z = (unsigned)a.P;
-    }
+    if (a.codes) grid.z = split_projections(a.P, a.cross, (int64_t)cus / blocks, &a.p_per);
     // With a wave alone on its SIMD the form with more operands in flight is faster at d_pad = 1024 with blocks of 64 (128
     // tokens, d = 768, weighted pass 42.8 -> 41.0 us, 202 tokens 38.5 -> 37.3, 2 tokens 37.3 / 37.5), at other shapes it is
     // not (block 32: 10 tokens 31.1 / 31.4, block 16: 216 tokens of 256 36.3 / 37.1, block 64: 5 tokens of 512 28.7 / 30.4).
