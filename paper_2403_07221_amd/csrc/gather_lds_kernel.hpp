@@ -216,7 +216,7 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t v, int q)
 
 // FR = 16 KB copy rounds per table slice (one round = every thread copies 16 bytes = G rows): 1, 2, 4.
 // Tables per stage TPS: two (FR <= 2: both halves of a code word are consumed in one stage) or one
-// (FR = 4: a 64 KB slice fills a buffer; even stages take the low half of the code word, odd stages
+// (FR = 4: a 64 KB slice fills a buffer; and the multi-probe form; even stages take the low half of the code word, odd stages
 // the high half).  SW = lanes per token: 8 (128-byte column slices; tau = 7, 8, 9 <-> FR = 1, 2, 4)
 // or 4 (64-byte slices; tau = 8, 9, 10 <-> FR = 1, 2, 4).  The packed codes must be scaled by the LDS row
 // stride (gather_lds_shift).
@@ -230,13 +230,15 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
     static_assert(TOK <= kLdsMaxTok, "packed-code padding covers 16 token slots");
     static_assert(FR == 1 || FR == 2 || FR == 4, "table slices of 16, 32 or 64 KB");
     static_assert(SW == 8 || SW == 4, "128- or 64-byte column slices");
-    constexpr int TPS = FR <= 2 ? 2 : 1;
+    constexpr int TPS = FR <= 2 && !PROBES ? 2 : 1;
     constexpr int G = kLdsThreads / SW;   // token groups per workgroup = rows per copy round
     constexpr uint32_t PIECE = SW * 16u;  // bytes of a row inside the slice
     static_assert(TPS * FR * 16 * 1024 <= kLdsBufBytes, "a stage fits one buffer");
     // Multi-probe form, tables of up to 32 KB: the rows of two consecutive tables alternate in LDS (four tables in all),
     // and half of the token groups of a read pass lag one table behind the others, so that a pass reads one table in each
-    // half of the banks (see read_role).  Every group still takes its tables, and their probes, in the same order.
+    // half of the banks (see read_role).  Every group still takes its tables, and their probes, in the same order.  (Over
+    // 64-byte rows a pass holds two tokens of each table, which still meet half of the time: 16384 tokens, k = 96, tau = 9
+    // 844 us with the lag, 949 without.)
     constexpr bool LAG = PROBES && FR <= 2;
     constexpr uint32_t kLdsShift = (SW == 8 ? 7 : 6) + (LAG ? 1 : 0);  // log2 of the LDS row stride: the codes' scale
     constexpr uint32_t FILLS = LAG ? 2 * FR : TPS * FR;                // copy rounds of a stage

@@ -563,7 +563,8 @@ __device__ __forceinline__ uint32_t hash_code_at(const uint32_t *bitw, unsigned 
     return (uint32_t)(both >> sh) & ((1u << tau) - 1u);
 }
 
-template <int R, int WMODE>
+// SPLIT: the projections are spread over workgroups (as in hash_kernel; a form of its own, for the scalar registers it takes)
+template <int R, int WMODE, bool SPLIT>
 __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void hash1024_kernel(HashArgs a)
 {
     constexpr bool WEIGHTED = WMODE != 0;
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
     const unsigned lane = threadIdx.x & 63u;
     const unsigned wave = threadIdx.x >> 6;
     const int P = a.P;
-    const int pb = (int)blockIdx.y * a.p_per, pe = P < pb + a.p_per ? P : pb + a.p_per;  // as in hash_kernel
+    const int pb = SPLIT ? (int)blockIdx.y * a.p_per : 0, pe = SPLIT && pb + a.p_per < P ? pb + a.p_per : P;
     const int ps = pb > 0 && a.cross ? pb - 1 : pb;
     uint32_t *tp = lds + wave * h1024_wave_words(P, WEIGHTED);  // transpose area, the bit string, the z tail
     uint32_t *bitw = tp + kH1024TransposeWords;
@@ -657,7 +658,7 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
                 a.packed[(long long)s * a.n_pad + t] = (hash_code_at(bitw, 2u * s, a.tau) << a.packed_shift) |
                                                        (hash_code_at(bitw, 2u * s + 1u, a.tau) << (16 + a.packed_shift));
         } else {
-            for (int j = first_table(a, pb, N) + (int)lane; j < end_table(a, pe, N); j += 64)
+            for (int j = (SPLIT ? first_table(a, pb, N) : 0) + (int)lane; j < (SPLIT ? end_table(a, pe, N) : a.k); j += 64)
                 a.codes[t * a.k + j] = (uint16_t)hash_code_at(bitw, (unsigned)j, a.tau);
         }
         wave_lds_fence();

@@ -93,8 +93,8 @@ thread_local int t_attr_only = 0;
 
 enum Mode { kPlain = 0, kWeighted = 1, kProbes = 2 };  // what a gather does with a selected row (the staged kernel's MODE)
 
-// token slots the staged gather is built with (64-byte slices: from 8 on)
-constexpr int kLdsSlots[] = {4, 6, 8, 10, 12, 13, 14, 16};
+// token slots the staged gather is built with (64-byte slices: from 6 on)
+constexpr int kLdsSlots[] = {4, 6, 7, 8, 10, 12, 13, 14, 16};
 
 // ---------------------------------------------------------------- kernel launchers (templates: every part may use them)
 template <int KIND, int LPT>
@@ -156,8 +156,8 @@ int launch_gather_lds_t(const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_
         }
         if (fr == 2) return launch_gather_lds_fr<TOK, 2, MODE, 8>(a, grid, lds, s);
         if (fr == 1) return launch_gather_lds_fr<TOK, 1, MODE, 8>(a, grid, lds, s);
-    } else if (sw == 4 && TOK >= 8) {
-        constexpr int T = TOK >= 8 ? TOK : 8;
+    } else if (sw == 4 && TOK >= 6) {
+        constexpr int T = TOK >= 6 ? TOK : 6;
         if constexpr (MODE != kProbes) {
             if (fr == 1) return launch_gather_lds_fr<T, 1, MODE, 4>(a, grid, lds, s);
         }
@@ -174,6 +174,7 @@ int launch_gather_lds_mode(int tok, const GatherLdsArgs &a, int fr, int sw, dim3
     switch (tok) {
         case 4: return launch_gather_lds_t<4, MODE>(a, fr, sw, grid, lds, s);
         case 6: return launch_gather_lds_t<6, MODE>(a, fr, sw, grid, lds, s);
+        case 7: return launch_gather_lds_t<7, MODE>(a, fr, sw, grid, lds, s);
         case 8: return launch_gather_lds_t<8, MODE>(a, fr, sw, grid, lds, s);
         case 10: return launch_gather_lds_t<10, MODE>(a, fr, sw, grid, lds, s);
         case 12: return launch_gather_lds_t<12, MODE>(a, fr, sw, grid, lds, s);
@@ -747,12 +748,20 @@ void launch_hash_t(const HashArgs &a, bool probes, dim3 grid, size_t lds, hipStr
 template <int R>
 void launch_hash1024_t(const HashArgs &a, bool probes, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (probes)
-        hipLaunchKernelGGL((hash1024_kernel<R, 2>), grid, dim3(kHashThreads), lds, s, a);
-    else if (a.weights || a.wpk)
-        hipLaunchKernelGGL((hash1024_kernel<R, 1>), grid, dim3(kHashThreads), lds, s, a);
-    else
-        hipLaunchKernelGGL((hash1024_kernel<R, 0>), grid, dim3(kHashThreads), lds, s, a);
+    if (grid.y > 1) {
+        if (probes)
+            hipLaunchKernelGGL((hash1024_kernel<R, 2, true>), grid, dim3(kHashThreads), lds, s, a);
+        else if (a.weights || a.wpk)
+            hipLaunchKernelGGL((hash1024_kernel<R, 1, true>), grid, dim3(kHashThreads), lds, s, a);
+        else
+            hipLaunchKernelGGL((hash1024_kernel<R, 0, true>), grid, dim3(kHashThreads), lds, s, a);
+    } else if (probes) {
+        hipLaunchKernelGGL((hash1024_kernel<R, 2, false>), grid, dim3(kHashThreads), lds, s, a);
+    } else if (a.weights || a.wpk) {
+        hipLaunchKernelGGL((hash1024_kernel<R, 1, false>), grid, dim3(kHashThreads), lds, s, a);
+    } else {
+        hipLaunchKernelGGL((hash1024_kernel<R, 0, false>), grid, dim3(kHashThreads), lds, s, a);
+    }
 }
 
 // What a hash launch writes: codes[n][k] (and weights[n][k], or shares[n][k][1+tau] with `probes`), or --
@@ -1023,15 +1032,16 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     p->tok = (int)((chunk + groups - 1) / groups);
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
     for (int built : kLdsSlots)
-        if (built >= p->tok && (sw == 8 || built >= 8)) {
+        if (built >= p->tok && (sw == 8 || built >= 6)) {
             p->tok = built;
             break;
         }
     p->sw = sw;
     p->fr = rows / groups;
     // log2 of the LDS row stride: the multi-probe form alternates the rows of a stage's two tables
-    p->shift = (sw == 8 ? 7 : 6) + (mode == kProbes && p->fr <= 2 ? 1 : 0);
-    p->lds = gather_lds_bytes(tau, sw, mode == kProbes && p->fr <= 2);
+    const bool alternating = mode == kProbes && p->fr <= 2;
+    p->shift = (sw == 8 ? 7 : 6) + (alternating ? 1 : 0);
+    p->lds = gather_lds_bytes(tau, sw, alternating);
     if (p->lds < (size_t)kLdsMinBytes) p->lds = kLdsMinBytes;
     p->grid = (unsigned)cus;
     p->tail = tail;
