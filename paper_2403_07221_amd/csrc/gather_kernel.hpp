@@ -56,7 +56,7 @@ struct GatherArgs {
     int code_stride;   // codes (and weights, and groups of 1 + tau shares) per token in the arrays; k unless
                        // the launch covers only some of the tables
     int four_rows;     // plain sum: 1: four rows of a token in flight; 0: sixteen
-    int deep;          // 1: few wavefronts (DEEP)
+    int deep;          // few wavefronts: DEEP, 8 or 16; else 0
     int accumulate;    // 1: the sums start from what y holds (fp32 y, fp32 rows) instead of zero
     // The 16-byte piece q of row r = (j << tau) + code in slice s sits at
     //   tables + (s / spp) * slice_stride + (s % spp) * LPT*16 + r * row_stride + q*16
@@ -175,10 +175,10 @@ __device__ __forceinline__ void left_over(int rest, F f)
 }
 
 // WMODE: 0 = plain sum, 1 = weighted form, 2 = multi-probe form
-// DEEP (plain and weighted): for few wavefronts, whose registers nobody else needs: sixteen rows more are requested before
-// sixteen are added, and codes and weights ahead of the rows before them, so that no request waits for an earlier one's data
+// DEEP (plain and weighted; 0, 8 or 16): for few wavefronts, whose registers nobody else needs: DEEP rows more are requested
+// before DEEP are added, and codes and weights ahead of the rows before them, so that no request waits for an earlier one's data
 // (loads return in order: a code requested behind rows is there only when they are).
-template <int KIND, int LPT, int WMODE, bool DEEP>
+template <int KIND, int LPT, int WMODE, int DEEP>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
 {
     constexpr int TPW = 64 / LPT;  // tokens per wave
@@ -235,38 +235,36 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
     // codes with the last whole chunk instead held them through the loop (72 -> 76, 93 -> 102 registers): k = 100
     // weighted 261 -> 286.
     const int nch = k >> 3, rest = k & 7;
-    int done = 0;  // tables summed by the deep form: its whole groups of sixteen
-    if constexpr (DEEP) {
-        static_assert(WMODE != 2, "built for the plain and the weighted sum");
+    int done = 0;  // tables summed by the deep form: its whole groups
+    if constexpr (DEEP != 0) {
+        static_assert(WMODE != 2 && (DEEP == 8 || DEEP == 16), "built for the plain and the weighted sum");
+        constexpr int GN = DEEP, NC = GN / 8;  // tables of a group, chunks of their codes
         const float *wrow = WMODE == 1 ? a.weights + t * a.code_stride : nullptr;
-        const int ng = k >> 4;
+        const int ng = k / GN;
         if (ng > 0) {
-            struct Codes {
-                CodeChunk lo, hi;
-            };
-            Codes cc[2];
-            float w[2][16];
-            uint4 r[2][16];
-            auto load_codes = [&](Codes &c, int g) {
+            CodeChunk cc[2][NC];
+            float w[2][GN];
+            uint4 r[2][GN];
+            auto load_codes = [&](CodeChunk(&c)[NC], int g) {
                 const int gc = g < ng ? g : ng - 1;
-                c.lo.load(crow + gc * 16);
-                c.hi.load(crow + gc * 16 + 8);
+#pragma unroll
+                for (int h = 0; h < NC; ++h) c[h].load(crow + gc * GN + h * 8);
             };
-            auto load_weights = [&](float(&f)[16], int g) {
+            auto load_weights = [&](float(&f)[GN], int g) {
                 if constexpr (WMODE == 1) {
                     const int gc = g < ng ? g : ng - 1;
-                    __builtin_memcpy(&f[0], wrow + gc * 16, 32);
-                    __builtin_memcpy(&f[8], wrow + gc * 16 + 8, 32);
+#pragma unroll
+                    for (int h = 0; h < NC; ++h) __builtin_memcpy(&f[h * 8], wrow + gc * GN + h * 8, 32);
                 }
             };
-            auto issue = [&](int g, const Codes &c, uint4(&x)[16]) {
+            auto issue = [&](int g, const CodeChunk(&c)[NC], uint4(&x)[GN]) {
 #pragma unroll
-                for (int u = 0; u < 16; ++u) x[u] = row(g * 16 + u, u < 8 ? c.lo.code(u & 7) : c.hi.code(u & 7));
+                for (int u = 0; u < GN; ++u) x[u] = row(g * GN + u, c[u >> 3].code(u & 7));
                 __builtin_amdgcn_sched_barrier(0);
             };
-            auto add = [&](const uint4(&x)[16], const float(&f)[16]) {
+            auto add = [&](const uint4(&x)[GN], const float(&f)[GN]) {
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
+                for (int u = 0; u < GN; ++u) {
                     if constexpr (WMODE == 1) acc.fma(x[u], f[u]);
                     else acc.add(x[u]);
                 }
@@ -289,7 +287,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
                 if (g + 1 < ng) turn(std::integral_constant<int, 1>{}, g + 1);
             }
         }
-        done = ng << 4;
+        done = ng * GN;
     }
     if constexpr (WMODE == 2) {
         // The probes of all tables as one sequence, eight rows at a time, the next eight in flight while these are

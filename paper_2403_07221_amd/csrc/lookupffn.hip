@@ -101,22 +101,24 @@ template <int KIND, int LPT>
 void launch_gather_t(const GatherArgs &a, bool probes, dim3 grid, int threads, hipStream_t s)
 {
     if (probes) {
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 2, false>), grid, dim3(threads), 0, s, a);
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 2, 0>), grid, dim3(threads), 0, s, a);
         return;
     }
     if constexpr (LPT == 4 || LPT == 8 || LPT == 16) {  // the host asks for the deep form with these only
         if (a.deep) {
-            if (a.weights)
-                hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, true>), grid, dim3(threads), 0, s, a);
+            if (a.weights && a.deep == 8)
+                hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, 8>), grid, dim3(threads), 0, s, a);
+            else if (a.weights)
+                hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, 16>), grid, dim3(threads), 0, s, a);
             else
-                hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0, true>), grid, dim3(threads), 0, s, a);
+                hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0, 16>), grid, dim3(threads), 0, s, a);
             return;
         }
     }
     if (a.weights)
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, false>), grid, dim3(threads), 0, s, a);
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, 0>), grid, dim3(threads), 0, s, a);
     else
-        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0, false>), grid, dim3(threads), 0, s, a);
+        hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0, 0>), grid, dim3(threads), 0, s, a);
 }
 
 template <int KIND>
@@ -238,7 +240,7 @@ int gather_direct_part(int kind, int lpt, const GatherArgs &a, bool probes, dim3
 int gather_direct_load()
 {
     hipFuncAttributes attr;
-    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(gather_kernel<kElemF32, 8, 0, false>));
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(gather_kernel<kElemF32, 8, 0, 0>));
     return e == hipSuccess ? LFFN_OK : hip_fail(e, "hipFuncGetAttributes(gather_kernel)");
 }
 #endif
@@ -893,7 +895,7 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
     }
     // as many workgroups to the projections as leave a SIMD at most two waves
     unsigned p_groups = 1;
-    if (a.codes && N >= 64) {
+    if (a.codes && N >= 64 && a.P > 1) {
         int cus = 0;
         int rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;
@@ -1189,10 +1191,14 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
     //   weighted, fp32, k = 170, tau = 9, 512 wide: 64 tokens 16.5 / 12.0, 256 27.5 / 22.7, 500 39.4 / 36.7; fp16: 128 tokens
     //   16.0 / 11.2, 500 20.5 / 12.9, 1000 21.8 / 18.8, 2000 (eight wavefronts) 33.7 / 35.4; k = 96, 768 wide 500 tokens
     //   12.7 / 10.4, 1000 (six) 14.8 / 14.7; k = 64, 64 wide 10.0 / 9.9
+    // From five to eight (fp32 rows seven) sixteen in flight: weighted, fp16, k = 96, 768 wide 1000 tokens 14.8 / 13.4, k = 128,
+    // 344 wide 2000 19.1 / 16.6, 3000 (nine) 26.6 / 27.6; fp32, k = 128, 344 wide 1000 tokens 21.0 / 19.4, 1500 (eight) 27.9 / 28.9.
     //   plain: fp32 k = 170 64 tokens 14.3 / 12.0, k = 128, 344 wide 256 tokens 10.8 / 10.0, k = 96 64 tokens 9.2 / 9.3; fp16
     //   k = 128 9.8 / 10.4
-    a.deep = (lpt == 4 || lpt == 8 || lpt == 16) && cu_waves < 5 &&
-             (mode == kWeighted ? a.k >= 96 : mode == kPlain && !T.kind && a.k >= 128);
+    if (lpt == 4 || lpt == 8 || lpt == 16) {
+        if (mode == kWeighted && a.k >= 96) a.deep = cu_waves < 5 ? 16 : cu_waves < (T.kind ? 8 : 7) ? 8 : 0;
+        else if (mode == kPlain && !T.kind && a.k >= 128 && cu_waves < 5) a.deep = 16;
+    }
     if (opt.xcd_order == 1) xcd = true;
     if (opt.xcd_order == -1) xcd = false;
     a.xcd_mode = xcd;
@@ -1463,18 +1469,19 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
     const int64_t blocks = (n + per_block - 1) / per_block;
     dim3 grid = grid_of(blocks);  // a workgroup past the batch does a full hash of no token
-    int cus = 0;
-    int rc = device_cus(&cus);
+    const bool deep_ok = block == 64 && L == 10;
+    int cus = 0, rc = LFFN_OK;
+    if (a.P > 1 || deep_ok) rc = device_cus(&cus);
     if (rc != LFFN_OK) return rc;
     // as many workgroups to the projections as find a compute unit each (2 tokens: d = 64, block 32, 20 projections pass
     // 77 -> 16 us, d = 256, 6 projections with tables across them 93 -> 40)
     a.p_per = a.P;
     a.cross = N % tau != 0;
-    if (a.codes) grid.z = split_projections(a.P, a.cross, (int64_t)cus / blocks, &a.p_per);
+    if (a.codes && a.P > 1) grid.z = split_projections(a.P, a.cross, (int64_t)cus / blocks, &a.p_per);
     // With a wave alone on its SIMD the form with more operands in flight is faster at d_pad = 1024 with blocks of 64 (128
     // tokens, d = 768, weighted pass 42.8 -> 41.0 us, 202 tokens 38.5 -> 37.3, 2 tokens 37.3 / 37.5), at other shapes it is
     // not (block 32: 10 tokens 31.1 / 31.4, block 16: 216 tokens of 256 36.3 / 37.1, block 64: 5 tokens of 512 28.7 / 30.4).
-    if (block == 64 && L == 10 && blocks * grid.z <= cus) rc = lffn_host::bh_few_part(wmode, a, grid, s);
+    if (deep_ok && blocks * grid.z <= cus) rc = lffn_host::bh_few_part(wmode, a, grid, s);
     else if (L <= 8) rc = lffn_host::bh_lo_part(L, wmode, a, block, grid, s);
     else if (L == 9) rc = lffn_host::bh_512_part(wmode, a, block, grid, s);
     else rc = lffn_host::bh_1024_part(wmode, a, block, grid, s);

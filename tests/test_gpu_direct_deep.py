@@ -1,5 +1,5 @@
-"""The direct gather's form for few wavefronts and many tables (thirty-two rows in flight): numbers of tables around its groups
-of sixteen and the chunks of eight behind them, one token to the edge of its rule, every row type and slice width.
+"""The direct gather's form for few wavefronts and many tables (sixteen or thirty-two rows in flight): numbers of tables around its groups
+of eight and sixteen and the chunks of eight behind them, one token to the edge of its rule, every row type and slice width.
 
 Bars: plain bit-equal to the sequential fp32 sum; weighted within k * 2^-24 * sum |w row| <= 2e-5 of the output's rms for the
 171 terms at most and weights below one."""
@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("k", [96, 97, 103, 104, 111, 112, 127, 128, 135, 144, 159, 160, 170, 171])
 @pytest.mark.parametrize("n,tau,d_out,tdt,prep", [(1, 4, 40, "f32", False), (9, 9, 264, "f32", True), (300, 6, 128, "f32", False),
-                                                  (67, 5, 136, "bf16", False), (130, 4, 648, "f16", False)])
+                                                  (67, 5, 136, "bf16", False), (130, 4, 648, "f16", False), (1001, 4, 768, "f16", False),
+                                                  (900, 4, 344, "f32", False)])
 def test_deep_direct_gather(n, k, tau, d_out, tdt, prep):
     print(f"deep direct gather n={n} k={k} tau={tau} d_out={d_out} {tdt}", flush=True)
     rng = np.random.default_rng(n + 31 * k)
