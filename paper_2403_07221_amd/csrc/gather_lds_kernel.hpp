@@ -29,10 +29,11 @@
 // bank conflicts of the row reads (no copies: 95 us; neither: 57).  So the next stage's copies are the first thing a stage
 // issues (spread over its reads: 112 -> 109 us), nothing may wait for them in mid-stage (scratch reloads did: weighted 165 ->
 // 141 us, tau = 10 335 -> 291), and a wave's instructions are laid out so that neighbours do not depend on one another (a
-// row's address and weight are formed one slot ahead: 109 -> 105.5 us; multi-probe 1030 -> 729).  With the multi-probe
-// form's lagging groups and shares loaded two sweeps ahead, pass before and after all of it: plain 118 -> 105.6, weighted
-// 165 -> 136, multi-probe 898 -> 682, 65536 bf16 tokens 383 -> 349, tau = 10, k = 128, 1024 wide 335 -> 267, tau = 9, k = 170,
-// 32768 tokens, weighted 876 -> 765 us.
+// row's address and weight are formed one slot ahead: 109 -> 105.5 us; multi-probe 1030 -> 729).  With the stages brought
+// into the L2 ahead of their copies, more slot counts, and the multi-probe form's lagging groups and shares loaded two sweeps
+// ahead, pass before and after all of it: plain 118 -> 100, weighted 165 -> 129, multi-probe 899 -> 663 ... 683, 65536 bf16
+// tokens 384 -> 328, tau = 10, k = 128, 1024 wide 335 -> 239, 32768 tokens, k = 256, 512 wide 393 -> 285, tau = 9, k = 170, 32768
+// tokens, weighted 873 -> 759 us (the last hashes with BH for 398 of it, unchanged).
 //
 // Weighted form (Sec. 4: y = sum_j w_j T_j[code_j]): the fp32 weights come table-major and
 // token-contiguous (wpk[j][n_pad]) and are quad-shared like the code words; each row is
@@ -90,6 +91,7 @@ struct GatherLdsArgs {
     int token_splits;   // a unit = (slice, one of token_splits equal token ranges)
     int n_units;        // n_slices * token_splits
     int blocks_per_xcd; // gridDim.x / kXcds
+    int unit_chunks;    // (not multi-probe) 0, or the chunks of a unit where the workgroups of an XCD divide all chunks of its units
     // Where the piece (slice, table j, row r, 16-byte piece q) lives:
     //   tables + (slice / spp) * slice_stride + (slice % spp) * SW*16 + j * table_stride + r * row_stride + q*16
     // row-major tables: spp = 1, slice_stride = SW*16, row_stride = d_out*4, table_stride = rows * row_stride;
@@ -261,7 +263,23 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
     if ((uint32_t)a.n_units <= xcd) return;
     const uint32_t m = ((uint32_t)a.n_units - xcd + kXcds - 1) / kXcds;  // units dealt to this XCD
     uint32_t u_first, u_step, u_end, part, parts;
-    if (m >= Bx) {  // at least one unit per workgroup: take whole units c, c+Bx, ...
+    // Where whole chunks divide better than token ranges do (65536 tokens in three slices an XCD: three chunks of 16 slots for every
+    // workgroup instead of four of 13: bf16 tables, k = 96, pass 347 -> 328 us) a workgroup takes the chunks i_first ... i_end - 1 of
+    // the XCD's, and may change slice between.  Not the multi-probe form: the same code made it 2 % slower at 16384 tokens, where
+    // it is not taken (683 -> 698 us; its stage loop has no register to spare).
+    const uint32_t unit_chunks = PROBES ? 0u : (uint32_t)a.unit_chunks;
+    uint32_t i_first = 0, i_end = 0, per_block = 1;
+    if (unit_chunks) {
+        i_first = split_at(m * unit_chunks, Bx, c);
+        i_end = split_at(m * unit_chunks, Bx, c + 1);
+        if (i_end <= i_first) return;
+        per_block = (m * unit_chunks + Bx - 1) / Bx;
+        u_first = i_first / unit_chunks;
+        u_step = 1;
+        u_end = (i_end - 1) / unit_chunks + 1;
+        part = 0;
+        parts = 1;
+    } else if (m >= Bx) {  // at least one unit per workgroup: take whole units c, c+Bx, ...
         u_first = c;
         u_step = Bx;
         u_end = m;
@@ -295,6 +313,15 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
         const uint32_t s1 = split_at(n, (uint32_t)a.token_splits, split + 1);
         const uint32_t r0 = s0 + split_at(s1 - s0, parts, part), r1 = s0 + split_at(s1 - s0, parts, part + 1);
         if (r1 <= r0) continue;  // uniform over the workgroup
+        uint32_t nchunks = (r1 - r0 + G * TOK - 1) / (G * TOK), ch_first = 0, ch_end = nchunks;
+        uint32_t share = part, shares = parts;  // of the prefetch below: this workgroup's, of the unit's
+        if (unit_chunks) {
+            nchunks = unit_chunks;
+            ch_first = ui == u_first ? i_first - ui * unit_chunks : 0u;
+            ch_end = i_end - ui * unit_chunks < unit_chunks ? i_end - ui * unit_chunks : unit_chunks;
+            share = (ch_first + per_block - 1) / per_block;  // (the unit's workgroups in order, nearly)
+            shares = (unit_chunks + 2 * per_block - 2) / per_block;
+        }
 
         // Fill role of this thread: LDS bytes 16 tid .. 16 tid + 15 of every copy round, i.e. column piece fq of row
         // tid / SW (of table (tid / SW) % 2 and row tid / (2 SW) where the rows of two tables alternate).
@@ -328,9 +355,9 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
         constexpr uint32_t kPrefetch = 3;
         const uint32_t rows_a_line = a.row_stride < 128u ? 128u / a.row_stride : 1u;
         const uint32_t tbl_lines = rows / rows_a_line, stage_lines = (uint32_t)TPS * tbl_lines;
-        const bool prefetches = !PROBES && wave * 64u * parts < stage_lines;  // wave-uniform
-        uint32_t line = tid * parts + part;
-        if (line >= stage_lines) line = part % stage_lines;
+        const bool prefetches = !PROBES && wave * 64u * shares < stage_lines;  // wave-uniform
+        uint32_t line = tid * shares + share;
+        if (line >= stage_lines) line = share % stage_lines;
         const uint32_t poff = (line / tbl_lines) * (uint32_t)table_stride + (line % tbl_lines) * rows_a_line * a.row_stride;
         auto prefetch = [&](uint32_t s) {
             if (prefetches && s < nstages)
@@ -338,8 +365,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
         };
 
         const uint32_t len = r1 - r0;
-        const uint32_t nchunks = (len + G * TOK - 1) / (G * TOK);
-        for (uint32_t ch = 0; ch < nchunks; ++ch) {
+        for (uint32_t ch = ch_first; ch < ch_end; ++ch) {
             const uint32_t c0 = r0 + split_at(len, nchunks, ch), c1 = r0 + split_at(len, nchunks, ch + 1);
             // Token slots.  The lanes of a token group would all hold the same code word and
             // weights, so these are quad-shared: a lane keeps those of the slots 4m + r, r = its

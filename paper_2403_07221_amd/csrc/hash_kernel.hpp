@@ -243,8 +243,9 @@ __device__ __forceinline__ int end_table(const HashArgs &a, int pe, int N) { ret
 // WMODE: 0 = codes only, 1 = codes and gather weights (Sec. 4), 2 = codes and multi-probe shares
 //
 // Projections of few tokens go out over workgroups (grid y, p_per each; widths from 64 on), which a wave otherwise takes
-// one after another: 7 tokens of 119, k = 170, tau = 8 (11 projections), weighted, hash 21 -> 7 us.  A table that runs over
-// from the projection before is the business of the workgroup it ends in, which hashes that projection too.
+// one after another: pass of 210 tokens of 512, k = 170, tau = 8 (three projections), weighted, 34 -> 27 us, 491 tokens of 64
+// (18 projections) 41 -> 21.  A table that runs over from the projection before is the business of the workgroup it ends in,
+// which hashes that projection too.
 template <int LOG2N, int WMODE>
 __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
 {

@@ -1031,13 +1031,33 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
     // Staging pays only when a chunk re-uses each staged row a few times.
     if (opt.gather_path < 2 && chunk < 2 * (int64_t)rows) return LFFN_OK;
-    p->tok = (int)((chunk + groups - 1) / groups);
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
-    for (int built : kLdsSlots)
-        if (built >= p->tok && (sw == 8 || built >= 6)) {
-            p->tok = built;
-            break;
+    auto slots_of = [&](int64_t tokens) {
+        const int tok = (int)((tokens + groups - 1) / groups);
+        for (int built : kLdsSlots)
+            if (built >= tok && (sw == 8 || built >= 6)) return built;
+        return tok;
+    };
+    p->tok = slots_of(chunk);
+    // Every chunk streams all tables.  Where the workgroups of an XCD take fewer turns when they divide whole chunks instead of token
+    // ranges (whose shortest division decides: 32 workgroups over three slices give one of them 10), they do that, unless its
+    // slots cost more (a turn's fill and hand-over count as one slot).  65536 bf16 tokens, k = 96, 768 wide, pass 347 -> 328 us.
+    const int m = (a.n_units + kXcds - 1) / kXcds, Bx = a.blocks_per_xcd;
+    const int64_t unit_tokens = (n + a.token_splits - 1) / a.token_splits;
+    const int64_t turns = nchunks * (m > Bx ? (m + Bx - 1) / Bx : 1);
+    int64_t cost = turns * (p->tok + 1);
+    for (int built : kLdsSlots) {
+        if (mode == kProbes || built > tok_max || (sw == 4 && built < 6)) continue;
+        const int64_t unit_chunks = (unit_tokens + (int64_t)groups * built - 1) / ((int64_t)groups * built);
+        if (unit_chunks * m >= (int64_t)1 << 30) continue;
+        const int64_t t = (unit_chunks * m + Bx - 1) / Bx;
+        const int tok = slots_of((unit_tokens + unit_chunks - 1) / unit_chunks);
+        if (t < turns && tok <= tok_max && t * (tok + 1) < cost) {
+            cost = t * (tok + 1);
+            a.unit_chunks = (int)unit_chunks;
+            p->tok = tok;
         }
+    }
     p->sw = sw;
     p->fr = rows / groups;
     // log2 of the LDS row stride: the multi-probe form alternates the rows of a stage's two tables
