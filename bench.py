@@ -437,9 +437,10 @@ def main():
     }
     if staged:
         # measured with a stand-alone read loop (16 waves per CU, 16-byte reads, row offsets in registers):
-        # contiguous 147.7 TB/s; 8 lanes per random 128-byte row 82.8 TB/s; 4 lanes per random 64-byte row 68.5 TB/s
+        # contiguous 147.7 TB/s; random 128-byte rows by eight consecutive lanes 82.8 TB/s and in the kernel's lane order
+        # 170 / 144 times that; 4 lanes per random 64-byte row 68.5 TB/s
         wide = w.tau <= 8 if args.slice_lanes == 0 else args.slice_lanes == 8
-        ceiling = 82800.0 if wide else 68500.0
+        ceiling = 97700.0 if wide else 68500.0
         roofline["random_row_ceiling"] = ceiling
         roofline["frac_of_random_row_ceiling"] = roofline["achieved"] / ceiling
     if bh:
