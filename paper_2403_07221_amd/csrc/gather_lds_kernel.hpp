@@ -132,15 +132,20 @@ __device__ __forceinline__ const char *scalar_ptr(const char *p)
 // address lds_base + 16 * lane (lds_base and gbase wave-uniform).  Issued through inline asm so
 // that the compiler does not serialise later LDS reads of the *other* buffer behind it; the
 // caller waits with s_waitcnt vmcnt(0) before the barrier that publishes the buffer.
+// The compiler may form gbase in vector registers and read it into scalar ones right before the statement, and it places no
+// waits inside: a memory instruction needs five wait states after that, a scalar one none.  So a scalar instruction moves the
+// address first, which is also the one state a copy needs after the write of M0.  (16384-token passes: as before, tau = 10
+// 240.6 -> 242.9 us; five states of waiting instead 101.0 -> 101.5 and 240.3 -> 236.9.)
 __device__ __forceinline__ void lds_dma16(const char *gbase, uint32_t voff, uint32_t lds_base)
 {
     const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
+    const char *from;
     // M0 is written here, so it is named as clobbered: the compiler then keeps none of its own M0
     // values live across the statement (it warns that M0 is a reserved register; that is the point).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(from)
                  : "s"(m), "v"(voff), "s"(scalar_ptr(gbase))
                  : "memory", "m0");
 #pragma clang diagnostic pop
@@ -149,14 +154,15 @@ __device__ __forceinline__ void lds_dma16(const char *gbase, uint32_t voff, uint
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Four bytes a lane: brings a cache line per lane into the L2 (the LDS bytes are never read; an LDS copy has no destination
-// register that would have to be waited for).
+// register that would have to be waited for); its address as in lds_dma16.
 __device__ __forceinline__ void lds_dma4(const char *gbase, uint32_t voff, uint32_t lds_base)
 {
     const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
+    const char *from;
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 1\n\tglobal_load_lds_dword %1, %2"
-                 :
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
+                 : "=&s"(from)
                  : "s"(m), "v"(voff), "s"(scalar_ptr(gbase))
                  : "memory", "m0");
 #pragma clang diagnostic pop
@@ -164,7 +170,7 @@ __device__ __forceinline__ void lds_dma4(const char *gbase, uint32_t voff, uint3
 
 // The same as lds_dma16 for the lanes of `lanes` only (every lane is active outside): a lane's 16 bytes go to lds_base + 16 * lane whichever
 // others take part.  The mask is set inside the statement: a branch on the lane would make the compiler treat uniform values
-// that change beside it as divergent.
+// that change beside it as divergent.  (Three moves and s_nop 1 are the five wait states its address may need.)
 __device__ __forceinline__ void lds_dma16_lanes(const char *gbase, uint32_t voff, uint32_t lds_base, uint64_t lanes)
 {
     const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
