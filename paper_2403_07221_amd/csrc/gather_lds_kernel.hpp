@@ -464,7 +464,9 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                     // Slot i of the stage: token slot i % TOK of table i / TOK.  Reads run D rows ahead of the sums; a read's
                     // address and a row's weight are formed one slot before they are used, so that the instructions of a slot do
                     // not depend on one another (formed where they are used, every slot waited for them).
-                    constexpr int NS = TPS * TOK, D = TOK > 13 ? 4 : 5;  // (16 slots spill with five rows in flight)
+                    // (16 slots spill with five rows in flight; four slots of one table are all a stage has)
+                    constexpr int NS = TPS * TOK, D = TOK > 13 || NS < 5 ? 4 : 5;
+                    static_assert(D <= NS, "the first reads stay inside the stage");
                     u32x4 rd[D];
                     auto slot_at = [&](int i) { return quad_bcast(half[i / TOK][(i % TOK) >> 2], (i % TOK) & 3) + qs; };
                     auto slot_w = [&](int i) { return quad_bcast(w[i / TOK][(i % TOK) >> 2], (i % TOK) & 3); };

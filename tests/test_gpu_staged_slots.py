@@ -23,6 +23,7 @@ def _staged():
     yield
     B.lookupffn_set_option("gather_path", 0)
     B.lookupffn_set_option("token_slots", 0)
+    B.lookupffn_set_option("slice_lanes", 0)
 
 
 def make(n, k, tau, d_out):
@@ -70,3 +71,19 @@ def test_infinite_rows_reach_only_the_tokens_that_probe_them(tau):
     assert np.all(np.isinf(y[hit])) and hit.any()
     ref = oracle.gather_probes(codes[~hit], p[~hit], tables)
     assert rms_err(y[~hit], ref) <= TOL
+
+
+@pytest.mark.parametrize("n", [1, 1025])
+def test_one_wide_table_a_stage(n):
+    """A stage of one 64 KB table slice and four token slots: the rows read ahead of the sums are the whole stage."""
+    k, tau, d_out = 4, 9, 96
+    print(f"staged, 128-byte slices of 512-row tables n={n}", flush=True)
+    B.lookupffn_set_option("token_slots", 4)
+    B.lookupffn_set_option("slice_lanes", 8)
+    codes, tables, g = make(n, k, tau, d_out)
+    w = g.standard_normal((n, k), dtype=np.float32)
+    cd, td = B.to_device(codes.view(np.int16)), B.to_device(tables)
+    assert np.array_equal(B.lookupffn_gather(cd, td).cpu().numpy(), oracle.gather(codes, tables, acc64=False))
+    y = B.lookupffn_gather_weighted(cd, B.to_device(w), td).cpu().numpy()
+    assert rms_err(y, oracle.gather_weighted(codes, w, tables)) <= TOL
+    assert B.lookupffn_last_gather_kernel() == "gather_lds_kernel"
