@@ -105,6 +105,11 @@ struct GatherLdsArgs {
 
 constexpr int kPrefetchLds = kLdsThreads * 4;  // where the prefetching copies put their bytes
 
+// Multi-probe form: a lane without a table takes its share from this byte offset of a buffer that ends before it (and so gets
+// zero): the (1 + tau) * n_pad shares of a table, and a window of 16 token slots past any of them.
+constexpr uint32_t kProbesNoTable = 1u << 31;
+constexpr uint32_t kProbesWindow = 16 * 256 * 4;
+
 // bytes of LDS the kernel needs: two buffers and that (sw = lanes per token; alternating rows: and one row piece of zeros)
 __host__ __device__ inline size_t gather_lds_bytes(int tau, int sw, bool alternating)
 {
@@ -516,7 +521,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                 // ---- multi-probe form: one table a step, 1 + tau sweeps over it ------------------------------
                 const uint32_t tau = (uint32_t)a.tau, k = (uint32_t)a.k, lag = LAG ? (tid >> 4) & 1u : 0u;
                 const uint32_t nsteps = k + (LAG ? 1u : 0u);
-                const uint32_t crow = (uint32_t)a.n_pad * 4u;  // bytes between word rows (times 1 + tau: 31 bits, host)
+                const uint32_t crow = (uint32_t)a.n_pad * 4u;  // bytes between word rows (host: kProbesPiece)
                 // code words of the lane's table t - lag (any valid row where it has none)
                 auto load_codes = [&](uint32_t t) {
                     const uint32_t rb = t ? (t - 1u) >> 1 : 0u, ra = (t < k ? t : k - 1u) >> 1;
@@ -533,13 +538,14 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                 const char *srow_at = reinterpret_cast<const char *>(a.wpk) + (size_t)c0 * 4u;
                 uint32_t lt = 0, lp = 0;  // step and probe of the sweep that is loaded next
                 uint32_t sx;              // the lane's offset from that row
-                const uint32_t sx_first = LAG && lag ? 1u << 31 : 0u, sx_mid = LAG && !lag ? sstep : 0u,
-                               sx_last = LAG && !lag ? 1u << 31 : 0u;
+                const uint32_t sx_first = LAG && lag ? kProbesNoTable : 0u, sx_mid = LAG && !lag ? sstep : 0u,
+                               sx_last = LAG && !lag ? kProbesNoTable : 0u;
                 auto share_lane = [&]() {
                     const uint32_t first = lt == 0 ? ~0u : 0u, last = lt < k ? 0u : ~0u;  // (masks: a choice between the three
                     sx = (sx_first & first) | (sx_mid & ~(first | last)) | (sx_last & last);  // ends up in scratch memory)
                 };
                 share_lane();
+                static_assert(WQ * 16 * G <= (int)kProbesWindow, "the host keeps this much below kProbesNoTable");
                 auto load_share = [&](int mm) -> float {
                     return __uint_as_float(load_reg(srow_at, mm, sx, (LAG ? sstep : 0u) + WQ * 16 * G));
                 };

@@ -26,7 +26,7 @@ namespace lffn {
 // holding the LDS byte offsets (code << 7, i.e. code * 128-byte row pieces) of tables 2s (low
 // half) and 2s+1 (high half).  The token axis is padded so that a workgroup may read a full
 // 16 x 256 token window past any token without leaving the buffer; padding entries are zero.
-__host__ __device__ inline long long packed_n_pad(long long n) { return ((n + 127) / 128) * 128 + 16 * 256; }
+__host__ __device__ constexpr long long packed_n_pad(long long n) { return ((n + 127) / 128) * 128 + 16 * 256; }
 constexpr int kPackedShift = 7;
 // index of (table j, token t) in the staged gather's weight array: table-major, token-contiguous
 __host__ __device__ inline long long wpk_index(long long j, long long t, long long n_pad)

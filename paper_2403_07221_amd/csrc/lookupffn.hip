@@ -992,10 +992,8 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     const int groups = kLdsThreads / sw;
     // the kernel indexes tokens and bytes inside one table with 32 bits
     if (n >= (int64_t(1) << 31) - 4096 || (int64_t)rows * d_out * 4 >= (int64_t(1) << 32)) return LFFN_OK;
-    // ... and the multi-probe form the bytes of a stage's two tables, and those between their shares
-    if (mode == kProbes && ((int64_t)rows * d_out * 8 >= (int64_t(1) << 32) ||
-                            (tau + 1) * packed_n_pad(n) * 4 >= (int64_t(1) << 31)))
-        return LFFN_OK;
+    // (the multi-probe form bytes between two tables of a batch's shares too: kProbesPiece)
+    if (mode == kProbes && (int64_t)rows * d_out * 8 >= (int64_t(1) << 32)) return LFFN_OK;
     int cus = 0;
     int rc = device_cus(&cus);
     if (rc != LFFN_OK) return rc;
@@ -1119,6 +1117,7 @@ int launch_gather_lds(const LdsPlan &p, const uint32_t *packed, const float *wpk
     if ((kLdsThreads / p.sw) * p.fr != (1 << a.tau) || a.n_pad < a.n + 16 * 256 || (a.k & 1) || T.kind ||
         (mode != kPlain) != (wpk != nullptr) || !packed)
         return LFFN_E_UNSUPPORTED;
+    if (mode == kProbes && (a.tau + 1) * a.n_pad * 4 + kProbesWindow > (long long)kProbesNoTable) return LFFN_E_UNSUPPORTED;
     const dim3 grid(p.grid);
     int rc = LFFN_E_UNSUPPORTED;
     TimedLaunch tl(1, s);
@@ -1366,11 +1365,31 @@ int launch_gather_ring(const RingPlan &p, const uint16_t *codes, uint32_t *packe
     return LFFN_OK;
 }
 
+// Tokens that the multi-probe form of the staged gather takes at once: the shares of a table must end before kProbesNoTable.
+constexpr int64_t kProbesPiece = int64_t(1) << 25;
+static_assert((10 + 1) * packed_n_pad(kProbesPiece) * 4 + kProbesWindow <= kProbesNoTable, "up to tau = 10");
+
 // Gather from ABI-layout codes (and weights / shares): the staged kernel through the re-pack kernels when
 // the plan says so and the scratch has room, else the direct kernel.
 int gather_from_abi(Mode mode, const uint16_t *codes, const float *weights, const TableRef &T, void *y, int64_t n,
                     int k, int tau, int d_out, const LdsPlan &plan, Scratch *sc, hipStream_t s, const Options &opt)
 {
+    if (mode == kProbes && plan.use && n > kProbesPiece) {  // nearly equal pieces, one after another through the same scratch
+        const int64_t pieces = (n + kProbesPiece - 1) / kProbesPiece;
+        const int64_t m = ((n + pieces - 1) / pieces + 127) / 128 * 128;
+        for (int64_t t = 0; t < n; t += m) {
+            const int64_t len = std::min(m, n - t);
+            LdsPlan piece;
+            int rc = plan_gather_lds(len, k, tau, d_out, T, mode, opt, &piece);
+            if (rc != LFFN_OK) return rc;
+            Scratch scratch = *sc;
+            rc = gather_from_abi(mode, codes + t * k, weights + t * k * (1 + tau), T,
+                                 static_cast<char *>(y) + t * d_out * (T.y_kind ? 2 : 4), len, k, tau, d_out, piece,
+                                 &scratch, s, opt);
+            if (rc != LFFN_OK) return rc;
+        }
+        return LFFN_OK;
+    }
     RingPlan ring;
     int rrc = plan_gather_ring(n, k, tau, d_out, T, mode, opt, &ring);
     if (rrc != LFFN_OK) return rrc;
