@@ -990,10 +990,9 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     if (T.prepared && sw * 16 > T.pw) sw = T.pw / 16;  // a token's row piece must lie inside one prepared piece
     if (sw == 4 && tau < 8) return LFFN_OK;
     const int groups = kLdsThreads / sw;
-    // the kernel indexes tokens and bytes inside one table with 32 bits
+    // the kernel indexes tokens and bytes inside one table with 32 bits (the multi-probe form also the bytes between two tables of a
+    // batch's shares: kProbesPiece)
     if (n >= (int64_t(1) << 31) - 4096 || (int64_t)rows * d_out * 4 >= (int64_t(1) << 32)) return LFFN_OK;
-    // (the multi-probe form bytes between two tables of a batch's shares too: kProbesPiece)
-    if (mode == kProbes && (int64_t)rows * d_out * 8 >= (int64_t(1) << 32)) return LFFN_OK;
     int cus = 0;
     int rc = device_cus(&cus);
     if (rc != LFFN_OK) return rc;

@@ -1,4 +1,5 @@
-"""Multi-probe batches beyond 2^25 tokens, which the staged gather takes in pieces: every token against the direct kernel.
+"""Multi-probe batches at the limits of the staged gather's 32-bit offsets -- more than 2^25 tokens, which it takes in pieces; two
+tables of more than 4 GiB together -- every token against the direct kernel.
 
 Bar: the same bits.  Both kernels add a token's rows table by table and probe by probe with one fused multiply-add each.
 """
@@ -19,8 +20,16 @@ def _path():
 
 @pytest.mark.parametrize("tau,k", [(7, 2), (9, 3)])
 def test_pieces(tau, k):
-    n, d_out = (1 << 25) + 4097, 16
-    print(f"multi-probe pieces n={n} tau={tau} k={k}", flush=True)
+    check((1 << 25) + 4097, k, tau, 16)
+
+
+@pytest.mark.parametrize("tau,d_out", [(8, (1 << 21) + 256), (10, (1 << 19) + 256)])
+def test_wide_tables(tau, d_out):
+    check(2 << tau, 2, tau, d_out)
+
+
+def check(n, k, tau, d_out):
+    print(f"multi-probe n={n} tau={tau} k={k} d_out={d_out}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(tau)
     codes = torch.randint(0, 1 << tau, (n, k), generator=g, device="cuda", dtype=torch.int16)
     shares = torch.rand(n, k, 1 + tau, generator=g, device="cuda")

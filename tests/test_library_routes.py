@@ -51,3 +51,12 @@ def test_multi_probe_batch_in_pieces(recorder):
         assert a.y == R.FAKE + start * d_out * 4
         start += a.n
     assert start == n
+
+
+@pytest.mark.parametrize("mode", ["plain", "weighted", "probes"])
+@pytest.mark.parametrize("tau,d_out,staged", [(8, 1 << 21, True), (8, (1 << 22) - 4, True), (8, 1 << 22, False), (9, 1 << 20, True),
+                                              (10, (1 << 20) - 4, True), (10, 1 << 20, False)])
+def test_wide_tables(recorder, mode, tau, d_out, staged):
+    """The staged kernel's offsets are 32-bit inside one table; two of them may be larger."""
+    launches = R.record(recorder, [R.gather(mode, 4096, 2, tau, d_out)])[0]
+    assert launches[-1].kernel == ("gather_lds_kernel" if staged else "gather_kernel")
