@@ -265,7 +265,9 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
     constexpr uint32_t buf_bytes = tbl_bytes * TPS;  // one buffer (one stage)
     const uint32_t n = (uint32_t)a.n;                // the host uses this kernel only for n < 2^31
     const uint32_t nstages = (uint32_t)a.k / TPS;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)sbuf;  // LDS byte address of the staging area
+    // LDS byte address of the staging area.  It is 0: the multi-probe form flips bits of its rows' addresses and counts them from
+    // there, so no __shared__ variable may be added to this kernel (a test of the built library looks).
+    const uint32_t lds0 = (uint32_t)(uintptr_t)sbuf;
 
     // ---- which (unit, token range) pairs does this workgroup own? ---------------------
     const uint32_t xcd = blockIdx.x % kXcds;

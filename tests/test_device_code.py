@@ -1,8 +1,11 @@
-"""The device code of the built library, disassembled: what its inline assembly must leave to no compiler.
+"""The device code of the built library: what its sources rely on and no compiler checks.
 
-The compiler does not look into an inline assembly statement when it places wait states.  The CDNA instruction set asks for
-five between a vector instruction that writes a scalar register (v_readfirstlane, v_cmp) and a memory instruction that reads it;
-with fewer the memory instruction may take the register's old value, here the address of a copy into LDS.
+Wait states.  The compiler does not look into an inline assembly statement when it places them.  The CDNA instruction set asks
+for five between a vector instruction that writes a scalar register (v_readfirstlane, v_cmp) and a memory instruction that reads
+it; with fewer the memory instruction may take the register's old value, here the address of a copy into LDS.
+
+LDS addresses.  The staged gather's multi-probe form reads its rows at addresses counted from zero (it flips their bits), so the
+dynamic LDS must start there: the kernel has no static one.
 """
 import re
 import shutil
@@ -14,6 +17,7 @@ import pytest
 from paper_2403_07221_amd import build
 
 OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/lib/llvm/bin/llvm-objdump"
+READELF = shutil.which("llvm-readelf") or "/opt/rocm/lib/llvm/bin/llvm-readelf"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 VALU_TO_VMEM = 5  # wait states
 
@@ -104,3 +108,15 @@ def test_memory_instructions_wait_for_their_scalar_operands(tmp_path):
         copies += listing.count("global_load_lds")
         assert too_early(listing) == []
     assert copies > 100
+
+
+@pytest.mark.skipif(not shutil.which(READELF), reason="llvm-readelf not found")
+def test_staged_gather_has_no_static_lds(tmp_path):
+    sizes = []
+    for i, code in enumerate(code_objects()):
+        path = tmp_path / f"{i}.co"
+        path.write_bytes(code)
+        notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        sizes += [int(size) for size, name in re.findall(r"\.group_segment_fixed_size: (\d+).*?\.name: +(_Z\w+)", notes, re.S)
+                  if "gather_lds_kernel" in name]
+    assert len(sizes) > 100 and set(sizes) == {0}
