@@ -13,7 +13,7 @@ LIB = PKG / "liblookupffn.so"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 N_PARTS = 13         # csrc/lookupffn.hip compiles as parts 0 .. 12 (-DLFFN_PART=i), linked together
-SLOW_FIRST = [6, 11, 3, 2, 5, 4]   # the BH and the staged gather's kernels take the longest: start them first
+SLOW_FIRST = [0, 4, 3, 2, 11, 6, 5]   # the hash kernels of every width and the staged gather's take the longest: start them first
 OBJ_DIR = PKG / "_build"
 
 FLAGS = [

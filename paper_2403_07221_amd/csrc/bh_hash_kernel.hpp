@@ -60,11 +60,11 @@ struct BhArgs {
     int packed_shift;     // log2 of the row-piece bytes the packed codes are scaled by
     long long n;
     int d, k, tau, n_factors, P;
-    int p_per;            // projections per workgroup: grid z covers P; fewer than P only with `codes`
-    int cross;            // tables run over from one projection into the next
     int x_kind;           // element type of x: 0 fp32, 1 bf16, 2 IEEE half
     int x_vec4;           // rows may be read four coordinates at a time (alignment checked by the host)
     float scale;
+    int p_per;            // SPLIT: projections per workgroup: grid z covers P; fewer than P only with `codes`
+    int cross;            // SPLIT: tables run over from one projection into the next
 };
 
 // Shape constants of d_pad = 2^LOG2N.  WINDOW: the weights of a tau other than 4, 8, 16 are formed (z window in LDS).
@@ -194,9 +194,11 @@ __device__ __forceinline__ void lds_barrier()
 // beyond: it keeps up to sixteen in flight instead of four and may use any number of registers for them (built for
 // d_pad = 1024, block 64).
 //
-// Projections of few tokens go out over workgroups (grid z, p_per each), which ran one after another in one: a table
+// SPLIT: projections of few tokens go out over workgroups (grid z, p_per each), which ran one after another in one: a table
 // that runs over from the projection before is the business of the workgroup it ends in, which hashes that projection too.
-template <int LOG2N, int TB, int WMODE, bool FEW>
+// (A form of its own: the bounds of the projections cost a workgroup that has all of them up to 6 %, 20 tokens of 145, k = 12
+// 17.3 -> 18.4 us.)
+template <int LOG2N, int TB, int WMODE, bool FEW, bool SPLIT>
 __global__ __launch_bounds__(kBhThreads, FEW ? 1 : 3) void bh_hash_kernel(BhArgs a)
 {
     using L = BhLds<LOG2N, WMODE == 2>;
@@ -232,8 +234,9 @@ __global__ __launch_bounds__(kBhThreads, FEW ? 1 : 3) void bh_hash_kernel(BhArgs
     // do, which is no loss against the earlier form of the kernel that shared copies in LDS (65536 tokens, one projection,
     // tau = 8, blocks 16 / 32 / 64, that form against this: d = 256 60 / 75 / 105 -> 45 / 58 / 86 us, d = 512
     // 150 / 142 / 201 -> 87 / 116 / 171).
-    const int pb = (int)blockIdx.z * a.p_per, pe = P < pb + a.p_per ? P : pb + a.p_per;  // the projections emitted here
-    const int ps = pb > 0 && a.cross ? pb - 1 : pb;                                       // the first one hashed
+    // the projections emitted here, and the first one hashed
+    const int pb = SPLIT ? (int)blockIdx.z * a.p_per : 0, pe = SPLIT && pb + a.p_per < P ? pb + a.p_per : P;
+    const int ps = pb > 0 && a.cross ? pb - 1 : pb;
     const unsigned n_pf = (unsigned)(P * a.n_factors);
     constexpr unsigned UB = 4 * TB * 1024;  // operand bytes of a unit
     const __amdgpu_buffer_rsrc_t ops = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.apack), 0, (int)(n_pf * (N / 64) * UB), 0x00020000);

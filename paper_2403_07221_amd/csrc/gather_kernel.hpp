@@ -56,7 +56,6 @@ struct GatherArgs {
     int code_stride;   // codes (and weights, and groups of 1 + tau shares) per token in the arrays; k unless
                        // the launch covers only some of the tables
     int four_rows;     // plain sum: 1: four rows of a token in flight; 0: sixteen
-    int deep;          // few wavefronts: DEEP, 8 or 16; else 0
     int accumulate;    // 1: the sums start from what y holds (fp32 y, fp32 rows) instead of zero
     // The 16-byte piece q of row r = (j << tau) + code in slice s sits at
     //   tables + (s / spp) * slice_stride + (s % spp) * LPT*16 + r * row_stride + q*16
@@ -65,6 +64,7 @@ struct GatherArgs {
     uint32_t row_stride;
     uint32_t spp;
     unsigned long long slice_stride;
+    int deep;          // few wavefronts: DEEP, 8 or 16; else 0
 };
 
 // KIND: element type of the rows (0 fp32, 1 bf16, 2 IEEE half)

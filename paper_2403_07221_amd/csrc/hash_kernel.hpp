@@ -45,10 +45,10 @@ struct HashArgs {
     int packed_shift;     // log2 of the row-piece bytes the packed codes are scaled by (7: 128-byte pieces, 6: 64-byte)
     long long n;
     int d, k, tau, n_rounds, P;
-    int p_per;            // projections per workgroup (grid y covers all); fewer than all only with `codes`
-    int cross;            // tables run over from one projection into the next
     int x_kind;           // element type of x: 0 fp32, 1 bf16, 2 IEEE half
     float scale;          // (float)(1 / sqrt(N))
+    int p_per;            // SPLIT: projections per workgroup (grid y covers all); fewer than all only with `codes`
+    int cross;            // SPLIT: tables run over from one projection into the next
 };
 
 constexpr int kHashThreads = 256;
@@ -242,11 +242,12 @@ __device__ __forceinline__ int end_table(const HashArgs &a, int pe, int N) { ret
 
 // WMODE: 0 = codes only, 1 = codes and gather weights (Sec. 4), 2 = codes and multi-probe shares
 //
-// Projections of few tokens go out over workgroups (grid y, p_per each; widths from 64 on), which a wave otherwise takes
+// SPLIT: projections of few tokens go out over workgroups (grid y, p_per each; widths from 64 on), which a wave otherwise takes
 // one after another: pass of 210 tokens of 512, k = 170, tau = 8 (three projections), weighted, 34 -> 27 us, 491 tokens of 64
 // (18 projections) 41 -> 21.  A table that runs over from the projection before is the business of the workgroup it ends in,
-// which hashes that projection too.
-template <int LOG2N, int WMODE>
+// which hashes that projection too.  (A form of its own: their bounds cost a wave that has all projections 0.2 ... 0.3 us, 200 tokens
+// of 512, k = 60, weighted 5.4 -> 5.7.)
+template <int LOG2N, int WMODE, bool SPLIT>
 __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
 {
     constexpr bool WEIGHTED = WMODE != 0;
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
     const unsigned wave = tid >> 6;
     const int P = a.P, R = a.n_rounds;
     // the projections emitted here and, where tables cross into the first of them, the one before it
-    const int pb = (int)blockIdx.y * a.p_per, pe = P < pb + a.p_per ? P : pb + a.p_per;
+    const int pb = SPLIT ? (int)blockIdx.y * a.p_per : 0, pe = SPLIT && pb + a.p_per < P ? pb + a.p_per : P;
     const int ps = pb > 0 && a.cross ? pb - 1 : pb;
 
     // ---- block prologue: pack the sign diagonals into per-lane flip words ----------------
@@ -386,7 +387,8 @@ __global__ __launch_bounds__(kHashThreads) void hash_kernel(HashArgs a)
                 a.packed[(long long)s * a.n_pad + t] =
                     (code_at(2u * s) << a.packed_shift) | (code_at(2u * s + 1u) << (16 + a.packed_shift));
         } else {
-            for (int j = first_table(a, pb, N) + (int)lane; j < end_table(a, pe, N); j += 64) a.codes[t * a.k + j] = (uint16_t)code_at((unsigned)j);
+            for (int j = (SPLIT ? first_table(a, pb, N) : 0) + (int)lane; j < (SPLIT ? end_table(a, pe, N) : a.k); j += 64)
+                a.codes[t * a.k + j] = (uint16_t)code_at((unsigned)j);
         }
         wave_lds_fence();
     }
@@ -564,7 +566,7 @@ __device__ __forceinline__ uint32_t hash_code_at(const uint32_t *bitw, unsigned 
     return (uint32_t)(both >> sh) & ((1u << tau) - 1u);
 }
 
-// SPLIT: the projections are spread over workgroups (as in hash_kernel; a form of its own, for the scalar registers it takes)
+// SPLIT: the projections are spread over workgroups, as in hash_kernel
 template <int R, int WMODE, bool SPLIT>
 __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void hash1024_kernel(HashArgs a)
 {
@@ -604,8 +606,8 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
             sw[rd][3] = w.w;
         }
     };
-    const bool one = pe - ps == 1;
-    if (one && gw < a.n) load_masks(ps);
+    const int np = pe - ps;
+    if (np == 1 && gw < a.n) load_masks(ps);
 
     float xn[NREG];
     if (gw < a.n) h1024_load_row(a.x, gw, a.d, a.x_kind, vec_ok, lane, xn);
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(kHashThreads) __attribute__((amdgpu_waves_per_eu(4,
         if (t + n_waves < a.n) h1024_load_row(a.x, t + n_waves, a.d, a.x_kind, vec_ok, lane, xn);
 
         for (int p = ps; p < pe; ++p) {
-            if (!one) load_masks(p);
+            if (np > 1) load_masks(p);
             float v[NREG];
 #pragma unroll
             for (int e = 0; e < NREG; ++e) v[e] = xv[e];

@@ -187,16 +187,32 @@ int launch_gather_lds_mode(int tok, const GatherLdsArgs &a, int fr, int sw, dim3
     return LFFN_E_UNSUPPORTED;
 }
 
-template <int L, int TB, int WMODE, bool FEW>
-int launch_bh_k(const BhArgs &a, dim3 grid, hipStream_t s)
+template <int L, int TB, int WMODE, bool FEW, bool SPLIT>
+int launch_bh_s(const BhArgs &a, dim3 grid, hipStream_t s)
 {
-    auto kern = bh_hash_kernel<L, TB, WMODE, FEW>;
+    auto kern = bh_hash_kernel<L, TB, WMODE, FEW, SPLIT>;
     const bool query = lffn_host::attr_only();
     const size_t lds = query ? 160 * 1024 : BhLds<L, WMODE == 2>::bytes(a.P);
     int rc = allow_lds(reinterpret_cast<const void *>(kern), lds);
     if (rc != LFFN_OK || query) return rc;
     hipLaunchKernelGGL(kern, grid, dim3(kBhThreads), lds, s, a);
     return LFFN_OK;
+}
+
+template <int L, int TB, int WMODE, bool FEW>
+int launch_bh_k(const BhArgs &a, dim3 grid, hipStream_t s)
+{
+    // The form for some of the projections also takes all of them where the compiler made it the faster one: d_pad = 1024, weights
+    // in registers, blocks of 16 and 32 (k = 96, tau = 8: 4096 tokens 27.3 -> 26.5 us, 32768 tokens, block 16 103.4 -> 101.1).
+    if constexpr (L == 10 && WMODE == 1 && TB <= 2) {
+        return launch_bh_s<L, TB, WMODE, FEW, true>(a, grid, s);
+    } else {
+        if (grid.z > 1 || lffn_host::attr_only()) {
+            const int rc = launch_bh_s<L, TB, WMODE, FEW, true>(a, grid, s);
+            if (rc != LFFN_OK || grid.z > 1) return rc;
+        }
+        return launch_bh_s<L, TB, WMODE, FEW, false>(a, grid, s);
+    }
 }
 
 template <int L, int WMODE>
@@ -736,34 +752,46 @@ int check_gather(const uint16_t *codes, const void *tables, const void *y, int64
 }
 
 // ---------------------------------------------------------------- launches
+// grid y > 1: the form whose workgroups take some of the projections each (SPLIT), built for widths from 64 on
+template <int L, bool SPLIT>
+void launch_hash_s(const HashArgs &a, bool probes, dim3 grid, size_t lds, hipStream_t s)
+{
+    if (probes)
+        hipLaunchKernelGGL((hash_kernel<L, 2, SPLIT>), grid, dim3(kHashThreads), lds, s, a);
+    else if (a.weights || a.wpk)
+        hipLaunchKernelGGL((hash_kernel<L, 1, SPLIT>), grid, dim3(kHashThreads), lds, s, a);
+    else
+        hipLaunchKernelGGL((hash_kernel<L, 0, SPLIT>), grid, dim3(kHashThreads), lds, s, a);
+}
+
 template <int L>
 void launch_hash_t(const HashArgs &a, bool probes, dim3 grid, size_t lds, hipStream_t s)
 {
+    if constexpr (L >= 6) {
+        if (grid.y > 1) {
+            launch_hash_s<L, true>(a, probes, grid, lds, s);
+            return;
+        }
+    }
+    launch_hash_s<L, false>(a, probes, grid, lds, s);
+}
+
+template <int R, bool SPLIT>
+void launch_hash1024_s(const HashArgs &a, bool probes, dim3 grid, size_t lds, hipStream_t s)
+{
     if (probes)
-        hipLaunchKernelGGL((hash_kernel<L, 2>), grid, dim3(kHashThreads), lds, s, a);
+        hipLaunchKernelGGL((hash1024_kernel<R, 2, SPLIT>), grid, dim3(kHashThreads), lds, s, a);
     else if (a.weights || a.wpk)
-        hipLaunchKernelGGL((hash_kernel<L, 1>), grid, dim3(kHashThreads), lds, s, a);
+        hipLaunchKernelGGL((hash1024_kernel<R, 1, SPLIT>), grid, dim3(kHashThreads), lds, s, a);
     else
-        hipLaunchKernelGGL((hash_kernel<L, 0>), grid, dim3(kHashThreads), lds, s, a);
+        hipLaunchKernelGGL((hash1024_kernel<R, 0, SPLIT>), grid, dim3(kHashThreads), lds, s, a);
 }
 
 template <int R>
 void launch_hash1024_t(const HashArgs &a, bool probes, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (grid.y > 1) {
-        if (probes)
-            hipLaunchKernelGGL((hash1024_kernel<R, 2, true>), grid, dim3(kHashThreads), lds, s, a);
-        else if (a.weights || a.wpk)
-            hipLaunchKernelGGL((hash1024_kernel<R, 1, true>), grid, dim3(kHashThreads), lds, s, a);
-        else
-            hipLaunchKernelGGL((hash1024_kernel<R, 0, true>), grid, dim3(kHashThreads), lds, s, a);
-    } else if (probes) {
-        hipLaunchKernelGGL((hash1024_kernel<R, 2, false>), grid, dim3(kHashThreads), lds, s, a);
-    } else if (a.weights || a.wpk) {
-        hipLaunchKernelGGL((hash1024_kernel<R, 1, false>), grid, dim3(kHashThreads), lds, s, a);
-    } else {
-        hipLaunchKernelGGL((hash1024_kernel<R, 0, false>), grid, dim3(kHashThreads), lds, s, a);
-    }
+    if (grid.y > 1) launch_hash1024_s<R, true>(a, probes, grid, lds, s);
+    else launch_hash1024_s<R, false>(a, probes, grid, lds, s);
 }
 
 // What a hash launch writes: codes[n][k] (and weights[n][k], or shares[n][k][1+tau] with `probes`), or --

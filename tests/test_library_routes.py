@@ -60,3 +60,42 @@ def test_wide_tables(recorder, mode, tau, d_out, staged):
     """The staged kernel's offsets are 32-bit inside one table; two of them may be larger."""
     launches = R.record(recorder, [R.gather(mode, 4096, 2, tau, d_out)])[0]
     assert launches[-1].kernel == ("gather_lds_kernel" if staged else "gather_kernel")
+
+
+def hash_call(mode, n, d, k, tau, rounds=3, x_dtype=0):
+    name = "lookupffn_hash" + {"plain": "", "weighted": "_weighted", "probes": "_probes"}[mode]
+    return [name, *[R.FAKE] * (3 if mode == "plain" else 4), n, d, k, tau, rounds, x_dtype, None]
+
+
+def hash_bh_call(mode, n, d, k, tau, block, factors=4):
+    name = "lookupffn_hash_bh" + ("_weighted" if mode == "weighted" else "")
+    return [name, *[R.FAKE] * (4 if mode == "weighted" else 3), n, d, k, tau, PREPARED | block, factors, 0, None, 0, None]
+
+
+# Projections of few tokens go out over workgroups; every other call takes the form without their bounds, which is the faster one.
+# Tables that run over from one projection into the next (their tau does not divide d_pad) take two projections to a workgroup.
+@pytest.mark.parametrize("mode", ["plain", "weighted", "probes"])
+@pytest.mark.parametrize("n,d,k,tau,groups", [(1, 64, 7, 9, 1), (1, 64, 8, 8, 1), (1, 64, 9, 8, 2), (1, 64, 14, 9, 1), (1, 64, 15, 9, 3),
+                                              (200, 512, 60, 8, 1), (200, 512, 170, 8, 3), (700, 512, 170, 8, 2),
+                                              (2000, 512, 170, 8, 1), (1, 1024, 128, 8, 1), (1, 768, 170, 9, 1), (3, 1024, 256, 10, 3)])
+def test_projections_of_few_tokens(recorder, mode, n, d, k, tau, groups):
+    ((launch,),) = R.record(recorder, [hash_call(mode, n, d, k, tau)])
+    assert launch.kernel == ("hash1024_kernel" if d > 512 else "hash_kernel")
+    assert launch.grid[1] == groups and launch.params[-1] == (groups > 1)
+
+
+@pytest.mark.parametrize("mode", ["plain", "weighted"])
+@pytest.mark.parametrize("n,d,k,tau,block,groups,few", [
+    (1, 64, 8, 8, 16, 1, 0), (1, 64, 20, 8, 16, 3, 0), (1, 64, 20, 9, 16, 3, 0), (20, 145, 12, 8, 32, 1, 0),
+    (2000, 256, 96, 8, 64, 3, 0), (16384, 256, 96, 8, 64, 1, 0), (1, 768, 170, 9, 64, 1, 1), (128, 1024, 256, 16, 64, 4, 1),
+    (1000, 1024, 256, 16, 64, 4, 1), (1100, 1024, 256, 16, 64, 2, 1), (4096, 1024, 96, 8, 64, 1, 1), (4097, 1024, 96, 8, 64, 1, 0)])
+def test_bh_projections_of_few_tokens(recorder, mode, n, d, k, tau, block, groups, few):
+    ((launch,),) = R.record(recorder, [hash_bh_call(mode, n, d, k, tau, block)])
+    assert launch.kernel == "bh_hash_kernel" and launch.grid[2] == groups
+    assert launch.params[-2:] == (few, groups > 1)
+
+
+@pytest.mark.parametrize("block,bounds", [(16, 1), (32, 1), (64, 0)])
+def test_bh_weights_in_registers_keep_the_form_with_bounds(recorder, block, bounds):
+    ((launch,),) = R.record(recorder, [hash_bh_call("weighted", 16384, 1024, 96, 8, block)])
+    assert launch.grid[2] == 1 and launch.params[-2:] == (0, bounds)
