@@ -106,13 +106,18 @@ void launch_gather_t(const GatherArgs &a, bool probes, dim3 grid, int threads, h
     }
     if constexpr (LPT == 4 || LPT == 8 || LPT == 16) {  // the host asks for the deep form with these only
         if (a.deep) {
-            if (a.weights && a.deep == 8)
+            if (a.weights && a.deep == 8) {
                 hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, 8>), grid, dim3(threads), 0, s, a);
-            else if (a.weights)
+                return;
+            }
+            if (a.weights) {
                 hipLaunchKernelGGL((gather_kernel<KIND, LPT, 1, 16>), grid, dim3(threads), 0, s, a);
-            else
+                return;
+            }
+            if constexpr (KIND == kElemF32) {  // ... and for a plain sum with fp32 rows only
                 hipLaunchKernelGGL((gather_kernel<KIND, LPT, 0, 16>), grid, dim3(threads), 0, s, a);
-            return;
+                return;
+            }
         }
     }
     if (a.weights)

@@ -120,3 +120,15 @@ def test_staged_gather_has_no_static_lds(tmp_path):
         sizes += [int(size) for size, name in re.findall(r"\.group_segment_fixed_size: (\d+).*?\.name: +(_Z\w+)", notes, re.S)
                   if "gather_lds_kernel" in name]
     assert len(sizes) > 100 and set(sizes) == {0}
+
+
+@pytest.mark.skipif(not shutil.which(READELF), reason="llvm-readelf not found")
+def test_deep_direct_gather_is_built_as_it_is_launched(tmp_path):
+    """(row type, row pieces a token, mode, depth): weighted at either depth for every row type, plain for fp32 rows."""
+    path, forms = tmp_path / "a.co", set()
+    for code in code_objects():
+        path.write_bytes(code)
+        notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        forms |= {tuple(map(int, m)) for m in re.findall(r"_ZN4lffn13gather_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)EEE", notes)}
+    deep = {f for f in forms if f[3]}
+    assert deep == {(t, w, 1, d) for t in (0, 1, 2) for w in (4, 8, 16) for d in (8, 16)} | {(0, w, 0, 16) for w in (4, 8, 16)}
