@@ -1237,18 +1237,23 @@ int launch_gather_direct(const uint16_t *codes, const float *weights, const Tabl
     const int64_t cu_waves = (n + tpw - 1) / tpw * a.n_slices / cus;
     a.four_rows = mode == kPlain && beyond_l2 && !T.prepared && cu_waves >= 9 &&
                   (T.kind ? !ragged || cu_waves <= 128 : ragged && cu_waves <= 30);
-    // The form with thirty-two rows in flight: up to five wavefronts a compute unit (more lose what their registers cost),
-    // where the walk through the tables is long enough to show.  Gather alone, us, without / with it:
-    //   weighted, fp32, k = 170, tau = 9, 512 wide: 64 tokens 16.5 / 12.0, 256 27.5 / 22.7, 500 39.4 / 36.7; fp16: 128 tokens
-    //   16.0 / 11.2, 500 20.5 / 12.9, 1000 21.8 / 18.8, 2000 (eight wavefronts) 33.7 / 35.4; k = 96, 768 wide 500 tokens
-    //   12.7 / 10.4, 1000 (six) 14.8 / 14.7; k = 64, 64 wide 10.0 / 9.9
+    // The form with thirty-two rows in flight: up to five wavefronts a compute unit (more lose what their registers cost), where
+    // the walk through the tables is long enough to show.  Us without / with it:
+    //   passes on new tokens, weighted, 768 wide: fp32 k = 48 1 token 9.8 / 9.4, 16 13.0 / 11.9, k = 96 1 token 13.7 / 12.6, 16
+    //   18.4 / 15.7, k = 170, tau = 9 1 token 23.3 / 20.8; fp16 k = 48 1 token 9.5 / 9.2, 16 11.6 / 10.8; 256 wide k = 64 1 token
+    //   8.4 / 8.4, 16 10.5 / 9.6; plain (BH hash) k = 96 1 token 13.5 / 12.5, 16 19.8 / 17.4
+    //   gather alone, the same tokens again and again (the rows of a few then stay in the L2): weighted, fp32, 768 wide, 4 tokens
+    //   k = 48 3.8 / 3.9, k = 96 5.7 / 5.8, 64 tokens k = 32 4.7 / 4.3, k = 48 5.5 / 5.1, k = 96 10.4 / 8.2, 344 wide 500 tokens k = 24
+    //   5.4 / 5.7, k = 40 6.8 / 6.9; k = 170, tau = 9, 512 wide 256 tokens 27.5 / 22.7, 500 39.4 / 36.7; fp16 768 wide k = 16 1 token
+    //   2.8 / 2.8, 500 tokens k = 48 8.0 / 7.1, k = 170 20.5 / 12.9, 1000 21.8 / 18.8, 2000 (eight wavefronts) 33.7 / 35.4
+    //   plain, fp32, 768 wide k = 48 8 tokens 3.7 / 3.8, k = 96 7.4 / 6.2, 64 tokens 9.7 / 7.9; 64 wide 64 tokens k = 64 3.8 / 4.0, k = 96
+    //   5.9 / 5.6, 8 tokens 4.5 / 4.6; fp16 64 tokens k = 128 9.8 / 10.4
     // From five to eight (fp32 rows seven) sixteen in flight: weighted, fp16, k = 96, 768 wide 1000 tokens 14.8 / 13.4, k = 128,
-    // 344 wide 2000 19.1 / 16.6, 3000 (nine) 26.6 / 27.6; fp32, k = 128, 344 wide 1000 tokens 21.0 / 19.4, 1500 (eight) 27.9 / 28.9.
-    //   plain: fp32 k = 170 64 tokens 14.3 / 12.0, k = 128, 344 wide 256 tokens 10.8 / 10.0, k = 96 64 tokens 9.2 / 9.3; fp16
-    //   k = 128 9.8 / 10.4
+    // 344 wide 2000 19.1 / 16.6, 3000 (nine) 26.6 / 27.6; fp32, k = 128, 344 wide 1000 tokens 21.0 / 19.4, 1500 (eight) 27.9 /
+    // 28.9.
     if (lpt == 4 || lpt == 8 || lpt == 16) {
-        if (mode == kWeighted && a.k >= 96) a.deep = cu_waves < 5 ? 16 : cu_waves < (T.kind ? 8 : 7) ? 8 : 0;
-        else if (mode == kPlain && !T.kind && a.k >= 128 && cu_waves < 5) a.deep = 16;
+        if (mode == kWeighted && a.k >= 48) a.deep = cu_waves < 5 ? 16 : cu_waves < (T.kind ? 8 : 7) ? 8 : 0;
+        else if (mode == kPlain && !T.kind && a.k >= 96 && cu_waves < 5) a.deep = 16;
     }
     if (opt.xcd_order == 1) xcd = true;
     if (opt.xcd_order == -1) xcd = false;

@@ -99,3 +99,16 @@ def test_bh_projections_of_few_tokens(recorder, mode, n, d, k, tau, block, group
 def test_bh_weights_in_registers_keep_the_form_with_bounds(recorder, block, bounds):
     ((launch,),) = R.record(recorder, [hash_bh_call("weighted", 16384, 1024, 96, 8, block)])
     assert launch.grid[2] == 1 and launch.params[-2:] == (0, bounds)
+
+
+# The direct gather's deep form: both sides of each line of its rule (256 compute units; row types fp32, bf16, half)
+@pytest.mark.parametrize("mode,n,k,d_out,table,deep", [
+    ("weighted", 5, 47, 768, 0, 0), ("weighted", 5, 48, 768, 0, 16), ("weighted", 1, 48, 768, 0, 16), ("weighted", 1, 47, 768, 2, 0),
+    ("weighted", 1, 48, 768, 2, 16), ("weighted", 1, 48, 768, 1, 16), ("weighted", 424, 48, 768, 0, 16), ("weighted", 425, 48, 768, 0, 8),
+    ("weighted", 592, 48, 768, 0, 8), ("weighted", 593, 48, 768, 0, 0), ("weighted", 848, 48, 768, 2, 16), ("weighted", 849, 48, 768, 2, 8),
+    ("weighted", 1360, 48, 768, 2, 8), ("weighted", 1361, 48, 768, 2, 0), ("weighted", 64, 48, 8, 2, 0),
+    ("plain", 64, 95, 768, 0, 0), ("plain", 64, 96, 768, 0, 16), ("plain", 1, 96, 64, 0, 16), ("plain", 424, 96, 768, 0, 16),
+    ("plain", 425, 96, 768, 0, 0), ("plain", 64, 170, 768, 2, 0), ("plain", 64, 170, 768, 1, 0), ("probes", 64, 170, 768, 0, 0)])
+def test_deep_direct_gather(recorder, mode, n, k, d_out, table, deep):
+    launch = R.record(recorder, [R.option("gather_path", 1), R.gather(mode, n, k, 8, d_out, table)])[1][0]
+    assert launch.kernel == "gather_kernel" and launch.params[0] == table and launch.params[3] == deep
