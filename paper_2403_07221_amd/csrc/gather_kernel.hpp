@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a)
     } else if constexpr (WMODE == 1) {
         const float *wrow = a.weights + t * a.code_stride;
         const int ch0 = DEEP ? done >> 3 : 0;
-        if (ch0 < nch) {
+        if (DEEP ? ch0 < nch : nch) {  // (for the general form `nch > 0` compiles to a loop that is 3 % slower)
             CodeChunk cn;
             float wn[8];
             cn.load(crow + ch0 * 8);
