@@ -363,12 +363,24 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
 
         // L2 prefetch role.  The workgroups of a unit stream the same slice in step, so each copy of a stage used to wait for
         // the memory behind the L2.  They share out the lines of the stage kPrefetch stages ahead: 16384 tokens, k = 96, tau = 8
-        // pass 106 -> 100 us, weighted 136 -> 129, k = 256, 512 wide 386 -> 361, tau = 10 264 -> 243.  (Every workgroup
-        // asking for every line doubles the requests of the copies, which is what they are bound by: slower.)
+        // pass 106 -> 100 us, weighted 136 -> 129, k = 256, 512 wide 386 -> 361, tau = 10 264 -> 243.  The fewer share a slice the
+        // more of its lines each asks for twice, and the copies are bound by such requests, so it takes four workgroups to a unit,
+        // or two where the tables are too large to stay in the memory-side cache (256 MB) from one call to the next.
+        // Gather, k = 96, without / with it, tables of 700 MB in turn (three sets of tables in turn, which stay there):
+        //   one workgroup (29 slices of 128 bytes): 7946 tokens 118 / 204 us (119 / 205), weighted 131 / 225
+        //   two (13): 15892 tokens 89.8 / 81.7 (69.2 / 75.2), weighted 109 / 104 (87 / 97), 29798 tokens 105 / 106 (97.2 / 99.8);
+        //   of 1024 rows (13 slices of 64 bytes, 164 MB) 51650 tokens 177 / 162, weighted 212 / 204
+        //   four (7): 31784 tokens 87.6 / 75.0 (65.5 / 68.5), 59596 tokens 106 / 104 (98.4 / 99.4)
+        //   ten (24): 9932 tokens 88.0 / 76.3 (62.4 / 68.4), weighted 105 / 96 (80.5 / 82.1)
+        // Stages of 32 KB are gone before it pays (tau = 7, four workgroups 68.5 / 71.0, weighted 89.9 / 94.5, ten 95.5 / 97.0),
+        // except under many weighted slots (ten 125 / 120, sixteen 128 / 121).
+        constexpr bool kPrefetches = !PROBES && (FR >= 2 || (WEIGHTED && TOK >= 13));
+        const bool large = (uint64_t)a.k * rows * (uint32_t)a.nvec * 16u >= 128u << 20;
+        const uint32_t sharing = unit_chunks ? shares : Bx / m;  // the fewest workgroups of any unit
         constexpr uint32_t kPrefetch = 3;
         const uint32_t rows_a_line = a.row_stride < 128u ? 128u / a.row_stride : 1u;
         const uint32_t tbl_lines = rows / rows_a_line, stage_lines = (uint32_t)TPS * tbl_lines;
-        const bool prefetches = !PROBES && wave * 64u * shares < stage_lines;  // wave-uniform
+        const bool prefetches = kPrefetches && sharing >= (large ? 2u : 4u) && wave * 64u * shares < stage_lines;  // wave-uniform
         uint32_t line = tid * shares + share;
         if (line >= stage_lines) line = share % stage_lines;
         const uint32_t poff = (line / tbl_lines) * (uint32_t)table_stride + (line % tbl_lines) * rows_a_line * a.row_stride;
