@@ -169,7 +169,7 @@ __global__ __launch_bounds__(1024) void forward_stack_kernel(StackArgs a)
     auto request_signs = [&](const int8_t *sg) {
 #pragma unroll
         for (int rd = 0; rd < R; ++rd)
-            lds_dma16(reinterpret_cast<const char *>(sg) + rd * N, lane * 16u, (uint32_t)(uintptr_t)tp + rd * N);
+            lds_dma16<false>(reinterpret_cast<const char *>(sg) + rd * N, lane * 16u, (uint32_t)(uintptr_t)tp + rd * N);
     };
     const bool hasher = __builtin_amdgcn_readfirstlane((int)wave) == 0;
     if (hasher) request_signs(a.signs[0]);

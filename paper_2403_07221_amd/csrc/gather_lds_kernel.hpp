@@ -138,21 +138,30 @@ __device__ __forceinline__ const char *scalar_ptr(const char *p)
 // that the compiler does not serialise later LDS reads of the *other* buffer behind it; the
 // caller waits with s_waitcnt vmcnt(0) before the barrier that publishes the buffer.
 // The compiler may form gbase in vector registers and read it into scalar ones right before the statement, and it places no
-// waits inside: a memory instruction needs five wait states after that, a scalar one none.  So a scalar instruction moves the
-// address first, which is also the one state a copy needs after the write of M0.  (16384-token passes: as before, tau = 10
-// 240.6 -> 242.9 us; five states of waiting instead 101.0 -> 101.5 and 240.3 -> 236.9.)
+// waits inside: a memory instruction needs five wait states after that, a scalar one none (and a copy one after the write of
+// M0).  So a scalar instruction moves the address first, or, WAIT, the five states are waited: faster where the four copies of a
+// 64 KB slice go out together (16384 tokens, tau = 10, k = 128, 1024 wide gather 210.7 / 203.8 us), slower elsewhere (16384, tau
+// = 8, k = 96, 768 wide 83.6 / 85.8).
+template <bool WAIT>
 __device__ __forceinline__ void lds_dma16(const char *gbase, uint32_t voff, uint32_t lds_base)
 {
     const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
-    const char *from;
     // M0 is written here, so it is named as clobbered: the compiler then keeps none of its own M0
     // values live across the statement (it warns that M0 is a reserved register; that is the point).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
-                 : "=&s"(from)
-                 : "s"(m), "v"(voff), "s"(scalar_ptr(gbase))
-                 : "memory", "m0");
+    if constexpr (WAIT) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(m), "v"(voff), "s"(scalar_ptr(gbase))
+                     : "memory", "m0");
+    } else {
+        const char *from;
+        asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                     : "=&s"(from)
+                     : "s"(m), "v"(voff), "s"(scalar_ptr(gbase))
+                     : "memory", "m0");
+    }
 #pragma clang diagnostic pop
 }
 
@@ -356,8 +365,8 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                                 lds0 + ((s >> 1) & 1u) * kLdsBufBytes + (idx * kLdsThreads + wave * 64u) * 16u,
                                 s & 1u ? ~kEven : kEven);
             } else {
-                lds_dma16(slice_base + (size_t)(s * TPS + idx / FR) * table_stride + (size_t)(idx % FR * G) * a.row_stride,
-                          foff, lds0 + (s & 1u) * buf_bytes + (idx * kLdsThreads + wave * 64u) * 16u);
+                lds_dma16<FR == 4 && !PROBES>(slice_base + (size_t)(s * TPS + idx / FR) * table_stride + (size_t)(idx % FR * G) * a.row_stride,
+                                              foff, lds0 + (s & 1u) * buf_bytes + (idx * kLdsThreads + wave * 64u) * 16u);
             }
         };
 
