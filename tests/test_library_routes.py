@@ -6,6 +6,7 @@ import shutil
 import pytest
 
 import recorded as R
+import staged_forms as forms
 
 pytestmark = pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
 PREPARED = 0x100
@@ -112,3 +113,29 @@ def test_bh_weights_in_registers_keep_the_form_with_bounds(recorder, block, boun
 def test_deep_direct_gather(recorder, mode, n, k, d_out, table, deep):
     launch = R.record(recorder, [R.option("gather_path", 1), R.gather(mode, n, k, 8, d_out, table)])[1][0]
     assert launch.kernel == "gather_kernel" and launch.params[0] == table and launch.params[3] == deep
+
+
+MODE = {"plain": 0, "weighted": 1, "probes": 2}
+
+
+@pytest.mark.parametrize("tau,lanes", forms.WIDTHS)
+def test_staged_forms_take_their_slots(recorder, tau, lanes):
+    """The batches of the GPU tests of the staged gather's forms (staged_forms.py): slots, copy rounds, mode, lanes."""
+    cases = [(mode, slots) for t, w, slots in forms.RANGES if (t, w) == (tau, lanes) for mode in MODE
+             if mode != "probes" or forms.has_probes(tau, lanes)]
+    calls = [R.option("gather_path", 2), R.option("slice_lanes", lanes)]
+    for mode, slots in cases:
+        calls += [R.option("token_slots", slots), R.gather(mode, forms.tokens(lanes, slots), forms.TABLES, tau, forms.width(lanes),
+                                                           0 if (tau, lanes) == (9, 8) else PREPARED)]
+    for (mode, slots), launches in zip(cases, R.record(recorder, calls)[3::2]):
+        staged = [x for x in launches if x.kernel == "gather_lds_kernel"]
+        assert [x.params for x in staged] == [(slots, (1 << tau) // (1024 // lanes), MODE[mode], lanes)]
+        assert staged[0].args(R.GatherLdsArgs).unit_chunks == 0
+
+
+def test_staged_forms_divide_whole_chunks(recorder):
+    for d_out, tau, n, allowed, slots in forms.CHUNKS:
+        for mode in ("plain", "weighted"):
+            calls = [R.option("gather_path", 2), R.option("token_slots", allowed), R.gather(mode, n, 4, tau, d_out, PREPARED)]
+            (launch,) = [x for x in R.record(recorder, calls)[2] if x.kernel == "gather_lds_kernel"]
+            assert launch.params[0] == slots and launch.args(R.GatherLdsArgs).unit_chunks > 0, (d_out, tau, n)
