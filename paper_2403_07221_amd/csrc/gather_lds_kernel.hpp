@@ -583,13 +583,28 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                         share_lane();
                     }
                 };
+                // Four slots: a step is shorter than the memory's latency, and to wait for a share is to wait for every request before
+                // it (they return in order), the next table's rows among them.  So a table's shares are all requested a step ahead,
+                // after its rows, and nothing waits before the step's end (4966 tokens, k = 48, tau = 7, 512 wide 155 -> 117 us;
+                // 123 when a stage was two tables).
+                constexpr bool kShort = TOK == 4;
+                constexpr int NP = kShort ? __builtin_ctz(rows) + 1 : 1;  // 1 + tau
+                float wn[NP];
                 float wA[WQ], wB[WQ];  // shares of this sweep and of the next, then of the one after
+                if constexpr (kShort) {
 #pragma unroll
-                for (int mm = 0; mm < WQ; ++mm) wA[mm] = load_share(mm);
-                next_row();
+                    for (int p = 0; p < NP; ++p) {
+                        wn[p] = load_share(0);
+                        next_row();
+                    }
+                } else {
 #pragma unroll
-                for (int mm = 0; mm < WQ; ++mm) wB[mm] = load_share(mm);
-                next_row();
+                    for (int mm = 0; mm < WQ; ++mm) wA[mm] = load_share(mm);
+                    next_row();
+#pragma unroll
+                    for (int mm = 0; mm < WQ; ++mm) wB[mm] = load_share(mm);
+                    next_row();
+                }
                 if (LAG && tid < PIECE / 16) sbuf[2 * kLdsBufBytes / 16 + tid] = make_uint4(0u, 0u, 0u, 0u);  // the zero row
                 __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
                 hand_over();
@@ -639,21 +654,51 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                     using ph1 = std::integral_constant<int, TOK % D>;
 #pragma unroll
                     for (int i = 0; i < D; ++i) rd[i] = lds_row(off[i]);
-                    uint32_t pr = 0;
-                    for (; pr < tau; pr += 2) {
-                        sweep(ph0{}, pr, wA);
-                        sweep(ph1{}, pr + 1, wB);
-                    }
-                    if (pr == tau) {  // an odd number of sweeps: the sets change places
-                        sweep(ph0{}, pr, wA);
+                    if constexpr (kShort) {
+                        float ws[NP];
 #pragma unroll
-                        for (int mm = 0; mm < WQ; ++mm) {
-                            const float x = wA[mm];
-                            wA[mm] = wB[mm];
-                            wB[mm] = x;
+                        for (int p = 0; p < NP; ++p) ws[p] = wn[p];
+                        uint32_t at = off[0] ^ flip_of(1u);
+                        float wb = quad_bcast(ws[0], 0);
+#pragma unroll
+                        for (int e = 0; e < NP * TOK; ++e) {  // slot i of sweep p
+                            constexpr int kShares = 2;        // of a sweep
+                            const int p = e / TOK, i = e % TOK, pn = (e + 1) / TOK, in_ = (e + 1) % TOK;
+                            if (i == 0 && p < (int)FILLS && t + 1 < k) fill_piece(t + 1, p);
+                            if (i == 1 && p == 1) load_codes(tn);
+                            if (i >= TOK - kShares && p * kShares + i - (TOK - kShares) < NP) {
+                                wn[p * kShares + i - (TOK - kShares)] = load_share(0);
+                                next_row();
+                            }
+                            const u32x4 v = rd[i];
+                            const uint32_t ac = at;
+                            const float wc = wb;
+                            if (e + 1 < NP * TOK) {
+                                wb = quad_bcast(ws[pn < NP ? pn : 0], in_);
+                                at = off[in_] ^ flip_of(pn + 1u);
+                            }
+                            acc[i].fma(make_uint4(v.x, v.y, v.z, v.w), wc);
+                            acc[i].pin();
+                            if (p + 1 < NP) rd[i] = lds_row(ac);
+                            __builtin_amdgcn_sched_barrier(0);
                         }
+                    } else {
+                        uint32_t pr = 0;
+                        for (; pr < tau; pr += 2) {
+                            sweep(ph0{}, pr, wA);
+                            sweep(ph1{}, pr + 1, wB);
+                        }
+                        if (pr == tau) {  // an odd number of sweeps: the sets change places
+                            sweep(ph0{}, pr, wA);
+#pragma unroll
+                            for (int mm = 0; mm < WQ; ++mm) {
+                                const float x = wA[mm];
+                                wA[mm] = wB[mm];
+                                wB[mm] = x;
+                            }
+                        }
+                        load_codes(tn);
                     }
-                    load_codes(tn);
                     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the next table's rows, codes and first shares have landed
                     hand_over();
                 }
