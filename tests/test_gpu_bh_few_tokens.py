@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("d,k,tau,block", [
     (64, 40, 9, 16), (64, 17, 5, 64), (100, 96, 8, 32), (256, 170, 9, 32), (300, 200, 7, 16), (500, 256, 4, 64),
-    (768, 170, 9, 64), (1024, 256, 16, 16), (1024, 140, 15, 32), (1000, 228, 9, 64)])
+    (768, 170, 9, 64),  # two projections with a table across them: stay together
+    (1024, 256, 16, 16), (1024, 140, 15, 32), (1000, 228, 9, 64), (1024, 256, 16, 64)])
 @pytest.mark.parametrize("n", [1, 19])
 def test_projections_over_workgroups(n, d, k, tau, block):
     print(f"bh few tokens n={n} d={d} k={k} tau={tau} block={block}", flush=True)

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,k,tau,R", [(64, 40, 9, 2), (33, 17, 16, 4), (119, 170, 8, 4), (256, 170, 9, 3), (500, 200, 11, 1),
-                                       (768, 170, 13, 2), (1024, 256, 9, 3), (1024, 256, 16, 4), (700, 205, 15, 5), (2048, 500, 13, 2)])
+                                       (1000, 300, 11, 1), (768, 170, 13, 2), (1024, 256, 9, 3), (1024, 256, 16, 4), (700, 205, 15, 5), (2048, 500, 13, 2)])
 @pytest.mark.parametrize("n", [1, 13])
 def test_projections_over_workgroups(n, d, k, tau, R):
     print(f"hash few tokens n={n} d={d} k={k} tau={tau} R={R}", flush=True)

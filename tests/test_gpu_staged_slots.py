@@ -1,5 +1,6 @@
-"""The staged gather where its stages and lagging groups begin and end: few tables, every table size and slice width, token
-counts round a chunk's edges.  Multi-probe groups that lag a table behind read zeros in the first and the last step, so an
+"""The staged gather where its stages and lagging groups begin and end: few tables, every table size, small batches (chunks of a
+few tokens in the forms of four slots, or six for 64-byte slices, whatever limit is set; the other slot counts:
+test_gpu_staged_forms.py).  Multi-probe groups that lag a table behind read zeros in the first and the last step, so an
 infinite row of those tables reaches only the tokens that probe it.
 
 Bars: plain bit-equal to the sequential fp32 sum; weighted and multi-probe within 1e-5 of the output's rms (k (1 + tau) <= 88

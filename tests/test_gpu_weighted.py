@@ -162,18 +162,18 @@ def test_gather_weighted_unit_weights_equal_the_plain_gather(lpt):
 LDS_SHAPES = [
     # n, k, tau, d_out      (gather_path = 2 forces the LDS-staged kernel: fp32 tables, tau 7 .. 10; odd k has a file of its own)
     (1003, 96, 8, 768),      # three slices per XCD, ragged chunks
-    (16384, 32, 8, 768),     # the benchmark's split, two chunks of 6 tokens per lane
+    (16384, 32, 8, 768),     # the benchmark's split, 13 token slots per lane (every slot count: test_gpu_staged_forms.py)
     (5000, 24, 7, 200),      # ragged last slice, 128-row tables
     (130, 2, 7, 4),          # a single 16-byte piece per row
-    (120000, 4, 7, 128),     # several chunks per workgroup, 12 tokens per lane
+    (120000, 4, 7, 128),     # 16 token slots per lane
     (300, 2, 7, 8192),       # as many slice-units as workgroups
     (1, 6, 8, 64),           # one token
     (777, 2, 8, 64),         # a single stage
-    (700, 6, 8, 64),         # an odd number of stages, 6 tokens per lane
-    (3000, 170, 9, 768),     # tau = 9: one table per stage
+    (700, 6, 8, 64),         # an odd number of stages, 4 token slots per lane
+    (3000, 170, 9, 768),     # tau = 9: 64-byte column slices, two tables per stage
     (1500, 2, 9, 64),        # tau = 9, a single code word
     (9000, 6, 9, 200),       # tau = 9, three code words, ragged last slice
-    (5000, 128, 10, 1024),   # tau = 10: 64-byte column slices
+    (5000, 128, 10, 1024),   # tau = 10: one table per stage
     (9000, 6, 10, 200),
 ]
 

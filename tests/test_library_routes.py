@@ -78,17 +78,18 @@ def hash_bh_call(mode, n, d, k, tau, block, factors=4):
 @pytest.mark.parametrize("mode", ["plain", "weighted", "probes"])
 @pytest.mark.parametrize("n,d,k,tau,groups", [(1, 64, 7, 9, 1), (1, 64, 8, 8, 1), (1, 64, 9, 8, 2), (1, 64, 14, 9, 1), (1, 64, 15, 9, 3),
                                               (200, 512, 60, 8, 1), (200, 512, 170, 8, 3), (700, 512, 170, 8, 2),
-                                              (2000, 512, 170, 8, 1), (1, 1024, 128, 8, 1), (1, 768, 170, 9, 1), (3, 1024, 256, 10, 3)])
+                                              (2000, 512, 170, 8, 1), (1, 1024, 128, 8, 1), (1, 768, 170, 9, 1), (3, 1024, 256, 10, 3),
+                                              (13, 1000, 300, 11, 4), (13, 2048, 500, 13, 4)])
 def test_projections_of_few_tokens(recorder, mode, n, d, k, tau, groups):
     ((launch,),) = R.record(recorder, [hash_call(mode, n, d, k, tau)])
-    assert launch.kernel == ("hash1024_kernel" if d > 512 else "hash_kernel")
+    assert launch.kernel == ("hash1024_kernel" if 512 < d <= 1024 else "hash_kernel")
     assert launch.grid[1] == groups and launch.params[-1] == (groups > 1)
 
 
 @pytest.mark.parametrize("mode", ["plain", "weighted"])
 @pytest.mark.parametrize("n,d,k,tau,block,groups,few", [
     (1, 64, 8, 8, 16, 1, 0), (1, 64, 20, 8, 16, 3, 0), (1, 64, 20, 9, 16, 3, 0), (20, 145, 12, 8, 32, 1, 0),
-    (2000, 256, 96, 8, 64, 3, 0), (16384, 256, 96, 8, 64, 1, 0), (1, 768, 170, 9, 64, 1, 1), (128, 1024, 256, 16, 64, 4, 1),
+    (2000, 256, 96, 8, 64, 3, 0), (16384, 256, 96, 8, 64, 1, 0), (1, 768, 170, 9, 64, 1, 1), (19, 1000, 228, 9, 64, 3, 1), (19, 1024, 256, 16, 64, 4, 1), (128, 1024, 256, 16, 64, 4, 1),
     (1000, 1024, 256, 16, 64, 4, 1), (1100, 1024, 256, 16, 64, 2, 1), (4096, 1024, 96, 8, 64, 1, 1), (4097, 1024, 96, 8, 64, 1, 0)])
 def test_bh_projections_of_few_tokens(recorder, mode, n, d, k, tau, block, groups, few):
     ((launch,),) = R.record(recorder, [hash_bh_call(mode, n, d, k, tau, block)])
