@@ -14,10 +14,13 @@ from paper_2403_07221_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("k", [48, 49, 55, 63, 64, 71, 79, 80, 95, 96, 97, 103, 104, 111, 112, 127, 128, 135, 144, 159, 160, 170, 171])
-@pytest.mark.parametrize("n,tau,d_out,tdt,prep", [(1, 4, 40, "f32", False), (9, 9, 264, "f32", True), (300, 6, 128, "f32", False),
-                                                  (67, 5, 136, "bf16", False), (130, 4, 648, "f16", False), (1001, 4, 768, "f16", False),
-                                                  (900, 4, 344, "f32", False)])
+KS = [48, 49, 55, 63, 64, 71, 79, 80, 95, 96, 97, 103, 104, 111, 112, 127, 128, 135, 144, 159, 160, 170, 171]
+SHAPES = [(1, 4, 40, "f32", False), (9, 9, 264, "f32", True), (300, 6, 128, "f32", False), (67, 5, 136, "bf16", False),
+          (130, 4, 648, "f16", False), (1001, 4, 768, "f16", False), (900, 4, 344, "f32", False)]
+
+
+@pytest.mark.parametrize("k", KS)
+@pytest.mark.parametrize("n,tau,d_out,tdt,prep", SHAPES)
 def test_deep_direct_gather(n, k, tau, d_out, tdt, prep):
     print(f"deep direct gather n={n} k={k} tau={tau} d_out={d_out} {tdt}", flush=True)
     rng = np.random.default_rng(n + 31 * k)

@@ -7,6 +7,7 @@ import pytest
 
 import recorded as R
 import staged_forms as forms
+import test_gpu_direct_deep as deep_tests
 
 pytestmark = pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
 PREPARED = 0x100
@@ -140,3 +141,11 @@ def test_staged_forms_divide_whole_chunks(recorder):
             calls = [R.option("gather_path", 2), R.option("token_slots", allowed), R.gather(mode, n, 4, tau, d_out, PREPARED)]
             (launch,) = [x for x in R.record(recorder, calls)[2] if x.kernel == "gather_lds_kernel"]
             assert launch.params[0] == slots and launch.args(R.GatherLdsArgs).unit_chunks > 0, (d_out, tau, n)
+
+
+def test_deep_direct_gather_tests_take_the_deep_form(recorder):
+    kind = {"f32": 0, "bf16": 1, "f16": 2}
+    calls = [R.option("gather_path", 1)] + [R.gather("weighted", n, k, tau, d_out, kind[t] | (PREPARED if prep else 0))
+                                            for n, tau, d_out, t, prep in deep_tests.SHAPES for k in deep_tests.KS]
+    depths = [launches[0].params[3] for launches in R.record(recorder, calls)[1:]]
+    assert set(depths) == {8, 16}
