@@ -435,10 +435,12 @@ def main():
                        "frac_of_hbm_peak_on_compulsory_bytes":
                            (compulsory + w.d * xb * w.n_tokens) * w.n_layers / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS},
     }
-    if staged:
-        # measured with a stand-alone read loop (16 waves per CU, 16-byte reads, row offsets in registers):
-        # contiguous 147.7 TB/s; random 128-byte rows by eight consecutive lanes 82.8 TB/s and in the kernel's lane order
-        # 170 / 144 times that; 4 lanes per random 64-byte row 68.5 TB/s
+    if staged and not args.probes:
+        # Random rows of one table, as the plain and weighted forms read them, measured with a stand-alone read loop (16 waves per
+        # CU, 16-byte reads, row offsets in registers): contiguous 147.7 TB/s; 128-byte rows by eight consecutive lanes 82.8 TB/s,
+        # 4 lanes per 64-byte row 68.5 TB/s.  In the kernel's lane order 128-byte rows came at 170 bytes a clock and compute unit
+        # against 144 in consecutive order: 97.7 TB/s is derived, 82.8 times that.  (The multi-probe form reads two tables side by
+        # side in the banks, which these do not describe.)
         wide = w.tau <= 8 if args.slice_lanes == 0 else args.slice_lanes == 8
         ceiling = 97700.0 if wide else 68500.0
         roofline["random_row_ceiling"] = ceiling
