@@ -1554,9 +1554,12 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     a.p_per = a.P;
     a.cross = N % tau != 0;
     if (a.codes && a.P > 1) grid.z = split_projections(a.P, a.cross, (int64_t)cus / blocks, &a.p_per);
-    // With a wave alone on its SIMD the form with more operands in flight is faster at d_pad = 1024 with blocks of 64 (128
-    // tokens, d = 768, weighted pass 42.8 -> 41.0 us, 202 tokens 38.5 -> 37.3, 2 tokens 37.3 / 37.5), at other shapes it is
-    // not (block 32: 10 tokens 31.1 / 31.4, block 16: 216 tokens of 256 36.3 / 37.1, block 64: 5 tokens of 512 28.7 / 30.4).
+    // With a wave alone on its SIMD the form with more operands in flight is faster at d_pad = 1024 with blocks of 64: the factors
+    // come from beyond the L2 wherever a model has more than a few layers.  Hash without / with it, us, k = 96, tau = 8, twelve
+    // layers in turn: 1 token 27.8 / 27.5, 128 31.9 / 30.8, weighted 34.2 / 32.4, 4096 tokens 32.4 / 31.7 (passes of 128 tokens,
+    // weighted 52.5 / 43.0); three layers in turn, whose factors stay in the L2: 128 tokens 29.1 / 30.5, weighted 31.5 / 32.1, 4096
+    // 32.4 / 31.8; k = 170, tau = 9, weighted 128 tokens 75.0 / 67.6 either way.  At other shapes it is not (block 32: 10 tokens
+    // 31.1 / 31.4, block 16: 216 tokens of 256 36.3 / 37.1, block 64: 5 tokens of 512 28.7 / 30.4).
     if (deep_ok && blocks * grid.z <= cus) rc = lffn_host::bh_few_part(wmode, a, grid, s);
     else if (L <= 8) rc = lffn_host::bh_lo_part(L, wmode, a, block, grid, s);
     else if (L == 9) rc = lffn_host::bh_512_part(wmode, a, block, grid, s);
