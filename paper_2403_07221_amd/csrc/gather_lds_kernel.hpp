@@ -381,9 +381,10 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
         //   of 1024 rows (13 slices of 64 bytes, 164 MB) 51650 tokens 177 / 162, weighted 212 / 204
         //   four (7): 31784 tokens 87.6 / 75.0 (65.5 / 68.5), 59596 tokens 106 / 104 (98.4 / 99.4)
         //   ten (24): 9932 tokens 88.0 / 76.3 (62.4 / 68.4), weighted 105 / 96 (80.5 / 82.1)
-        // Stages of 32 KB are gone before it pays (tau = 7, four workgroups 68.5 / 71.0, weighted 89.9 / 94.5, ten 95.5 / 97.0),
-        // except under many weighted slots (ten 125 / 120, sixteen 128 / 121).
-        constexpr bool kPrefetches = !PROBES && (FR >= 2 || (WEIGHTED && TOK >= 13));
+        // Stages of 32 KB (tau = 7) wait less for their copies and more for the requests: with seven slots or fewer it pays (16 slices, k =
+        // 128, cold 4966 tokens 80.0 / 73.0, warm 57.1 / 59.3; 10926 tokens 87.9 / 81.3), with more only under the weighted sum's
+        // loads (19865 tokens 93.5 / 95.9, weighted 126.8 / 123.9; 15892 tokens, eight slots, 86.3 / 85.9, weighted 109.2 / 108.6).
+        constexpr bool kPrefetches = !PROBES && (FR >= 2 || TOK <= 7 || (WEIGHTED && TOK >= 10));
         const bool large = (uint64_t)a.k * rows * (uint32_t)a.nvec * 16u >= 128u << 20;
         const uint32_t sharing = unit_chunks ? shares : Bx / m;  // the fewest workgroups of any unit
         constexpr uint32_t kPrefetch = 3;
