@@ -79,10 +79,11 @@ def parse_args():
     return ap.parse_args()
 
 
-def traffic_from_profiles(w, weighted: bool = False):
+def traffic_from_profiles(w, weighted: bool = False, probes: bool = False, block: int = 0):
     """(HBM bytes per gather launch, file) from a committed rocprofv3 --pmc summary, if there is one: a
     figure measured in an earlier run of the same command under the profiler, not in this run."""
-    f = ROOT / "profiles" / f"gather_config{w.index}{'_weighted' if weighted else ''}_pmc_hbm_traffic.txt"
+    form = (f"_bh4_block{block}" if block else "") + ("_weighted" if weighted else "_probes" if probes else "")
+    f = ROOT / "profiles" / f"gather_config{w.index}{form}_pmc_hbm_traffic.txt"
     if not f.exists():
         return None, None
     for line in f.read_text().splitlines():
@@ -378,7 +379,7 @@ def main():
     each = sorted(gather_each)
     times = {"avg_kernel_ms": gather_avg_ms, "min_kernel_ms": each[0] if each else None,
              "median_kernel_ms": each[len(each) // 2] if each else None, "launches_timed": len(each)}
-    traffic, traffic_file = traffic_from_profiles(w, args.weighted)
+    traffic, traffic_file = traffic_from_profiles(w, args.weighted, args.probes, args.block if bh else 0)
     # The staged kernel serves every (token, table[, probe]) row piece from LDS, so LDS read bandwidth is the
     # resource that binds it: 256 CUs x 256 bytes per clock (16-byte reads) x 2.4 GHz.  The direct kernel is
     # priced against HBM on the bytes that must cross it.

@@ -4,6 +4,7 @@ import sys
 from pathlib import Path
 
 import numpy as np
+import pytest
 
 from paper_2403_07221_amd import synth
 
@@ -47,3 +48,19 @@ def test_bench_refuses_more_than_one_gpu_with_a_message():
     r = subprocess.run([sys.executable, str(ROOT / "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("form, options", [
+    ({}, "--config 2"), ({"weighted": True}, "--config 2 --weighted"), ({"probes": True}, "--config 2 --probes"),
+    ({"block": 64}, "--config 2 --hash bh4 --block 64"),
+    ({"weighted": True, "block": 16}, "--config 2 --hash bh4 --block 16 --weighted")])
+def test_bench_quotes_the_traffic_of_the_command_it_runs(form, options):
+    import bench
+    traffic, file = bench.traffic_from_profiles(synth.C2, **form)
+    assert traffic > 1e8
+    assert f"of the kernels of bench.py {options} (rocprofv3" in (ROOT / file).read_text().splitlines()[0]
+
+
+def test_bench_quotes_no_traffic_of_another_form():
+    import bench
+    assert bench.traffic_from_profiles(synth.C2, probes=True, block=32) == (None, None)
