@@ -2,7 +2,7 @@
 // (tau <= 8), plain sum:
 //   y[t][:] = sum_{j<k} tables[j][code[t][j]][:]        (Sec. 3.1, eq. "lookup")
 // Runs on request only (option gather_path = 4): measured on the RoBERTa-base shape (16384 tokens, k = 96,
-// d_out = 768) it takes 99 us + 11 us for its code re-pack against 77 us for gather_lds_kernel.  Its row reads
+// d_out = 768) it takes 99 us + 11 us for its code re-pack against 76 ... 89 us (from box to box) for gather_lds_kernel.  Its row reads
 // are conflict-free (measured alone: 135-140 TB/s over the chip against 69-80 TB/s for rows picked at random),
 // but it pays a barrier, an LDS write and two buffer loads per table on top, and a burst of output stores at
 // the end of its single pass.  Kept because it is the measured answer to "take the bank conflicts out" of the plain sum.
