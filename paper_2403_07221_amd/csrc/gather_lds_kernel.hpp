@@ -412,8 +412,17 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
             // per load instruction.  Slots past the chunk end read the codes of later tokens or of the
             // zero padding (always a valid row), add them, and store nothing.
             constexpr int WQ = (TOK + 3) / 4, FQ = TOK / 4;
+            // kRun: slot i of group g is token c0 + WQ*(4g + i%4) + i/4 instead, so that a lane's words of a row are neighbours and
+            // come with one load of 16 (12) bytes instead of four (three) of 4.  Only with sixteen slots, or twelve and weights: us a
+            // pass without / with it, k = 96, 768 wide: 65536 bf16 rows 328.4 / 320.5, weighted 423 / 413; k = 256, 512 wide 32768
+            // tokens 287.9 / 286.1, weighted 360 / 353; tau = 9, 43690 tokens weighted 371 / 365; twelve slots (12288 tokens, 1024 wide)
+            // 94.1 / 94.9, weighted 113.8 / 112.1.  Where a stage has fewer slots, or slots that fill no whole quad (a second load), the
+            // wider load comes back too late: eight slots (8192 tokens) 80.3 / 83.5, weighted 97.6 / 102.8, multi-probe 444 / 478,
+            // thirteen 100.6 / 101.3, weighted 129.2 / 132.7; tables of 32 KB stages (tau = 7) 136.9 / 138.6, of 64 KB (tau = 10) 235 / 241.
+            constexpr bool kRun = FR == 2 && !PROBES && (TOK == 16 || (TOK == 12 && WEIGHTED));
+            constexpr int WL = kRun ? 1 : WQ;  // loads of a word row
             const uint32_t r4 = q & 3u;
-            const uint32_t lq_full = (4u * g + r4) * 4u;  // byte offset of the lane's token in a full quad register
+            const uint32_t lq_full = (4u * g + r4) * (kRun ? 4u * WQ : 4u);  // byte offset of the lane's token in a full quad register
             const uint32_t lq_tail = (r4 * G + g) * 4u;   // same for the tail register
             // Register mm's dword of the word row at `row` (uniform: the row's word of token c0), `lane_extra` bytes
             // further: a buffer load, whose per-lane part is one 32-bit offset for every row.  (With plain pointers the
@@ -424,9 +433,21 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                     __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row), 0, (int)bytes, kBufferRsrcFlags);
                 return __builtin_amdgcn_raw_buffer_load_b32(rs, (mm < FQ ? lq_full : lq_tail) + lane_extra, mm * (16 * G), 0);
             };
-            // code words of word row `wrow` (one word = two tables), register mm
-            auto load_code = [&](uint32_t wrow, int mm) -> uint32_t {
-                return load_reg(reinterpret_cast<const char *>(a.packed) + ((size_t)wrow * a.n_pad + c0) * 4u, mm, 0u, WQ * 16 * G);
+            // load u (< WL) of the word row at `row` to `to`
+            auto load_words = [&](auto(&to)[WQ], const char *row, int u, uint32_t lane_extra, uint32_t bytes) {
+                typedef std::remove_reference_t<decltype(to[0])> word_t;
+                if constexpr (kRun) {
+                    const __amdgpu_buffer_rsrc_t rs =
+                        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row), 0, (int)bytes, kBufferRsrcFlags);
+                    auto put = [&](auto v) {
+#pragma unroll
+                        for (int m = 0; m < WQ; ++m) to[m] = __builtin_bit_cast(word_t, (uint32_t)v[m]);
+                    };
+                    if constexpr (WQ == 3) put(__builtin_amdgcn_raw_buffer_load_b96(rs, lq_full + lane_extra, 0, 0));
+                    else put(__builtin_amdgcn_raw_buffer_load_b128(rs, lq_full + lane_extra, 0, 0));
+                } else {
+                    to[u] = __builtin_bit_cast(word_t, load_reg(row, u, lane_extra, bytes));
+                }
             };
 
             Acc<false> acc[TOK];
@@ -447,14 +468,14 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
 #pragma unroll
             for (uint32_t idx = 0; idx < FILLS; ++idx) fill_piece(0, idx);
             uint32_t cr[WQ];
+            // load u of the code words of word row `wrow` (one word = two tables)
+            auto load_code = [&](uint32_t wrow, int u) {
+                load_words(cr, reinterpret_cast<const char *>(a.packed) + ((size_t)wrow * a.n_pad + c0) * 4u, u, 0u, WQ * 16 * G);
+            };
 #pragma unroll
-            for (int mm = 0; mm < WQ; ++mm) cr[mm] = load_code(0, mm);
+            for (int u = 0; u < WL; ++u) load_code(0, u);
 
             if constexpr (!PROBES) {
-                auto load_weight = [&](uint32_t j, int mm) -> float {
-                    return __uint_as_float(load_reg(
-                        reinterpret_cast<const char *>(a.wpk) + ((size_t)j * a.n_pad + c0) * 4u, mm, 0u, WQ * 16 * G));
-                };
                 uint32_t half[TPS][WQ];  // LDS row offsets, quad-shared, of the stage's tables
                 float w[TPS][WQ];        // their weights
                 auto split_codes = [&](uint32_t s) {
@@ -469,11 +490,15 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                     }
                 };
                 float wn[TPS][WQ];
+                // load u of the weights of table j, the stage's table tt
+                auto load_weight = [&](uint32_t j, int tt, int u) {
+                    load_words(wn[tt], reinterpret_cast<const char *>(a.wpk) + ((size_t)j * a.n_pad + c0) * 4u, u, 0u, WQ * 16 * G);
+                };
                 if constexpr (WEIGHTED) {
 #pragma unroll
-                    for (int u = 0; u < TPS; ++u)
+                    for (int tt = 0; tt < TPS; ++tt)
 #pragma unroll
-                        for (int mm = 0; mm < WQ; ++mm) wn[u][mm] = load_weight(u, mm);
+                        for (int u = 0; u < WL; ++u) load_weight(tt, tt, u);
                 }
                 __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
                 split_codes(0);
@@ -513,13 +538,13 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                         }
                         if (TPS == 2 || (s & 1u)) {
 #pragma unroll
-                            for (int mm = 0; mm < WQ; ++mm)
-                                if (2 + mm == i) cr[mm] = load_code(sn * TPS / 2, mm);
+                            for (int u = 0; u < WL; ++u)
+                                if (2 + u == i) load_code(sn * TPS / 2, u);
                         }
                         if constexpr (WEIGHTED) {
 #pragma unroll
-                            for (int x = 0; x < TPS * WQ; ++x)
-                                if ((2 + WQ + x) % NS == i) wn[x / WQ][x % WQ] = load_weight(sn * TPS + x / WQ, x % WQ);
+                            for (int x = 0; x < TPS * WL; ++x)
+                                if ((2 + WL + x) % NS == i) load_weight(sn * TPS + x / WL, x / WL, x % WL);
                         }
                         const u32x4 v = rd[i % D];
                         const uint4 r = make_uint4(v.x, v.y, v.z, v.w);
@@ -552,7 +577,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                     const char *row = reinterpret_cast<const char *>(a.packed) + ((size_t)(LAG ? rb : ra) * a.n_pad + c0) * 4u;
                     const uint32_t extra = LAG && !lag ? (ra - rb) * crow : 0u;
 #pragma unroll
-                    for (int mm = 0; mm < WQ; ++mm) cr[mm] = load_reg(row, mm, extra, (LAG ? crow : 0u) + WQ * 16 * G);
+                    for (int u = 0; u < WL; ++u) load_words(cr, row, u, extra, (LAG ? crow : 0u) + WQ * 16 * G);
                 };
                 // Shares.  Row (j, probe) of wpk is row j * (1 + tau) + probe, so the rows of successive sweeps follow one
                 // another; `srow_at` is the row of the next sweep to be loaded for the lagging lanes (table 0 in the first step,
@@ -570,9 +595,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                 };
                 share_lane();
                 static_assert(WQ * 16 * G <= (int)kProbesWindow, "the host keeps this much below kProbesNoTable");
-                auto load_share = [&](int mm) -> float {
-                    return __uint_as_float(load_reg(srow_at, mm, sx, (LAG ? sstep : 0u) + WQ * 16 * G));
-                };
+                auto load_share = [&](float(&to)[WQ], int u) { load_words(to, srow_at, u, sx, (LAG ? sstep : 0u) + WQ * 16 * G); };
                 auto next_row = [&]() __attribute__((always_inline)) {
                     if (lp < tau) {
                         ++lp;
@@ -590,20 +613,20 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                 // 123 when a stage was two tables).
                 constexpr bool kShort = TOK == 4;
                 constexpr int NP = kShort ? __builtin_ctz(rows) + 1 : 1;  // 1 + tau
-                float wn[NP];
+                float wn[NP][WQ];
                 float wA[WQ], wB[WQ];  // shares of this sweep and of the next, then of the one after
                 if constexpr (kShort) {
 #pragma unroll
                     for (int p = 0; p < NP; ++p) {
-                        wn[p] = load_share(0);
+                        load_share(wn[p], 0);
                         next_row();
                     }
                 } else {
 #pragma unroll
-                    for (int mm = 0; mm < WQ; ++mm) wA[mm] = load_share(mm);
+                    for (int u = 0; u < WQ; ++u) load_share(wA, u);
                     next_row();
 #pragma unroll
-                    for (int mm = 0; mm < WQ; ++mm) wB[mm] = load_share(mm);
+                    for (int u = 0; u < WQ; ++u) load_share(wB, u);
                     next_row();
                 }
                 if (LAG && tid < PIECE / 16) sbuf[2 * kLdsBufBytes / 16 + tid] = make_uint4(0u, 0u, 0u, 0u);  // the zero row
@@ -644,7 +667,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                             acc[i].fma(make_uint4(v.x, v.y, v.z, v.w), wc);
                             acc[i].pin();
                             rd[(i + PH) % D] = lds_row(ac);
-                            if ((i & 3) == 3 || i == TOK - 1) w[i >> 2] = load_share(i >> 2);  // two sweeps ahead
+                            if ((i & 3) == 3 || i == TOK - 1) load_share(w, i >> 2);  // two sweeps ahead
                             if (i == TOK - 1 && pr >= 1 && pr <= FILLS && t + 1 < k) fill_piece(t + 1, pr - 1);
                             __builtin_amdgcn_sched_barrier(0);
                         }
@@ -658,7 +681,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                     if constexpr (kShort) {
                         float ws[NP];
 #pragma unroll
-                        for (int p = 0; p < NP; ++p) ws[p] = wn[p];
+                        for (int p = 0; p < NP; ++p) ws[p] = wn[p][0];
                         uint32_t at = off[0] ^ flip_of(1u);
                         float wb = quad_bcast(ws[0], 0);
 #pragma unroll
@@ -668,7 +691,7 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                             if (i == 0 && p < (int)FILLS && t + 1 < k) fill_piece(t + 1, p);
                             if (i == 1 && p == 1) load_codes(tn);
                             if (i >= TOK - kShares && p * kShares + i - (TOK - kShares) < NP) {
-                                wn[p * kShares + i - (TOK - kShares)] = load_share(0);
+                                load_share(wn[p * kShares + i - (TOK - kShares)], 0);
                                 next_row();
                             }
                             const u32x4 v = rd[i];
@@ -715,7 +738,8 @@ __global__ __launch_bounds__(kLdsThreads) void gather_lds_kernel(GatherLdsArgs a
                 const uint32_t svec = slice * (uint32_t)SW + sq;
 #pragma unroll
                 for (int i = 0; i < TOK; ++i) {
-                    const uint32_t t = i < 4 * FQ ? c0 + (4u * G) * (uint32_t)(i >> 2) + 4u * sg + (uint32_t)(i & 3)
+                    const uint32_t t = kRun ? c0 + WQ * (4u * sg + (uint32_t)(i & 3)) + (uint32_t)(i >> 2)
+                                     : i < 4 * FQ ? c0 + (4u * G) * (uint32_t)(i >> 2) + 4u * sg + (uint32_t)(i & 3)
                                                   : c0 + (uint32_t)G * (uint32_t)i + sg;
                     if (t >= c1 || svec >= (uint32_t)a.nvec) continue;
                     store_y4(a.y, (size_t)t * a.d_out + (size_t)svec * 4u, acc[i].f[0], acc[i].f[1], acc[i].f[2],
