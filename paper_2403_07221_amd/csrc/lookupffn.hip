@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -14,6 +15,7 @@
 #include <vector>
 
 #include "bh_hash_kernel.hpp"
+#include "bh_lane_kernel.hpp"
 #include "forward_small_kernel.hpp"
 #include "forward_stack_kernel.hpp"
 #include "gather_kernel.hpp"
@@ -24,7 +26,7 @@
 
 // Build parts.  This file compiles whole (LFFN_PART undefined) or as parts that are linked together, so
 // that the kernel families compile side by side: part 0 holds the C ABI, the host logic and the hash and
-// re-pack kernels; parts 1 .. 11 hold one family of kernel launchers each (declared just below).  No
+// re-pack kernels; parts 1 .. 13 hold one family of kernel launchers each (declared just below).  No
 // kernel is instantiated in two parts.
 #ifdef LFFN_PART
 #define LFFN_HAS(p) (LFFN_PART == (p))
@@ -68,6 +70,9 @@ int bh_512_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s)
 int bh_1024_part(int wmode, const BhArgs &a, int block, dim3 grid, hipStream_t s);
 // part 12: blocks of 64 at d_pad = 1024 for grids of no more workgroups than compute units
 int bh_few_part(int wmode, const BhArgs &a, dim3 grid, hipStream_t s);
+// part 13: BH of few tokens, a coordinate to a lane, two or four tokens to a workgroup
+int bh_lane_part(int L, bool weights, int tokens, const BhArgs &a, int block, dim3 grid, hipStream_t s);
+int bh_lane_load();
 }  // namespace lffn_host
 
 namespace {
@@ -476,6 +481,44 @@ int bh_few_part(int wmode, const BhArgs &a, dim3 grid, hipStream_t s)
         case 2: return launch_bh_k<10, 4, 2, true>(a, grid, s);
     }
     return LFFN_E_UNSUPPORTED;
+}
+#endif
+
+#if LFFN_HAS(13)
+template <int L, int TB, int T>
+int launch_bh_lane_t(bool weights, const BhArgs &a, dim3 grid, hipStream_t s)
+{
+    constexpr size_t lds = BhLane<L, T>::WORDS * 4;
+    static_assert(lds <= 64 * 1024, "no LDS beyond what every kernel may use");
+    if (weights) hipLaunchKernelGGL((bh_lane_kernel<L, TB, T, true>), grid, dim3(1 << L), lds, s, a);
+    else hipLaunchKernelGGL((bh_lane_kernel<L, TB, T, false>), grid, dim3(1 << L), lds, s, a);
+    return LFFN_OK;
+}
+
+template <int L, int TB>
+int launch_bh_lane(bool weights, int tokens, const BhArgs &a, dim3 grid, hipStream_t s)
+{
+    return tokens == 2 ? launch_bh_lane_t<L, TB, 2>(weights, a, grid, s) : launch_bh_lane_t<L, TB, 4>(weights, a, grid, s);
+}
+
+int bh_lane_part(int L, bool weights, int tokens, const BhArgs &a, int block, dim3 grid, hipStream_t s)
+{
+    switch (L * 100 + block) {
+#define LFFN_CASE(l) \
+    case l * 100 + 16: return launch_bh_lane<l, 1>(weights, tokens, a, grid, s); \
+    case l * 100 + 32: return launch_bh_lane<l, 2>(weights, tokens, a, grid, s); \
+    case l * 100 + 64: return launch_bh_lane<l, 4>(weights, tokens, a, grid, s);
+        LFFN_CASE(6) LFFN_CASE(7) LFFN_CASE(8) LFFN_CASE(9) LFFN_CASE(10)
+#undef LFFN_CASE
+    }
+    return LFFN_E_UNSUPPORTED;
+}
+
+int bh_lane_load()
+{
+    hipFuncAttributes attr;
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(bh_lane_kernel<10, 4, 4, true>));
+    return e == hipSuccess ? LFFN_OK : hip_fail(e, "hipFuncGetAttributes(bh_lane_kernel)");
 }
 #endif
 
@@ -1509,10 +1552,11 @@ int launch_bh_pack(const float *bmats, float *apack, int d, int k, int tau, int 
     return LFFN_OK;
 }
 
-// Hashes with the packed factors `apack`; `pack_from` != NULL: re-order them from there first.
+// Hashes with the packed factors `apack`; `pack_from` != NULL: re-order them from there first.  few_ok: bh_lane_kernel may take
+// the batch (the forward passes; the stand-alone hash keeps bh_hash_kernel, and so the one can be held against the other).
 int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in, float *apack_scratch,
                    const HashOut &out, int64_t n, int d, int k, int tau, int block, int n_factors, int x_dtype,
-                   hipStream_t s)
+                   bool few_ok, hipStream_t s)
 {
     const int L = log2_pad(d);
     const int N = 1 << L;
@@ -1540,15 +1584,40 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
         int rc = launch_bh_pack(pack_from, apack_scratch, d, k, tau, block, n_factors, s);
         if (rc != LFFN_OK) return rc;
     }
+    // Few tokens: bh_lane_kernel, a wave to 64 coordinates of two or four tokens, while its workgroups fill the chip no more than
+    // twice (once with blocks of 64 at d_pad 512 and 1024, whose factors a workgroup takes longest to read).  Hash alone, twelve
+    // layers in turn, us, bh_hash_kernel / two tokens a workgroup / four:
+    //   d = 768, k = 96, tau = 8, weights, block 64: 1 token 29.2 / 13.7 / 15.5, 128 32.4 / 14.6 / 16.5, 512 32.6 / 16.7 / 16.6, 1024
+    //   32.6 / 29.7 / 17.8, 2048 32.5 / 54.7 / 32.4; block 16: 128 21.1 / 6.6 / 8.5, 2048 21.6 / 20.6 / 15.6, 4096 22.3 / 38.5 / 28.7;
+    //   codes, block 32: 128 23.9 / 9.2 / 11.0, 2048 23.8 / 30.1 / 20.4, 4096 24.5 / 57.0 / 38.3
+    //   d = 768, k = 170, tau = 9 (two projections): 128 67.7 / 26.2 / 29.9, 1024 68.1 / 53.9 / 31.8
+    //   d = 512, k = 256 (four), block 64: 128 32.8 / 10.5 / 10.8, 512 32.8 / 27.8 / 17.6, 1024 32.6 / 48.0 / 30.4, 2048 32.9 / 86.7 / 54.9
+    //   d = 256, k = 96 (three), block 64: 256 29.2 / 9.4 / 7.8, 2048 29.3 / 36.2 / 22.6, 4096 29.6 / 64.1 / 41.9
+    //   d = 64, k = 8, block 64: 128 9.6 / 4.8 / 6.2, 4096 9.7 / 7.6 / 6.4; k = 96 (twelve), block 16: 256 7.0 / 4.3 / 4.2, 2048 9.7 / 11.6
+    //   / 9.7, 4096 12.4 / 20.6 / 16.8
+    // (It writes the ABI layout: batches small enough for it do not take the staged gather.)
+    int cus = 0, rc = device_cus(&cus);
+    if (rc != LFFN_OK) return rc;
+    const int64_t fill = (int64_t)cus * (1024 / N);  // workgroups that the chip holds
+    if (few_ok && a.codes && n * a.P <= (block == 64 && N >= 512 ? 4 : 8) * fill) {
+        const int tokens = n * a.P <= 2 * (int64_t)cus * std::max(1, 256 / N) ? 2 : 4;
+        const int64_t groups = (n + tokens - 1) / tokens;
+        dim3 grid = grid_of(groups);
+        a.p_per = a.P;
+        a.cross = N % tau != 0;
+        if (a.P > 1) grid.z = split_projections(a.P, a.cross, std::max<int64_t>(1, fill / groups), &a.p_per);
+        rc = lffn_host::bh_lane_part(L, out.weights != nullptr, tokens, a, block, grid, s);
+        if (rc != LFFN_OK) return rc;
+        LFFN_HIP(hipGetLastError());
+        tl.done();
+        return LFFN_OK;
+    }
     const int wmode = !out.weights ? 0 : bh_weights_in_registers(tau) ? 1 : 2;
     const int wpg = L == 10 ? 4 : L == 9 ? 2 : 1;  // waves that share a token group
     const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
     const int64_t blocks = (n + per_block - 1) / per_block;
     dim3 grid = grid_of(blocks);  // a workgroup past the batch does a full hash of no token
     const bool deep_ok = block == 64 && L == 10;
-    int cus = 0, rc = LFFN_OK;
-    if (a.P > 1 || deep_ok) rc = device_cus(&cus);
-    if (rc != LFFN_OK) return rc;
     // as many workgroups to the projections as find a compute unit each (2 tokens: d = 64, block 32, 20 projections pass
     // 77 -> 16 us, d = 256, 6 projections with tables across them 93 -> 40)
     a.p_per = a.P;
@@ -1757,7 +1826,7 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
     auto run_hash = [&](const HashOut &out) -> int {
         if (h.bh())
             return launch_hash_bh(x, h.bh_prepared ? nullptr : h.bmats, h.bh_prepared ? h.bmats : nullptr, apack, out, n,
-                                  d, k, tau, h.block, h.n_factors, x_dtype, s);
+                                  d, k, tau, h.block, h.n_factors, x_dtype, true, s);
         return launch_hash(x, h.signs, out, n, d, k, tau, h.n_rounds, x_dtype, s, opt);
     };
     // the hash kernels write the staged gather's layout themselves, scaled for its row pieces (unless the
@@ -1860,7 +1929,7 @@ int hash_bh_core(const void *x, const float *bmats, uint16_t *codes, float *weig
     out.codes = codes;
     out.weights = weighted ? weights : nullptr;
     return launch_hash_bh(x, h.bh_prepared ? nullptr : bmats, h.bh_prepared ? bmats : nullptr, apack, out, n, d, k,
-                          tau, h.block, n_factors, x_dtype, s);
+                          tau, h.block, n_factors, x_dtype, false, s);
 }
 
 bool bh_shape_ok(int d, int k, int tau, int block, int n_factors)
@@ -1911,6 +1980,8 @@ int lookupffn_init(void)
     rc = lffn_host::hash_row8_load();
     if (rc != LFFN_OK) return rc;
     rc = lffn_host::forward_stack_load();
+    if (rc != LFFN_OK) return rc;
+    rc = lffn_host::bh_lane_load();
     if (rc != LFFN_OK) return rc;
     {
         GatherRingArgs ra{};
