@@ -135,7 +135,7 @@ int64_t lookupffn_workspace_bytes(int64_t n_tokens, int k);
  * d_out == d when n_layers > 1; no residual and no normalisation in between), y receives the last layer's
  * output.  `signs` and `tables` are HOST arrays of n_layers DEVICE pointers (read during the call, not kept):
  * signs[l] as in lookupffn_hash, tables[l] as in lookupffn_gather, all layers with the same k, tau, dtypes
- * and layout (LFFN_PREPARED in table_dtype: every tables[l] is a prepared copy).  One workgroup per token;
+ * and layout (LFFN_PREPARED in table_dtype: every tables[l] is a prepared copy).  A token stays in one workgroup;
  * the per-element sums are the same sequential fp32 sums as lookupffn_forward makes, so the result equals
  * a loop of n_layers lookupffn_forward calls bit for bit.  No scratch memory, no allocation, no
  * synchronisation: the call can be captured in a HIP graph.  y must not overlap x unless it is x with rows of the

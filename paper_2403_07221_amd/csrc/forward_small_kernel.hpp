@@ -4,9 +4,9 @@
 // What bounds it: launches.  The two-kernel path runs a hash kernel that fills a corner of the chip, writes the codes
 // to memory, and a second kernel that waits for the first to drain; here a workgroup owns a token, its waves
 // take the projections in turn (each wave holds the row and transforms it with the generic hash kernel's own
-// butterflies, so the same bits), the sign strings meet in LDS, and every lane then sums its dword of the k selected
-// rows in table order with forward_stack_kernel's gather.  64 tokens of 64, k = 8: 12.8 -> 9.4 us a pass; 64 tokens of
-// 512, k = 256: 28.6 -> 13.4 us.  Same sequential fp32 sum, bit-equal to the other kernels.
+// butterflies, so the same bits), the sign strings meet in LDS, and the waves then sum the k selected rows in table
+// order with forward_stack_kernel's gather.  64 tokens of 64, k = 8: 12.8 -> 9.4 us a pass; 64 tokens of 512, k = 256:
+// 28.6 -> 12.2 us.  Same sequential fp32 sum, bit-equal to the other kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -84,12 +84,10 @@ __global__ __launch_bounds__(1024) void forward_small_kernel(StackArgs a)
     __syncthreads();
     // row offsets; those past k stay 0, a valid row
     for (int j = (int)tid; j < n_off; j += (int)blockDim.x)
-        rowoff[j] = j < a.k ? (((uint32_t)j << a.tau) + hash_code_at(bitw, (unsigned)j, a.tau)) * a.row_stride : 0u;
+        rowoff[stack_offset_at(j, n_off)] = j < a.k ? (((uint32_t)j << a.tau) + hash_code_at(bitw, (unsigned)j, a.tau)) * a.row_stride : 0u;
     __syncthreads();
 
-    stack_gather<KIND>(a, a.tables[0], rowoff, n_off, tid, [&](uint32_t col, float acc0, float acc1) {
-        stack_store_y<KIND>(a, t, col, acc0, acc1);
-    });
+    stack_gather<KIND>(a, a.tables[0], rowoff, n_off, tid, 1, [&](uint32_t, uint32_t col, float acc0, float acc1) { stack_store_y<KIND>(a, t, col, acc0, acc1); });
 }
 
 }  // namespace lffn

@@ -55,7 +55,7 @@ int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3
 // part 7: the lagged, bank-interleaved staged gather (prepared tables, tau <= 8)
 int gather_ring_part(int threads, int tok, const GatherRingArgs &a, dim3 grid, hipStream_t s);
 // part 8: hash and gather of a few tokens, one or several chained layers, in one launch
-int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
+int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int tokens, size_t lds, hipStream_t s);
 int forward_small_part(int L, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
 int forward_stack_load();
 // parts 9, 10: the hash with a token per row of lanes, d_pad = 1024 (four tokens per wavefront) and 512 (eight)
@@ -328,28 +328,33 @@ int gather_ring_part(int threads, int tok, const GatherRingArgs &a, dim3 grid, h
 #endif
 
 #if LFFN_HAS(8)
-template <int R>
-int launch_forward_stack_r(int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s)
+template <int R, int T>
+int launch_forward_stack_r(int kind, const StackArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
     switch (kind) {
-        case kElemF32: hipLaunchKernelGGL((forward_stack_kernel<R, kElemF32>), grid, dim3(threads), lds, s, a); break;
-        case kElemBF16: hipLaunchKernelGGL((forward_stack_kernel<R, kElemBF16>), grid, dim3(threads), lds, s, a); break;
-        case kElemF16: hipLaunchKernelGGL((forward_stack_kernel<R, kElemF16>), grid, dim3(threads), lds, s, a); break;
+        case kElemF32: hipLaunchKernelGGL((forward_stack_kernel<R, kElemF32, T>), grid, dim3(kStackThreads), lds, s, a); break;
+        case kElemBF16: hipLaunchKernelGGL((forward_stack_kernel<R, kElemBF16, T>), grid, dim3(kStackThreads), lds, s, a); break;
+        case kElemF16: hipLaunchKernelGGL((forward_stack_kernel<R, kElemF16, T>), grid, dim3(kStackThreads), lds, s, a); break;
         default: return LFFN_E_DTYPE;
     }
     return LFFN_OK;
 }
 
-int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s)
+template <int T>
+int launch_forward_stack_t(int n_rounds, int kind, const StackArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (threads < 64 || threads > 1024 || threads % 64) return LFFN_E_UNSUPPORTED;
     switch (n_rounds) {
-        case 1: return launch_forward_stack_r<1>(kind, a, grid, threads, lds, s);
-        case 2: return launch_forward_stack_r<2>(kind, a, grid, threads, lds, s);
-        case 3: return launch_forward_stack_r<3>(kind, a, grid, threads, lds, s);
-        case 4: return launch_forward_stack_r<4>(kind, a, grid, threads, lds, s);
+        case 1: return launch_forward_stack_r<1, T>(kind, a, grid, lds, s);
+        case 2: return launch_forward_stack_r<2, T>(kind, a, grid, lds, s);
+        case 3: return launch_forward_stack_r<3, T>(kind, a, grid, lds, s);
+        case 4: return launch_forward_stack_r<4, T>(kind, a, grid, lds, s);
     }
     return LFFN_E_UNSUPPORTED;
+}
+
+int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int tokens, size_t lds, hipStream_t s)
+{
+    return tokens == 2 ? launch_forward_stack_t<2>(n_rounds, kind, a, grid, lds, s) : launch_forward_stack_t<1>(n_rounds, kind, a, grid, lds, s);
 }
 
 template <int L>
@@ -379,7 +384,7 @@ int forward_small_part(int L, int kind, const StackArgs &a, dim3 grid, int threa
 int forward_stack_load()
 {
     hipFuncAttributes attr;
-    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(forward_stack_kernel<3, kElemF32>));
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(forward_stack_kernel<3, kElemF32, 1>));
     return e == hipSuccess ? LFFN_OK : hip_fail(e, "hipFuncGetAttributes(forward_stack_kernel)");
 }
 #endif
@@ -1659,7 +1664,7 @@ bool stack_shape_ok(const void *x, const int8_t *const *signs, const void *const
     for (int l = 0; l < n_layers; ++l)
         if (!aligned(signs[l], 16)) return false;
     const int P = (int)(((int64_t)k * tau + 1023) / 1024);
-    if (stack_lds_bytes(P, k) > 64 * 1024) return false;
+    if (!stack_range_ok(P, k)) return false;
     return stack_table_bytes(table_ref(tables[0], table_dtype, tau), k, tau, d_out) < (int64_t(1) << 31);
 }
 
@@ -1756,14 +1761,22 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
         a.slice_stride = 0;
         a.table_bytes = (uint32_t)((int64_t)k * rows * row_bytes);
     }
-    int threads = (int)((a.row_dwords + 63) / 64 * 64);
-    if (threads > 1024) threads = 1024;
-    if (L != 10) threads = std::max(threads, 64 * std::min(a.P, 16));  // a wave per projection
     // forward_small_kernel is the call's hash and its gather, and counts as each with its whole duration
     TimedLaunch th(0, s, L != 10), tl(1, s);
-    int rc = L == 10
-        ? lffn_host::forward_stack_part(n_rounds, T.kind, a, grid_of(n), threads, stack_lds_bytes(a.P, k), s)
-        : lffn_host::forward_small_part(L, T.kind, a, grid_of(n), threads, small_lds_bytes(a.P, N, k), s);
+    int rc;
+    if (L == 10) {
+        // two tokens to a workgroup where there are more tokens than compute units (and the LDS is what every kernel may use)
+        int cus = 0;
+        rc = device_cus(&cus);
+        if (rc != LFFN_OK) return rc;
+        const int tokens = n > cus && stack_lds_bytes(k, 2) <= 64 * 1024 ? 2 : 1;
+        rc = lffn_host::forward_stack_part(n_rounds, T.kind, a, grid_of((n + tokens - 1) / tokens), tokens, stack_lds_bytes(k, tokens), s);
+    } else {
+        int threads = (int)((a.row_dwords + 63) / 64 * 64);
+        if (threads > 1024) threads = 1024;
+        threads = std::max(threads, 64 * std::min(a.P, 16));  // a wave per projection
+        rc = lffn_host::forward_small_part(L, T.kind, a, grid_of(n), threads, small_lds_bytes(a.P, N, k), s);
+    }
     if (rc != LFFN_OK) return rc;
     LFFN_HIP(hipGetLastError());
     tl.done();
