@@ -12,7 +12,7 @@ SRC = PKG / "csrc" / "lookupffn.hip"
 LIB = PKG / "liblookupffn.so"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-N_PARTS = 14         # csrc/lookupffn.hip compiles as parts 0 .. 13 (-DLFFN_PART=i), linked together
+N_PARTS = 15         # csrc/lookupffn.hip compiles as parts 0 .. 14 (-DLFFN_PART=i), linked together
 SLOW_FIRST = [0, 4, 3, 2, 11, 6, 5]   # the hash kernels of every width and the staged gather's take the longest: start them first
 OBJ_DIR = PKG / "_build"
 

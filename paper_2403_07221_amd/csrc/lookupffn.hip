@@ -22,11 +22,12 @@
 #include "gather_lds_kernel.hpp"
 #include "gather_ring_kernel.hpp"
 #include "hash_kernel.hpp"
+#include "hash_lane_kernel.hpp"
 #include "hash_row_kernel.hpp"
 
 // Build parts.  This file compiles whole (LFFN_PART undefined) or as parts that are linked together, so
 // that the kernel families compile side by side: part 0 holds the C ABI, the host logic and the hash and
-// re-pack kernels; parts 1 .. 13 hold one family of kernel launchers each (declared just below).  No
+// re-pack kernels; parts 1 .. 14 hold one family of kernel launchers each (declared just below).  No
 // kernel is instantiated in two parts.
 #ifdef LFFN_PART
 #define LFFN_HAS(p) (LFFN_PART == (p))
@@ -73,6 +74,9 @@ int bh_few_part(int wmode, const BhArgs &a, dim3 grid, hipStream_t s);
 // part 13: BH of few tokens, a coordinate to a lane, two or four tokens to a workgroup
 int bh_lane_part(int L, bool weights, int tokens, const BhArgs &a, int block, dim3 grid, hipStream_t s);
 int bh_lane_load();
+// part 14: the sign-diagonal hash of few tokens, likewise
+int hash_lane_part(int L, int tokens, int wmode, const HashArgs &a, dim3 grid, hipStream_t s);
+int hash_lane_load();
 }  // namespace lffn_host
 
 namespace {
@@ -527,6 +531,39 @@ int bh_lane_load()
 }
 #endif
 
+#if LFFN_HAS(14)
+template <int L, int T>
+int launch_hash_lane_t(int wmode, const HashArgs &a, dim3 grid, hipStream_t s)
+{
+    constexpr size_t lds = BhLane<L, T>::WORDS * 4;
+    static_assert(lds <= 64 * 1024, "no LDS beyond what every kernel may use");
+    switch (wmode) {
+        case 0: hipLaunchKernelGGL((hash_lane_kernel<L, T, 0>), grid, dim3(1 << L), lds, s, a); break;
+        case 1: hipLaunchKernelGGL((hash_lane_kernel<L, T, 1>), grid, dim3(1 << L), lds, s, a); break;
+        case 2: hipLaunchKernelGGL((hash_lane_kernel<L, T, 2>), grid, dim3(1 << L), lds, s, a); break;
+        default: return LFFN_E_UNSUPPORTED;
+    }
+    return LFFN_OK;
+}
+
+int hash_lane_part(int L, int tokens, int wmode, const HashArgs &a, dim3 grid, hipStream_t s)
+{
+    switch (L) {
+#define LFFN_CASE(l) case l: return tokens == 2 ? launch_hash_lane_t<l, 2>(wmode, a, grid, s) : launch_hash_lane_t<l, 4>(wmode, a, grid, s);
+        LFFN_CASE(6) LFFN_CASE(7) LFFN_CASE(8) LFFN_CASE(9) LFFN_CASE(10)
+#undef LFFN_CASE
+    }
+    return LFFN_E_UNSUPPORTED;
+}
+
+int hash_lane_load()
+{
+    hipFuncAttributes attr;
+    hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(hash_lane_kernel<10, 4, 1>));
+    return e == hipSuccess ? LFFN_OK : hip_fail(e, "hipFuncGetAttributes(hash_lane_kernel)");
+}
+#endif
+
 #if LFFN_HAS(0)
 int hip_fail(hipError_t e, const char *what)
 {
@@ -915,8 +952,10 @@ unsigned split_projections(int P, bool cross, int64_t most, int *p_per)
     return (unsigned)((P + *p_per - 1) / *p_per);
 }
 
+// few_ok: hash_lane_kernel may take the batch (the forward passes; the stand-alone hash keeps the kernels that give a token to a
+// wave, and so the one can be held against the others).
 int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t n, int d, int k, int tau,
-                int n_rounds, int x_dtype, hipStream_t s, const Options &opt)
+                int n_rounds, int x_dtype, bool few_ok, hipStream_t s, const Options &opt)
 {
     const int L = log2_pad(d);
     const int N = 1 << L;
@@ -942,6 +981,32 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
     if (!a.codes && !a.packed) return LFFN_E_NULL;
     if (out.probes && (!a.codes || !a.weights)) return LFFN_E_UNSUPPORTED;  // shares exist in the ABI layout only
     TimedLaunch tl(0, s);
+    // Few tokens: hash_lane_kernel, two or four tokens to a workgroup, while its workgroups fill the chip no more than twice.
+    // Hash alone, three rounds, us, a token to a wave / two tokens a workgroup / four:
+    //   d = 700, k = 97, tau = 7, weights: 1 token 6.0 / 4.2 / 4.9, 512 7.9 / 4.9 / 5.4, 1000 8.0 / 6.2 / 5.5, 2000 10.7 / 10.5 / 7.7; codes,
+    //   k = 96, tau = 8: 512 6.0 / 4.7 / 5.4, 2000 8.3 / 9.9 / 7.7, 4000 9.9 / 17.6 / 12.8; shares 512 9.4 / 6.0 / 6.9, 2000 14.5 / 13.2 / 11.0
+    //   d = 768, k = 170, tau = 9 (two projections), weights: 512 12.7 / 7.9 / 9.2, 1000 12.8 / 9.8 / 9.4, 2000 17.7 / 17.8 / 13.5
+    //   d = 512, k = 256, tau = 8 (four), weights: 64 5.7 / 4.2 / 4.7, 512 6.9 / 7.4 / 5.7, 1000 11.7 / 12.9 / 9.1
+    //   d = 256, k = 96 (three), codes: 64 3.8 / 3.7 / 4.1, 1000 5.3 / 6.0 / 4.8, 2000 7.5 / 9.3 / 6.9, 4000 10.0 / 11.6 / 11.1
+    //   d = 64, k = 96 (twelve), codes: 64 3.0 / 3.1 / 3.3, 1000 6.8 / 5.8 / 4.5, 2000 10.3 / 8.4 / 6.4
+    const int64_t parts = n * a.P;  // transforms
+    if (few_ok && a.codes && opt.hash_path == 0 && L >= 6 && L <= 10) {
+        int cus = 0;
+        int rc = device_cus(&cus);
+        if (rc != LFFN_OK) return rc;
+        const int64_t fill = (int64_t)cus * (1024 / N);  // workgroups that the chip holds
+        if (parts <= 8 * fill) {
+            const int tokens = parts <= 2 * fill ? 2 : 4;
+            const int64_t groups = (n + tokens - 1) / tokens;
+            const unsigned p_groups = a.P > 1 ? split_projections(a.P, a.cross, std::max<int64_t>(1, fill / groups), &a.p_per) : 1u;
+            rc = lffn_host::hash_lane_part(L, tokens, out.probes ? 2 : out.weights ? 1 : 0, a, dim3((unsigned)groups, p_groups), s);
+            if (rc != LFFN_OK) return rc;
+            LFFN_HIP(hipGetLastError());
+            tl.done();
+            t_last_hash = "hash_lane_kernel";
+            return LFFN_OK;
+        }
+    }
     // d_pad = 1024 or 512, up to four rounds, codes alone or with the gather weights (reduced in registers when
     // tau divides the lanes of a token: a table is then a run of lanes of one register; else through a z window
     // in LDS): a token per row of 16 (8) lanes, four (eight) tokens per wavefront, no LDS transposes.  A lane holds every 16th (8th) coordinate: d a multiple
@@ -1840,7 +1905,7 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
         if (h.bh())
             return launch_hash_bh(x, h.bh_prepared ? nullptr : h.bmats, h.bh_prepared ? h.bmats : nullptr, apack, out, n,
                                   d, k, tau, h.block, h.n_factors, x_dtype, true, s);
-        return launch_hash(x, h.signs, out, n, d, k, tau, h.n_rounds, x_dtype, s, opt);
+        return launch_hash(x, h.signs, out, n, d, k, tau, h.n_rounds, x_dtype, true, s, opt);
     };
     // the hash kernels write the staged gather's layout themselves, scaled for its row pieces (unless the
     // variant is the multi-probe one, whose shares exist in the ABI layout only)
@@ -1996,6 +2061,8 @@ int lookupffn_init(void)
     if (rc != LFFN_OK) return rc;
     rc = lffn_host::bh_lane_load();
     if (rc != LFFN_OK) return rc;
+    rc = lffn_host::hash_lane_load();
+    if (rc != LFFN_OK) return rc;
     {
         GatherRingArgs ra{};
         for (int threads : {512, 1024})
@@ -2029,7 +2096,7 @@ int lookupffn_hash(const void *x, const int8_t *signs, uint16_t *codes, int64_t 
     if (rc != LFFN_OK || n_tokens == 0) return rc;
     HashOut out;
     out.codes = codes;
-    return launch_hash(x, signs, out, n_tokens, d, k, tau, n_rounds, x_dtype, static_cast<hipStream_t>(hip_stream),
+    return launch_hash(x, signs, out, n_tokens, d, k, tau, n_rounds, x_dtype, false, static_cast<hipStream_t>(hip_stream),
                        options_snapshot());
 }
 
@@ -2042,7 +2109,7 @@ int lookupffn_hash_weighted(const void *x, const int8_t *signs, uint16_t *codes,
     HashOut out;
     out.codes = codes;
     out.weights = weights;
-    return launch_hash(x, signs, out, n_tokens, d, k, tau, n_rounds, x_dtype, static_cast<hipStream_t>(hip_stream),
+    return launch_hash(x, signs, out, n_tokens, d, k, tau, n_rounds, x_dtype, false, static_cast<hipStream_t>(hip_stream),
                        options_snapshot());
 }
 
@@ -2056,7 +2123,7 @@ int lookupffn_hash_probes(const void *x, const int8_t *signs, uint16_t *codes, f
     out.codes = codes;
     out.weights = shares;
     out.probes = true;
-    return launch_hash(x, signs, out, n_tokens, d, k, tau, n_rounds, x_dtype, static_cast<hipStream_t>(hip_stream),
+    return launch_hash(x, signs, out, n_tokens, d, k, tau, n_rounds, x_dtype, false, static_cast<hipStream_t>(hip_stream),
                        options_snapshot());
 }
 

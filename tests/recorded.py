@@ -18,6 +18,7 @@ SIGNATURES = {
     "lookupffn_gather": "pppqiiiipqp", "lookupffn_gather_weighted": "ppppqiiiipqp", "lookupffn_gather_probes": "ppppqiiiipqp",
     "lookupffn_hash": "pppqiiiiip", "lookupffn_hash_weighted": "ppppqiiiiip", "lookupffn_hash_probes": "ppppqiiiiip",
     "lookupffn_hash_bh": "pppqiiiiiipqp", "lookupffn_hash_bh_weighted": "ppppqiiiiiipqp",
+    "lookupffn_forward": "ppppqiiiiiiipqp", "lookupffn_forward_weighted": "ppppqiiiiiiipqp", "lookupffn_forward_probes": "ppppqiiiiiiipqp",
     "lookupffn_forward_bh": "ppppqiiiiiiiipqp", "lookupffn_forward_bh_weighted": "ppppqiiiiiiiipqp",
     "lookupffn_set_option": "si",
 }
