@@ -133,15 +133,23 @@ def _dev(t: torch.Tensor, name: str) -> int:
     return t.data_ptr()
 
 
-def _stream(t: torch.Tensor) -> int:
-    return torch.cuda.current_stream(t.device).cuda_stream
+def _call(entry: str, device: int, stream_of: torch.Tensor, *args) -> None:
+    """Calls an entry point on device `device` with `args` and the current stream of stream_of's device.
+
+    A small batch's call takes longer on the host than on the GPU, so the device is only changed where it is another one
+    (a torch.cuda.device block takes 1.2 us) and the stream's handle is asked for without an object around it (1.8 us): 64 tokens of
+    64, k = 8 9.4 -> 6.5 us a call."""
+    f = getattr(lib(), entry)
+    stream = torch._C._cuda_getCurrentRawStream(stream_of.get_device())
+    if device == torch.cuda.current_device():
+        _check(f(*args, stream))
+    else:
+        with torch.cuda.device(device):
+            _check(f(*args, stream))
 
 
 def _pad(d: int) -> int:
-    p = 1
-    while p < d:
-        p <<= 1
-    return p
+    return 1 << max(d - 1, 0).bit_length()
 
 
 def _check_signs(signs: torch.Tensor, d: int, k: int, tau: int):
@@ -149,7 +157,8 @@ def _check_signs(signs: torch.Tensor, d: int, k: int, tau: int):
         raise TypeError("signs must be int8 [P][n_rounds][d_pad]")
     n_pad = _pad(d)
     P = -(-k * tau // n_pad)
-    if signs.shape[0] != P or signs.shape[2] != n_pad:
+    shape = signs.shape
+    if shape[0] != P or shape[2] != n_pad:
         raise ValueError(f"signs has shape {tuple(signs.shape)}, expected ({P}, n_rounds, {n_pad})")
 
 
@@ -200,9 +209,8 @@ def lookupffn_prepare_tables(tables: torch.Tensor, out: torch.Tensor | None = No
     need = lib().lookupffn_prepared_tables_bytes(k, tau, d_out, code)
     if out is None:
         out = torch.empty(need, dtype=torch.uint8, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib().lookupffn_prepare_tables(ptr, k, tau, d_out, code, _dev(out, "prepared"),
-                                              out.numel() * out.element_size(), _stream(tables)))
+    _call("lookupffn_prepare_tables", dev.index, tables, ptr, k, tau, d_out, code, _dev(out, "prepared"),
+          out.numel() * out.element_size())
     return PreparedTables(out, k, tau, d_out, code)
 
 
@@ -216,9 +224,8 @@ def lookupffn_hash(x: torch.Tensor, signs: torch.Tensor, k: int, tau: int,
     assert codes.dtype == torch.int16 and tuple(codes.shape) == (n, k)
     if n == 0:
         return codes            # torch gives empty tensors a NULL data pointer; nothing to launch
-    with torch.cuda.device(x.device):
-        _check(lib().lookupffn_hash(_dev(x, "x"), _dev(signs, "signs"), _dev(codes, "codes"), n, d, k, tau,
-                                    signs.shape[1], _dtype_code(x), _stream(x)))
+    _call("lookupffn_hash", x.device.index, x, _dev(x, "x"), _dev(signs, "signs"), _dev(codes, "codes"), n, d, k,
+          tau, signs.shape[1], _dtype_code(x))
     return codes
 
 
@@ -238,9 +245,7 @@ def _gather(entry: str, codes, weights, tables, y, workspace, wshape):
         return y
     ws_ptr, ws_bytes = _ws(workspace)
     args = [_dev(codes, "codes")] + ([_dev(weights, "weights")] if weights is not None else [])
-    with torch.cuda.device(dev):
-        _check(getattr(lib(), entry)(*args, tptr, _dev(y, "y"), n, k, tau, d_out, tcode, ws_ptr, ws_bytes,
-                                     _stream(codes)))
+    _call(entry, dev.index, codes, *args, tptr, _dev(y, "y"), n, k, tau, d_out, tcode, ws_ptr, ws_bytes)
     return y
 
 
@@ -275,10 +280,8 @@ def lookupffn_hash_weighted(x: torch.Tensor, signs: torch.Tensor, k: int, tau: i
     assert weights.dtype == torch.float32 and tuple(weights.shape) == (n, k)
     if n == 0:
         return codes, weights
-    with torch.cuda.device(x.device):
-        _check(lib().lookupffn_hash_weighted(_dev(x, "x"), _dev(signs, "signs"), _dev(codes, "codes"),
-                                             _dev(weights, "weights"), n, d, k, tau, signs.shape[1],
-                                             _dtype_code(x), _stream(x)))
+    _call("lookupffn_hash_weighted", x.device.index, x, _dev(x, "x"), _dev(signs, "signs"), _dev(codes, "codes"),
+          _dev(weights, "weights"), n, d, k, tau, signs.shape[1], _dtype_code(x))
     return codes, weights
 
 
@@ -296,10 +299,8 @@ def lookupffn_hash_probes(x: torch.Tensor, signs: torch.Tensor, k: int, tau: int
     shares = torch.empty((n, k, tau + 1), dtype=torch.float32, device=x.device)
     if n == 0:
         return codes, shares
-    with torch.cuda.device(x.device):
-        _check(lib().lookupffn_hash_probes(_dev(x, "x"), _dev(signs, "signs"), _dev(codes, "codes"),
-                                           _dev(shares, "shares"), n, d, k, tau, signs.shape[1], _dtype_code(x),
-                                           _stream(x)))
+    _call("lookupffn_hash_probes", x.device.index, x, _dev(x, "x"), _dev(signs, "signs"), _dev(codes, "codes"),
+          _dev(shares, "shares"), n, d, k, tau, signs.shape[1], _dtype_code(x))
     return codes, shares
 
 
@@ -349,10 +350,8 @@ def lookupffn_forward(x: torch.Tensor, signs: torch.Tensor, tables,
     if n == 0:
         return y
     ws_ptr, ws_bytes = _ws(workspace)
-    with torch.cuda.device(x.device):
-        _check(getattr(lib(), _entry)(_dev(x, "x"), _dev(signs, "signs"), tptr, _dev(y, "y"),
-                                      n, d, k, tau, d_out, signs.shape[1], _dtype_code(x), tcode,
-                                      ws_ptr, ws_bytes, _stream(x)))
+    _call(_entry, x.device.index, x, _dev(x, "x"), _dev(signs, "signs"), tptr, _dev(y, "y"), n, d, k, tau, d_out,
+          signs.shape[1], _dtype_code(x), tcode, ws_ptr, ws_bytes)
     return y
 
 
@@ -378,9 +377,8 @@ def lookupffn_forward_stack(x: torch.Tensor, signs, tables, y: torch.Tensor | No
     vp = ctypes.c_void_p
     sp = (vp * n_layers)(*[_dev(sg, "signs") for sg in signs])
     tp = (vp * n_layers)(*[r[0] for r in refs])
-    with torch.cuda.device(x.device):
-        _check(lib().lookupffn_forward_stack(_dev(x, "x"), sp, tp, _dev(y, "y"), n, d, k, tau, d_out,
-                                             signs[0].shape[1], n_layers, _dtype_code(x), tcode, _stream(x)))
+    _call("lookupffn_forward_stack", x.device.index, x, _dev(x, "x"), sp, tp, _dev(y, "y"), n, d, k, tau, d_out,
+          signs[0].shape[1], n_layers, _dtype_code(x), tcode)
     return y
 
 
@@ -398,9 +396,8 @@ def lookupffn_forward_static(x: torch.Tensor, signs: torch.Tensor, tables, y: to
     tcode |= _y_flag(y)      # a bfloat16 / float16 y is stored in that type
     if n == 0:
         return y
-    with torch.cuda.device(x.device):
-        _check(lib().lookupffn_forward_static(_dev(x, "x"), _dev(signs, "signs"), tptr, _dev(y, "y"), n, d, k, tau,
-                                              d_out, signs.shape[1], _dtype_code(x), tcode, _stream(x)))
+    _call("lookupffn_forward_static", x.device.index, x, _dev(x, "x"), _dev(signs, "signs"), tptr, _dev(y, "y"), n,
+          d, k, tau, d_out, signs.shape[1], _dtype_code(x), tcode)
     return y
 
 
@@ -416,9 +413,8 @@ def lookupffn_prepare_bh(bmats: torch.Tensor, d: int, k: int, tau: int) -> Prepa
     block, m = _check_bmats(bmats, d, k, tau)
     need = lib().lookupffn_prepared_bh_bytes(d, k, tau, block, m)
     out = torch.empty(max(need, 256), dtype=torch.uint8, device=bmats.device)
-    with torch.cuda.device(bmats.device):
-        _check(lib().lookupffn_prepare_bh(_dev(bmats, "bmats"), d, k, tau, block, m, _dev(out, "prepared"),
-                                          out.numel(), _stream(bmats)))
+    _call("lookupffn_prepare_bh", bmats.device.index, bmats, _dev(bmats, "bmats"), d, k, tau, block, m,
+          _dev(out, "prepared"), out.numel())
     return PreparedBh(out, block, m)
 
 
@@ -456,9 +452,8 @@ def lookupffn_hash_bh(x: torch.Tensor, bmats, k: int, tau: int, codes: torch.Ten
     if n == 0:
         return codes
     ws_ptr, ws_bytes = _ws(workspace)
-    with torch.cuda.device(x.device):
-        _check(lib().lookupffn_hash_bh(_dev(x, "x"), bptr, _dev(codes, "codes"), n, d, k, tau, block,
-                                       m, _dtype_code(x), ws_ptr, ws_bytes, _stream(x)))
+    _call("lookupffn_hash_bh", x.device.index, x, _dev(x, "x"), bptr, _dev(codes, "codes"), n, d, k, tau, block, m,
+          _dtype_code(x), ws_ptr, ws_bytes)
     return codes
 
 
@@ -475,10 +470,8 @@ def lookupffn_forward_bh(x: torch.Tensor, bmats, tables, y: torch.Tensor | None 
     if n == 0:
         return y
     ws_ptr, ws_bytes = _ws(workspace)
-    with torch.cuda.device(x.device):
-        _check(getattr(lib(), _entry)(_dev(x, "x"), bptr, tptr, _dev(y, "y"),
-                                      n, d, k, tau, d_out, block, m, _dtype_code(x), tcode,
-                                      ws_ptr, ws_bytes, _stream(x)))
+    _call(_entry, x.device.index, x, _dev(x, "x"), bptr, tptr, _dev(y, "y"), n, d, k, tau, d_out, block, m,
+          _dtype_code(x), tcode, ws_ptr, ws_bytes)
     return y
 
 
@@ -502,10 +495,8 @@ def lookupffn_hash_bh_weighted(x: torch.Tensor, bmats, k: int, tau: int,
     if n == 0:
         return codes, weights
     ws_ptr, ws_bytes = _ws(workspace)
-    with torch.cuda.device(x.device):
-        _check(lib().lookupffn_hash_bh_weighted(_dev(x, "x"), bptr, _dev(codes, "codes"),
-                                                _dev(weights, "weights"), n, d, k, tau, block, m, _dtype_code(x),
-                                                ws_ptr, ws_bytes, _stream(x)))
+    _call("lookupffn_hash_bh_weighted", x.device.index, x, _dev(x, "x"), bptr, _dev(codes, "codes"),
+          _dev(weights, "weights"), n, d, k, tau, block, m, _dtype_code(x), ws_ptr, ws_bytes)
     return codes, weights
 
 
