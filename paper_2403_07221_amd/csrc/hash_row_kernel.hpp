@@ -154,6 +154,53 @@ __device__ __forceinline__ void row_weights(const HashArgs &a, const float (&v)[
     }
 }
 
+// Multi-probe shares (hash_kernel.hpp's emit_weights, WMODE 2) of the tables in projection p for tau = 2^SH, into the
+// staged gather's [k][1 + tau][n_pad]: the product q over a table's lanes is all-reduced as above, lane x of the run holds
+// e_x = exp(-2 |z_x|) of its own coordinate, so the share of probe 1 + x is stored from where it stands, a register one
+// store of 64 lanes; those of the selected rows go out as the weights do, S registers to a store.  (The ABI layout, by a lane per
+// table through LDS, and two passes to turn codes and shares around took 104 us of a pass of 16384 tokens of 768, k = 96: pass
+// 670 -> 629 us; 16000 bf16 tokens of 512, k = 60 314 -> 259.)
+template <int SH, int LPT>
+__device__ __forceinline__ void row_shares(const HashArgs &a, const float (&v)[kRowRegs], int p, int n_reg, unsigned c,
+                                           long long t, bool t_ok)
+{
+    constexpr int PER_REG = LPT >> SH;
+    constexpr int TAU = 1 << SH;
+    static_assert(TAU == 8 && TAU <= LPT, "a table's coordinates lie in one register");
+    const unsigned x = c & (unsigned)(TAU - 1);
+    const int j0 = p * ((64 * LPT) >> SH) + (int)(c >> SH);  // the table whose coordinate register 0 holds here
+    const int jl = j0 + (int)x * PER_REG;                    // the one whose selected row's share goes out from here in block 0
+    const long long step = (long long)PER_REG * (TAU + 1) * a.n_pad;
+    float *probe = a.wpk + ((long long)j0 * (TAU + 1) + 1 + x) * a.n_pad + t;
+    float *selected = a.wpk + (long long)jl * (TAU + 1) * a.n_pad + t;
+#pragma unroll
+    for (int m0 = 0; m0 < kRowRegs; m0 += 8) {
+        if (m0 < n_reg) {
+            float e[8], q[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                e[u] = __builtin_amdgcn_exp2f(__builtin_fabsf(v[m0 + u]) * -2.885390082f);  // exp(-2 |z|) = 2^(-2 |z| log2 e)
+                q[u] = 1.0f + e[u];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] *= row_partner<0>(q[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] *= row_partner<1>(q[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] *= row_partner<2>(q[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] = __builtin_amdgcn_rcpf(q[u]);  // q >= 1; the share of the selected row
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (t_ok && j0 + (m0 + u) * PER_REG < a.k) probe[(m0 + u) * step] = q[u] * e[u];
+            float s = q[0];
+#pragma unroll
+            for (int u = 1; u < 8; ++u) s = x == (unsigned)u ? q[u] : s;
+            if (t_ok && jl + m0 * PER_REG < a.k) selected[m0 * step] = s;
+        }
+    }
+}
+
 // lane order -> c order inside every 16-bit group of w: the four bits of the odd nibbles reversed
 __device__ __forceinline__ uint32_t row_c_order(uint32_t w)
 {
@@ -207,7 +254,8 @@ __device__ __forceinline__ void row_reg_stage(float (&v)[kRowRegs])
 // 230 registers per lane: two waves per SIMD, which is enough because a wave's instructions are independent
 // for 64 registers at a stretch; the grid is sized so that a wave works through several groups of tokens.
 // WMODE: 0 codes only; 1 codes and gather weights, tau divides LPT (reduced in registers); 2 codes and gather
-// weights of any tau <= 16, through a z window in LDS (one token at a time, a lane per table)
+// weights of any tau <= 16, through a z window in LDS (one token at a time, a lane per table); 3 codes and multi-probe
+// shares of tau = 8
 template <int R, int MFULL, int WMODE, int LPT>
 __global__ __launch_bounds__(kRowThreads) void hash_row_kernel(HashArgs a)
 {
@@ -395,6 +443,11 @@ __global__ __launch_bounds__(kRowThreads) void hash_row_kernel(HashArgs a)
                         if constexpr (LPT == 16) row_weights<4, LPT>(a, v, p, n_reg, c, t, t_ok);
                         break;
                 }
+            }
+            if constexpr (WMODE == 3) {
+                const long long bits_left = (long long)a.k * a.tau - (long long)p * N;
+                const int n_reg = bits_left >= N ? kRowRegs : (int)((bits_left + LPT - 1) / LPT);
+                row_shares<3, LPT>(a, v, p, n_reg, c, t, t_ok);
             }
             // Any other tau (a table then crosses registers, and may cross from one projection into the next): z
             // goes through LDS, one token at a time; the wave's lanes take a table each and form the same sum and

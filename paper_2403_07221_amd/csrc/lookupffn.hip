@@ -60,8 +60,8 @@ int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, in
 int forward_small_part(int L, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
 int forward_stack_load();
 // parts 9, 10: the hash with a token per row of lanes, d_pad = 1024 (four tokens per wavefront) and 512 (eight)
-int hash_row16_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s);
-int hash_row8_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s);
+int hash_row16_part(int n_rounds, bool shares, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s);
+int hash_row8_part(int n_rounds, bool shares, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s);
 int hash_row16_load();
 int hash_row8_load();
 // parts 4 .. 6: the BH hash kernel, d_pad = 64 .. 256, 512 and 1024.  wmode: 0 codes only, 1 weights of tau 4, 8, 16, 2 weights
@@ -395,8 +395,11 @@ int forward_stack_load()
 
 #if LFFN_HAS(9) || LFFN_HAS(10)
 // WMODE of the lane-row kernel: 0 codes only, 1 weights reduced in registers (tau divides the lanes of a token),
-// 2 weights of any tau through the z window
-inline int row_wmode(const HashArgs &a, int lpt) { return !(a.weights || a.wpk) ? 0 : lpt % a.tau == 0 ? 1 : 2; }
+// 2 weights of any tau through the z window, 3 multi-probe shares
+inline int row_wmode(const HashArgs &a, bool shares, int lpt)
+{
+    return shares ? 3 : !(a.weights || a.wpk) ? 0 : lpt % a.tau == 0 ? 1 : 2;
+}
 
 template <int MFULL, int WMODE, int LPT>
 int launch_hash_row_r(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
@@ -413,29 +416,31 @@ int launch_hash_row_r(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hi
 
 // MFULL: the kernel built for one row length, three rounds; else the form with run-time bounds
 template <int MFULL, int LPT>
-int launch_hash_row_m(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
+int launch_hash_row_m(int n_rounds, bool shares, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
-    const int wmode = row_wmode(a, LPT);
+    const int wmode = row_wmode(a, shares, LPT);
     if (MFULL != 0) {
         if (wmode == 0) hipLaunchKernelGGL((hash_row_kernel<3, MFULL, 0, LPT>), grid, dim3(kRowThreads), lds, s, a);
         else if (wmode == 1) hipLaunchKernelGGL((hash_row_kernel<3, MFULL, 1, LPT>), grid, dim3(kRowThreads), lds, s, a);
+        else if (wmode == 3) hipLaunchKernelGGL((hash_row_kernel<3, MFULL, 3, LPT>), grid, dim3(kRowThreads), lds, s, a);
         else hipLaunchKernelGGL((hash_row_kernel<3, MFULL, 2, LPT>), grid, dim3(kRowThreads), lds, s, a);
         return LFFN_OK;
     }
     return wmode == 0   ? launch_hash_row_r<0, 0, LPT>(n_rounds, a, grid, lds, s)
            : wmode == 1 ? launch_hash_row_r<0, 1, LPT>(n_rounds, a, grid, lds, s)
+           : wmode == 3 ? launch_hash_row_r<0, 3, LPT>(n_rounds, a, grid, lds, s)
                         : launch_hash_row_r<0, 2, LPT>(n_rounds, a, grid, lds, s);
 }
 #endif
 
 #if LFFN_HAS(9)
-int hash_row16_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
+int hash_row16_part(int n_rounds, bool shares, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
     // built for the row lengths of the paper's models (d = 768 and 1024, three rounds); any other multiple of
     // 16 in range takes the form with run-time bounds
-    if (n_rounds == 3 && a.d == 768) return launch_hash_row_m<48, 16>(3, a, grid, lds, s);
-    if (n_rounds == 3 && a.d == 1024) return launch_hash_row_m<64, 16>(3, a, grid, lds, s);
-    return launch_hash_row_m<0, 16>(n_rounds, a, grid, lds, s);
+    if (n_rounds == 3 && a.d == 768) return launch_hash_row_m<48, 16>(3, shares, a, grid, lds, s);
+    if (n_rounds == 3 && a.d == 1024) return launch_hash_row_m<64, 16>(3, shares, a, grid, lds, s);
+    return launch_hash_row_m<0, 16>(n_rounds, shares, a, grid, lds, s);
 }
 
 int hash_row16_load()
@@ -447,10 +452,10 @@ int hash_row16_load()
 #endif
 
 #if LFFN_HAS(10)
-int hash_row8_part(int n_rounds, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
+int hash_row8_part(int n_rounds, bool shares, const HashArgs &a, dim3 grid, size_t lds, hipStream_t s)
 {
-    if (n_rounds == 3 && a.d == 512) return launch_hash_row_m<64, 8>(3, a, grid, lds, s);  // the paper's small models
-    return launch_hash_row_m<0, 8>(n_rounds, a, grid, lds, s);
+    if (n_rounds == 3 && a.d == 512) return launch_hash_row_m<64, 8>(3, shares, a, grid, lds, s);  // the paper's small models
+    return launch_hash_row_m<0, 8>(n_rounds, shares, a, grid, lds, s);
 }
 
 int hash_row8_load()
@@ -889,7 +894,7 @@ void launch_hash1024_t(const HashArgs &a, bool probes, dim3 grid, size_t lds, hi
 struct HashOut {
     uint16_t *codes = nullptr;
     uint32_t *packed = nullptr;
-    float *weights = nullptr;  // beside `codes`: [n][k] or [n][k][1+tau]; beside `packed`: wpk[k][n_pad]
+    float *weights = nullptr;  // beside `codes`: [n][k] or [n][k][1+tau]; beside `packed`: wpk[k][n_pad] or [k][1+tau][n_pad]
     bool probes = false;
     int shift = kPackedShift;  // what the packed codes are scaled by: log2 of the staged gather's row-piece bytes
 };
@@ -909,7 +914,8 @@ bool hash_extents_ok(const HashOut &o, int64_t n, int k, int tau, int64_t n_pad,
     // packed[s * n_pad + t], s < k/2, t < n_pad;  wpk[j * n_pad + t], j < k, t < n
     if (n_pad < n) return false;
     if (cap_packed && (int64_t)(k / 2) * n_pad * 4 > cap_packed) return false;
-    if (o.weights && cap_weights && ((int64_t)(k - 1) * n_pad + n) * 4 > cap_weights) return false;
+    const int64_t rows = o.probes ? (int64_t)k * (tau + 1) : k;  // [k][1 + tau][n_pad] shares
+    if (o.weights && cap_weights && ((rows - 1) * n_pad + n) * 4 > cap_weights) return false;
     return true;
 }
 
@@ -952,6 +958,27 @@ unsigned split_projections(int P, bool cross, int64_t most, int *p_per)
     return (unsigned)((P + *p_per - 1) / *p_per);
 }
 
+// Whether hash_row_kernel takes a hash: d_pad = 1024 or 512, up to four rounds, codes alone or with the gather weights (reduced
+// in registers when tau divides the lanes of a token: a table is then a run of lanes of one register; else through a z window in
+// LDS), or with the multi-probe shares of tau = 8 in the staged gather's layout: a token per row of 16 (8) lanes, four (eight)
+// tokens per wavefront, no LDS transposes.  A lane holds every 16th (8th) coordinate: d a multiple of 16 makes "in range" a
+// per-register question.
+// It needs a batch that gives most SIMDs two waves of tokens to pull ahead; below that one group's latency
+// decides and the one-token kernels are faster.  Measured crossovers: d_pad = 1024 about 2048 tokens (4096
+// with weights), d_pad = 512 (twice the tokens per wave) about 6000 (10000 with weights).
+bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, int64_t n, int d, int k, int tau, int n_rounds,
+                 const Options &opt)
+{
+    const int L = log2_pad(d);
+    if ((L != 10 && L != 9) || d % 16 != 0 || n_rounds < 1 || n_rounds > 4 || !aligned(signs, 16)) return false;
+    if (probes && (!packed || tau != 8)) return false;
+    const int lpt = L == 10 ? 16 : 8;
+    const int64_t row_from = lpt == 16 ? (weights ? 4096 : 2048) : (weights ? 12288 : 6144);
+    if (!(opt.hash_path == 3 || (opt.hash_path == 0 && n >= row_from))) return false;
+    const int P = (int)(((int64_t)k * tau + (1 << L) - 1) >> L);
+    return hrow_lds_bytes(P, n_rounds, lpt, weights && lpt % tau != 0) <= 64 * 1024;
+}
+
 // few_ok: hash_lane_kernel may take the batch (the forward passes; the stand-alone hash keeps the kernels that give a token to a
 // wave, and so the one can be held against the others).
 int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t n, int d, int k, int tau,
@@ -979,7 +1006,9 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
     a.p_per = a.P;
     a.cross = N % tau != 0;
     if (!a.codes && !a.packed) return LFFN_E_NULL;
-    if (out.probes && (!a.codes || !a.weights)) return LFFN_E_UNSUPPORTED;  // shares exist in the ABI layout only
+    const bool row_ok = hash_row_ok(signs, out.packed != nullptr && !out.codes, out.weights != nullptr, out.probes, n, d, k, tau, n_rounds, opt);
+    // shares: in the ABI layout, or in the staged gather's from hash_row_kernel alone
+    if (out.probes && (!out.weights || (!a.codes && !row_ok))) return LFFN_E_UNSUPPORTED;
     TimedLaunch tl(0, s);
     // Few tokens: hash_lane_kernel, two or four tokens to a workgroup, while its workgroups fill the chip no more than twice.
     // Hash alone, three rounds, us, a token to a wave / two tokens a workgroup / four:
@@ -1007,20 +1036,8 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
             return LFFN_OK;
         }
     }
-    // d_pad = 1024 or 512, up to four rounds, codes alone or with the gather weights (reduced in registers when
-    // tau divides the lanes of a token: a table is then a run of lanes of one register; else through a z window
-    // in LDS): a token per row of 16 (8) lanes, four (eight) tokens per wavefront, no LDS transposes.  A lane holds every 16th (8th) coordinate: d a multiple
-    // of 16 makes "in range" a per-register question.
-    // It needs a batch that gives most SIMDs two waves of tokens to pull ahead; below that one group's latency
-    // decides and the one-token kernels are faster.  Measured crossovers: d_pad = 1024 about 2048 tokens (4096
-    // with weights), d_pad = 512 (twice the tokens per wave) about 6000 (10000 with weights).
-    const int lpt = L == 10 ? 16 : 8;
-    const bool row_weights_ok = !out.weights || !out.probes;
-    const bool row_window = out.weights && lpt % tau != 0;  // weights through the z window in LDS
-    const int64_t row_from = lpt == 16 ? (out.weights ? 4096 : 2048) : (out.weights ? 12288 : 6144);
-    const bool row_wanted = opt.hash_path == 3 || (opt.hash_path == 0 && n >= row_from);
-    if (row_wanted && (L == 10 || L == 9) && d % 16 == 0 && n_rounds >= 1 && n_rounds <= 4 && row_weights_ok &&
-        aligned(signs, 16) && hrow_lds_bytes(a.P, n_rounds, lpt, row_window) <= 64 * 1024) {
+    if (row_ok) {
+        const int lpt = L == 10 ? 16 : 8;
         // two workgroups per compute unit fill it (two waves per SIMD); a larger batch is worked through in
         // several groups of tokens per wave, the next group's rows in flight during a transform
         int cus = 0;
@@ -1030,9 +1047,9 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
         int64_t blocks = (groups + kRowWaves - 1) / kRowWaves;
         const int64_t cap = opt.hash_blocks ? opt.hash_blocks : 2 * (int64_t)cus;
         if (blocks > cap) blocks = cap;
-        const size_t lds = hrow_lds_bytes(a.P, n_rounds, lpt, row_window);
-        rc = lpt == 16 ? lffn_host::hash_row16_part(n_rounds, a, dim3((unsigned)blocks), lds, s)
-                       : lffn_host::hash_row8_part(n_rounds, a, dim3((unsigned)blocks), lds, s);
+        const size_t lds = hrow_lds_bytes(a.P, n_rounds, lpt, out.weights && lpt % tau != 0);
+        rc = lpt == 16 ? lffn_host::hash_row16_part(n_rounds, out.probes, a, dim3((unsigned)blocks), lds, s)
+                       : lffn_host::hash_row8_part(n_rounds, out.probes, a, dim3((unsigned)blocks), lds, s);
         if (rc != LFFN_OK) return rc;
         LFFN_HIP(hipGetLastError());
         tl.done();
@@ -1907,18 +1924,20 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
                                   d, k, tau, h.block, h.n_factors, x_dtype, true, s);
         return launch_hash(x, h.signs, out, n, d, k, tau, h.n_rounds, x_dtype, true, s, opt);
     };
-    // the hash kernels write the staged gather's layout themselves, scaled for its row pieces (unless the
-    // variant is the multi-probe one, whose shares exist in the ABI layout only)
+    // the hash kernels write the staged gather's layout themselves, scaled for its row pieces; multi-probe shares only
+    // hash_row_kernel does, and a batch that goes in pieces is cut from the ABI layout
     RingPlan ring;
     rc = plan_gather_ring(n, k, tau, d_out, T, mode, opt, &ring);
     if (rc != LFFN_OK) return rc;
-    if (!ring.use && plan.use && !plan.tail && mode != kProbes) {
+    if (!ring.use && plan.use && !plan.tail &&
+        (mode != kProbes || (n <= kProbesPiece && hash_row_ok(h.signs, true, true, true, n, d, k, tau, h.n_rounds, opt)))) {
         HashOut out;
         out.shift = plan.shift;
-        const int64_t pb = packed_bytes(n, k), wb = mode == kWeighted ? wpk_bytes(n, k) : 0;
+        out.probes = mode == kProbes;
+        const int64_t pb = packed_bytes(n, k), wb = mode == kWeighted ? wpk_bytes(n, k) : mode == kProbes ? spk_bytes(n, k, tau) : 0;
         out.packed = sc.take<uint32_t>(pb);
-        out.weights = mode == kWeighted ? sc.take<float>(wb) : nullptr;
-        if (!out.packed || (mode == kWeighted && !out.weights)) return LFFN_E_WORKSPACE;
+        out.weights = mode != kPlain ? sc.take<float>(wb) : nullptr;
+        if (!out.packed || (mode != kPlain && !out.weights)) return LFFN_E_WORKSPACE;
         if (!hash_extents_ok(out, n, k, tau, plan.a.n_pad, 0, pb, wb)) return LFFN_E_WORKSPACE;
         rc = run_hash(out);
         if (rc != LFFN_OK) return rc;
