@@ -965,7 +965,8 @@ unsigned split_projections(int P, bool cross, int64_t most, int *p_per)
 // per-register question.
 // It needs a batch that gives most SIMDs two waves of tokens to pull ahead; below that one group's latency
 // decides and the one-token kernels are faster.  Measured crossovers: d_pad = 1024 about 2048 tokens (4096
-// with weights), d_pad = 512 (twice the tokens per wave) about 6000 (10000 with weights).
+// with weights), d_pad = 512 (twice the tokens per wave) about 6000 (10000 with weights); with shares, which the others leave in
+// the ABI layout, 1200 (k = 96, d = 768, staged pass of 1500 tokens 229 / 221 us, 4000 243 / 223; d = 512 233 / 228, 8000 404 / 376).
 bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, int64_t n, int d, int k, int tau, int n_rounds,
                  const Options &opt)
 {
@@ -973,7 +974,7 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
     if ((L != 10 && L != 9) || d % 16 != 0 || n_rounds < 1 || n_rounds > 4 || !aligned(signs, 16)) return false;
     if (probes && (!packed || tau != 8)) return false;
     const int lpt = L == 10 ? 16 : 8;
-    const int64_t row_from = lpt == 16 ? (weights ? 4096 : 2048) : (weights ? 12288 : 6144);
+    const int64_t row_from = probes ? 1536 : lpt == 16 ? (weights ? 4096 : 2048) : (weights ? 12288 : 6144);
     if (!(opt.hash_path == 3 || (opt.hash_path == 0 && n >= row_from))) return false;
     const int P = (int)(((int64_t)k * tau + (1 << L) - 1) >> L);
     return hrow_lds_bytes(P, n_rounds, lpt, weights && lpt % tau != 0) <= 64 * 1024;
@@ -1116,6 +1117,28 @@ int64_t lds_tokens_per_block(int64_t n, int n_units, int token_splits, int Bx)
     return (unit_tokens + blocks - 1) / blocks;
 }
 
+// Four times the tokens a chunk has to have for staging to pay.  A stage costs its copies and at least its fewest slots' row
+// reads however few the tokens; the direct kernel costs by the row.  Lines in token slots (kLdsThreads / sw tokens each), where
+// the slowest of the shapes measured (k 64 ... 250, 64 ... 1024 wide, prepared and not) draws level; direct / staged, us:
+//   multi-probe, tau 8: 1.75 slots (2240 tokens, k = 96, 768 wide 269 / 240, 64 wide 1.15 : 1; 4096 of the first 471 / 236), tau 9
+//   and 10: 2.25 (2880 tokens, k = 96, 768 wide, tau 9 551 / 433, tau 10 770 / 495; 64 wide 1.07 and 1.12 : 1)
+//   plain, tau 8: 3.75 (4800 tokens, k = 96, 768 wide 73 / 64; k = 64, 256 wide 58.7 / 57.3); weighted 3.25 (4160 82 / 71; 66 / 65)
+//   both, tau 9: 2.5 (3200 tokens, k = 170, 768 wide 175 / 133, 64 wide 1.06 : 1), tau 10: 3.25 (6656, k = 96, 512 wide 138 / 114,
+//   weighted 198 / 138; k = 64, 1024 wide 99.9 / 98.9)
+// Below 64 tables the fill and the hand-over weigh more, an odd one is a launch of its own with codes and weights to turn around
+// (multi-probe 2.5 and 2.75 slots; k = 24, 768 wide, 3200 tokens, tau 8 106 / 91; weighted, k = 97, 4160 tokens of 768 98 / 108), and
+// copies of 64 bytes from row-major tables are half a line: two tokens a row there, as for tau 7.
+int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared)
+{
+    const int64_t two_a_row = 8 * (int64_t)rows, slot = kLdsThreads / sw;
+    if (tau == 7 || (sw == 4 && !prepared)) return two_a_row;
+    int64_t line = two_a_row;  // in quarters of a slot from here
+    const bool small = k < 64 || k % 2;
+    if (mode == kProbes) line = (sw == 8 ? (small ? 10 : 7) : (small ? 11 : 9)) * slot;
+    else if (!small) line = (sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? 10 : 13) * slot;
+    return std::min(line, two_a_row);
+}
+
 // Launch shape of the LDS-staged gather for one problem size (no pointers involved).
 struct LdsPlan {
     bool use = false;
@@ -1189,8 +1212,7 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
-    // Staging pays only when a chunk re-uses each staged row a few times.
-    if (opt.gather_path < 2 && chunk < 2 * (int64_t)rows) return LFFN_OK;
+    if (opt.gather_path < 2 && chunk * 4 < staged_from(mode, k, tau, sw, rows, T.prepared)) return LFFN_OK;
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
     auto slots_of = [&](int64_t tokens) {
         const int tok = (int)((tokens + groups - 1) / groups);

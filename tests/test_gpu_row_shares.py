@@ -19,13 +19,13 @@ def d_pad(d):
 
 
 @pytest.mark.parametrize("n,d,k,d_out,rounds,x_dtype,y_dtype,kernel", [
-    (4096, 768, 96, 128, 3, "float32", "float32", "hash_row_kernel"),     # smallest batch; the form built for 768
+    (1536, 768, 96, 128, 3, "float32", "float32", "hash_row_kernel"),     # smallest batch; the form built for 768
     (4097, 1024, 130, 64, 3, "bfloat16", "float32", "hash_row_kernel"),   # two projections, tokens beyond a wave's four
     (5003, 528, 6, 72, 1, "float16", "bfloat16", "hash_row_kernel"),      # a few registers hold coordinates
     (4999, 640, 250, 32, 4, "float32", "float32", "hash_row_kernel"),     # the last register half full
-    (12288, 512, 66, 40, 3, "float32", "float32", "hash_row_kernel"),     # eight lanes a token, two projections
+    (1539, 512, 66, 40, 3, "float32", "float32", "hash_row_kernel"),     # eight lanes a token, two projections
     (12293, 272, 64, 128, 2, "bfloat16", "float16", "hash_row_kernel"),
-    (4095, 768, 96, 128, 3, "float32", "float32", "hash1024_kernel"),     # below the line
+    (1535, 768, 96, 128, 3, "float32", "float32", "hash_lane_kernel"),    # below the line
     (4100, 768, 97, 128, 3, "float32", "float32", "hash1024_kernel"),     # odd k: the last table apart
     (4100, 776, 96, 128, 3, "float32", "float32", "hash1024_kernel"),     # rows no multiple of 16
 ])

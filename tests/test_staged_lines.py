@@ -1,0 +1,28 @@
+"""From how many tokens a forward pass stages its tables (256 compute units): a token to either side of each line, where lines
+differ -- mode, tau, prepared or row-major tables, few or an odd number of them."""
+import shutil
+
+import pytest
+
+import recorded as R
+
+PREPARED = 0x100
+CASES = [  # entry, k, tau, d_out, prepared, tokens of the line
+    ("lookupffn_forward", 96, 8, 768, True, 4791), ("lookupffn_forward", 96, 8, 768, False, 4791),
+    ("lookupffn_forward_weighted", 96, 8, 768, True, 4151), ("lookupffn_forward_probes", 96, 8, 768, True, 2231),
+    ("lookupffn_forward", 170, 9, 768, True, 3196), ("lookupffn_forward_weighted", 128, 10, 1024, True, 3325),
+    ("lookupffn_forward_probes", 64, 9, 1024, True, 2301), ("lookupffn_forward", 170, 9, 768, False, 5116),
+    ("lookupffn_forward", 62, 8, 768, True, 5111), ("lookupffn_forward_weighted", 97, 8, 768, True, 5111),
+    ("lookupffn_forward_probes", 24, 8, 768, True, 3191), ("lookupffn_forward_probes", 97, 8, 768, True, 3191),
+    ("lookupffn_forward_probes", 96, 7, 768, True, 2551), ("lookupffn_forward_probes", 24, 10, 512, True, 5625),
+]
+
+
+@pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
+@pytest.mark.parametrize("entry,k,tau,d_out,prepared,line", CASES)
+def test_line(tmp_path, entry, k, tau, d_out, prepared, line):
+    lib = R.build(tmp_path)
+    for n in (line - 1, line):
+        call = [entry, R.FAKE, R.FAKE, R.FAKE, R.FAKE, n, 768, k, tau, d_out, 3, 0, PREPARED if prepared else 0, R.FAKE, 1 << 40, None]
+        kernels = [launch.kernel for launch in R.record(lib, [call])[0]]
+        assert ("gather_lds_kernel" in kernels) == (n == line), (n, kernels)
