@@ -433,7 +433,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
 
-// ---- pieces of the d_pad = 1024 transform, shared by hash1024_kernel and the small-batch forward kernel ----
+// ---- pieces of the d_pad = 1024 transform of hash1024_kernel ----
 
 // LDS byte addresses of a lane's pieces of the per-wave transpose area (at LDS byte address tp0) in both layouts
 struct H1024Lane {

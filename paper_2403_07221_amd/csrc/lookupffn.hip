@@ -631,7 +631,7 @@ struct Options {
     int small_tokens = 0;     // 0 = default, -1 = never: up to this many tokens lookupffn_forward runs as one
                               // hash-and-gather launch (when the shape is that kernel's)
 };
-constexpr int kSmallTokensDefault = 512;  // k = 96, d_out = 768: 23 us against 33 us at 512 tokens, even at about 900
+constexpr int kSmallTokensDefault = 512;  // k = 96, d_out = 768: 12.6 us against 13.8 at 200 tokens, 24.6 against 17.8 at 512; k = 32, 256 wide 7.8 / 8.9 there
 std::mutex g_opt_mu;
 Options g_opt;
 Options options_snapshot()
@@ -1154,7 +1154,9 @@ struct LdsPlan {
                     // k is odd (the staged kernel takes its tables in pairs), else 0
 };
 
-int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mode mode, const Options &opt,
+// hashed: the codes are this library's own, in a forward pass.  A gather of a caller's codes turns them around first and takes
+// scratch memory for it, which between the two lines it did without: it keeps two tokens a row.
+int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mode mode, bool hashed, const Options &opt,
                     LdsPlan *p)
 {
     p->use = false;
@@ -1212,7 +1214,7 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
-    if (opt.gather_path < 2 && chunk * 4 < staged_from(mode, k, tau, sw, rows, T.prepared)) return LFFN_OK;
+    if (opt.gather_path < 2 && chunk * 4 < (hashed ? staged_from(mode, k, tau, sw, rows, T.prepared) : 8 * (int64_t)rows)) return LFFN_OK;
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
     auto slots_of = [&](int64_t tokens) {
         const int tok = (int)((tokens + groups - 1) / groups);
@@ -1569,7 +1571,7 @@ int gather_from_abi(Mode mode, const uint16_t *codes, const float *weights, cons
         for (int64_t t = 0; t < n; t += m) {
             const int64_t len = std::min(m, n - t);
             LdsPlan piece;
-            int rc = plan_gather_lds(len, k, tau, d_out, T, mode, opt, &piece);
+            int rc = plan_gather_lds(len, k, tau, d_out, T, mode, true, opt, &piece);
             if (rc != LFFN_OK) return rc;
             Scratch scratch = *sc;
             rc = gather_from_abi(mode, codes + t * k, weights + t * k * (1 + tau), T,
@@ -1776,6 +1778,8 @@ bool stack_shape_ok(const void *x, const int8_t *const *signs, const void *const
 // entry points accept: rows and signs are read element by element) and a table set below 2 GiB.  `by_rate`: leave out
 // the batches that the two kernels finish sooner.  A token's rows come in through one compute unit, a lane to each of up
 // to 1024 dwords.  One launch against two, us a pass (fp32, tau = 8 where not said):
+// (two kernels as they were before hash_lane_kernel; with it, tau = 8, us: 256 tokens of 512, k = 96, 768 wide 15.0 / 14.0; 512 tokens, k = 64, 256
+// wide 9.5 / 10.7; of 64, k = 8 3.2 / 5.3; of 256, k = 96, 256 wide 10.6 / 11.7)
 //   256 tokens: k = 96, 768 wide 14.9 / 18.7; k = 256, 512 wide 22.5 / 30.9; k = 256, 1024 wide 38.2 / 49.6
 //   512 tokens: k = 64, 256 wide (32 MiB of rows) 10.0 / 12.9; tau = 7, k = 97, 512 wide (97 MiB) 17.5 / 14.3; k = 96,
 //   768 wide (144 MiB) 26.6 / 21.3; k = 8, 64 wide 10.3 / 12.7
@@ -1936,7 +1940,7 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
     if (rc != LFFN_OK) return rc;
     const TableRef T = table_ref(tables, table_dtype, tau);
     LdsPlan plan;
-    rc = plan_gather_lds(n, k, tau, d_out, T, mode, opt, &plan);
+    rc = plan_gather_lds(n, k, tau, d_out, T, mode, true, opt, &plan);
     if (rc != LFFN_OK) return rc;
     float *apack = (h.bh() && !h.bh_prepared) ? sc.take<float>(bh_pack_bytes(d, k, tau, h.block, h.n_factors)) : nullptr;
     if (h.bh() && !h.bh_prepared && !apack) return LFFN_E_WORKSPACE;
@@ -1992,7 +1996,7 @@ int gather_core(Mode mode, const uint16_t *codes, const float *weights, const vo
     const Options opt = options_snapshot();
     const TableRef T = table_ref(tables, table_dtype, tau);
     LdsPlan plan;
-    rc = plan_gather_lds(n, k, tau, d_out, T, mode, opt, &plan);
+    rc = plan_gather_lds(n, k, tau, d_out, T, mode, false, opt, &plan);
     if (rc != LFFN_OK) return rc;
     RingPlan ring;
     rc = plan_gather_ring(n, k, tau, d_out, T, mode, opt, &ring);

@@ -26,3 +26,12 @@ def test_line(tmp_path, entry, k, tau, d_out, prepared, line):
         call = [entry, R.FAKE, R.FAKE, R.FAKE, R.FAKE, n, 768, k, tau, d_out, 3, 0, PREPARED if prepared else 0, R.FAKE, 1 << 40, None]
         kernels = [launch.kernel for launch in R.record(lib, [call])[0]]
         assert ("gather_lds_kernel" in kernels) == (n == line), (n, kernels)
+
+
+@pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
+@pytest.mark.parametrize("mode,n,staged", [("plain", 5110, False), ("plain", 5111, True), ("weighted", 5110, False),
+                                           ("probes", 5110, False), ("probes", 5111, True)])
+def test_line_of_a_callers_codes(tmp_path, mode, n, staged):
+    """Codes of the caller's: two tokens a row, and no scratch memory below that."""
+    launches = R.record(R.build(tmp_path), [R.gather(mode, n, 96, 8, 768, PREPARED)])[0]
+    assert [launch.kernel for launch in launches][-1] == ("gather_lds_kernel" if staged else "gather_kernel")
