@@ -40,7 +40,7 @@ struct HashArgs {
     uint16_t *codes;      // [n][k], or NULL when `packed` is written instead
     uint32_t *packed;     // packed codes (see above), or NULL
     float *weights;       // [n][k] gather weights of the weighted variant (Sec. 4), or NULL
-    float *wpk;           // the same weights table-major, [k][n_pad], for the LDS-staged gather, or NULL
+    float *wpk;           // the same weights table-major, [k][n_pad], for the LDS-staged gather (hash_row_kernel, WMODE 3: shares [k][1+tau][n_pad]), or NULL
     long long n_pad;      // token stride of `packed`
     int packed_shift;     // log2 of the row-piece bytes the packed codes are scaled by (7: 128-byte pieces, 6: 64-byte)
     long long n;
