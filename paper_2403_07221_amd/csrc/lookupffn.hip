@@ -1663,6 +1663,33 @@ int launch_bh_pack(const float *bmats, float *apack, int d, int k, int tau, int 
     return LFFN_OK;
 }
 
+// Up to how many transforms, in fills of the chip (cus * 1024 / d_pad: the workgroups that it holds), bh_lane_kernel takes a batch:
+// two or four tokens to a workgroup, a wave to 64 coordinates of them.  Hash alone, us, bh_hash_kernel / two tokens a workgroup / four:
+//   d = 768, k = 96, tau = 8, weights, block 64: 1 token 29.2 / 13.7 / 15.5, 128 32.4 / 14.6 / 16.5, 512 32.6 / 16.7 / 16.6, 1024
+//   32.6 / 29.7 / 17.8, 2048 32.5 / 54.7 / 32.4; block 16: 128 21.1 / 6.6 / 8.5, 2048 21.6 / 20.6 / 15.6, 4096 22.3 / 38.5 / 28.7;
+//   codes, block 32: 128 23.9 / 9.2 / 11.0, 2048 23.8 / 30.1 / 20.4, 4096 24.5 / 57.0 / 38.3
+//   d = 768, k = 170, tau = 9 (two projections): 128 67.7 / 26.2 / 29.9, 1024 68.1 / 53.9 / 31.8
+//   d = 512, k = 256 (four), block 64: 128 32.8 / 10.5 / 10.8, 512 32.8 / 27.8 / 17.6, 1024 32.6 / 48.0 / 30.4, 2048 32.9 / 86.7 / 54.9
+//   d = 256, codes, k = 96 (three), block 64: 1800 (5.3 fills) 25.9 / 35.1 / 22.1, 2300 (6.7) 25.8 / 39.9 / 31.1; k = 8, block 16: 8192 (8)
+//   15.3 / 15.2 / 12.6
+//   d = 64, codes, k = 24 (three), block 64: 2600 (1.9) 10.0 / 12.2 / 9.0, 4096 (3) 10.1 / 16.2 / 11.6
+// Every group of tokens reads all factors, n_factors * block KB into a compute unit for each fill, bh_hash_kernel a quarter
+// to a sixteenth of that, and it spreads the projections of narrow rows out: the more bytes and the narrower the row, the
+// sooner it is ahead.  Fills at the first loss, blocks 16 / 32 / 64, of 1 ... 36 projections, codes and weights: d = 128 one factor
+// 8 / 8 / 4.5, two 6 / 4.1 / 4, four 4.1 / 4.1 / 3, sixteen 4.1 / 3.5 / 2.5; d = 64 one 8 / 6 / 2.75, two 5.3 / 3.4 / 2.15, four
+// 3 / 2.3 / 2.05, sixteen 2.05 / 2.05 / 1.2.  So a part of the width and one that goes with 1 / bytes.  d = 256 first loses at 6.7,
+// and not before 8 with narrow blocks of one projection or two or where tables cross into a projection that both then hash
+// twice (k = 40, tau = 9, 3500 tokens, block 64 46.6 / 41.8 / 30.0); three in a chain lose at 6.7 (k = 96, block 32, 2300 tokens 19.3 / 23.3 /
+// 21.2).
+double bh_lane_most(int N, int P, bool cross, int block, int n_factors)
+{
+    if (N >= 512) return block == 64 ? 4 : 8;
+    if (N == 256) return (P > 1 && cross) || (P <= 2 && block < 64) ? 8 : 6;
+    const int bytes = n_factors * block;  // KB a compute unit and fill
+    const double most = std::min(8.0, (N == 128 ? 2.5 : 1.0) + 100.0 / bytes);
+    return N == 64 && bytes <= 256 ? std::max(most, 2.0) : most;
+}
+
 // Hashes with the packed factors `apack`; `pack_from` != NULL: re-order them from there first.  few_ok: bh_lane_kernel may take
 // the batch (the forward passes; the stand-alone hash keeps bh_hash_kernel, and so the one can be held against the other).
 int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in, float *apack_scratch,
@@ -1695,22 +1722,10 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
         int rc = launch_bh_pack(pack_from, apack_scratch, d, k, tau, block, n_factors, s);
         if (rc != LFFN_OK) return rc;
     }
-    // Few tokens: bh_lane_kernel, a wave to 64 coordinates of two or four tokens, while its workgroups fill the chip no more than
-    // twice (once with blocks of 64 at d_pad 512 and 1024, whose factors a workgroup takes longest to read).  Hash alone, twelve
-    // layers in turn, us, bh_hash_kernel / two tokens a workgroup / four:
-    //   d = 768, k = 96, tau = 8, weights, block 64: 1 token 29.2 / 13.7 / 15.5, 128 32.4 / 14.6 / 16.5, 512 32.6 / 16.7 / 16.6, 1024
-    //   32.6 / 29.7 / 17.8, 2048 32.5 / 54.7 / 32.4; block 16: 128 21.1 / 6.6 / 8.5, 2048 21.6 / 20.6 / 15.6, 4096 22.3 / 38.5 / 28.7;
-    //   codes, block 32: 128 23.9 / 9.2 / 11.0, 2048 23.8 / 30.1 / 20.4, 4096 24.5 / 57.0 / 38.3
-    //   d = 768, k = 170, tau = 9 (two projections): 128 67.7 / 26.2 / 29.9, 1024 68.1 / 53.9 / 31.8
-    //   d = 512, k = 256 (four), block 64: 128 32.8 / 10.5 / 10.8, 512 32.8 / 27.8 / 17.6, 1024 32.6 / 48.0 / 30.4, 2048 32.9 / 86.7 / 54.9
-    //   d = 256, k = 96 (three), block 64: 256 29.2 / 9.4 / 7.8, 2048 29.3 / 36.2 / 22.6, 4096 29.6 / 64.1 / 41.9
-    //   d = 64, k = 8, block 64: 128 9.6 / 4.8 / 6.2, 4096 9.7 / 7.6 / 6.4; k = 96 (twelve), block 16: 256 7.0 / 4.3 / 4.2, 2048 9.7 / 11.6
-    //   / 9.7, 4096 12.4 / 20.6 / 16.8
-    // (It writes the ABI layout: batches small enough for it do not take the staged gather.)
     int cus = 0, rc = device_cus(&cus);
     if (rc != LFFN_OK) return rc;
     const int64_t fill = (int64_t)cus * (1024 / N);  // workgroups that the chip holds
-    if (few_ok && a.codes && n * a.P <= (block == 64 && N >= 512 ? 4 : 8) * fill) {
+    if (few_ok && a.codes && (double)(n * a.P) <= bh_lane_most(N, a.P, N % tau != 0, block, n_factors) * (double)fill) {
         const int tokens = n * a.P <= 2 * (int64_t)cus * std::max(1, 256 / N) ? 2 : 4;
         const int64_t groups = (n + tokens - 1) / tokens;
         dim3 grid = grid_of(groups);
