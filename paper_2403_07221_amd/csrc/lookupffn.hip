@@ -543,7 +543,12 @@ int launch_hash_lane_t(int wmode, const HashArgs &a, dim3 grid, hipStream_t s)
     constexpr size_t lds = BhLane<L, T>::WORDS * 4;
     static_assert(lds <= 64 * 1024, "no LDS beyond what every kernel may use");
     switch (wmode) {
-        case 0: hipLaunchKernelGGL((hash_lane_kernel<L, T, 0>), grid, dim3(1 << L), lds, s, a); break;
+        case 0:  // (codes alone of narrow rows: four tokens only)
+            if constexpr (T == 4 || L >= 9) {
+                hipLaunchKernelGGL((hash_lane_kernel<L, T, 0>), grid, dim3(1 << L), lds, s, a);
+                break;
+            }
+            return LFFN_E_UNSUPPORTED;
         case 1: hipLaunchKernelGGL((hash_lane_kernel<L, T, 1>), grid, dim3(1 << L), lds, s, a); break;
         case 2: hipLaunchKernelGGL((hash_lane_kernel<L, T, 2>), grid, dim3(1 << L), lds, s, a); break;
         default: return LFFN_E_UNSUPPORTED;
@@ -980,6 +985,40 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
     return hrow_lds_bytes(P, n_rounds, lpt, weights && lpt % tau != 0) <= 64 * 1024;
 }
 
+// Tokens of a workgroup of hash_lane_kernel where it takes the batch of `parts` transforms on a chip that holds `fill` workgroups
+// (cus * 1024 / d_pad), else 0.  wmode: 0 codes alone, 1 weights, 2 shares; cross: tables cross into the next projection, which the
+// workgroup they end in then hashes too.
+// Hash alone, three rounds, us, a token to a wave / two tokens a workgroup / four:
+//   d = 700, k = 97, tau = 7, weights: 1 token 6.0 / 4.2 / 4.9, 512 7.9 / 4.9 / 5.4, 1000 8.0 / 6.2 / 5.5, 2000 10.7 / 10.5 / 7.7; codes,
+//   k = 96, tau = 8: 512 6.0 / 4.7 / 5.4, 2000 8.3 / 9.9 / 7.7, 4000 9.9 / 17.6 / 12.8; shares 512 9.4 / 6.0 / 6.9, 2000 14.5 / 13.2 / 11.0
+//   d = 768, k = 170, tau = 9 (two projections), weights: 512 12.7 / 7.9 / 9.2, 1000 12.8 / 9.8 / 9.4, 2000 17.7 / 17.8 / 13.5
+//   d = 512, k = 256, tau = 8 (four), weights: 64 5.7 / 4.2 / 4.7, 512 6.9 / 7.4 / 5.7, 1000 11.7 / 12.9 / 9.1
+// so two tokens to the second fill (to the fourth where tables cross at d_pad = 1024: two rounds, codes, 512 tokens of 768, k = 170, tau = 9
+// 7.6 / 6.9 / 8.0), four to the eighth.  Where it stops before (fills; us a token to a wave / the kernel's better):
+//   weights and shares: d = 128, one projection, 0.5 ... 1.5 4.1 / 4.2, 4.5 / 4.7, two with tables that cross (a chain in
+//   either kernel) 1.3 a pass 9.6 / 10.4, twelve 0.4 5.1 / 5.4 (shares); d = 256 where
+//   tables cross, three projections, two rounds, weights 1536 (4.5) 8.5 / 8.7, shares 10.1 / 11.1, d = 512 shares 1024 (6) 13.1 / 14.8
+//   codes alone, whose transforms of 64 ... 256 cost a wave of its own least: d = 64, one projection, 64 tokens 3.0 / 3.2, 2048 3.2 / 3.5, 8192 4.3 /
+//   4.1, twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 10.6 / 6.7, two rounds 64 3.1 / 3.3, 2048 8.1 / 6.1; d = 128, one 2048 3.5 / 4.1, 16384
+//   6.8 / 6.9, six 256 (0.8) 3.7 / 4.0, 1024 (3) 5.6 / 5.2, 3072 (9) 9.2 / 10.4, tables that cross 1024 6.2 / 6.9; d = 256, one 2048 4.3 /
+//   4.5, two 1536 (3) 6.0 / 5.1, 3072 (6) 6.9 / 7.7, two rounds 2048 (4) 4.7 / 4.9; d = 512, two projections 1024 (4) 6.1 / 5.6, two
+//   rounds 1536 (6) 6.5 / 7.4, tables that cross 64 5.3 / 5.5; d = 1024, one, two rounds 1536 (6) 6.0 / 6.3, two 1024 (8) 6.8 / 7.8
+int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, int64_t parts, int64_t fill)
+{
+    bool takes;
+    if (wmode != 0) {
+        if (N == 128) takes = parts >= (P == 1 || (P == 2 && cross) ? 2 : cross ? 1 : 0) * fill;
+        else takes = !cross || N < 256 || N > (wmode == 1 ? 256 : 512) || parts <= 4 * fill;
+    } else if (N == 64) takes = (int64_t)P * n_rounds >= 9 && 4 * parts >= 3 * fill;
+    else if (N <= 256) takes = P * N > 256 && n_rounds >= 3 && !cross && parts > 2 * fill && parts <= 5 * fill;
+    else if (P == 1) takes = N == 512 || n_rounds >= 3 || parts <= 4 * fill;
+    else if (N == 512 && cross) takes = n_rounds >= 3 && parts <= 2 * fill;
+    else takes = parts <= 4 * fill;
+    if (!takes || parts > 8 * fill) return 0;
+    if (wmode == 0 && N <= 256) return 4;
+    return parts <= (cross && N == 1024 ? 4 : 2) * fill ? 2 : 4;
+}
+
 // few_ok: hash_lane_kernel may take the batch (the forward passes; the stand-alone hash keeps the kernels that give a token to a
 // wave, and so the one can be held against the others).
 int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t n, int d, int k, int tau,
@@ -1011,25 +1050,18 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
     // shares: in the ABI layout, or in the staged gather's from hash_row_kernel alone
     if (out.probes && (!out.weights || (!a.codes && !row_ok))) return LFFN_E_UNSUPPORTED;
     TimedLaunch tl(0, s);
-    // Few tokens: hash_lane_kernel, two or four tokens to a workgroup, while its workgroups fill the chip no more than twice.
-    // Hash alone, three rounds, us, a token to a wave / two tokens a workgroup / four:
-    //   d = 700, k = 97, tau = 7, weights: 1 token 6.0 / 4.2 / 4.9, 512 7.9 / 4.9 / 5.4, 1000 8.0 / 6.2 / 5.5, 2000 10.7 / 10.5 / 7.7; codes,
-    //   k = 96, tau = 8: 512 6.0 / 4.7 / 5.4, 2000 8.3 / 9.9 / 7.7, 4000 9.9 / 17.6 / 12.8; shares 512 9.4 / 6.0 / 6.9, 2000 14.5 / 13.2 / 11.0
-    //   d = 768, k = 170, tau = 9 (two projections), weights: 512 12.7 / 7.9 / 9.2, 1000 12.8 / 9.8 / 9.4, 2000 17.7 / 17.8 / 13.5
-    //   d = 512, k = 256, tau = 8 (four), weights: 64 5.7 / 4.2 / 4.7, 512 6.9 / 7.4 / 5.7, 1000 11.7 / 12.9 / 9.1
-    //   d = 256, k = 96 (three), codes: 64 3.8 / 3.7 / 4.1, 1000 5.3 / 6.0 / 4.8, 2000 7.5 / 9.3 / 6.9, 4000 10.0 / 11.6 / 11.1
-    //   d = 64, k = 96 (twelve), codes: 64 3.0 / 3.1 / 3.3, 1000 6.8 / 5.8 / 4.5, 2000 10.3 / 8.4 / 6.4
     const int64_t parts = n * a.P;  // transforms
     if (few_ok && a.codes && opt.hash_path == 0 && L >= 6 && L <= 10) {
         int cus = 0;
         int rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;
         const int64_t fill = (int64_t)cus * (1024 / N);  // workgroups that the chip holds
-        if (parts <= 8 * fill) {
-            const int tokens = parts <= 2 * fill ? 2 : 4;
+        const int wmode = out.probes ? 2 : out.weights ? 1 : 0;
+        const int tokens = hash_lane_tokens(N, a.P, n_rounds, wmode, a.P > 1 && a.cross, parts, fill);
+        if (tokens) {
             const int64_t groups = (n + tokens - 1) / tokens;
             const unsigned p_groups = a.P > 1 ? split_projections(a.P, a.cross, std::max<int64_t>(1, fill / groups), &a.p_per) : 1u;
-            rc = lffn_host::hash_lane_part(L, tokens, out.probes ? 2 : out.weights ? 1 : 0, a, dim3((unsigned)groups, p_groups), s);
+            rc = lffn_host::hash_lane_part(L, tokens, wmode, a, dim3((unsigned)groups, p_groups), s);
             if (rc != LFFN_OK) return rc;
             LFFN_HIP(hipGetLastError());
             tl.done();
