@@ -1160,14 +1160,19 @@ int64_t lds_tokens_per_block(int64_t n, int n_units, int token_splits, int Bx)
 // Below 64 tables the fill and the hand-over weigh more, an odd one is a launch of its own with codes and weights to turn around
 // (multi-probe 2.5 and 2.75 slots; k = 24, 768 wide, 3200 tokens, tau 8 106 / 91; weighted, k = 97, 4160 tokens of 768 98 / 108), and
 // copies of 64 bytes from row-major tables are half a line: two tokens a row there, as for tau 7.
-int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared)
+// chain: the hash of a staged batch (in the packed layout) takes the projections in a chain where that of a direct one spreads them
+// over workgroups.  BH, d_pad <= 256, four factors, pass, direct / staged: tau 8, k = 96, 768 wide, d = 256, block 64, 4362 tokens 97 / 133,
+// d = 64, block 32, 4865 79 / 97, k = 250, d = 128, block 64, 4309 282 / 330: two tokens a row; tau 9, d = 64, block 32, 3586 108 / 128,
+// 4210 120 / 115, block 64 4411 135 / 142: 3.5 slots; tau 10, d = 64, block 64, k = 96 4307 219 / 273, k = 170 5304 426 / 429, 512 wide, d = 128
+// 6731 116 / 128, k = 80 5215 151 / 168: 4.5 slots.  (d_pad = 512, two projections, block 64, tau 8, 4948 tokens 107 / 100.)
+int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, bool chain)
 {
     const int64_t two_a_row = 8 * (int64_t)rows, slot = kLdsThreads / sw;
-    if (tau == 7 || (sw == 4 && !prepared)) return two_a_row;
+    if (tau == 7 || (sw == 4 && !prepared) || (sw == 8 && chain)) return two_a_row;
     int64_t line = two_a_row;  // in quarters of a slot from here
     const bool small = k < 64 || k % 2;
     if (mode == kProbes) line = (sw == 8 ? (small ? 10 : 7) : (small ? 11 : 9)) * slot;
-    else if (!small) line = (sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? 10 : 13) * slot;
+    else if (!small) line = (sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? (chain ? 14 : 10) : (chain ? 18 : 13)) * slot;
     return std::min(line, two_a_row);
 }
 
@@ -1186,9 +1191,13 @@ struct LdsPlan {
                     // k is odd (the staged kernel takes its tables in pairs), else 0
 };
 
-// hashed: the codes are this library's own, in a forward pass.  A gather of a caller's codes turns them around first and takes
-// scratch memory for it, which between the two lines it did without: it keeps two tokens a row.
-int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mode mode, bool hashed, const Options &opt,
+// Whose codes a gather sums by: a caller's, or this library's own in a forward pass, from a hash that is the same for a direct
+// and a staged gather or whose projections only the direct one spreads over workgroups (staged_from's chain).  A gather of a
+// caller's codes turns them around first and takes scratch memory for it, which between the lines it did without: it
+// keeps two tokens a row.
+enum class Codes { kCallers, kHashed, kHashedInChain };
+
+int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mode mode, Codes codes, const Options &opt,
                     LdsPlan *p)
 {
     p->use = false;
@@ -1246,7 +1255,7 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
-    if (opt.gather_path < 2 && chunk * 4 < (hashed ? staged_from(mode, k, tau, sw, rows, T.prepared) : 8 * (int64_t)rows)) return LFFN_OK;
+    if (opt.gather_path < 2 && chunk * 4 < (codes == Codes::kCallers ? 8 * (int64_t)rows : staged_from(mode, k, tau, sw, rows, T.prepared, codes == Codes::kHashedInChain))) return LFFN_OK;
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
     auto slots_of = [&](int64_t tokens) {
         const int tok = (int)((tokens + groups - 1) / groups);
@@ -1603,7 +1612,7 @@ int gather_from_abi(Mode mode, const uint16_t *codes, const float *weights, cons
         for (int64_t t = 0; t < n; t += m) {
             const int64_t len = std::min(m, n - t);
             LdsPlan piece;
-            int rc = plan_gather_lds(len, k, tau, d_out, T, mode, true, opt, &piece);
+            int rc = plan_gather_lds(len, k, tau, d_out, T, mode, Codes::kHashed, opt, &piece);
             if (rc != LFFN_OK) return rc;
             Scratch scratch = *sc;
             rc = gather_from_abi(mode, codes + t * k, weights + t * k * (1 + tau), T,
@@ -1722,6 +1731,19 @@ double bh_lane_most(int N, int P, bool cross, int block, int n_factors)
     return N == 64 && bytes <= 256 ? std::max(most, 2.0) : most;
 }
 
+// Workgroups to the tokens of bh_hash_kernel's grid, and whether it spreads their projections over others with codes in the ABI layout
+int64_t bh_token_blocks(int64_t n, int L)
+{
+    const int wpg = L == 10 ? 4 : L == 9 ? 2 : 1;  // waves that share a token group
+    const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
+    return (n + per_block - 1) / per_block;
+}
+bool bh_spreads(int64_t n, int d, int k, int tau, int cus)
+{
+    const int L = log2_pad(d);
+    return (int64_t)k * tau > (int64_t(1) << L) && 2 * bh_token_blocks(n, L) <= cus;
+}
+
 // Hashes with the packed factors `apack`; `pack_from` != NULL: re-order them from there first.  few_ok: bh_lane_kernel may take
 // the batch (the forward passes; the stand-alone hash keeps bh_hash_kernel, and so the one can be held against the other).
 int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in, float *apack_scratch,
@@ -1771,9 +1793,7 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
         return LFFN_OK;
     }
     const int wmode = !out.weights ? 0 : bh_weights_in_registers(tau) ? 1 : 2;
-    const int wpg = L == 10 ? 4 : L == 9 ? 2 : 1;  // waves that share a token group
-    const int64_t per_block = (int64_t)(kBhWaves / wpg) * kBhTok;
-    const int64_t blocks = (n + per_block - 1) / per_block;
+    const int64_t blocks = bh_token_blocks(n, L);
     dim3 grid = grid_of(blocks);  // a workgroup past the batch does a full hash of no token
     const bool deep_ok = block == 64 && L == 10;
     // as many workgroups to the projections as find a compute unit each (2 tokens: d = 64, block 32, 20 projections pass
@@ -1986,8 +2006,15 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
     rc = get_scratch(workspace, workspace_bytes, need, &sc);
     if (rc != LFFN_OK) return rc;
     const TableRef T = table_ref(tables, table_dtype, tau);
+    Codes codes = Codes::kHashed;
+    if (h.bh() && d <= 256) {
+        int cus = 0;
+        rc = device_cus(&cus);
+        if (rc != LFFN_OK) return rc;
+        if (bh_spreads(n, d, k, tau, cus)) codes = Codes::kHashedInChain;
+    }
     LdsPlan plan;
-    rc = plan_gather_lds(n, k, tau, d_out, T, mode, true, opt, &plan);
+    rc = plan_gather_lds(n, k, tau, d_out, T, mode, codes, opt, &plan);
     if (rc != LFFN_OK) return rc;
     float *apack = (h.bh() && !h.bh_prepared) ? sc.take<float>(bh_pack_bytes(d, k, tau, h.block, h.n_factors)) : nullptr;
     if (h.bh() && !h.bh_prepared && !apack) return LFFN_E_WORKSPACE;
@@ -2043,7 +2070,7 @@ int gather_core(Mode mode, const uint16_t *codes, const float *weights, const vo
     const Options opt = options_snapshot();
     const TableRef T = table_ref(tables, table_dtype, tau);
     LdsPlan plan;
-    rc = plan_gather_lds(n, k, tau, d_out, T, mode, false, opt, &plan);
+    rc = plan_gather_lds(n, k, tau, d_out, T, mode, Codes::kCallers, opt, &plan);
     if (rc != LFFN_OK) return rc;
     RingPlan ring;
     rc = plan_gather_ring(n, k, tau, d_out, T, mode, opt, &ring);

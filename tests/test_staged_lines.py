@@ -35,3 +35,19 @@ def test_line_of_a_callers_codes(tmp_path, mode, n, staged):
     """Codes of the caller's: two tokens a row, and no scratch memory below that."""
     launches = R.record(R.build(tmp_path), [R.gather(mode, n, 96, 8, 768, PREPARED)])[0]
     assert [launch.kernel for launch in launches][-1] == ("gather_lds_kernel" if staged else "gather_kernel")
+
+
+# A BH hash of several projections, which a direct gather's codes have spread over workgroups: as far as that holds its lines are
+# others (one projection, rows of 512 and wider, and batches that fill the chip with tokens keep those above)
+@pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
+@pytest.mark.parametrize("weighted,d,k,tau,d_out,line", [
+    (False, 256, 96, 8, 768, 5111), (True, 64, 96, 8, 768, 5111), (True, 512, 128, 8, 768, 4151), (False, 512, 96, 8, 768, 4791),
+    (False, 64, 170, 9, 768, 4476), (True, 200, 170, 9, 768, 4476), (True, 512, 170, 9, 768, 3196), (True, 128, 128, 10, 1024, 4605), (True, 512, 128, 10, 768, 4156),
+    (True, 768, 96, 8, 768, 4151), (False, 64, 64, 8, 128, 30657), (True, 64, 64, 8, 128, 26561)])
+def test_line_of_bh_codes(tmp_path, weighted, d, k, tau, d_out, line):
+    lib = R.build(tmp_path)
+    for n in (line - 1, line):
+        call = ["lookupffn_forward_bh" + ("_weighted" if weighted else ""), R.FAKE, R.FAKE, R.FAKE, R.FAKE, n, d, k, tau, d_out, PREPARED | 16, 4, 0,
+                PREPARED, R.FAKE, 1 << 40, None]
+        kernels = [launch.kernel for launch in R.record(lib, [call])[0]]
+        assert ("gather_lds_kernel" in kernels) == (n == line), (n, kernels)
