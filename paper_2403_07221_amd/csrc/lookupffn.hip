@@ -1149,6 +1149,12 @@ int64_t lds_tokens_per_block(int64_t n, int n_units, int token_splits, int Bx)
     return (unit_tokens + blocks - 1) / blocks;
 }
 
+// Whose codes a gather sums by, and in which layout they are before a staged one: a caller's, or this library's own in a forward
+// pass, which the hash leaves in the ABI layout (kTurned: two passes turn them around) or writes packed (kPackedInChain: where
+// the hash of a direct gather has its projections spread over workgroups).  A gather of a caller's codes takes scratch memory
+// to turn them around, which between the lines it did without: it keeps two tokens a row.
+enum class Codes { kCallers, kTurned, kPacked, kPackedInChain };
+
 // Four times the tokens a chunk has to have for staging to pay.  A stage costs its copies and at least its fewest slots' row
 // reads however few the tokens; the direct kernel costs by the row.  Lines in token slots (kLdsThreads / sw tokens each), where
 // the slowest of the shapes measured (k 64 ... 250, 64 ... 1024 wide, prepared and not) draws level; direct / staged, us:
@@ -1160,18 +1166,27 @@ int64_t lds_tokens_per_block(int64_t n, int n_units, int token_splits, int Bx)
 // Below 64 tables the fill and the hand-over weigh more, an odd one is a launch of its own with codes and weights to turn around
 // (multi-probe 2.5 and 2.75 slots; k = 24, 768 wide, 3200 tokens, tau 8 106 / 91; weighted, k = 97, 4160 tokens of 768 98 / 108), and
 // copies of 64 bytes from row-major tables are half a line: two tokens a row there, as for tau 7.
-// chain: the hash of a staged batch (in the packed layout) takes the projections in a chain where that of a direct one spreads them
+// A few tables' codes and shares that are turned around between the two kernels (all but hash_row_kernel's) cost as much as they
+// save.  Multi-probe, below ten tables, tau 8 and 9: two tokens a row (tau 9, 768 wide, k = 4 3830 tokens 31 / 46, k = 7 4617 68 / 83, k = 8 3899
+// 54 / 64, tau 8, 512 wide 0.9 : 1; k = 10 1 : 1 at the line above); below six, tau 10: 4.5 slots (k = 2 0.83 : 1 at 2.8, 1 : 1 at 4.6); an odd
+// number below twelve: 3.5 (tau 10, k = 7 0.87 : 1 at 2.9, 1 : 1 at 3.5, tau 9, k = 11 0.83 : 1 and 1 : 1).  What hash_row_kernel writes: 1.1 ... 2 : 1
+// from the line above on for k = 2 ... 10.
+// In a chain: the hash of a staged batch (in the packed layout) takes the projections in a chain where that of a direct one spreads them
 // over workgroups.  BH, d_pad <= 256, four factors, pass, direct / staged: tau 8, k = 96, 768 wide, d = 256, block 64, 4362 tokens 97 / 133,
 // d = 64, block 32, 4865 79 / 97, k = 250, d = 128, block 64, 4309 282 / 330: two tokens a row; tau 9, d = 64, block 32, 3586 108 / 128,
 // 4210 120 / 115, block 64 4411 135 / 142: 3.5 slots; tau 10, d = 64, block 64, k = 96 4307 219 / 273, k = 170 5304 426 / 429, 512 wide, d = 128
 // 6731 116 / 128, k = 80 5215 151 / 168: 4.5 slots.  (d_pad = 512, two projections, block 64, tau 8, 4948 tokens 107 / 100.)
-int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, bool chain)
+int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, Codes codes)
 {
     const int64_t two_a_row = 8 * (int64_t)rows, slot = kLdsThreads / sw;
-    if (tau == 7 || (sw == 4 && !prepared) || (sw == 8 && chain)) return two_a_row;
+    if (tau == 7 || (sw == 4 && !prepared)) return two_a_row;
+    if (codes == Codes::kPackedInChain && sw == 8) return two_a_row;
+    if (codes == Codes::kTurned && tau <= 9 && k < 10) return two_a_row;
     int64_t line = two_a_row;  // in quarters of a slot from here
     const bool small = k < 64 || k % 2;
-    if (mode == kProbes) line = (sw == 8 ? (small ? 10 : 7) : (small ? 11 : 9)) * slot;
+    const bool chain = codes == Codes::kPackedInChain, turned = codes == Codes::kTurned;
+    if (mode == kProbes && turned && k < 12 && (k < 6 || k % 2)) line = (k < 6 ? 18 : 14) * slot;
+    else if (mode == kProbes) line = (sw == 8 ? (small ? 10 : 7) : (small ? 11 : 9)) * slot;
     else if (!small) line = (sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? (chain ? 14 : 10) : (chain ? 18 : 13)) * slot;
     return std::min(line, two_a_row);
 }
@@ -1190,12 +1205,6 @@ struct LdsPlan {
     int tail = 0;   // tables left to the direct kernel, which adds them onto the staged kernel's y: 1 when
                     // k is odd (the staged kernel takes its tables in pairs), else 0
 };
-
-// Whose codes a gather sums by: a caller's, or this library's own in a forward pass, from a hash that is the same for a direct
-// and a staged gather or whose projections only the direct one spreads over workgroups (staged_from's chain).  A gather of a
-// caller's codes turns them around first and takes scratch memory for it, which between the lines it did without: it
-// keeps two tokens a row.
-enum class Codes { kCallers, kHashed, kHashedInChain };
 
 int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mode mode, Codes codes, const Options &opt,
                     LdsPlan *p)
@@ -1255,7 +1264,7 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
-    if (opt.gather_path < 2 && chunk * 4 < (codes == Codes::kCallers ? 8 * (int64_t)rows : staged_from(mode, k, tau, sw, rows, T.prepared, codes == Codes::kHashedInChain))) return LFFN_OK;
+    if (opt.gather_path < 2 && chunk * 4 < (codes == Codes::kCallers ? 8 * (int64_t)rows : staged_from(mode, k, tau, sw, rows, T.prepared, codes))) return LFFN_OK;
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
     auto slots_of = [&](int64_t tokens) {
         const int tok = (int)((tokens + groups - 1) / groups);
@@ -1612,7 +1621,7 @@ int gather_from_abi(Mode mode, const uint16_t *codes, const float *weights, cons
         for (int64_t t = 0; t < n; t += m) {
             const int64_t len = std::min(m, n - t);
             LdsPlan piece;
-            int rc = plan_gather_lds(len, k, tau, d_out, T, mode, Codes::kHashed, opt, &piece);
+            int rc = plan_gather_lds(len, k, tau, d_out, T, mode, Codes::kTurned, opt, &piece);
             if (rc != LFFN_OK) return rc;
             Scratch scratch = *sc;
             rc = gather_from_abi(mode, codes + t * k, weights + t * k * (1 + tau), T,
@@ -2006,12 +2015,14 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
     rc = get_scratch(workspace, workspace_bytes, need, &sc);
     if (rc != LFFN_OK) return rc;
     const TableRef T = table_ref(tables, table_dtype, tau);
-    Codes codes = Codes::kHashed;
-    if (h.bh() && d <= 256) {
+    // a batch that goes in pieces is cut from the ABI layout
+    const bool row_shares = mode == kProbes && n <= kProbesPiece && hash_row_ok(h.signs, true, true, true, n, d, k, tau, h.n_rounds, opt);
+    Codes codes = k % 2 || (mode == kProbes && !row_shares) ? Codes::kTurned : Codes::kPacked;
+    if (h.bh() && d <= 256 && codes == Codes::kPacked) {
         int cus = 0;
         rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;
-        if (bh_spreads(n, d, k, tau, cus)) codes = Codes::kHashedInChain;
+        if (bh_spreads(n, d, k, tau, cus)) codes = Codes::kPackedInChain;
     }
     LdsPlan plan;
     rc = plan_gather_lds(n, k, tau, d_out, T, mode, codes, opt, &plan);
@@ -2025,12 +2036,11 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
         return launch_hash(x, h.signs, out, n, d, k, tau, h.n_rounds, x_dtype, true, s, opt);
     };
     // the hash kernels write the staged gather's layout themselves, scaled for its row pieces; multi-probe shares only
-    // hash_row_kernel does, and a batch that goes in pieces is cut from the ABI layout
+    // hash_row_kernel does
     RingPlan ring;
     rc = plan_gather_ring(n, k, tau, d_out, T, mode, opt, &ring);
     if (rc != LFFN_OK) return rc;
-    if (!ring.use && plan.use && !plan.tail &&
-        (mode != kProbes || (n <= kProbesPiece && hash_row_ok(h.signs, true, true, true, n, d, k, tau, h.n_rounds, opt)))) {
+    if (!ring.use && plan.use && !plan.tail && (mode != kProbes || row_shares)) {
         HashOut out;
         out.shift = plan.shift;
         out.probes = mode == kProbes;
