@@ -324,7 +324,7 @@ const char *lookupffn_last_hip_error(void);
 /* Which gather kernel the calling thread's most recent gather launch used: "gather_kernel" (direct, rows
  * fetched through L2), "gather_lds_kernel" (table slices staged in LDS, double-buffered),
  * "forward_stack_kernel" or "forward_small_kernel" (hash and gather of a few tokens in one launch, d of 513 .. 1024 and of
- * 33 .. 512), "gather_ring_kernel" (on request: prepared tables of up to 256 rows, plain sum; slices staged in an LDS ring,
+ * 33 .. 512), "forward_narrow_kernel" (lookupffn_forward_stack of one layer of rows up to 2 KB and many tokens), "gather_ring_kernel" (on request: prepared tables of up to 256 rows, plain sum; slices staged in an LDS ring,
  * token groups lagged so that their reads never meet in a bank); "" before the first launch. */
 const char *lookupffn_last_gather_kernel(void);
 /* The same for the sign-diagonal hash: "hash_row_kernel" (d_pad = 1024 or 512, a token per row of 16 or 8

@@ -16,6 +16,7 @@
 
 #include "bh_hash_kernel.hpp"
 #include "bh_lane_kernel.hpp"
+#include "forward_narrow_kernel.hpp"
 #include "forward_small_kernel.hpp"
 #include "forward_stack_kernel.hpp"
 #include "gather_kernel.hpp"
@@ -57,6 +58,7 @@ int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3
 int gather_ring_part(int threads, int tok, const GatherRingArgs &a, dim3 grid, hipStream_t s);
 // part 8: hash and gather of a few tokens, one or several chained layers, in one launch
 int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int tokens, size_t lds, hipStream_t s);
+int forward_narrow_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
 int forward_small_part(int L, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
 int forward_stack_load();
 // parts 9, 10: the hash with a token per row of lanes, d_pad = 1024 (four tokens per wavefront) and 512 (eight)
@@ -359,6 +361,30 @@ int launch_forward_stack_t(int n_rounds, int kind, const StackArgs &a, dim3 grid
 int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int tokens, size_t lds, hipStream_t s)
 {
     return tokens == 2 ? launch_forward_stack_t<2>(n_rounds, kind, a, grid, lds, s) : launch_forward_stack_t<1>(n_rounds, kind, a, grid, lds, s);
+}
+
+template <int R>
+int launch_forward_narrow_r(int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s)
+{
+    switch (kind) {
+        case kElemF32: hipLaunchKernelGGL((forward_narrow_kernel<R, kElemF32>), grid, dim3(threads), lds, s, a); break;
+        case kElemBF16: hipLaunchKernelGGL((forward_narrow_kernel<R, kElemBF16>), grid, dim3(threads), lds, s, a); break;
+        case kElemF16: hipLaunchKernelGGL((forward_narrow_kernel<R, kElemF16>), grid, dim3(threads), lds, s, a); break;
+        default: return LFFN_E_DTYPE;
+    }
+    return LFFN_OK;
+}
+
+int forward_narrow_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s)
+{
+    if (threads < 64 || threads > kNarrowDwords || threads % 64) return LFFN_E_UNSUPPORTED;
+    switch (n_rounds) {
+        case 1: return launch_forward_narrow_r<1>(kind, a, grid, threads, lds, s);
+        case 2: return launch_forward_narrow_r<2>(kind, a, grid, threads, lds, s);
+        case 3: return launch_forward_narrow_r<3>(kind, a, grid, threads, lds, s);
+        case 4: return launch_forward_narrow_r<4>(kind, a, grid, threads, lds, s);
+    }
+    return LFFN_E_UNSUPPORTED;
 }
 
 template <int L>
@@ -1948,13 +1974,19 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
     // forward_small_kernel is the call's hash and its gather, and counts as each with its whole duration
     TimedLaunch th(0, s, L != 10), tl(1, s);
     int rc;
+    bool narrow = false;
     if (L == 10) {
-        // two tokens to a workgroup where there are more tokens than compute units (and the LDS is what every kernel may use)
+        // One layer of rows up to 2 KB, more tokens than forward_stack_kernel takes in one round of two to a compute unit: forward_narrow_kernel.
+        // That kernel / this, 500 shapes of 513 ... 16384 tokens: 64 ... 256 dwords 1.97 ... 1.42 : 1 (0.97 ... 3.9), 320 1.23 : 1 (0.98 ... 1.67), 512
+        // 1.16 : 1 (0.91 ... 1.5), 640 1.0 : 1 (0.82 ... 1.3).
+        // Else two tokens to a workgroup where there are more tokens than compute units (and the LDS is what every kernel may use).
         int cus = 0;
         rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;
         const int tokens = n > cus && stack_lds_bytes(k, 2) <= 64 * 1024 ? 2 : 1;
-        rc = lffn_host::forward_stack_part(n_rounds, T.kind, a, grid_of((n + tokens - 1) / tokens), tokens, stack_lds_bytes(k, tokens), s);
+        if ((narrow = n_layers == 1 && n > 2 * (int64_t)cus && a.row_dwords <= kNarrowDwords))
+            rc = lffn_host::forward_narrow_part(n_rounds, T.kind, a, grid_of(n), (int)((a.row_dwords + 63) / 64 * 64), narrow_lds_bytes(a.P, k), s);
+        else rc = lffn_host::forward_stack_part(n_rounds, T.kind, a, grid_of((n + tokens - 1) / tokens), tokens, stack_lds_bytes(k, tokens), s);
     } else {
         int threads = (int)((a.row_dwords + 63) / 64 * 64);
         if (threads > 1024) threads = 1024;
@@ -1965,7 +1997,7 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
     LFFN_HIP(hipGetLastError());
     tl.done();
     th.done();
-    t_last_gather = t_last_hash = L == 10 ? "forward_stack_kernel" : "forward_small_kernel";
+    t_last_gather = t_last_hash = narrow ? "forward_narrow_kernel" : L == 10 ? "forward_stack_kernel" : "forward_small_kernel";
     return LFFN_OK;
 }
 
