@@ -28,6 +28,10 @@ ONE_LAUNCH = ("forward_small_kernel", "forward_stack_kernel")
     (128, 64, 64, "bf16", "f32", 0, False),     # same number of columns, other types
     (100, 1024, 1024, "f32", "f32", 0, True),   # the d_pad = 1024 kernel
     (100, 1024, 512, "f32", "f32", 0, False),
+    (257, 1024, 1024, "f32", "f32", 0, True),   # two tokens to a workgroup, the last one alone
+    (512, 1024, 1024, "f32", "f32", 0, True),
+    (511, 1024, 512, "f16", "f32", 0, True),    # rows of one length in bytes
+    (257, 1024, 1024, "f32", "f32", 4096, False),
 ])
 def test_forward_over_its_own_input(n, d, d_out, xdt, ydt, shift, one):
     print(f"overlap n={n} d={d} d_out={d_out} {xdt} -> {ydt} y at x{shift:+d}", flush=True)
