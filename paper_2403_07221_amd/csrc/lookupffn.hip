@@ -1021,11 +1021,13 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
 //   d = 512, k = 256, tau = 8 (four), weights: 64 5.7 / 4.2 / 4.7, 512 6.9 / 7.4 / 5.7, 1000 11.7 / 12.9 / 9.1
 // so two tokens to the second fill (to the fourth where tables cross at d_pad = 1024: two rounds, codes, 512 tokens of 768, k = 170, tau = 9
 // 7.6 / 6.9 / 8.0), four to the eighth.  Where it stops before (fills; us a token to a wave / the kernel's better):
-//   weights and shares: d = 128, one projection, 0.5 ... 1.5 4.1 / 4.2, 4.5 / 4.7, two with tables that cross (a chain in
-//   either kernel) 1.3 a pass 9.6 / 10.4, twelve 0.4 5.1 / 5.4 (shares); d = 256 where
+//   weights and shares: d = 128, one projection, 0.5 ... 1.5 4.1 / 4.2, 4.5 / 4.7, twelve with tables that cross 0.4 5.1 / 5.4 (shares); two
+//   with tables that cross, a chain in either kernel, us longer than a token to a wave: d = 64 weights 0.5 ... 1 0.2, up to 1.4 (2 and up 1 shorter, 0
+//   ... 0.25 0.6), shares 0.25 ... 1 0.4 ... 0.8, up to 2.1, d = 128 2 ... 4 0.6 and 1.4 (5 and up 0.2 ... 2 shorter), d = 256 shares 0.4; d = 256 where
 //   tables cross, three projections, two rounds, weights 1536 (4.5) 8.5 / 8.7, shares 10.1 / 11.1, d = 512 shares 1024 (6) 13.1 / 14.8
 //   codes alone, whose transforms of 64 ... 256 cost a wave of its own least: d = 64, one projection, 64 tokens 3.0 / 3.2, 2048 3.2 / 3.5, 8192 4.3 /
-//   4.1, twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 10.6 / 6.7, two rounds 64 3.1 / 3.3, 2048 8.1 / 6.1; d = 128, one 2048 3.5 / 4.1, 16384
+//   4.1, twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 10.6 / 6.7, two rounds 64 3.1 / 3.3, 2048 8.1 / 6.1,
+//   four with tables that cross 4659 (4.6) a pass 10.3 / 11.8; d = 128, one 2048 3.5 / 4.1, 16384
 //   6.8 / 6.9, six 256 (0.8) 3.7 / 4.0, 1024 (3) 5.6 / 5.2, 3072 (9) 9.2 / 10.4, tables that cross 1024 6.2 / 6.9; d = 256, one 2048 4.3 /
 //   4.5, two 1536 (3) 6.0 / 5.1, 3072 (6) 6.9 / 7.7, two rounds 2048 (4) 4.7 / 4.9; d = 512, two projections 1024 (4) 6.1 / 5.6, two
 //   rounds 1536 (6) 6.5 / 7.4, tables that cross 64 5.3 / 5.5; d = 1024, one, two rounds 1536 (6) 6.0 / 6.3, two 1024 (8) 6.8 / 7.8
@@ -1033,9 +1035,11 @@ int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, int64_t 
 {
     bool takes;
     if (wmode != 0) {
-        if (N == 128) takes = parts >= (P == 1 || (P == 2 && cross) ? 2 : cross ? 1 : 0) * fill;
+        if (P == 2 && cross && N <= 256 && (N < 256 || wmode == 2))
+            takes = N < 256 && (parts >= (N == 64 ? 2 : 5) * fill || (N == 64 && wmode == 1 && 4 * parts <= fill));
+        else if (N == 128) takes = parts >= (P == 1 ? 2 : cross ? 1 : 0) * fill;
         else takes = !cross || N < 256 || N > (wmode == 1 ? 256 : 512) || parts <= 4 * fill;
-    } else if (N == 64) takes = (int64_t)P * n_rounds >= 9 && 4 * parts >= 3 * fill;
+    } else if (N == 64) takes = (cross ? P >= 8 : (int64_t)P * n_rounds >= 9) && 4 * parts >= 3 * fill;
     else if (N <= 256) takes = P * N > 256 && n_rounds >= 3 && !cross && parts > 2 * fill && parts <= 5 * fill;
     else if (P == 1) takes = N == 512 || n_rounds >= 3 || parts <= 4 * fill;
     else if (N == 512 && cross) takes = n_rounds >= 3 && parts <= 2 * fill;

@@ -14,7 +14,7 @@ if torch.cuda.is_available():
 
 CASES = [  # n, d, k, tau, rounds, x dtype, forward passes that take the kernel: plain, weighted, probes
     (1, 64, 8, 8, 2, "float32", "wp"), (3, 33, 90, 9, 3, "bfloat16", "wp"), (2049, 64, 8, 8, 1, "float32", "wp"), (5, 100, 33, 7, 3, "float16", ""),
-    (17, 128, 40, 4, 5, "float32", "wp"), (16, 200, 96, 8, 3, "float32", "wp"), (683, 256, 96, 8, 3, "float32", "cwp"), (15, 255, 37, 13, 4, "bfloat16", "wp"),
+    (17, 128, 40, 4, 5, "float32", "wp"), (16, 200, 96, 8, 3, "float32", "wp"), (683, 256, 96, 8, 3, "float32", "cwp"), (15, 255, 37, 13, 4, "bfloat16", "w"),
     (47, 511, 133, 9, 3, "float16", "cwp"), (31, 512, 256, 8, 3, "float32", "cwp"), (1, 513, 96, 8, 3, "float32", "cwp"), (1001, 700, 97, 7, 3, "float16", "cwp"),
     (513, 768, 96, 8, 3, "float32", "cwp"), (512, 768, 170, 9, 2, "float32", "cwp"), (6, 1024, 171, 12, 1, "float32", "cwp"), (7, 1000, 300, 11, 3, "float32", "cwp"),
     (2048, 1023, 64, 16, 3, "float32", "cwp"),
@@ -78,7 +78,9 @@ def test_route(tmp_path, mode, n, d, k, tau, tokens, groups):
     ("plain", 2047, 768, 96, 8, 3, 4), ("plain", 513, 768, 170, 9, 3, 0), ("plain", 512, 768, 170, 9, 2, 2),
     ("weighted", 512, 768, 170, 9, 2, 2), ("weighted", 513, 768, 170, 9, 2, 4), ("weighted", 512, 768, 256, 8, 2, 4),
     ("weighted", 4095, 128, 8, 8, 3, 0), ("weighted", 4096, 128, 8, 8, 3, 2), ("weighted", 4097, 128, 8, 8, 3, 4), ("probes", 341, 128, 97, 7, 3, 0),
-    ("probes", 342, 128, 97, 7, 3, 2), ("weighted", 2047, 128, 24, 9, 2, 0), ("weighted", 2049, 128, 24, 9, 2, 4), ("weighted", 1, 128, 64, 8, 3, 2), ("weighted", 1365, 256, 97, 7, 3, 4), ("weighted", 1366, 256, 97, 7, 3, 0),
+    ("probes", 342, 128, 97, 7, 3, 2), ("weighted", 5119, 128, 24, 9, 2, 0), ("weighted", 5120, 128, 24, 9, 2, 4), ("plain", 4659, 64, 24, 9, 3, 0), ("plain", 1024, 64, 56, 9, 3, 4),
+    ("probes", 4095, 64, 8, 10, 3, 0), ("probes", 4096, 64, 8, 10, 3, 2), ("weighted", 512, 64, 8, 10, 3, 2), ("weighted", 513, 64, 8, 10, 3, 0),
+    ("probes", 60, 256, 40, 9, 3, 0), ("weighted", 60, 256, 40, 9, 3, 2), ("weighted", 1, 128, 64, 8, 3, 2), ("weighted", 1365, 256, 97, 7, 3, 4), ("weighted", 1366, 256, 97, 7, 3, 0),
     ("probes", 1366, 256, 96, 8, 3, 4), ("probes", 682, 512, 170, 9, 3, 4), ("probes", 683, 512, 170, 9, 3, 0), ("weighted", 683, 512, 170, 9, 3, 4)])
 def test_lines(tmp_path, mode, n, d, k, tau, rounds, tokens):
     name = "lookupffn_forward" + ("" if mode == "plain" else "_" + mode)
