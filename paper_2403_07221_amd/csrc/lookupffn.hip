@@ -1198,7 +1198,8 @@ enum class Codes { kCallers, kTurned, kPacked, kPackedInChain };
 // copies of 64 bytes from row-major tables are half a line: two tokens a row there, as for tau 7.
 // A few tables' codes and shares that are turned around between the two kernels (all but hash_row_kernel's) cost as much as they
 // save.  Multi-probe, below ten tables, tau 8 and 9: two tokens a row (tau 9, 768 wide, k = 4 3830 tokens 31 / 46, k = 7 4617 68 / 83, k = 8 3899
-// 54 / 64, tau 8, 512 wide 0.9 : 1; k = 10 1 : 1 at the line above); below six, tau 10: 4.5 slots (k = 2 0.83 : 1 at 2.8, 1 : 1 at 4.6); an odd
+// 54 / 64, tau 8, 512 wide 0.9 : 1; tau 9, k = 10 1 : 1 at the line above); below sixteen, tau 8: 3 slots (k = 12, 768
+// wide, 3311 51 / 55, k = 10 0.94 : 1 at 2.6, 1 : 1 at 3); below six, tau 10: 4.5 slots (k = 2 0.83 : 1 at 2.8, 1 : 1 at 4.6); an odd
 // number below twelve: 3.5 (tau 10, k = 7 0.87 : 1 at 2.9, 1 : 1 at 3.5, tau 9, k = 11 0.83 : 1 and 1 : 1).  What hash_row_kernel writes: 1.1 ... 2 : 1
 // from the line above on for k = 2 ... 10.
 // In a chain: the hash of a staged batch (in the packed layout) takes the projections in a chain where that of a direct one spreads them
@@ -1216,7 +1217,7 @@ int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, 
     const bool small = k < 64 || k % 2;
     const bool chain = codes == Codes::kPackedInChain, turned = codes == Codes::kTurned;
     if (mode == kProbes && turned && k < 12 && (k < 6 || k % 2)) line = (k < 6 ? 18 : 14) * slot;
-    else if (mode == kProbes) line = (sw == 8 ? (small ? 10 : 7) : (small ? 11 : 9)) * slot;
+    else if (mode == kProbes) line = (sw == 8 ? (turned && k < 16 ? 12 : small ? 10 : 7) : (small ? 11 : 9)) * slot;
     else if (!small) line = (sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? (chain ? 14 : 10) : (chain ? 18 : 13)) * slot;
     return std::min(line, two_a_row);
 }

@@ -56,8 +56,8 @@ def test_line_of_bh_codes(tmp_path, weighted, d, k, tau, d_out, line):
 # Multi-probe with a few tables: what is turned around between the kernels (odd numbers, and all but what hash_row_kernel writes) has later lines
 @pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
 @pytest.mark.parametrize("d,k,tau,d_out,line", [
-    (768, 8, 8, 768, 3191), (760, 8, 8, 768, 5111), (256, 8, 8, 768, 5111), (256, 10, 8, 768, 3191), (768, 9, 8, 768, 5111), (768, 11, 8, 768, 4471),
-    (768, 13, 8, 768, 3191), (768, 8, 9, 768, 5116), (768, 10, 9, 768, 3516), (768, 11, 9, 768, 4476), (768, 13, 9, 768, 3516), (768, 4, 10, 512, 9209),
+    (768, 8, 8, 768, 3191), (760, 8, 8, 768, 5111), (256, 8, 8, 768, 5111), (256, 10, 8, 768, 3831), (256, 14, 8, 768, 3831), (256, 16, 8, 768, 3191), (768, 9, 8, 768, 5111), (768, 11, 8, 768, 4471),
+    (768, 13, 8, 768, 3831), (768, 17, 8, 768, 3191), (768, 12, 8, 768, 3191), (768, 8, 9, 768, 5116), (768, 10, 9, 768, 3516), (768, 11, 9, 768, 4476), (768, 13, 9, 768, 3516), (768, 4, 10, 512, 9209),
     (768, 6, 10, 512, 5625), (768, 7, 10, 512, 7161), (768, 12, 10, 512, 5625), (768, 13, 10, 512, 5625)])
 def test_line_of_few_tables(tmp_path, d, k, tau, d_out, line):
     lib = R.build(tmp_path)
