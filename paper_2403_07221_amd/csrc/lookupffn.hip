@@ -1013,7 +1013,7 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
 
 // Tokens of a workgroup of hash_lane_kernel where it takes the batch of `parts` transforms on a chip that holds `fill` workgroups
 // (cus * 1024 / d_pad), else 0.  wmode: 0 codes alone, 1 weights, 2 shares; cross: tables cross into the next projection, which the
-// workgroup they end in then hashes too.
+// workgroup they end in then hashes too; odd_row: hash1024_kernel loads the rows element by element.
 // Hash alone, three rounds, us, a token to a wave / two tokens a workgroup / four:
 //   d = 700, k = 97, tau = 7, weights: 1 token 6.0 / 4.2 / 4.9, 512 7.9 / 4.9 / 5.4, 1000 8.0 / 6.2 / 5.5, 2000 10.7 / 10.5 / 7.7; codes,
 //   k = 96, tau = 8: 512 6.0 / 4.7 / 5.4, 2000 8.3 / 9.9 / 7.7, 4000 9.9 / 17.6 / 12.8; shares 512 9.4 / 6.0 / 6.9, 2000 14.5 / 13.2 / 11.0
@@ -1030,8 +1030,9 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
 //   four with tables that cross 4659 (4.6) a pass 10.3 / 11.8; d = 128, one 2048 3.5 / 4.1, 16384
 //   6.8 / 6.9, six 256 (0.8) 3.7 / 4.0, 1024 (3) 5.6 / 5.2, 3072 (9) 9.2 / 10.4, tables that cross 1024 6.2 / 6.9; d = 256, one 2048 4.3 /
 //   4.5, two 1536 (3) 6.0 / 5.1, 3072 (6) 6.9 / 7.7, two rounds 2048 (4) 4.7 / 4.9; d = 512, two projections 1024 (4) 6.1 / 5.6, two
-//   rounds 1536 (6) 6.5 / 7.4, tables that cross 64 5.3 / 5.5; d = 1024, one, two rounds 1536 (6) 6.0 / 6.3, two 1024 (8) 6.8 / 7.8
-int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, int64_t parts, int64_t fill)
+//   rounds 1536 (6) 6.5 / 7.4, tables that cross 64 5.3 / 5.5; d_pad = 1024 from 4 to 8, a pass 8 wide: one, two rounds 0.96 : 1, three
+//   1.02 : 1, two 0.96 : 1, with tables that cross 0.98 and 1.01 : 1, three 1.0 ... 1.5 : 1, rows of no multiple of four 1.0 ... 1.2 : 1 in all of these
+int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, bool odd_row, int64_t parts, int64_t fill)
 {
     bool takes;
     if (wmode != 0) {
@@ -1041,9 +1042,8 @@ int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, int64_t 
         else takes = !cross || N < 256 || N > (wmode == 1 ? 256 : 512) || parts <= 4 * fill;
     } else if (N == 64) takes = (cross ? P >= 8 : (int64_t)P * n_rounds >= 9) && 4 * parts >= 3 * fill;
     else if (N <= 256) takes = P * N > 256 && n_rounds >= 3 && !cross && parts > 2 * fill && parts <= 5 * fill;
-    else if (P == 1) takes = N == 512 || n_rounds >= 3 || parts <= 4 * fill;
-    else if (N == 512 && cross) takes = n_rounds >= 3 && parts <= 2 * fill;
-    else takes = parts <= 4 * fill;
+    else if (N == 512) takes = P == 1 || (cross ? n_rounds >= 3 && parts <= 2 * fill : parts <= 4 * fill);
+    else takes = parts <= 4 * fill || odd_row || (P == 1 ? n_rounds >= 3 : cross && (n_rounds >= 3 || P > 2));
     if (!takes || parts > 8 * fill) return 0;
     if (wmode == 0 && N <= 256) return 4;
     return parts <= (cross && N == 1024 ? 4 : 2) * fill ? 2 : 4;
@@ -1087,7 +1087,7 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
         if (rc != LFFN_OK) return rc;
         const int64_t fill = (int64_t)cus * (1024 / N);  // workgroups that the chip holds
         const int wmode = out.probes ? 2 : out.weights ? 1 : 0;
-        const int tokens = hash_lane_tokens(N, a.P, n_rounds, wmode, a.P > 1 && a.cross, parts, fill);
+        const int tokens = hash_lane_tokens(N, a.P, n_rounds, wmode, a.P > 1 && a.cross, d % 4 != 0, parts, fill);
         if (tokens) {
             const int64_t groups = (n + tokens - 1) / tokens;
             const unsigned p_groups = a.P > 1 ? split_projections(a.P, a.cross, std::max<int64_t>(1, fill / groups), &a.p_per) : 1u;
