@@ -1020,29 +1020,36 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
 //   d = 768, k = 170, tau = 9 (two projections), weights: 512 12.7 / 7.9 / 9.2, 1000 12.8 / 9.8 / 9.4, 2000 17.7 / 17.8 / 13.5
 //   d = 512, k = 256, tau = 8 (four), weights: 64 5.7 / 4.2 / 4.7, 512 6.9 / 7.4 / 5.7, 1000 11.7 / 12.9 / 9.1
 // so two tokens to the second fill (to the fourth where tables cross at d_pad = 1024: two rounds, codes, 512 tokens of 768, k = 170, tau = 9
-// 7.6 / 6.9 / 8.0), four to the eighth.  Where it stops before (fills; us a token to a wave / the kernel's better):
-//   weights and shares: d = 128, one projection, 0.5 ... 1.5 4.1 / 4.2, 4.5 / 4.7, twelve with tables that cross 0.4 5.1 / 5.4 (shares); two
-//   with tables that cross, a chain in either kernel, us longer than a token to a wave: d = 64 weights 0.5 ... 1 0.2, up to 1.4 (2 and up 1 shorter, 0
-//   ... 0.25 0.6), shares 0.25 ... 1 0.4 ... 0.8, up to 2.1, d = 128 2 ... 4 0.6 and 1.4 (5 and up 0.2 ... 2 shorter), d = 256 shares 0.4; d = 256 where
-//   tables cross, three projections, two rounds, weights 1536 (4.5) 8.5 / 8.7, shares 10.1 / 11.1, d = 512 shares 1024 (6) 13.1 / 14.8
-//   codes alone, whose transforms of 64 ... 256 cost a wave of its own least: d = 64, one projection, 64 tokens 3.0 / 3.2, 2048 3.2 / 3.5, 8192 4.3 /
-//   4.1, twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 10.6 / 6.7, two rounds 64 3.1 / 3.3, 2048 8.1 / 6.1,
-//   four with tables that cross 4659 (4.6) a pass 10.3 / 11.8; d = 128, one 2048 3.5 / 4.1, 16384
-//   6.8 / 6.9, six 256 (0.8) 3.7 / 4.0, 1024 (3) 5.6 / 5.2, 3072 (9) 9.2 / 10.4, tables that cross 1024 6.2 / 6.9; d = 256, one 2048 4.3 /
-//   4.5, two 1536 (3) 6.0 / 5.1, 3072 (6) 6.9 / 7.7, two rounds 2048 (4) 4.7 / 4.9; d = 512, two projections 1024 (4) 6.1 / 5.6, two
-//   rounds 1536 (6) 6.5 / 7.4, tables that cross 64 5.3 / 5.5; d_pad = 1024 from 4 to 8, a pass 8 wide: one, two rounds 0.96 : 1, three
-//   1.02 : 1, two 0.96 : 1, with tables that cross 0.98 and 1.01 : 1, three 1.0 ... 1.5 : 1, rows of no multiple of four 1.0 ... 1.2 : 1 in all of these
+// 7.6 / 6.9 / 8.0), four to the eighth.  Where the others are ahead, at `f` fills (hash, or a pass 8 wide, us, a token to a wave / here):
+//   weights and shares
+//     d = 128, one projection: f = 0.5 4.1 / 4.2, 1.5 4.5 / 4.7; twelve that cross, shares: 0.4 5.1 / 5.4
+//     two projections that cross, a chain in either kernel: d = 64 weights up to 1.4 longer here between 0.25 and 2, shares up to 2.1 below
+//     2, d = 128 0.6 (weights) and 1.4 (shares) below 5, d = 256 shares 0.4
+//     three that cross: d = 256 f = 4.5 8.5 / 8.7, shares 10.1 / 11.1 (four and six: 2 ... 7 shorter), d = 512 shares 6 13.1 / 14.8
+//   codes alone, whose narrow transforms cost a wave of its own least
+//     d = 64: one projection, 64 tokens 3.0 / 3.2, 8192 4.3 / 4.1; twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 (6) 10.6 / 6.7; four that
+//     cross 4659 (4.6) 10.3 / 11.8
+//     d = 128: one 2048 (1) 3.5 / 4.1; six 256 (0.8) 3.7 / 4.0, 1024 (3) 5.6 / 5.2, 3072 (9) 9.2 / 10.4; six that cross 1024 6.2 / 6.9, twelve
+//     1536 (9) 12.8 / 12.2
+//     d = 256: one 2048 (2) 4.3 / 4.5; two f = 2 0.6 shorter, 4 even, 6 0.6 longer; three 3 2.4 shorter, 6 1.2 longer; four, 2 ... 8 0.6 ... 1.7 shorter;
+//     five 5 3 shorter; that cross, two to four longer, six 4 0.8 longer, 6 2 shorter
+//     d = 512: one even at 8; two, two rounds 3 0.4 shorter, 6 0.8 longer; that cross, two 0.8 0.3 shorter, 3 0.4 longer, three 3 1 shorter, 4 1
+//     longer, five 3 1.1 and 8 1.4 shorter, two rounds longer
+//     d_pad = 1024 from 4 to 8: one, two rounds 0.96 : 1, three 1.02 : 1; two 0.96 : 1, that cross 0.98 and 1.01 : 1; three that cross 1.0
+//     ... 1.5 : 1; odd rows 1.0 ... 1.2 : 1 in all of these
 int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, bool odd_row, int64_t parts, int64_t fill)
 {
     bool takes;
+    const bool chain = parts > (int64_t)P * fill * N / 256;  // more than four tokens a compute unit: the others take projections in turn
     if (wmode != 0) {
         if (P == 2 && cross && N <= 256 && (N < 256 || wmode == 2))
             takes = N < 256 && (parts >= (N == 64 ? 2 : 5) * fill || (N == 64 && wmode == 1 && 4 * parts <= fill));
         else if (N == 128) takes = parts >= (P == 1 ? 2 : cross ? 1 : 0) * fill;
-        else takes = !cross || N < 256 || N > (wmode == 1 ? 256 : 512) || parts <= 4 * fill;
-    } else if (N == 64) takes = (cross ? P >= 8 : (int64_t)P * n_rounds >= 9) && 4 * parts >= 3 * fill;
-    else if (N <= 256) takes = P * N > 256 && n_rounds >= 3 && !cross && parts > 2 * fill && parts <= 5 * fill;
-    else if (N == 512) takes = P == 1 || (cross ? n_rounds >= 3 && parts <= 2 * fill : parts <= 4 * fill);
+        else takes = !(P == 3 && cross && (N == 256 || (N == 512 && wmode == 2))) || parts <= 4 * fill;
+    } else if (N == 64) takes = (cross ? P >= 7 : (int64_t)P * n_rounds >= 9) && 4 * parts >= 3 * fill;
+    else if (N == 128) takes = n_rounds >= 3 && ((P > 2 && !cross && parts > 2 * fill && parts <= 5 * fill) || (P >= 12 && chain));
+    else if (N == 256) takes = n_rounds >= 3 && (cross ? P >= 5 && chain : P > 1 && parts > 2 * fill && 2 * parts <= (P == 2 ? 7 : P == 3 ? 10 : 16) * fill);
+    else if (N == 512) takes = P == 1 || (n_rounds >= 3 ? !cross || P > 4 || parts <= (P == 2 ? 1 : 3) * fill : !cross && parts < 4 * fill);
     else takes = parts <= 4 * fill || odd_row || (P == 1 ? n_rounds >= 3 : cross && (n_rounds >= 3 || P > 2));
     if (!takes || parts > 8 * fill) return 0;
     if (wmode == 0 && N <= 256) return 4;
@@ -1206,7 +1213,8 @@ enum class Codes { kCallers, kTurned, kPacked, kPackedInChain };
 // over workgroups.  BH, d_pad <= 256, four factors, pass, direct / staged: tau 8, k = 96, 768 wide, d = 256, block 64, 4362 tokens 97 / 133,
 // d = 64, block 32, 4865 79 / 97, k = 250, d = 128, block 64, 4309 282 / 330: two tokens a row; tau 9, d = 64, block 32, 3586 108 / 128,
 // 4210 120 / 115, block 64 4411 135 / 142: 3.5 slots; tau 10, d = 64, block 64, k = 96 4307 219 / 273, k = 170 5304 426 / 429, 512 wide, d = 128
-// 6731 116 / 128, k = 80 5215 151 / 168: 4.5 slots.  (d_pad = 512, two projections, block 64, tau 8, 4948 tokens 107 / 100.)
+// 6731 116 / 128, k = 80 5215 151 / 168: 4.5 slots, but for blocks of 16 and 32
+// of rows of 256 (block 16, two factors, k = 96 5125 203 / 162).  (d_pad = 512, two projections, block 64, tau 8, 4948 tokens 107 / 100.)
 int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, Codes codes)
 {
     const int64_t two_a_row = 8 * (int64_t)rows, slot = kLdsThreads / sw;
@@ -1758,17 +1766,18 @@ int launch_bh_pack(const float *bmats, float *apack, int d, int k, int tau, int 
 // to a sixteenth of that, and it spreads the projections of narrow rows out: the more bytes and the narrower the row, the
 // sooner it is ahead.  Fills at the first loss, blocks 16 / 32 / 64, of 1 ... 36 projections, codes and weights: d = 128 one factor
 // 8 / 8 / 4.5, two 6 / 4.1 / 4, four 4.1 / 4.1 / 3, sixteen 4.1 / 3.5 / 2.5; d = 64 one 8 / 6 / 2.75, two 5.3 / 3.4 / 2.15, four
-// 3 / 2.3 / 2.05, sixteen 2.05 / 2.05 / 1.2.  So a part of the width and one that goes with 1 / bytes.  d = 256 first loses at 6.7,
-// and not before 8 with narrow blocks of one projection or two or where tables cross into a projection that both then hash
-// twice (k = 40, tau = 9, 3500 tokens, block 64 46.6 / 41.8 / 30.0); three in a chain lose at 6.7 (k = 96, block 32, 2300 tokens 19.3 / 23.3 /
-// 21.2).
-double bh_lane_most(int N, int P, bool cross, int block, int n_factors)
+// 3 / 2.3 / 2.05, sixteen 2.05 / 2.05 / 1.2.  So a part of the width and one that goes with 1 / bytes, and more where bh_hash_kernel
+// forms the weights through its window (d = 64, k = 97, tau = 7, two factors, block 16, 2048 tokens, 5.5 fills 13.7 / 10.3 / 9.4).  d = 256
+// first loses at 6.7, and not before 8 with blocks of 16 and 32 or where tables cross into a projection that both then hash
+// twice (k = 40, tau = 9, 3500 tokens, block 64 46.6 / 41.8 / 30.0), but for three in a chain (k = 96, block 32, 2300 tokens 19.3 / 23.3 / 21.2).
+double bh_lane_most(int N, int P, bool cross, int block, int n_factors, bool window)
 {
     if (N >= 512) return block == 64 ? 4 : 8;
-    if (N == 256) return (P > 1 && cross) || (P <= 2 && block < 64) ? 8 : 6;
+    if (N == 256) return (P > 1 && cross) || (P != 3 && block < 64) ? 8 : 6;
     const int bytes = n_factors * block;  // KB a compute unit and fill
-    const double most = std::min(8.0, (N == 128 ? 2.5 : 1.0) + 100.0 / bytes);
-    return N == 64 && bytes <= 256 ? std::max(most, 2.0) : most;
+    const double most = (N == 128 ? 2.5 : bytes <= 512 ? 1.2 : 1.0) + (window ? 32.0 / block : 0.0) + 100.0 / bytes;
+    const double least = bytes > 256 ? 0.0 : N == 64 ? 2.0 : block < 64 ? 4.0 : 0.0;
+    return std::min(8.0, std::max(most, least));
 }
 
 // Workgroups to the tokens of bh_hash_kernel's grid, and whether it spreads their projections over others with codes in the ABI layout
@@ -1819,7 +1828,7 @@ int launch_hash_bh(const void *x, const float *pack_from, const float *apack_in,
     int cus = 0, rc = device_cus(&cus);
     if (rc != LFFN_OK) return rc;
     const int64_t fill = (int64_t)cus * (1024 / N);  // workgroups that the chip holds
-    if (few_ok && a.codes && (double)(n * a.P) <= bh_lane_most(N, a.P, N % tau != 0, block, n_factors) * (double)fill) {
+    if (few_ok && a.codes && (double)(n * a.P) <= bh_lane_most(N, a.P, N % tau != 0, block, n_factors, out.weights && !bh_weights_in_registers(tau)) * (double)fill) {
         const int tokens = n * a.P <= 2 * (int64_t)cus * std::max(1, 256 / N) ? 2 : 4;
         const int64_t groups = (n + tokens - 1) / tokens;
         dim3 grid = grid_of(groups);
@@ -2059,7 +2068,7 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
         int cus = 0;
         rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;
-        if (bh_spreads(n, d, k, tau, cus)) codes = Codes::kPackedInChain;
+        if (bh_spreads(n, d, k, tau, cus) && !(tau == 10 && d > 128 && h.block < 64)) codes = Codes::kPackedInChain;
     }
     LdsPlan plan;
     rc = plan_gather_lds(n, k, tau, d_out, T, mode, codes, opt, &plan);

@@ -81,13 +81,15 @@ def test_route(tmp_path, n, d, k, tau, block, tokens, groups):
 # The line of narrow rows in fills of the chip (n * P * d_pad / (256 * 1024)): both sides of it for the widths, bytes of factors and
 # projections that it tells apart
 @pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
-@pytest.mark.parametrize("d,k,tau,block,factors,most", [
-    (64, 8, 8, 64, 4, 8192), (64, 8, 8, 32, 4, 8192), (64, 8, 8, 16, 4, 10496), (64, 8, 8, 16, 1, 29696), (64, 24, 8, 64, 4, 2730),
-    (64, 8, 8, 64, 16, 4496), (128, 8, 8, 64, 4, 5920), (100, 24, 8, 64, 4, 2960), (128, 8, 8, 16, 4, 8320), (128, 8, 8, 16, 1, 16384),
-    (256, 8, 8, 64, 4, 6144), (256, 8, 8, 16, 4, 8192), (256, 96, 8, 32, 4, 2048), (200, 40, 9, 64, 4, 4096)])
-def test_line_of_narrow_rows(tmp_path, d, k, tau, block, factors, most):
+@pytest.mark.parametrize("weighted,d,k,tau,block,factors,most", [
+    (0, 64, 8, 8, 64, 4, 8192), (0, 64, 8, 8, 32, 4, 8192), (0, 64, 8, 8, 16, 4, 11315), (0, 64, 8, 8, 16, 1, 30515), (0, 64, 24, 8, 64, 4, 2730),
+    (0, 64, 8, 8, 64, 16, 4496), (0, 128, 8, 8, 64, 4, 5920), (0, 100, 24, 8, 64, 4, 2960), (0, 128, 8, 8, 16, 4, 8320), (0, 128, 8, 8, 16, 1, 16384),
+    (0, 128, 8, 8, 32, 4, 8192), (0, 256, 8, 8, 64, 4, 6144), (0, 256, 8, 8, 16, 4, 8192), (0, 256, 96, 8, 32, 4, 2048), (0, 256, 128, 8, 32, 4, 2048),
+    (0, 256, 128, 8, 64, 4, 1536), (0, 200, 40, 9, 64, 4, 4096), (1, 64, 7, 9, 16, 4, 19507), (1, 64, 8, 8, 16, 4, 11315), (1, 128, 14, 9, 32, 4, 8768)])
+def test_line_of_narrow_rows(tmp_path, weighted, d, k, tau, block, factors, most):
+    name = "lookupffn_forward_bh" + ("_weighted" if weighted else "")
     calls = [R.option("gather_path", 1)]
     for n in (most, most + 1):
-        calls.append(["lookupffn_forward_bh", R.FAKE, R.FAKE, R.FAKE, R.FAKE, n, d, k, tau, 32, 0x100 | block, factors, 0, 0, R.FAKE, 1 << 40, None])
+        calls.append([name, R.FAKE, R.FAKE, R.FAKE, R.FAKE, n, d, k, tau, 32, 0x100 | block, factors, 0, 0, R.FAKE, 1 << 40, None])
     kernels = [launches[0].kernel for launches in R.record(R.build(tmp_path), calls)[1:]]
     assert kernels == ["bh_lane_kernel", "bh_hash_kernel"]

@@ -72,16 +72,19 @@ def test_route(tmp_path, mode, n, d, k, tau, tokens, groups):
     ("plain", 4096, 64, 8, 8, 4, 0), ("plain", 2048, 64, 24, 8, 2, 0), ("plain", 2048, 64, 24, 8, 3, 4),
     ("plain", 1024, 128, 64, 8, 3, 0), ("plain", 1025, 128, 64, 8, 3, 4), ("plain", 2560, 128, 64, 8, 3, 4), ("plain", 2561, 128, 64, 8, 3, 0),
     ("plain", 2048, 128, 32, 8, 3, 0), ("plain", 1025, 128, 64, 8, 2, 0), ("plain", 1025, 128, 73, 7, 3, 0),
-    ("plain", 1024, 256, 64, 8, 3, 0), ("plain", 1025, 256, 64, 8, 3, 4), ("plain", 2560, 256, 64, 8, 4, 4), ("plain", 2561, 256, 64, 8, 4, 0),
-    ("plain", 4096, 512, 64, 8, 2, 4), ("plain", 1024, 512, 128, 8, 2, 4), ("plain", 1025, 512, 128, 8, 2, 0), ("plain", 600, 512, 97, 7, 3, 0),
-    ("plain", 512, 512, 97, 7, 3, 2), ("plain", 511, 512, 97, 7, 2, 0), ("plain", 1024, 768, 96, 8, 2, 4), ("plain", 1025, 768, 96, 8, 2, 0),
+    ("plain", 1024, 256, 64, 8, 3, 0), ("plain", 1025, 256, 64, 8, 3, 4), ("plain", 1792, 256, 64, 8, 4, 4), ("plain", 1793, 256, 64, 8, 4, 0),
+    ("plain", 1706, 256, 96, 8, 3, 4), ("plain", 1707, 256, 96, 8, 3, 0), ("plain", 2048, 256, 128, 8, 3, 4), ("plain", 2048, 256, 128, 8, 2, 0),
+    ("plain", 1024, 256, 170, 9, 3, 0), ("plain", 1025, 256, 170, 9, 3, 4), ("plain", 1200, 256, 112, 9, 3, 0), ("plain", 1025, 128, 170, 9, 3, 4), ("plain", 1024, 128, 170, 9, 3, 0),
+    ("plain", 4096, 512, 64, 8, 2, 4), ("plain", 1023, 512, 128, 8, 2, 4), ("plain", 1024, 512, 128, 8, 2, 0), ("plain", 2048, 512, 128, 8, 3, 4),
+    ("plain", 256, 512, 97, 7, 3, 2), ("plain", 257, 512, 97, 7, 3, 0), ("plain", 256, 512, 97, 7, 2, 0), ("plain", 512, 512, 128, 9, 3, 4), ("plain", 513, 512, 128, 9, 3, 0),
+    ("plain", 819, 512, 250, 10, 3, 4), ("plain", 1024, 768, 96, 8, 2, 4), ("plain", 1025, 768, 96, 8, 2, 0),
     ("plain", 2047, 768, 96, 8, 3, 4), ("plain", 513, 768, 170, 9, 2, 0), ("plain", 1024, 768, 170, 9, 3, 4), ("plain", 1025, 768, 170, 9, 3, 0),
     ("plain", 513, 768, 250, 8, 4, 0), ("plain", 1024, 767, 250, 8, 2, 4), ("plain", 682, 768, 300, 10, 2, 4), ("plain", 2047, 641, 96, 8, 2, 4), ("plain", 512, 768, 170, 9, 2, 2),
     ("weighted", 512, 768, 170, 9, 2, 2), ("weighted", 513, 768, 170, 9, 2, 4), ("weighted", 512, 768, 256, 8, 2, 4),
     ("weighted", 4095, 128, 8, 8, 3, 0), ("weighted", 4096, 128, 8, 8, 3, 2), ("weighted", 4097, 128, 8, 8, 3, 4), ("probes", 341, 128, 97, 7, 3, 0),
     ("probes", 342, 128, 97, 7, 3, 2), ("weighted", 5119, 128, 24, 9, 2, 0), ("weighted", 5120, 128, 24, 9, 2, 4), ("plain", 4659, 64, 24, 9, 3, 0), ("plain", 1024, 64, 56, 9, 3, 4),
     ("probes", 4095, 64, 8, 10, 3, 0), ("probes", 4096, 64, 8, 10, 3, 2), ("weighted", 512, 64, 8, 10, 3, 2), ("weighted", 513, 64, 8, 10, 3, 0),
-    ("probes", 60, 256, 40, 9, 3, 0), ("weighted", 60, 256, 40, 9, 3, 2), ("weighted", 1, 128, 64, 8, 3, 2), ("weighted", 1365, 256, 97, 7, 3, 4), ("weighted", 1366, 256, 97, 7, 3, 0),
+    ("probes", 60, 256, 40, 9, 3, 0), ("weighted", 60, 256, 40, 9, 3, 2), ("weighted", 1, 128, 64, 8, 3, 2), ("weighted", 1365, 256, 97, 7, 3, 4), ("weighted", 1366, 256, 97, 7, 3, 0), ("weighted", 1366, 256, 112, 9, 3, 4),
     ("probes", 1366, 256, 96, 8, 3, 4), ("probes", 682, 512, 170, 9, 3, 4), ("probes", 683, 512, 170, 9, 3, 0), ("weighted", 683, 512, 170, 9, 3, 4)])
 def test_lines(tmp_path, mode, n, d, k, tau, rounds, tokens):
     name = "lookupffn_forward" + ("" if mode == "plain" else "_" + mode)

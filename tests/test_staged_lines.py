@@ -42,7 +42,7 @@ def test_line_of_a_callers_codes(tmp_path, mode, n, staged):
 @pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
 @pytest.mark.parametrize("weighted,d,k,tau,d_out,line", [
     (False, 256, 96, 8, 768, 5111), (True, 64, 96, 8, 768, 5111), (True, 512, 128, 8, 768, 4151), (False, 512, 96, 8, 768, 4791),
-    (False, 64, 170, 9, 768, 4476), (True, 200, 170, 9, 768, 4476), (True, 512, 170, 9, 768, 3196), (True, 128, 128, 10, 1024, 4605), (True, 512, 128, 10, 768, 4156),
+    (False, 64, 170, 9, 768, 4476), (True, 200, 170, 9, 768, 4476), (True, 512, 170, 9, 768, 3196), (True, 128, 128, 10, 1024, 4605), (True, 512, 128, 10, 768, 4156), (True, 200, 96, 10, 768, 4156), (True, 128, 96, 10, 768, 5756),
     (True, 768, 96, 8, 768, 4151), (False, 64, 64, 8, 128, 30657), (True, 64, 64, 8, 128, 26561)])
 def test_line_of_bh_codes(tmp_path, weighted, d, k, tau, d_out, line):
     lib = R.build(tmp_path)
