@@ -1214,11 +1214,18 @@ enum class Codes { kCallers, kTurned, kPacked, kPackedInChain };
 // d = 64, block 32, 4865 79 / 97, k = 250, d = 128, block 64, 4309 282 / 330: two tokens a row; tau 9, d = 64, block 32, 3586 108 / 128,
 // 4210 120 / 115, block 64 4411 135 / 142: 3.5 slots; tau 10, d = 64, block 64, k = 96 4307 219 / 273, k = 170 5304 426 / 429, 512 wide, d = 128
 // 6731 116 / 128, k = 80 5215 151 / 168: 4.5 slots, but for blocks of 16 and 32
-// of rows of 256 (block 16, two factors, k = 96 5125 203 / 162).  (d_pad = 512, two projections, block 64, tau 8, 4948 tokens 107 / 100.)
-int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, Codes codes)
+// of rows of 256 (block 16, two factors, k = 96 5125 203 / 162).  d_pad = 512 spreads them up to 4096 tokens: tau 8, block 32, 536 wide 3575
+// 86 / 113, 984 wide 4000 133 / 156, but tau 9 1.1 ... 2 : 1.
+// Where an XCD's workgroups have a slice each (an odd number of slices, so that every XCD has all of them) none of them finds its copies
+// in the L2, and those beyond whole turns idle.  Plain, weighted, tau 8: two tokens a row (weighted, k = 64, 544 wide 3497 62 / 67, 712 3489
+// 67 / 75, 976 3905 84 / 94); else the line goes with the idle ones (plain, tau 10, d = 64, k = 96, 528 wide 7545 266 / 330; tau 9, 528 wide 6651 137 / 154;
+// multi-probe, tau 8, 584 wide 2004 185 / 208).
+// units: slices of the fullest XCD, for its `per_xcd` workgroups.
+int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, Codes codes, int units, int per_xcd)
 {
     const int64_t two_a_row = 8 * (int64_t)rows, slot = kLdsThreads / sw;
-    if (tau == 7 || (sw == 4 && !prepared)) return two_a_row;
+    const bool alone = 2 * units > per_xcd;
+    if (tau == 7 || (sw == 4 && !prepared) || (sw == 8 && mode != kProbes && alone)) return two_a_row;
     if (codes == Codes::kPackedInChain && sw == 8) return two_a_row;
     if (codes == Codes::kTurned && tau <= 9 && k < 10) return two_a_row;
     int64_t line = two_a_row;  // in quarters of a slot from here
@@ -1227,6 +1234,7 @@ int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, 
     if (mode == kProbes && turned && k < 12 && (k < 6 || k % 2)) line = (k < 6 ? 18 : 14) * slot;
     else if (mode == kProbes) line = (sw == 8 ? (turned && k < 16 ? 12 : small ? 10 : 7) : (small ? 11 : 9)) * slot;
     else if (!small) line = (sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? (chain ? 14 : 10) : (chain ? 18 : 13)) * slot;
+    if (alone) line = line * per_xcd * ((units + per_xcd - 1) / per_xcd) / units;
     return std::min(line, two_a_row);
 }
 
@@ -1298,12 +1306,13 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
         a.table_stride = (unsigned long long)rows * row_bytes;
         a.slice_stride = (unsigned long long)sw * 16;
     }
-    const int64_t tpb = lds_tokens_per_block(n, a.n_units, a.token_splits, a.blocks_per_xcd);
+    const int m = (a.n_units + kXcds - 1) / kXcds, Bx = a.blocks_per_xcd;
+    const int64_t tpb = lds_tokens_per_block(n, a.n_units, a.token_splits, Bx);
     int tok_max = 16;
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
-    if (opt.gather_path < 2 && chunk * 4 < (codes == Codes::kCallers ? 8 * (int64_t)rows : staged_from(mode, k, tau, sw, rows, T.prepared, codes))) return LFFN_OK;
+    if (opt.gather_path < 2 && chunk * 4 < (codes == Codes::kCallers ? 8 * (int64_t)rows : staged_from(mode, k, tau, sw, rows, T.prepared, codes, m, Bx))) return LFFN_OK;
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
     auto slots_of = [&](int64_t tokens) {
         const int tok = (int)((tokens + groups - 1) / groups);
@@ -1315,7 +1324,6 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     // Every chunk streams all tables.  Where the workgroups of an XCD take fewer turns when they divide whole chunks instead of token
     // ranges (whose shortest division decides: 32 workgroups over three slices give one of them 10), they do that, unless its
     // slots cost more (a turn's fill and hand-over count as one slot).  65536 bf16 tokens, k = 96, 768 wide, pass 347 -> 328 us.
-    const int m = (a.n_units + kXcds - 1) / kXcds, Bx = a.blocks_per_xcd;
     const int64_t unit_tokens = (n + a.token_splits - 1) / a.token_splits;
     const int64_t turns = nchunks * (m > Bx ? (m + Bx - 1) / Bx : 1);
     int64_t cost = turns * (p->tok + 1);
@@ -2064,7 +2072,7 @@ int forward_core(const HashSpec &h, Mode mode, const void *x, const void *tables
     // a batch that goes in pieces is cut from the ABI layout
     const bool row_shares = mode == kProbes && n <= kProbesPiece && hash_row_ok(h.signs, true, true, true, n, d, k, tau, h.n_rounds, opt);
     Codes codes = k % 2 || (mode == kProbes && !row_shares) ? Codes::kTurned : Codes::kPacked;
-    if (h.bh() && d <= 256 && codes == Codes::kPacked) {
+    if (h.bh() && d <= (tau <= 8 ? 512 : 256) && codes == Codes::kPacked) {
         int cus = 0;
         rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;

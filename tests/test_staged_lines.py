@@ -14,6 +14,9 @@ CASES = [  # entry, k, tau, d_out, prepared, tokens of the line
     ("lookupffn_forward_probes", 64, 9, 1024, True, 2301), ("lookupffn_forward", 170, 9, 768, False, 5116),
     ("lookupffn_forward", 62, 8, 768, True, 5111), ("lookupffn_forward_weighted", 97, 8, 768, True, 5111),
     ("lookupffn_forward_probes", 24, 8, 768, True, 3191), ("lookupffn_forward_probes", 97, 8, 768, True, 3191),
+    # a slice and less to a workgroup of an XCD, and two to one
+    ("lookupffn_forward_weighted", 64, 8, 544, True, 4089), ("lookupffn_forward_weighted", 64, 8, 352, True, 6641), ("lookupffn_forward", 96, 10, 528, True, 12905),
+    ("lookupffn_forward_weighted", 64, 9, 528, True, 8185), ("lookupffn_forward_weighted", 64, 9, 496, True, 5281), ("lookupffn_forward_probes", 80, 8, 584, True, 3017),
     ("lookupffn_forward_probes", 96, 7, 768, True, 2551), ("lookupffn_forward_probes", 24, 10, 512, True, 5625),
 ]
 
@@ -42,6 +45,7 @@ def test_line_of_a_callers_codes(tmp_path, mode, n, staged):
 @pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
 @pytest.mark.parametrize("weighted,d,k,tau,d_out,line", [
     (False, 256, 96, 8, 768, 5111), (True, 64, 96, 8, 768, 5111), (True, 512, 128, 8, 768, 4151), (False, 512, 96, 8, 768, 4791),
+    (True, 512, 96, 8, 672, 4089), (True, 512, 96, 8, 704, 4089), (True, 512, 64, 8, 704, 3321),
     (False, 64, 170, 9, 768, 4476), (True, 200, 170, 9, 768, 4476), (True, 512, 170, 9, 768, 3196), (True, 128, 128, 10, 1024, 4605), (True, 512, 128, 10, 768, 4156), (True, 200, 96, 10, 768, 4156), (True, 128, 96, 10, 768, 5756),
     (True, 768, 96, 8, 768, 4151), (False, 64, 64, 8, 128, 30657), (True, 64, 64, 8, 128, 26561)])
 def test_line_of_bh_codes(tmp_path, weighted, d, k, tau, d_out, line):
