@@ -570,7 +570,7 @@ int launch_hash_lane_t(int wmode, const HashArgs &a, dim3 grid, hipStream_t s)
     static_assert(lds <= 64 * 1024, "no LDS beyond what every kernel may use");
     switch (wmode) {
         case 0:  // (codes alone of narrow rows: four tokens only)
-            if constexpr (T == 4 || L >= 9) {
+            if constexpr (T == 4 || L >= 8) {
                 hipLaunchKernelGGL((hash_lane_kernel<L, T, 0>), grid, dim3(1 << L), lds, s, a);
                 break;
             }
@@ -1013,7 +1013,7 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
 
 // Tokens of a workgroup of hash_lane_kernel where it takes the batch of `parts` transforms on a chip that holds `fill` workgroups
 // (cus * 1024 / d_pad), else 0.  wmode: 0 codes alone, 1 weights, 2 shares; cross: tables cross into the next projection, which the
-// workgroup they end in then hashes too; odd_row: hash1024_kernel loads the rows element by element.
+// workgroup they end in then hashes too; slow_rows: the others load the rows element by element (d_pad = 1024) or in 16 bits (below).
 // Hash alone, three rounds, us, a token to a wave / two tokens a workgroup / four:
 //   d = 700, k = 97, tau = 7, weights: 1 token 6.0 / 4.2 / 4.9, 512 7.9 / 4.9 / 5.4, 1000 8.0 / 6.2 / 5.5, 2000 10.7 / 10.5 / 7.7; codes,
 //   k = 96, tau = 8: 512 6.0 / 4.7 / 5.4, 2000 8.3 / 9.9 / 7.7, 4000 9.9 / 17.6 / 12.8; shares 512 9.4 / 6.0 / 6.9, 2000 14.5 / 13.2 / 11.0
@@ -1026,18 +1026,17 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
 //     two projections that cross, a chain in either kernel: d = 64 weights up to 1.4 longer here between 0.25 and 2, shares up to 2.1 below
 //     2, d = 128 0.6 (weights) and 1.4 (shares) below 5, d = 256 shares 0.4
 //     three that cross: d = 256 f = 4.5 8.5 / 8.7, shares 10.1 / 11.1 (four and six: 2 ... 7 shorter), d = 512 shares 6 13.1 / 14.8
-//   codes alone, whose narrow transforms cost a wave of its own least
-//     d = 64: one projection, 64 tokens 3.0 / 3.2, 8192 4.3 / 4.1; twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 (6) 10.6 / 6.7; four that
-//     cross 4659 (4.6) 10.3 / 11.8
-//     d = 128: one 2048 (1) 3.5 / 4.1; six 256 (0.8) 3.7 / 4.0, 1024 (3) 5.6 / 5.2, 3072 (9) 9.2 / 10.4; six that cross 1024 6.2 / 6.9, twelve
-//     1536 (9) 12.8 / 12.2
-//     d = 256: one 2048 (2) 4.3 / 4.5; two f = 2 0.6 shorter, 4 even, 6 0.6 longer; three 3 2.4 shorter, 6 1.2 longer; four, 2 ... 8 0.6 ... 1.7 shorter;
-//     five 5 3 shorter; that cross, two to four longer, six 4 0.8 longer, 6 2 shorter
-//     d = 512: one even at 8; two, two rounds 3 0.4 shorter, 6 0.8 longer; that cross, two 0.8 0.3 shorter, 3 0.4 longer, three 3 1 shorter, 4 1
-//     longer, five 3 1.1 and 8 1.4 shorter, two rounds longer
+//   codes alone, whose narrow transforms cost a wave of its own least (passes of 25 ... 2000 shapes, x and signs from beyond the L2)
+//     d = 64: one projection, 64 tokens 3.0 / 3.2, 8192 4.3 / 4.1; twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 (6) 10.6 / 6.7; two to five
+//     that cross 0 ... 2.2 longer, seven and up 0.1 longer below 0.5
+//     d = 128: one 0.3 ... 1 longer, two 0.1 ... 0.8 (that cross 2); six f = 0.8 3.7 / 4.0, 3 5.6 / 5.2; that cross, up to eleven 1 longer ... 0.6
+//     shorter, twelve 0.8 longer below 0.5, 9 12.8 / 12.2
+//     d = 256: one 0.2 ... 0.5 longer; two 0.2 ... 0.7 shorter to 3.5, 4 1 longer, that cross 0.4 ... 1.4 longer; three to five 0.2 ... 1.8 shorter to
+//     3.5, then 1.2 longer ... 1.5 shorter (three and four that cross up to 2.5 longer), two fp32 rounds as much longer as shorter; six and up 0.2 ... 6 shorter
+//     d = 512: 0 ... 3.9 shorter, but for two that cross, two fp32 rounds 0.5 longer (three from 2 to 5 0.5 longer ... 1.8 shorter)
 //     d_pad = 1024 from 4 to 8: one, two rounds 0.96 : 1, three 1.02 : 1; two 0.96 : 1, that cross 0.98 and 1.01 : 1; three that cross 1.0
-//     ... 1.5 : 1; odd rows 1.0 ... 1.2 : 1 in all of these
-int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, bool odd_row, int64_t parts, int64_t fill)
+//     ... 1.5 : 1; rows of no multiple of four 1.0 ... 1.2 : 1 in all of these
+int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, bool slow_rows, int64_t parts, int64_t fill)
 {
     bool takes;
     const bool chain = parts > (int64_t)P * fill * N / 256;  // more than four tokens a compute unit: the others take projections in turn
@@ -1047,12 +1046,14 @@ int hash_lane_tokens(int N, int P, int n_rounds, int wmode, bool cross, bool odd
         else if (N == 128) takes = parts >= (P == 1 ? 2 : cross ? 1 : 0) * fill;
         else takes = !(P == 3 && cross && (N == 256 || (N == 512 && wmode == 2))) || parts <= 4 * fill;
     } else if (N == 64) takes = (cross ? P >= 7 : (int64_t)P * n_rounds >= 9) && 4 * parts >= 3 * fill;
-    else if (N == 128) takes = n_rounds >= 3 && ((P > 2 && !cross && parts > 2 * fill && parts <= 5 * fill) || (P >= 12 && chain));
-    else if (N == 256) takes = n_rounds >= 3 && (cross ? P >= 5 && chain : P > 1 && parts > 2 * fill && 2 * parts <= (P == 2 ? 7 : P == 3 ? 10 : 16) * fill);
-    else if (N == 512) takes = P == 1 || (n_rounds >= 3 ? !cross || P > 4 || parts <= (P == 2 ? 1 : 3) * fill : !cross && parts < 4 * fill);
-    else takes = parts <= 4 * fill || odd_row || (P == 1 ? n_rounds >= 3 : cross && (n_rounds >= 3 || P > 2));
+    else if (N == 128) takes = n_rounds >= 3 && (cross ? P >= 12 && chain : P > 2 && parts > 2 * fill && (P >= 6 || parts <= 5 * fill));
+    else if (N == 256 && P <= 2) takes = P == 2 && !cross && 2 * parts <= 7 * fill;
+    else if (N == 256)
+        takes = (n_rounds + slow_rows >= 3 || (P > 3 && !cross)) && (2 * parts <= 7 * fill || (cross ? P > 4 : P > 3 || parts <= 5 * fill));
+    else if (N == 512) takes = !(P == 2 && cross && n_rounds + slow_rows < 3);
+    else takes = parts <= 4 * fill || slow_rows || (P == 1 ? n_rounds >= 3 : cross && (n_rounds >= 3 || P > 2));
     if (!takes || parts > 8 * fill) return 0;
-    if (wmode == 0 && N <= 256) return 4;
+    if (wmode == 0 && N <= 128) return 4;
     return parts <= (cross && N == 1024 ? 4 : 2) * fill ? 2 : 4;
 }
 
@@ -1094,7 +1095,7 @@ int launch_hash(const void *x, const int8_t *signs, const HashOut &out, int64_t 
         if (rc != LFFN_OK) return rc;
         const int64_t fill = (int64_t)cus * (1024 / N);  // workgroups that the chip holds
         const int wmode = out.probes ? 2 : out.weights ? 1 : 0;
-        const int tokens = hash_lane_tokens(N, a.P, n_rounds, wmode, a.P > 1 && a.cross, d % 4 != 0, parts, fill);
+        const int tokens = hash_lane_tokens(N, a.P, n_rounds, wmode, a.P > 1 && a.cross, N == 1024 ? d % 4 != 0 : a.x_kind != 0, parts, fill);
         if (tokens) {
             const int64_t groups = (n + tokens - 1) / tokens;
             const unsigned p_groups = a.P > 1 ? split_projections(a.P, a.cross, std::max<int64_t>(1, fill / groups), &a.p_per) : 1u;

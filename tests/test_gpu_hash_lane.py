@@ -14,7 +14,7 @@ if torch.cuda.is_available():
 
 CASES = [  # n, d, k, tau, rounds, x dtype, forward passes that take the kernel: plain, weighted, probes
     (1, 64, 8, 8, 2, "float32", "wp"), (3, 33, 90, 9, 3, "bfloat16", "wp"), (2049, 64, 8, 8, 1, "float32", "wp"), (5, 100, 33, 7, 3, "float16", ""),
-    (17, 128, 40, 4, 5, "float32", "wp"), (16, 200, 96, 8, 3, "float32", "wp"), (683, 256, 96, 8, 3, "float32", "cwp"), (15, 255, 37, 13, 4, "bfloat16", "w"),
+    (17, 128, 40, 4, 5, "float32", "wp"), (16, 200, 96, 8, 3, "float32", "cwp"), (683, 256, 96, 8, 3, "float32", "cwp"), (15, 255, 37, 13, 4, "bfloat16", "w"),
     (47, 511, 133, 9, 3, "float16", "cwp"), (31, 512, 256, 8, 3, "float32", "cwp"), (1, 513, 96, 8, 3, "float32", "cwp"), (1001, 700, 97, 7, 3, "float16", "cwp"),
     (513, 768, 96, 8, 3, "float32", "cwp"), (512, 768, 170, 9, 2, "float32", "cwp"), (6, 1024, 171, 12, 1, "float32", "cwp"), (7, 1000, 300, 11, 3, "float32", "cwp"),
     (2048, 1023, 64, 16, 3, "float32", "cwp"),
@@ -72,11 +72,11 @@ def test_route(tmp_path, mode, n, d, k, tau, tokens, groups):
     ("plain", 4096, 64, 8, 8, 4, 0), ("plain", 2048, 64, 24, 8, 2, 0), ("plain", 2048, 64, 24, 8, 3, 4),
     ("plain", 1024, 128, 64, 8, 3, 0), ("plain", 1025, 128, 64, 8, 3, 4), ("plain", 2560, 128, 64, 8, 3, 4), ("plain", 2561, 128, 64, 8, 3, 0),
     ("plain", 2048, 128, 32, 8, 3, 0), ("plain", 1025, 128, 64, 8, 2, 0), ("plain", 1025, 128, 73, 7, 3, 0),
-    ("plain", 1024, 256, 64, 8, 3, 0), ("plain", 1025, 256, 64, 8, 3, 4), ("plain", 1792, 256, 64, 8, 4, 4), ("plain", 1793, 256, 64, 8, 4, 0),
-    ("plain", 1706, 256, 96, 8, 3, 4), ("plain", 1707, 256, 96, 8, 3, 0), ("plain", 2048, 256, 128, 8, 3, 4), ("plain", 2048, 256, 128, 8, 2, 0),
-    ("plain", 1024, 256, 170, 9, 3, 0), ("plain", 1025, 256, 170, 9, 3, 4), ("plain", 1200, 256, 112, 9, 3, 0), ("plain", 1025, 128, 170, 9, 3, 4), ("plain", 1024, 128, 170, 9, 3, 0),
-    ("plain", 4096, 512, 64, 8, 2, 4), ("plain", 1023, 512, 128, 8, 2, 4), ("plain", 1024, 512, 128, 8, 2, 0), ("plain", 2048, 512, 128, 8, 3, 4),
-    ("plain", 256, 512, 97, 7, 3, 2), ("plain", 257, 512, 97, 7, 3, 0), ("plain", 256, 512, 97, 7, 2, 0), ("plain", 512, 512, 128, 9, 3, 4), ("plain", 513, 512, 128, 9, 3, 0),
+    ("plain", 1024, 256, 64, 8, 3, 2), ("plain", 1025, 256, 64, 8, 2, 4), ("plain", 64, 256, 32, 8, 3, 0), ("plain", 64, 256, 56, 9, 3, 0), ("plain", 1792, 256, 64, 8, 4, 4), ("plain", 1793, 256, 64, 8, 4, 0),
+    ("plain", 1706, 256, 96, 8, 3, 4), ("plain", 1707, 256, 96, 8, 3, 0), ("plain", 2048, 256, 128, 8, 3, 4), ("plain", 2048, 256, 128, 8, 2, 4), ("plain", 300, 256, 96, 8, 2, 0),
+    ("plain", 1365, 256, 170, 9, 3, 4), ("plain", 300, 256, 170, 9, 2, 0), ("plain", 896, 256, 112, 9, 3, 4), ("plain", 897, 256, 112, 9, 3, 0), ("plain", 1025, 128, 170, 9, 3, 4), ("plain", 1024, 128, 170, 9, 3, 0),
+    ("plain", 4096, 512, 64, 8, 2, 4), ("plain", 2048, 512, 128, 8, 2, 4), ("plain", 2049, 512, 128, 8, 2, 0),
+    ("plain", 256, 512, 97, 7, 3, 2), ("plain", 256, 512, 97, 7, 2, 0), ("plain", 513, 512, 128, 9, 2, 4),
     ("plain", 819, 512, 250, 10, 3, 4), ("plain", 1024, 768, 96, 8, 2, 4), ("plain", 1025, 768, 96, 8, 2, 0),
     ("plain", 2047, 768, 96, 8, 3, 4), ("plain", 513, 768, 170, 9, 2, 0), ("plain", 1024, 768, 170, 9, 3, 4), ("plain", 1025, 768, 170, 9, 3, 0),
     ("plain", 513, 768, 250, 8, 4, 0), ("plain", 1024, 767, 250, 8, 2, 4), ("plain", 682, 768, 300, 10, 2, 4), ("plain", 2047, 641, 96, 8, 2, 4), ("plain", 512, 768, 170, 9, 2, 2),
@@ -86,8 +86,14 @@ def test_route(tmp_path, mode, n, d, k, tau, tokens, groups):
     ("probes", 4095, 64, 8, 10, 3, 0), ("probes", 4096, 64, 8, 10, 3, 2), ("weighted", 512, 64, 8, 10, 3, 2), ("weighted", 513, 64, 8, 10, 3, 0),
     ("probes", 60, 256, 40, 9, 3, 0), ("weighted", 60, 256, 40, 9, 3, 2), ("weighted", 1, 128, 64, 8, 3, 2), ("weighted", 1365, 256, 97, 7, 3, 4), ("weighted", 1366, 256, 97, 7, 3, 0), ("weighted", 1366, 256, 112, 9, 3, 4),
     ("probes", 1366, 256, 96, 8, 3, 4), ("probes", 682, 512, 170, 9, 3, 4), ("probes", 683, 512, 170, 9, 3, 0), ("weighted", 683, 512, 170, 9, 3, 4)])
-def test_lines(tmp_path, mode, n, d, k, tau, rounds, tokens):
+def test_lines(tmp_path, mode, n, d, k, tau, rounds, tokens, x_dtype=0):
     name = "lookupffn_forward" + ("" if mode == "plain" else "_" + mode)
-    call = [name, R.FAKE, R.FAKE, R.FAKE, R.FAKE, n, d, k, tau, 32, rounds, 0, 0, R.FAKE, 1 << 40, None]
+    call = [name, R.FAKE, R.FAKE, R.FAKE, R.FAKE, n, d, k, tau, 32, rounds, x_dtype, 0, R.FAKE, 1 << 40, None]
     launch = R.record(R.build(tmp_path), [R.option("gather_path", 1), R.option("small_tokens", -1), call])[2][0]
     assert (launch.params[1] if launch.kernel == "hash_lane_kernel" else 0) == tokens
+
+
+@pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
+@pytest.mark.parametrize("n,d,k,tau,rounds,tokens", [(300, 256, 96, 8, 2, 2), (300, 256, 170, 9, 2, 2), (300, 256, 170, 9, 1, 0), (256, 512, 97, 7, 2, 2), (64, 128, 96, 8, 2, 0)])
+def test_lines_of_16_bit_rows(tmp_path, n, d, k, tau, rounds, tokens):
+    test_lines(tmp_path, "plain", n, d, k, tau, rounds, tokens, x_dtype=2)
