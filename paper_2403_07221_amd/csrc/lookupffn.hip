@@ -1218,25 +1218,37 @@ enum class Codes { kCallers, kTurned, kPacked, kPackedInChain };
 // of rows of 256 (block 16, two factors, k = 96 5125 203 / 162).  d_pad = 512 spreads them up to 4096 tokens: tau 8, block 32, 536 wide 3575
 // 86 / 113, 984 wide 4000 133 / 156, but tau 9 1.1 ... 2 : 1.
 // Where an XCD's workgroups have a slice each (an odd number of slices, so that every XCD has all of them) none of them finds its copies
-// in the L2, and those beyond whole turns idle.  Plain, weighted, tau 8: two tokens a row (weighted, k = 64, 544 wide 3497 62 / 67, 712 3489
-// 67 / 75, 976 3905 84 / 94); else the line goes with the idle ones (plain, tau 10, d = 64, k = 96, 528 wide 7545 266 / 330; tau 9, 528 wide 6651 137 / 154;
-// multi-probe, tau 8, 584 wide 2004 185 / 208).
-// units: slices of the fullest XCD, for its `per_xcd` workgroups.
-int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, Codes codes, int units, int per_xcd)
+// in the L2, and those past whole turns idle, more than three in eight of them at some widths; the direct kernel is slower where the
+// tables go beyond the L2s and half the memory-side cache.  Passes, direct / staged:
+//   tau 8, plain: two tokens a row (k = 64, 544 wide 3976 48 / 56, 912 wide 4020 72 / 83); weighted, below 80 MB likewise (k = 64, 712 wide 3489
+//   67 / 75, 976 wide 3905 84 / 94), below 140 MB 3.5 slots (0.93 : 1 at 3.3, 1.06 and more from 3.6 on); multi-probe, idle 2.25 (584 wide
+//   2004 185 / 208; k = 96, 920 wide, no more than one in ten idle, 2233 361 / 233)
+//   tau 9, below 140 MB, idle past a turn: plain and weighted two tokens a row (560 wide 5135 116 / 141, 528 wide 6651 137 / 154; above it 1.1 ... 1.6 : 1:
+//   k = 146, 592 wide 7634 457 / 308; idle in the only turn 1 : 1 from the line on, k = 170, 296 wide 7735 293 / 199); multi-probe, idle
+//   3.25 (544 wide 2762 269 / 313)
+//   tau 10: plain, below 400 MB, 4 slots (720 wide 7636 227 / 234), idle 4.75 (528 wide 7545 266 / 330; above it k = 128, 880 wide 7092 629 / 550);
+//   weighted, idle 4.25 (552 wide 8620 224 / 252)
+// units: slices of the fullest XCD, for its `per_xcd` workgroups; bytes: of the tables.
+int64_t staged_from(Mode mode, int k, int tau, int sw, int rows, bool prepared, Codes codes, int units, int per_xcd, int64_t bytes)
 {
     const int64_t two_a_row = 8 * (int64_t)rows, slot = kLdsThreads / sw;
-    const bool alone = 2 * units > per_xcd;
-    if (tau == 7 || (sw == 4 && !prepared) || (sw == 8 && mode != kProbes && alone)) return two_a_row;
+    if (tau == 7 || (sw == 4 && !prepared)) return two_a_row;
     if (codes == Codes::kPackedInChain && sw == 8) return two_a_row;
     if (codes == Codes::kTurned && tau <= 9 && k < 10) return two_a_row;
-    int64_t line = two_a_row;  // in quarters of a slot from here
+    int64_t line = two_a_row / slot;  // in quarters of a slot
     const bool small = k < 64 || k % 2;
     const bool chain = codes == Codes::kPackedInChain, turned = codes == Codes::kTurned;
-    if (mode == kProbes && turned && k < 12 && (k < 6 || k % 2)) line = (k < 6 ? 18 : 14) * slot;
-    else if (mode == kProbes) line = (sw == 8 ? (turned && k < 16 ? 12 : small ? 10 : 7) : (small ? 11 : 9)) * slot;
-    else if (!small) line = (sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? (chain ? 14 : 10) : (chain ? 18 : 13)) * slot;
-    if (alone) line = line * per_xcd * ((units + per_xcd - 1) / per_xcd) / units;
-    return std::min(line, two_a_row);
+    if (mode == kProbes && turned && k < 12 && (k < 6 || k % 2)) line = k < 6 ? 18 : 14;
+    else if (mode == kProbes) line = sw == 8 ? (turned && k < 16 ? 12 : small ? 10 : 7) : (small ? 11 : 9);
+    else if (!small) line = sw == 8 ? (mode == kWeighted ? 13 : 15) : tau <= 9 ? (chain ? 14 : 10) : (chain ? 18 : 13);
+    const bool alone = 2 * units > per_xcd, idle = alone && 8 * units < 5 * per_xcd * ((units + per_xcd - 1) / per_xcd);
+    const bool probes = mode == kProbes, weighted = mode == kWeighted;
+    const int mb = (int)(bytes / 1000000);
+    int64_t least = 0;
+    if (sw == 8) least = probes ? (idle ? 9 : 0) : !alone ? 0 : !weighted || mb < 80 ? 16 : mb < 140 ? 14 : 0;
+    else if (tau <= 9) least = !idle || mb >= 140 ? 0 : probes ? 13 : units > per_xcd ? 16 : 0;
+    else if (alone && !probes) least = weighted ? (idle ? 17 : 0) : mb >= 400 ? 0 : idle ? 19 : 16;
+    return std::min(std::max(line, least) * slot, two_a_row);
 }
 
 // Launch shape of the LDS-staged gather for one problem size (no pointers involved).
@@ -1313,7 +1325,7 @@ int plan_gather_lds(int64_t n, int k, int tau, int d_out, const TableRef &T, Mod
     if (opt.token_slots && opt.token_slots < tok_max) tok_max = opt.token_slots;
     const int64_t nchunks = (tpb + (int64_t)groups * tok_max - 1) / ((int64_t)groups * tok_max);
     const int64_t chunk = (tpb + nchunks - 1) / nchunks;
-    if (opt.gather_path < 2 && chunk * 4 < (codes == Codes::kCallers ? 8 * (int64_t)rows : staged_from(mode, k, tau, sw, rows, T.prepared, codes, m, Bx))) return LFFN_OK;
+    if (opt.gather_path < 2 && chunk * 4 < (codes == Codes::kCallers ? 8 * (int64_t)rows : staged_from(mode, k, tau, sw, rows, T.prepared, codes, m, Bx, (int64_t)k * rows * d_out * 4))) return LFFN_OK;
     // the fewest slots built that hold a chunk: a slot without a token costs what any other does
     auto slots_of = [&](int64_t tokens) {
         const int tok = (int)((tokens + groups - 1) / groups);

@@ -15,8 +15,12 @@ CASES = [  # entry, k, tau, d_out, prepared, tokens of the line
     ("lookupffn_forward", 62, 8, 768, True, 5111), ("lookupffn_forward_weighted", 97, 8, 768, True, 5111),
     ("lookupffn_forward_probes", 24, 8, 768, True, 3191), ("lookupffn_forward_probes", 97, 8, 768, True, 3191),
     # a slice and less to a workgroup of an XCD, and two to one
-    ("lookupffn_forward_weighted", 64, 8, 544, True, 4089), ("lookupffn_forward_weighted", 64, 8, 352, True, 6641), ("lookupffn_forward", 96, 10, 528, True, 12905),
-    ("lookupffn_forward_weighted", 64, 9, 528, True, 8185), ("lookupffn_forward_weighted", 64, 9, 496, True, 5281), ("lookupffn_forward_probes", 80, 8, 584, True, 3017),
+    ("lookupffn_forward_weighted", 64, 8, 544, True, 4089), ("lookupffn_forward_weighted", 64, 8, 352, True, 6641), ("lookupffn_forward_weighted", 128, 8, 976, True, 3577),
+    ("lookupffn_forward", 128, 8, 976, True, 4089), ("lookupffn_forward_probes", 80, 8, 584, True, 2297), ("lookupffn_forward_weighted", 64, 9, 528, True, 8185),
+    ("lookupffn_forward_weighted", 64, 9, 496, True, 5113), ("lookupffn_forward_weighted", 146, 9, 592, True, 5113), ("lookupffn_forward_probes", 64, 9, 544, True, 3325),
+    ("lookupffn_forward", 96, 10, 528, True, 9721), ("lookupffn_forward", 64, 10, 720, True, 8185), ("lookupffn_forward_weighted", 96, 10, 528, True, 8697),
+    ("lookupffn_forward_weighted", 250, 8, 648, True, 3321), ("lookupffn_forward_probes", 96, 8, 920, True, 1785), ("lookupffn_forward", 64, 9, 560, True, 8185),
+    ("lookupffn_forward", 170, 9, 296, True, 5113), ("lookupffn_forward", 128, 10, 880, True, 6649),
     ("lookupffn_forward_probes", 96, 7, 768, True, 2551), ("lookupffn_forward_probes", 24, 10, 512, True, 5625),
 ]
 
