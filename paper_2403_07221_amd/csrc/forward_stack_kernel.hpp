@@ -42,6 +42,7 @@ struct StackArgs {
     const int8_t *signs[kStackMaxLayers];  // per layer [P][R][1024]
     const char *tables[kStackMaxLayers];   // per layer, all in the same layout
     long long n;
+    long long twos;  // forward_stack_kernel: workgroups that take two tokens; those after them take one
     int d, d_out, k, tau, P, n_layers;
     int n_rounds;  // read by forward_small_kernel; forward_stack_kernel has its own as a template parameter
     int x_kind;  // element type of x: 0 fp32, 1 bf16, 2 IEEE half
@@ -274,6 +275,8 @@ struct StackLane {
 
 // T tokens a workgroup: one, or two where there are more tokens than compute units (the kernel's registers leave room for one
 // workgroup on each): k = 96, 768 wide, us a pass, one / two: 257 tokens 19.2 / 15.4, 512 26.4 / 24.2; 64 wide 512 10.6 / 9.5.
+// Beyond whole rounds of two, a remainder of up to a token a compute unit takes one each: 519 tokens, four layers of 768, k = 170, all in
+// twos / so 423 / 353, 626 of 1024, k = 96, tau = 4 94.5 / 77.8.
 template <int R, int KIND, int T>
 __global__ __launch_bounds__(kStackThreads) void forward_stack_kernel(StackArgs a)
 {
@@ -287,9 +290,11 @@ __global__ __launch_bounds__(kStackThreads) void forward_stack_kernel(StackArgs 
     uint8_t *sign = reinterpret_cast<uint8_t *>(lds + T * 2 * N);
     uint32_t *rowoff = lds + T * (2 * N + kStackSignWords);
     const int n_off = stack_code_words(a.k);
-    const long long t0 = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * T;
+    const long long b = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    const bool both = T == 2 && b < a.twos;
+    const long long t0 = T == 1 ? b : both ? 2 * b : a.twos + b;
     if (t0 >= a.n) return;  // the whole workgroup
-    const int tokens = T == 1 || t0 + T <= a.n ? T : (int)(a.n - t0);
+    const int tokens = both && t0 + 2 <= a.n ? 2 : 1;
 
 #pragma unroll
     for (int i = 0; i < T; ++i)

@@ -2018,10 +2018,13 @@ int launch_forward_stack(const void *x, const int8_t *const *signs, const void *
         int cus = 0;
         rc = device_cus(&cus);
         if (rc != LFFN_OK) return rc;
+        // What is left over from whole rounds of two goes a token to a workgroup where that is one round.
         const int tokens = n > cus && stack_lds_bytes(k, 2) <= 64 * 1024 ? 2 : 1;
+        const int64_t left = n % (2 * (int64_t)cus), ones = tokens == 1 ? n : n > 2 * (int64_t)cus && left <= cus ? left : 0;
+        a.twos = (n - ones + 1) / 2;
         if ((narrow = n_layers == 1 && n > 2 * (int64_t)cus && a.row_dwords <= kNarrowDwords))
             rc = lffn_host::forward_narrow_part(n_rounds, T.kind, a, grid_of(n), (int)((a.row_dwords + 63) / 64 * 64), narrow_lds_bytes(a.P, k), s);
-        else rc = lffn_host::forward_stack_part(n_rounds, T.kind, a, grid_of((n + tokens - 1) / tokens), tokens, stack_lds_bytes(k, tokens), s);
+        else rc = lffn_host::forward_stack_part(n_rounds, T.kind, a, grid_of(a.twos + ones), tokens, stack_lds_bytes(k, tokens), s);
     } else {
         int threads = (int)((a.row_dwords + 63) / 64 * 64);
         if (threads > 1024) threads = 1024;

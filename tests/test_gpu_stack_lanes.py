@@ -18,7 +18,7 @@ CASES = [  # n, d, k, tau, d_out, rounds, x dtype, table dtype, prepared
     (1, 900, 40, 16, 8, 2, "float32", "bfloat16", False), (2, 700, 2100, 1, 20, 1, "float32", "float32", False),
     (2, 1024, 128, 10, 1024, 3, "float32", "float32", True), (2, 768, 24, 5, 4352, 3, "float32", "float32", True),
     (3, 768, 24, 5, 4360, 3, "float32", "bfloat16", False), (257, 768, 96, 8, 132, 3, "float32", "float32", True),
-    (300, 1024, 17, 8, 1032, 4, "float16", "float16", False), (511, 515, 60, 9, 64, 2, "float32", "float32", True),
+    (300, 1024, 17, 8, 1032, 4, "float16", "float16", False), (511, 515, 60, 9, 64, 2, "float32", "float32", True), (555, 768, 33, 8, 520, 3, "float32", "float32", True),
     (16, 100, 33, 9, 200, 3, "float32", "bfloat16", False), (9, 512, 100, 8, 1100, 3, "float32", "float32", True),
 ]
 
@@ -35,17 +35,17 @@ def test_one_launch_equals_two(n, d, k, tau, d_out, R, xdt, tdt, prepared):
     out = []
     try:
         for y_dtype in (torch.float32, torch.bfloat16, torch.float16):
-            for option in (512, -1):
+            for option in (1024, -1):
                 B.lookupffn_set_option("small_tokens", option)
                 out.append(B.lookupffn_forward(x, signs, tables, y=torch.empty(n, d_out, dtype=y_dtype, device="cuda")))
-                if option == 512:
+                if option == 1024:
                     assert B.lookupffn_last_hash_kernel() == ("forward_stack_kernel" if d > 512 else "forward_small_kernel")
             assert torch.equal(out[-2], out[-1])
     finally:
         B.lookupffn_set_option("small_tokens", 0)
 
 
-@pytest.mark.parametrize("n", [1, 257, 512])
+@pytest.mark.parametrize("n", [1, 257, 512, 513, 768, 769])
 @pytest.mark.parametrize("d,k,tau,R,tdt", [(768, 33, 8, 3, "float32"), (520, 170, 9, 1, "float16"), (1024, 230, 9, 4, "float32")])
 def test_chain_equals_its_layers(n, d, k, tau, R, tdt):
     g = torch.Generator(device="cuda").manual_seed(n + d)

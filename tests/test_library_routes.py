@@ -149,3 +149,13 @@ def test_deep_direct_gather_tests_take_the_deep_form(recorder):
                                             for n, tau, d_out, t, prep in deep_tests.SHAPES for k in deep_tests.KS]
     depths = [launches[0].params[3] for launches in R.record(recorder, calls)[1:]]
     assert set(depths) == {8, 16}
+
+
+# 256 compute units hold a workgroup of two tokens each: what is left over from whole rounds takes a token to a workgroup where one round
+# holds them.
+@pytest.mark.parametrize("n,tokens,groups", [(256, 1, 256), (257, 2, 129), (512, 2, 256), (513, 2, 257), (558, 2, 302), (768, 2, 512), (769, 2, 385),
+                                             (1023, 2, 512), (1024, 2, 512), (1108, 2, 596), (1281, 2, 641)])
+def test_groups_of_the_single_launch(recorder, n, tokens, groups):
+    call = ["lookupffn_forward", R.FAKE, R.FAKE << 1, R.FAKE << 2, R.FAKE << 3, n, 768, 96, 8, 768, 3, 0, 0, R.FAKE, 1 << 40, None]
+    (launch,) = R.record(recorder, [["lookupffn_set_option", "small_tokens", 4096], call])[-1]
+    assert (launch.kernel, launch.params[2], launch.grid, launch.block) == ("forward_stack_kernel", tokens, (groups, 1, 1), 1024)
