@@ -119,8 +119,9 @@ int64_t lookupffn_workspace_bytes_gather(int64_t n_tokens, int k);
  * Whole forward pass: Hash then Gather on the same stream (Sec. 3.1, eq. "lookup").
  * Scratch: lookupffn_workspace_bytes(n_tokens, k) bytes (0 if n_tokens == 0).
  * Batches of up to 512 tokens ("small_tokens" below) whose shape lookupffn_forward_stack takes run as that
- * call's single launch with n_layers = 1 (no scratch touched); so do, for widths d of 33 .. 512, those whose
- * selected rows one launch finishes sooner.  y has the same bits either way.  y may overlap x: such a call is two launches unless y is x with rows of the same length in bytes.
+ * call's single launch with n_layers = 1 (no scratch touched); so do, for widths d of 33 .. 512, those with few
+ * enough selected rows.  y has the same bits either way.  y may overlap x: such a call is two launches unless y
+ * is x with rows of the same length in bytes.
  */
 int lookupffn_forward(const void *x, const int8_t *signs, const void *tables, void *y,
                       int64_t n_tokens, int d, int k, int tau, int d_out,
@@ -208,6 +209,10 @@ int64_t lookupffn_workspace_bytes_weighted(int64_t n_tokens, int k);
  * lookupffn_hash_probes writes codes[n_tokens][k] and shares[n_tokens][k][1+tau] (fp32, 4-byte
  * aligned); lookupffn_gather_probes does the sum ((1 + tau) row reads per token and table);
  * lookupffn_forward_probes chains them.  Same hash, conventions and limits as the weighted variant.
+ * The codes are the same in every route.  The shares' product over a table is formed in coordinate order by
+ * lookupffn_hash_probes and as a tree in a staged pass that hash_row_kernel hashes (tau = 8; "hash_path" below), so there
+ * y may differ from lookupffn_hash_probes + lookupffn_gather_probes, and for one token between batch sizes, in the last
+ * bits (about 2.4e-7 of its norm; the error against 64 bits is the same).
  */
 int lookupffn_hash_probes(const void *x, const int8_t *signs, uint16_t *codes, float *shares,
                           int64_t n_tokens, int d, int k, int tau,
@@ -308,10 +313,13 @@ int lookupffn_timing_read_each(int which, double *ms_out, int64_t capacity, int6
  *                                     (four tokens per wavefront at d_pad = 1024, eight at 512); 3: that kernel
  *                                     for every batch size.  Default for n_rounds <= 4: the lane-row kernel when
  *                                     d_pad is 1024 or 512, d is a multiple of 16, the batch has at least 2048
- *                                     tokens (4096 with weights; at d_pad = 512: 6144 and 12288), codes alone or
- *                                     codes and gather weights are asked for (not the multi-probe shares) and
- *                                     its constants fit 64 KB of LDS; else, at d_pad = 1024, the two-layout
- *                                     one-token-per-wavefront kernel; else the generic one
+ *                                     tokens (4096 with weights; at d_pad = 512: 6144 and 12288; with the multi-probe
+ *                                     shares, in a staged pass with tau = 8 alone, 1536) and its constants fit
+ *                                     64 KB of LDS; else, at d_pad = 1024, the two-layout one-token-per-wavefront
+ *                                     kernel; else the generic one.  In a forward pass (not in a hash alone) whose
+ *                                     codes are not handed to a staged gather in its own layout, batches of few
+ *                                     tokens take hash_lane_kernel, a coordinate to a lane, where it is the faster
+ *                                     one; 1, 2 and 3 rule it out
  *   "hash_blocks"      1..65536       grid cap of the lane-row and two-layout hash kernels
  * Returns LFFN_E_SIZE for an unknown key or a value outside the documented set.  Process-wide; a call
  * reads the knobs once when it starts.
@@ -324,12 +332,14 @@ const char *lookupffn_last_hip_error(void);
 /* Which gather kernel the calling thread's most recent gather launch used: "gather_kernel" (direct, rows
  * fetched through L2), "gather_lds_kernel" (table slices staged in LDS, double-buffered),
  * "forward_stack_kernel" or "forward_small_kernel" (hash and gather of a few tokens in one launch, d of 513 .. 1024 and of
- * 33 .. 512), "forward_narrow_kernel" (lookupffn_forward_stack of one layer of rows up to 2 KB and many tokens), "gather_ring_kernel" (on request: prepared tables of up to 256 rows, plain sum; slices staged in an LDS ring,
- * token groups lagged so that their reads never meet in a bank); "" before the first launch. */
+ * 33 .. 512), "forward_narrow_kernel" (lookupffn_forward_stack, and lookupffn_forward with "small_tokens" raised, of one layer of rows
+ * up to 2 KB and more than two tokens to a compute unit), "gather_ring_kernel" (on request: prepared tables of up to 256 rows, plain
+ * sum; slices staged in an LDS ring, token groups lagged so that their reads never meet in a bank); "" before the first launch. */
 const char *lookupffn_last_gather_kernel(void);
 /* The same for the sign-diagonal hash: "hash_row_kernel" (d_pad = 1024 or 512, a token per row of 16 or 8
- * lanes), "hash1024_kernel" (d_pad = 1024, one token per wavefront), "hash_kernel" (any width),
- * "forward_stack_kernel" or "forward_small_kernel"; "" before the first launch (the BH hash has one kernel and is not reported). */
+ * lanes), "hash1024_kernel" (d_pad = 1024, one token per wavefront), "hash_kernel" (any width), "hash_lane_kernel" (few tokens of a
+ * forward pass, d_pad 64 .. 1024), "forward_stack_kernel", "forward_small_kernel" or "forward_narrow_kernel"; "" before the first
+ * launch (the BH hash, which has one kernel for few tokens and one for many, is not reported). */
 const char *lookupffn_last_hash_kernel(void);
 /* major*10000 + minor*100 + patch */
 int lookupffn_version(void);

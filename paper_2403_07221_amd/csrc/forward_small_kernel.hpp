@@ -5,8 +5,8 @@
 // to memory, and a second kernel that waits for the first to drain; here a workgroup owns a token, its waves
 // take the projections in turn (each wave holds the row and transforms it with the generic hash kernel's own
 // butterflies, so the same bits), the sign strings meet in LDS, and the waves then sum the k selected rows in table
-// order with forward_stack_kernel's gather.  64 tokens of 64, k = 8: 12.8 -> 9.4 us a pass; 64 tokens of 512, k = 256:
-// 28.6 -> 12.2 us.  Same sequential fp32 sum, bit-equal to the other kernels.
+// order with forward_stack_kernel's gather.  Two launches / this, us a pass: 64 tokens of 64, k = 8 5.6 / 3.7; 64 tokens of 512,
+// k = 256 17.9 / 12.8.  Same sequential fp32 sum, bit-equal to the other kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -63,7 +63,8 @@ __host__ __device__ inline int stack_code_words(int k) { return (k + kStackChunk
 constexpr int kStackThreads = 1024;
 constexpr int kStackSignWords = 2 * 1024 / 4;
 __host__ __device__ inline size_t stack_lds_bytes(int k, int tokens) { return tokens * ((size_t)2 * 1024 + kStackSignWords + stack_code_words(k)) * 4; }
-// The kernel's range of P and k: what an earlier form's LDS (a 4 KB transpose area, sign strings, offsets, two rows) fitted in 64 KB
+// The range of P and k of the entry point, and with it what it refuses: 64 KB for a 4 KB transpose area, sign strings, the row
+// offsets and two rows, which a form of a wave a token took.  It lies within what this kernel needs, stack_lds_bytes(k, 1) <= 64 KB.
 __host__ inline bool stack_range_ok(int P, int k)
 {
     return ((size_t)kH1024TransposeWords + ((hash_bit_words(P, 1024) + 3) & ~3) + stack_code_words(k) + 2 * 1024) * 4 <= 64 * 1024;

@@ -443,8 +443,8 @@ __global__ __launch_bounds__(kRowThreads) void hash_row_kernel(HashArgs a)
             row_collect_masks<0>(v, lo, hi);
             // ---- weighted variant (Sec. 4): w_j = |z_j|_1 / prod_b (1 + exp(-2 |z_jb|)).  tau divides LPT
             // (host-checked), so a table's coordinates are tau neighbouring c of one register: sum and product
-            // are all-reduced over those lanes with the exchanges' DPP controls, and the weight is
-            // sum * (1 / product).
+            // are folded over those lanes with the exchanges' DPP controls, the registers halved at each exchange (row_fold),
+            // and the weight is sum * (1 / product).
             if constexpr (WMODE == 1) {
                 const long long bits_left = (long long)a.k * a.tau - (long long)p * N;
                 const int n_reg = bits_left >= N ? kRowRegs : (int)((bits_left + LPT - 1) / LPT);  // registers that hold table coordinates

@@ -56,7 +56,7 @@ int gather_lds_weighted_part(int tok, const GatherLdsArgs &a, int fr, int sw, di
 int gather_lds_probes_part(int tok, const GatherLdsArgs &a, int fr, int sw, dim3 grid, size_t lds, hipStream_t s);
 // part 7: the lagged, bank-interleaved staged gather (prepared tables, tau <= 8)
 int gather_ring_part(int threads, int tok, const GatherRingArgs &a, dim3 grid, hipStream_t s);
-// part 8: hash and gather of a few tokens, one or several chained layers, in one launch
+// part 8: hash and gather in one launch: of a few tokens, one or several chained layers, and of one layer of narrow rows
 int forward_stack_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int tokens, size_t lds, hipStream_t s);
 int forward_narrow_part(int n_rounds, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
 int forward_small_part(int L, int kind, const StackArgs &a, dim3 grid, int threads, size_t lds, hipStream_t s);
@@ -662,7 +662,9 @@ struct Options {
     int small_tokens = 0;     // 0 = default, -1 = never: up to this many tokens lookupffn_forward runs as one
                               // hash-and-gather launch (when the shape is that kernel's)
 };
-constexpr int kSmallTokensDefault = 512;  // k = 96, d_out = 768: 12.6 us against 13.8 at 200 tokens, 24.6 against 17.8 at 512; k = 32, 256 wide 7.8 / 8.9 there
+// d_pad = 1024, one launch / two, us: k = 96, 768 wide 200 tokens 13.2 / 14.0, 257 16.0 / 15.0, 512 25.0 / 18.4; k = 32, 256 wide, 512 tokens 7.8 /
+// 8.5.  Past a token to a compute unit two launches are ahead where the rows are many bytes; the limit is one of tokens alone.
+constexpr int kSmallTokensDefault = 512;
 std::mutex g_opt_mu;
 Options g_opt;
 Options options_snapshot()
@@ -980,7 +982,8 @@ dim3 grid_of(int64_t blocks)
 
 // Projections of few tokens over up to `most` workgroups each: returns the groups and sets the projections of one.  A group
 // but the first also hashes the projection before its own where tables cross into it.  (For codes in the ABI layout only: a
-// word of the packed layout may hold tables of two projections.)
+// word of the packed layout may hold tables of two projections.  Where that costs a staged batch more than staging gains it
+// is not staged: staged_from.)
 unsigned split_projections(int P, bool cross, int64_t most, int *p_per)
 {
     const int64_t groups = most < P ? most : P;
@@ -1026,7 +1029,7 @@ bool hash_row_ok(const int8_t *signs, bool packed, bool weights, bool probes, in
 //     two projections that cross, a chain in either kernel: d = 64 weights up to 1.4 longer here between 0.25 and 2, shares up to 2.1 below
 //     2, d = 128 0.6 (weights) and 1.4 (shares) below 5, d = 256 shares 0.4
 //     three that cross: d = 256 f = 4.5 8.5 / 8.7, shares 10.1 / 11.1 (four and six: 2 ... 7 shorter), d = 512 shares 6 13.1 / 14.8
-//   codes alone, whose narrow transforms cost a wave of its own least (passes of 25 ... 2000 shapes, x and signs from beyond the L2)
+//   codes alone, whose narrow transforms cost a wave of its own least (whole passes, x and signs from beyond the L2)
 //     d = 64: one projection, 64 tokens 3.0 / 3.2, 8192 4.3 / 4.1; twelve 64 3.3 / 3.5, 512 (1.5) 4.9 / 4.1, 2048 (6) 10.6 / 6.7; two to five
 //     that cross 0 ... 2.2 longer, seven and up 0.1 longer below 0.5
 //     d = 128: one 0.3 ... 1 longer, two 0.1 ... 0.8 (that cross 2); six f = 0.8 3.7 / 4.0, 3 5.6 / 5.2; that cross, up to eleven 1 longer ... 0.6
@@ -1913,23 +1916,19 @@ bool stack_shape_ok(const void *x, const int8_t *const *signs, const void *const
 
 // Whether forward_small_kernel takes this single layer: d_pad 64 .. 512 (any number of rounds, any alignment the
 // entry points accept: rows and signs are read element by element) and a table set below 2 GiB.  `by_rate`: leave out
-// the batches that the two kernels finish sooner.  A token's rows come in through one compute unit, a lane to each of up
-// to 1024 dwords.  One launch against two, us a pass (fp32, tau = 8 where not said):
-// (two kernels as they were before hash_lane_kernel; with it, tau = 8, us: 256 tokens of 512, k = 96, 768 wide 15.0 / 14.0; 512 tokens, k = 64, 256
-// wide 9.5 / 10.7; of 64, k = 8 3.2 / 5.3; of 256, k = 96, 256 wide 10.6 / 11.7)
-//   256 tokens: k = 96, 768 wide 14.9 / 18.7; k = 256, 512 wide 22.5 / 30.9; k = 256, 1024 wide 38.2 / 49.6
-//   512 tokens: k = 64, 256 wide (32 MiB of rows) 10.0 / 12.9; tau = 7, k = 97, 512 wide (97 MiB) 17.5 / 14.3; k = 96,
-//   768 wide (144 MiB) 26.6 / 21.3; k = 8, 64 wide 10.3 / 12.7
-// So with at most a token to each compute unit the launch saved always counts, beyond that while the rows are few.  Wider
-// rows are taken 1024 dwords after another, and every turn of up to 32 rows is a chain of about 2 us of its own, however
-// few the tokens: up to four turns one launch wins (2048 wide, k = 64: 1 token 12.0 / 13.6, 128 tokens 14.3 / 15.9), with
-// more only when the two kernels are long too, for many tables and tokens (k = 8, 6144 wide 15.5 / 13.6; k = 40, 4096
-// wide 18.8 / 13.6; k = 64, 4096 wide: 1 token 18.6 / 13.5, 64 tokens 19.7 / 17.4, 128 tokens 23.0 / 25.6; k = 96, 2048
-// wide: 1 token 14.8 / 12.9, 64 tokens 15.5 / 17.9), and with a second token on a compute unit up to one and a half (300
-// tokens: k = 8, 4096 wide 21.3 / 13.5, 2048 wide 14.7 / 13.6; k = 16, 1280 wide 11.2 / 12.7).
-// Tables that do not stay in the 256 MiB memory-side cache gain at some sizes and lose at others, and keep the two kernels
-// (other tokens in every pass, tau = 10, k = 128, 1024 wide: 1 token 15.2 / 14.5, 16 tokens 16.4 / 18.3, 64 tokens 26.9 /
-// 24.8).
+// batches of many or wide rows.  A token's rows come in through one compute unit, a lane to each of up to 1024 dwords, wider rows
+// 1024 dwords after another, and every turn of up to 32 rows is a chain of its own however few the tokens.
+// Where the lines lie: up to a token to each compute unit all of up to four turns of 4 KB by 32 tables (by more when the tokens and
+// tables are many), beyond that while the rows are 40 MiB and one and a half turns; tables that stay in the 256 MiB memory-side cache.
+// One launch against two, us a pass (fp32 prepared, tau = 8, d = 512 where not said):
+//   k = 8, 64 wide, d = 64: 64 tokens 3.7 / 5.6, 512 3.8 / 5.7; k = 256, 512 wide: 64 12.8 / 17.9, 256 22.7 / 20.9
+//   k = 96, 768 wide: 128 tokens 11.1 / 12.1, 192 13.2 / 13.5, 256 15.6 / 14.5, 512 (144 MiB of rows) 24.8 / 18.4
+//   512 tokens: d = 256, k = 64, 256 wide 8.5 / 8.9, k = 96 10.8 / 10.6; tau = 7, k = 97, 512 wide (97 MiB) 18.0 / 14.0
+//   two turns and more: k = 64, 2048 wide: 1 token 11.3 / 8.4, 128 15.9 / 15.5; k = 96 1 token 13.0 / 9.9; k = 64, 4096 wide, 64 tokens 22.7 / 16.4;
+//   k = 8, 6144 wide, 128 tokens 12.0 / 9.2; 300 tokens: k = 8, 2048 wide 9.3 / 8.1, k = 16, 1280 wide 9.3 / 8.4
+//   tau = 10, k = 128, 1024 wide (512 MiB of tables, other tokens in every pass): 1 token 16.6 / 12.6, 64 29.6 / 20.7
+// The lines were drawn against a slower hash of few tokens and a slower direct gather: where rows are wide, or the tokens near the
+// compute units' number and the tables many, two launches are now up to a third shorter.
 constexpr int64_t kSmallRowBytes = 40 << 20, kSmallTableBytes = 256 << 20;
 bool small_shape_ok(int64_t n, int d, int k, int tau, int d_out, int table_dtype, const void *tables, bool by_rate)
 {
