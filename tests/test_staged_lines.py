@@ -59,6 +59,17 @@ def test_line_of_bh_codes(tmp_path, weighted, d, k, tau, d_out, line):
                 PREPARED, R.FAKE, 1 << 40, None]
         kernels = [launch.kernel for launch in R.record(lib, [call])[0]]
         assert ("gather_lds_kernel" in kernels) == (n == line), (n, kernels)
+    # the packed layout comes from the matrix cores' kernel alone, also where the batch is few enough tokens for the other
+    assert "bh_hash_kernel" in kernels and "bh_lane_kernel" not in kernels
+
+
+@pytest.mark.skipif(not shutil.which("gcc"), reason="gcc not found")
+@pytest.mark.parametrize("k,hash_kernel", [(8, "bh_hash_kernel"), (9, "bh_lane_kernel")])
+def test_hash_of_a_staged_batch_of_few_narrow_tokens(tmp_path, k, hash_kernel):
+    """An even number of tables is hashed into the staged gather's layout, an odd one turned around for it."""
+    call = ["lookupffn_forward_bh", R.FAKE, R.FAKE, R.FAKE, R.FAKE, 5200, 64, k, 8, 768, PREPARED | 16, 2, 0, PREPARED, R.FAKE, 1 << 40, None]
+    kernels = [launch.kernel for launch in R.record(R.build(tmp_path), [call])[0]]
+    assert "gather_lds_kernel" in kernels and hash_kernel in kernels
 
 
 # Multi-probe with a few tables: what is turned around between the kernels (odd numbers, and all but what hash_row_kernel writes) has later lines
